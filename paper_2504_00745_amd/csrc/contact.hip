@@ -276,13 +276,13 @@ __device__ inline int exact_pair(const DevParams &P, const double xi[3], const d
 
 // Contact force on granule q reading its candidates from global memory, in
 // two passes: the candidate pass runs only the double contact test and lists
-// touching partners in `plist` (kMaxPartners x 256 ints in LDS, column tid);
+// touching partners in `plist` (kMaxPartners x NT ints in LDS, column tid);
 // the force pass then evaluates the pair law for the listed partners in
 // canonical order.  Lanes of a wave touch partners at different candidate
 // positions, so evaluating forces inside the candidate loop would run the
 // expensive branch for almost every candidate.  A granule with more
 // partners than the list holds walks its candidates in canonical order.
-template <typename T, bool CAP>
+template <typename T, bool CAP, int NT>
 __device__ inline void contact_global(const DevParams &P, int64_t n, const double *__restrict__ x,
                                       const double *__restrict__ v, const double *__restrict__ r,
                                       const int32_t *__restrict__ cb, const int32_t *__restrict__ ce, int64_t q,
@@ -320,15 +320,15 @@ __device__ inline void contact_global(const DevParams &P, int64_t n, const doubl
                 double d2;
                 if (!touching(xi[0] - cx[u], xi[1] - cy[u], xi[2] - cz[u], ri + cr[u] + reach, d2) || d2 == 0.0)
                     continue;
-                if (cnt < kMaxPartners) plist[cnt * 256 + tid] = j;
+                if (cnt < kMaxPartners) plist[cnt * NT + tid] = j;
                 ++cnt;
             }
         }
     });
     if (cnt <= kMaxPartners) {
-        canon_sort(plist + tid, 256, cnt, q, [](int32_t j) { return (int64_t)j; });
+        canon_sort(plist + tid, NT, cnt, q, [](int32_t j) { return (int64_t)j; });
         for (int k = 0; k < cnt; ++k) {
-            const int32_t j = plist[k * 256 + tid];
+            const int32_t j = plist[k * NT + tid];
             nc += exact_pair<T, CAP>(P, xi, vi, ri, mi, q, j, fetch_partner(n, x, v, r, j), sri, sr, held, acc);
         }
     } else {  // rare: more partners than the list holds
@@ -377,8 +377,9 @@ __device__ inline void contact_global(const DevParams &P, int64_t n, const doubl
 constexpr int kHaloCells = 216;
 constexpr int kLdsPartners = 10;
 constexpr int kCand = 4;  // candidates read from LDS before they are tested
-constexpr int kPad = 1;   // empty slots after each cell
-constexpr int kCopyRounds = 8;  // shell copy rounds of 256 slots: covers every cap <= 2047
+constexpr int kPad = 1;   // empty slots after each cell (256 threads)
+constexpr int shell_pad(int nt) { return nt == 64 ? 0 : kPad; }
+constexpr int kCopyRounds = 8;  // shell copy rounds of one slot per thread: cap <= 8 x threads
 
 // Fixed compare-exchange networks sorting 4, 6, 8 and 10 entries (5, 12,
 // 19 and 29 comparators, the least known for those sizes).
@@ -413,7 +414,7 @@ __device__ inline void run_net(const int (&net)[C][2], uint32_t key[], uint32_t 
 // orders by distance, the lower position first), sorted in registers by the
 // smallest network that covers the longest list in the wave (none when no
 // list has two entries), written back.
-template <typename J>
+template <int NT, typename J>
 __device__ inline void lds_list_canonical(uint16_t *col, int m, int64_t q, J &&j_of)
 {
     static_assert(kLdsPartners == 10, "the networks sort up to ten entries");
@@ -425,7 +426,7 @@ __device__ inline void lds_list_canonical(uint16_t *col, int m, int64_t q, J &&j
         key[i] = 0xFFFFFFFFu;  // past the last entry: sorts last
         sl[i] = 0;
         if (i < m) {
-            sl[i] = col[i * 256];
+            sl[i] = col[i * NT];
             const int64_t j = j_of((int)sl[i]);
             key[i] = j > q ? (uint32_t)(2 * (j - q) + 1) : (uint32_t)(2 * (q - j));
         }
@@ -440,7 +441,7 @@ __device__ inline void lds_list_canonical(uint16_t *col, int m, int64_t q, J &&j
         run_net(kNet4, key, sl);
 #pragma unroll
     for (int i = 0; i < kLdsPartners; ++i)
-        if (i < m) col[i * 256] = (uint16_t)sl[i];
+        if (i < m) col[i * NT] = (uint16_t)sl[i];
 }
 
 // Candidate test of the LDS pass (see above): p = (p, Q) of a slot,
@@ -454,8 +455,11 @@ __device__ inline bool near_slot(float4 p, float mx, float my, float mz, float t
 // one register more than 128 and spills three.  The dry instantiation
 // serves beds whose neighbour list could never be kept (no skin: cells of
 // exactly 2 r_max), where building a list every step costs more.
-template <typename T, bool CAP>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CAP ? 4 : 1)))
+// NT: threads per workgroup; 64 serves beds whose bricks hold at most one
+// granule per lane (no empty slots after the cells there: the lanes of one
+// wave read a slot each).
+template <typename T, bool CAP, int NT>
+__global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(CAP ? 4 : 1)))
 k_contact_lds(DevParams P, int64_t n, const int32_t *__restrict__ bl,
                                                      const int32_t *__restrict__ bcnt, int cap,
                                                      const double *__restrict__ x, const double *__restrict__ v,
@@ -463,18 +467,20 @@ k_contact_lds(DevParams P, int64_t n, const int32_t *__restrict__ bl,
                                                      const int32_t *__restrict__ ce, const T *__restrict__ sr,
                                                      const double *__restrict__ held, T *__restrict__ F,
                                                      int32_t *__restrict__ ncont, int64_t *err,
-                                                     int32_t *__restrict__ hmax, int32_t *__restrict__ hclr)
+                                                     int32_t *__restrict__ hmax, int32_t *__restrict__ hclr, int only)
 {
     extern __shared__ float4 smem4[];
     float4 *spos = smem4;                                        // [cap + kCand] (p, Q), see above
-    uint16_t *plist = reinterpret_cast<uint16_t *>(spos + cap + kCand);  // [kLdsPartners][256] partner slots
-    int32_t *clo = reinterpret_cast<int32_t *>(plist + kLdsPartners * 256);  // [216] first slot of each cell
-    int32_t *cnum = clo + kHaloCells;                                      // [216] granules of each shell cell
-    int32_t *cgb = cnum + kHaloCells;                                      // [216] global begin of each shell cell
+    constexpr int kPad = shell_pad(NT);
+    uint16_t *plist = reinterpret_cast<uint16_t *>(spos + cap + kCand);  // [kLdsPartners][NT] partner slots
+    int32_t *cgb = reinterpret_cast<int32_t *>(plist + kLdsPartners * NT);  // [216] global begin of each shell cell
     int32_t *s_wave = cgb + kHaloCells;                                    // [4]
-    uint8_t *scell = reinterpret_cast<uint8_t *>(s_wave + 4);              // [cap] shell cell of each slot
+    uint16_t *clo = reinterpret_cast<uint16_t *>(s_wave + 4);              // [216] first slot of each cell
+    uint16_t *cnum = clo + kHaloCells;                                     // [216] granules of each shell cell
+    uint8_t *scell = reinterpret_cast<uint8_t *>(cnum + kHaloCells);         // [cap] shell cell of each slot
     const int tid = threadIdx.x;
     if (hclr && blockIdx.x == 0 && tid == 0) *hclr = 0;  // the next recording call's record
+    if (not_mine(only, kWaveFill, n, bcnt)) return;
     const int64_t b = brick_of_block(bl, bcnt);
     if (b < 0) return;
     const int32_t bc[3] = {(int32_t)(b % P.nb[0]), (int32_t)((b / P.nb[0]) % P.nb[1]),
@@ -484,66 +490,83 @@ k_contact_lds(DevParams P, int64_t n, const int32_t *__restrict__ bl,
     clip_range(n, gb, ge);
     if (ge <= gb) return;
     const double o[3] = {(c0[0] + 3) * P.cell, (c0[1] + 3) * P.cell, (c0[2] + 3) * P.cell};  // brick centre
-    // ---- shell cells: counts, then slots (count + kPad each) by a scan
-    int32_t num = 0, gbeg = 0;
-    if (tid < kHaloCells) {
-        const int hx = tid % 6, hy = (tid / 6) % 6, hz = tid / 36;
-        const int32_t cx = c0[0] + hx, cy = c0[1] + hy, cz = c0[2] + hz;
+    // ---- shell cells: counts, then slots (count + kPad each) by a scan;
+    // thread t takes cells t, t + NT, ...
+    constexpr int kCellRounds = (kHaloCells + NT - 1) / NT;
+    int32_t num[kCellRounds], gbeg[kCellRounds], first[kCellRounds];
+#pragma unroll
+    for (int w = 0; w < kCellRounds; ++w) {
+        const int c = tid + w * NT;
+        num[w] = gbeg[w] = 0;
+        if (c >= kHaloCells) continue;
+        const int32_t cx = c0[0] + c % 6, cy = c0[1] + (c / 6) % 6, cz = c0[2] + c / 36;
         if (cx >= 0 && cy >= 0 && cz >= 0 && cx < P.nc[0] && cy < P.nc[1] && cz < P.nc[2]) {
             const uint32_t k = key_of_cell(P, cx, cy, cz);
             int32_t e = ce[k];
-            gbeg = cb[k];
-            clip_range(n, gbeg, e);
-            num = e - gbeg;
+            gbeg[w] = cb[k];
+            clip_range(n, gbeg[w], e);
+            num[w] = e - gbeg[w];
         }
     }
-    const int32_t slots = tid < kHaloCells ? num + kPad : 0;
-    int32_t first = 0;
+    int32_t H = 0;  // slots of the shell
     {
         const int lane = tid & 63, wave = tid >> 6;
-        int32_t incl = slots;
-        for (int off = 1; off < 64; off <<= 1) {
-            const int32_t t = __shfl_up(incl, off);
-            if (lane >= off) incl += t;
-        }
-        if (lane == 63) s_wave[wave] = incl;
-        __syncthreads();
-        int32_t before = 0;
-        for (int w = 0; w < wave; ++w) before += s_wave[w];
-        first = before + incl - slots;
-        if (tid < kHaloCells) {
-            clo[tid] = first;
-            cnum[tid] = num;
-            cgb[tid] = gbeg;
+#pragma unroll
+        for (int w = 0; w < kCellRounds; ++w) {
+            const int32_t slots = tid + w * NT < kHaloCells ? num[w] + kPad : 0;
+            int32_t incl = slots;
+            for (int off = 1; off < 64; off <<= 1) {
+                const int32_t t = __shfl_up(incl, off);
+                if (lane >= off) incl += t;
+            }
+            first[w] = H + incl - slots;
+            if (NT == 64) {
+                H += __shfl(incl, 63);
+                continue;
+            }
+            if (lane == 63) s_wave[wave] = incl;
+            __syncthreads();
+            for (int t = 0; t < NT / 64; ++t) {
+                if (t < wave) first[w] += s_wave[t];
+                H += s_wave[t];
+            }
         }
     }
-    const int32_t H = s_wave[0] + s_wave[1] + s_wave[2] + s_wave[3];
     // the largest shell (an atomic only when this one is larger than the record)
-    if (hmax && tid == 0 && H > __hip_atomic_load(hmax, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-        atomicMax(hmax, H);
+    if (hmax && tid == 0) {
+        const int32_t Hr = H + (1 - kPad) * kHaloCells;  // recorded with the pads of the 256-thread form
+        if (Hr > __hip_atomic_load(hmax, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(hmax, Hr);
+    }
     if (H > cap) {  // shell too large for LDS: global candidate path for this brick
-        __syncthreads();  // every thread has read s_wave
+        __syncthreads();  // every thread has read s_wave (the slots alias nothing else in use)
         int32_t *glist = reinterpret_cast<int32_t *>(smem4);  // the slot arrays are unused on this path
-        for (int64_t q = gb + tid; q < ge; q += 256)
-            contact_global<T, CAP>(P, n, x, v, r, cb, ce, q, glist, tid, sr, held, F, ncont, err);
+        for (int64_t q = gb + tid; q < ge; q += NT)
+            contact_global<T, CAP, NT>(P, n, x, v, r, cb, ce, q, glist, tid, sr, held, F, ncont, err);
         return;
     }
     // ---- slot -> shell cell map (pads take their cell's number too)
-    if (tid < kHaloCells)
-        for (int32_t k = first; k < first + slots; ++k) scell[k] = (uint8_t)tid;
+#pragma unroll
+    for (int w = 0; w < kCellRounds; ++w) {
+        const int c = tid + w * NT;
+        if (c >= kHaloCells) continue;
+        clo[c] = (uint16_t)first[w];
+        cnum[c] = (uint16_t)num[w];
+        cgb[c] = gbeg[w];
+        for (int32_t k = first[w]; k < first[w] + num[w] + kPad; ++k) scell[k] = (uint8_t)c;
+    }
     __syncthreads();
     // with liquid bridges the candidate pass looks d_r further: each radius
     // grows by d_r / 2 in Q and b_i, so r_i + r_j grows by d_r
     const float hreach = CAP ? (float)(0.5 * P.dr_max) : 0.0f;
     // ---- copy the shell's granules, relative to the centre, in single precision.
-    // H <= cap < kCopyRounds * 256: all loads of a thread are issued before
+    // H <= cap <= kCopyRounds * NT: all loads of a thread are issued before
     // any of them is used, so they are in flight together.
     {
         double gx[kCopyRounds], gy[kCopyRounds], gz[kCopyRounds], gr[kCopyRounds];
         bool real[kCopyRounds];
 #pragma unroll
         for (int it = 0; it < kCopyRounds; ++it) {
-            const int k = tid + it * 256;
+            const int k = tid + it * NT;
             real[it] = false;
             gx[it] = gy[it] = gz[it] = gr[it] = 0.0;
             if (k < H) {
@@ -561,7 +584,7 @@ k_contact_lds(DevParams P, int64_t n, const int32_t *__restrict__ bl,
         }
 #pragma unroll
         for (int it = 0; it < kCopyRounds; ++it) {
-            const int k = tid + it * 256;
+            const int k = tid + it * NT;
             if (k >= H) continue;
             float4 p;
             if (real[it]) {
@@ -582,7 +605,7 @@ k_contact_lds(DevParams P, int64_t n, const int32_t *__restrict__ bl,
     // neighbour list, so a bed without bridges gives the dry contact's bits
     constexpr int L = 1;
     constexpr int sub = 0;
-    for (int64_t qb = gb; qb < ge; qb += 256) {  // same trip count in every lane
+    for (int64_t qb = gb; qb < ge; qb += NT) {  // same trip count in every lane
         const int64_t q = qb + tid;
         const bool live = q < ge;
         T acc[3] = {(T)0, (T)0, (T)0};
@@ -642,14 +665,14 @@ k_contact_lds(DevParams P, int64_t n, const int32_t *__restrict__ bl,
 #pragma unroll
                         for (int u = 0; u < kCand; ++u) {
                             if (k + u < k1 && k + u != kself && near_slot(p[u], mx, my, mz, thr)) {
-                                if (cnt < kLdsPartners) plist[cnt * 256 + tid] = (uint16_t)(k + u);
+                                if (cnt < kLdsPartners) plist[cnt * NT + tid] = (uint16_t)(k + u);
                                 ++cnt;
                             }
                         }
                     }
                 });
                 auto global_of = [&](int k) { const int c = scell[k]; return (int64_t)cgb[c] + (k - clo[c]); };
-                if (cnt <= kLdsPartners) lds_list_canonical(plist + tid, cnt, q, global_of);
+                if (cnt <= kLdsPartners) lds_list_canonical<NT>(plist + tid, cnt, q, global_of);
                 vi[0] = v[q];
                 vi[1] = v[n + q];
                 vi[2] = v[2 * n + q];
@@ -659,8 +682,8 @@ k_contact_lds(DevParams P, int64_t n, const int32_t *__restrict__ bl,
                     for (int i = 0; i < cnt; i += 2) {
                         // two partners per round, their loads in flight together
                         const bool two = i + 1 < cnt;
-                        const int32_t j0 = (int32_t)global_of(plist[i * 256 + tid]);
-                        const int32_t j1 = two ? (int32_t)global_of(plist[(i + 1) * 256 + tid]) : j0;
+                        const int32_t j0 = (int32_t)global_of(plist[i * NT + tid]);
+                        const int32_t j1 = two ? (int32_t)global_of(plist[(i + 1) * NT + tid]) : j0;
                         const Partner p0 = fetch_partner(n, x, v, r, j0);
                         const Partner p1 = fetch_partner(n, x, v, r, j1);
                         nc += exact_pair<T, CAP>(P, xi, vi, ri, mi, q, j0, p0, sri, sr, held, acc);
@@ -1025,12 +1048,13 @@ __global__ void __launch_bounds__(kListThreads) k_contact_list(DevParams P, int6
 
 }  // namespace
 
-// LDS bytes of the staged contact kernel for a shell capacity of cap granules.
-static size_t contact_lds_bytes(int cap)
+// LDS bytes of the staged contact kernel of nt threads for a shell capacity of
+// cap granules.
+static size_t contact_lds_bytes(int cap, int nt)
 {
-    size_t b = (size_t)(cap + kCand) * sizeof(float4) + (size_t)cap + sizeof(uint16_t) * kLdsPartners * 256 +
-               sizeof(int32_t) * (kHaloCells * 3 + 4);
-    const size_t fallback = sizeof(int32_t) * kMaxPartners * 256;  // list of the global path, aliasing the slots
+    const size_t b = (size_t)(cap + kCand) * sizeof(float4) + (size_t)cap + sizeof(uint16_t) * kLdsPartners * nt +
+                     (sizeof(int32_t) + 2 * sizeof(uint16_t)) * kHaloCells + 4 * sizeof(int32_t);
+    const size_t fallback = sizeof(int32_t) * kMaxPartners * nt;  // list of the global path, aliasing the slots
     return b > fallback ? b : fallback;
 }
 
@@ -1049,23 +1073,45 @@ static int shell_cap(const SizeRecord *ss)
     return want < kShellCapMax ? (int)want : kShellCapMax;
 }
 
+template <typename T, bool CAP, int NT>
+static void contact_kernel(const DevParams &P, int64_t n, const double *x, const double *v, const double *r,
+                           const int32_t *cb, const int32_t *ce, const BrickList &B, const T *sr, const double *held,
+                           T *F, int32_t *ncont, int64_t *err, hipStream_t s, int cap, int32_t *hm, int32_t *hc, int only)
+{
+    const int64_t nbricks = (int64_t)P.nb[0] * P.nb[1] * P.nb[2];
+    k_contact_lds<T, CAP, NT><<<brick_grid(nbricks), NT, contact_lds_bytes(cap, NT), s>>>(
+        P, n, B.list, B.count, cap, x, v, r, cb, ce, sr, held, F, ncont, err, hm, hc, only);
+}
+
 template <typename T>
 hipError_t launch_contact(const DevParams &P, int64_t n, const double *x, const double *v, const double *r,
                           const int32_t *cb, const int32_t *ce, const BrickList &B, const T *sr, const double *held,
                           T *F, int32_t *ncont, int64_t *err, hipStream_t s, SizeRecord *ss)
 {
     if (n == 0) return hipSuccess;
-    const int64_t nbricks = (int64_t)P.nb[0] * P.nb[1] * P.nb[2];
     const int cap = shell_cap(ss);
     const bool copy = record_copy(ss);  // only these calls record (the stores contend)
-    int32_t *hm = copy ? ss->dev + ss->par * kRecSlots : nullptr;
-    int32_t *hc = copy ? ss->dev + (ss->par ^ 1) * kRecSlots : nullptr;
-    if (sr)
-        k_contact_lds<T, true><<<brick_grid(nbricks), 256, contact_lds_bytes(cap), s>>>(
-            P, n, B.list, B.count, cap, x, v, r, cb, ce, sr, held, F, ncont, err, hm, hc);
-    else
-        k_contact_lds<T, false><<<brick_grid(nbricks), 256, contact_lds_bytes(cap), s>>>(
-            P, n, B.list, B.count, cap, x, v, r, cb, ce, nullptr, nullptr, F, ncont, err, hm, hc);
+    int32_t *hm = copy ? ss->dev + ss->par : nullptr;
+    int32_t *hc = copy ? ss->dev + (ss->par ^ 1) : nullptr;
+    const FillMode mode = fill_mode(P, n, B);
+    if (mode != kFillBlock) {
+        // no empty slots in the wave's shell; without a record, room for the
+        // 216 cells of a shell at 1.7 granules each
+        const int wc = cap == kShellCapMax ? 368 : cap - kHaloCells * kPad;
+        const int wcap = wc < kCopyRounds * 64 ? wc : kCopyRounds * 64;
+        const int only = mode == kFillBoth ? 1 : 0;
+        if (sr)
+            contact_kernel<T, true, 64>(P, n, x, v, r, cb, ce, B, sr, held, F, ncont, err, s, wcap, hm, hc, only);
+        else
+            contact_kernel<T, false, 64>(P, n, x, v, r, cb, ce, B, sr, held, F, ncont, err, s, wcap, hm, hc, only);
+    }
+    if (mode != kFillWave) {
+        const int only = mode == kFillBoth ? 2 : 0;
+        if (sr)
+            contact_kernel<T, true, 256>(P, n, x, v, r, cb, ce, B, sr, held, F, ncont, err, s, cap, hm, hc, only);
+        else
+            contact_kernel<T, false, 256>(P, n, x, v, r, cb, ce, B, sr, held, F, ncont, err, s, cap, hm, hc, only);
+    }
     hipError_t e = hipGetLastError();
     if (copy) {
         ss->par ^= 1;

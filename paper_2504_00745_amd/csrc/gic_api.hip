@@ -37,9 +37,8 @@ struct gic_ctx {
     bool live_ok;
     const int64_t *live_a, *live_m;
     // the largest brick shell of the direct contact kernel, for the size of
-    // its shell array, and the most granules in a brick of the P2G tile
-    // kernel, for its workgroup size (device records, pinned host copies)
-    SizeRecord shell, brick_n;
+    // its shell array (device record, pinned host copy)
+    SizeRecord shell;
     // The list holds the stepping path's state when nl_n == n and the state
     // to step is the array that the last step wrote (nl_x): its sorted
     // order is the one of the list's last build or check.
@@ -228,13 +227,13 @@ constexpr int64_t kSumNoallocMax = (int64_t)kSumParts << 20;
 
 // The brick schedule of the cell ranges a call is given, built on the stream
 // before its brick kernel; gic_step builds it once after its sort.
-hipError_t brick_list(gic_ctx *c, const int32_t *cb, const int32_t *ce, hipStream_t s)
+hipError_t brick_list(gic_ctx *c, int64_t n, const int32_t *cb, const int32_t *ce, hipStream_t s)
 {
     if (c->in_step) return hipSuccess;
     if (c->bl_pin && c->bl_cb == cb && c->bl_ce == ce) return hipSuccess;  // kept by gic_brick_list
     c->bl_pin = false;
     c->rng_ok = false;  // the brick list is now that of these tables
-    return launch_brick_list(cb, ce, c->bricks, s);
+    return launch_brick_list(cb, ce, c->bricks, n, s);
 }
 
 // Sort of a stepping call: keeps the neighbour list when the last step's
@@ -247,7 +246,7 @@ hipError_t step_sort(gic_ctx *c, int64_t n, const double *x, uint32_t *key, int3
     c->rng_ok = false;
     c->bl_pin = false;
     hipError_t e = launch_sort_cells(c->dp, n, x, key, order, cb, ce, c->K, c->sort, c->err, s, &c->nl, force, keep);
-    if (e == hipSuccess && n > 0) e = launch_brick_list(cb, ce, c->bricks, s, keep ? c->sort.ctl : nullptr);
+    if (e == hipSuccess && n > 0) e = launch_brick_list(cb, ce, c->bricks, n, s, keep ? c->sort.ctl : nullptr);
     if (e == hipSuccess) {
         c->rng_ok = true;
         c->rng_cb = cb;
@@ -409,16 +408,14 @@ gic_status gic_create(const gic_params *p, int64_t n_max, gic_ctx **out)
     ok &= hipMalloc(&c->p2gs.esc, sizeof(int32_t) * nn) == hipSuccess;
     ok &= hipMalloc(&c->esc_n2, sizeof(uint32_t) * 2) == hipSuccess;
     if (ok) ok = hipMemset(c->esc_n2, 0, sizeof(uint32_t) * 2) == hipSuccess;
-    ok &= hipMalloc(&c->shell.dev, sizeof(int32_t) * 2 * kRecSlots) == hipSuccess;
-    if (ok) ok = hipMemset(c->shell.dev, 0, sizeof(int32_t) * 2 * kRecSlots) == hipSuccess;
-    ok &= hipHostMalloc(&c->shell.host, sizeof(int32_t) * kRecSlots, hipHostMallocDefault) == hipSuccess;
-    if (ok)
-        for (int i = 0; i < kRecSlots; ++i) c->shell.host[i] = 0;  // no record yet: the largest shell array
-    ok &= hipMalloc(&c->brick_n.dev, sizeof(int32_t) * 2 * kRecSlots) == hipSuccess;
-    if (ok) ok = hipMemset(c->brick_n.dev, 0, sizeof(int32_t) * 2 * kRecSlots) == hipSuccess;
-    ok &= hipHostMalloc(&c->brick_n.host, sizeof(int32_t) * kRecSlots, hipHostMallocDefault) == hipSuccess;
-    if (ok)
-        for (int i = 0; i < kRecSlots; ++i) c->brick_n.host[i] = 0;  // no record yet: workgroups of 256
+    ok &= hipMalloc(&c->shell.dev, sizeof(int32_t) * 2) == hipSuccess;
+    if (ok) ok = hipMemset(c->shell.dev, 0, sizeof(int32_t) * 2) == hipSuccess;
+    ok &= hipHostMalloc(&c->shell.host, sizeof(int32_t) * 2, hipHostMallocDefault) == hipSuccess;
+    if (ok) {
+        c->shell.host[0] = 0;  // no record yet: the largest shell array
+        c->shell.host[1] = 0;  // and no count of occupied bricks
+        c->bricks.seen = c->shell.host + 1;
+    }
     if (ok && tiles_assemble(p)) {
         // one 4-channel node tile per occupied brick (at most min(bricks, n));
         // beyond 8 GiB the stepping path keeps the cleared grids and atomics
@@ -512,8 +509,6 @@ gic_status gic_destroy(gic_ctx *c)
     (void)hipFree(c->esc_n2);
     (void)hipFree(c->shell.dev);
     (void)hipHostFree(c->shell.host);
-    (void)hipFree(c->brick_n.dev);
-    (void)hipHostFree(c->brick_n.host);
     if (c->tm_ev) {
         for (int i = 0; i < c->tm_cap * kStageEvents; ++i) (void)hipEventDestroy(c->tm_ev[i]);
         delete[] c->tm_ev;
@@ -573,7 +568,7 @@ gic_status gic_brick_list(gic_ctx *c, const int32_t *cell_begin, const int32_t *
 {
     if (!c || !cell_begin || !cell_end) return GIC_E_ARG;
     c->bl_pin = false;
-    const hipError_t e = brick_list(c, cell_begin, cell_end, (hipStream_t)stream);
+    const hipError_t e = brick_list(c, -1, cell_begin, cell_end, (hipStream_t)stream);
     if (e != hipSuccess) return GIC_E_HIP;
     if (!c->in_step) {
         c->bl_pin = true;
@@ -628,7 +623,7 @@ gic_status gic_contact_forces(gic_ctx *c, int64_t n, const double *x, const doub
     if (n > 0 && (!x || !v || !r || !cell_begin || !cell_end || !f_contact)) return GIC_E_ARG;
     hipStream_t s = (hipStream_t)stream;
     if (n == 0) return GIC_OK;
-    if (brick_list(c, cell_begin, cell_end, s) != hipSuccess) return GIC_E_HIP;
+    if (brick_list(c, n, cell_begin, cell_end, s) != hipSuccess) return GIC_E_HIP;
     c->nl_n = -1;  // the list now belongs to these arrays, not to the stepping path
     return contact_impl(c, n, x, v, r, cell_begin, cell_end, f_contact, n_contacts, pair_cap > 0 ? pair_ids : nullptr,
                         pair_cap, 1, s);
@@ -643,14 +638,12 @@ gic_status gic_contact_capillary_forces(gic_ctx *c, int64_t n, const double *x, 
     if (n > 0 && (!x || !v || !r || !sr || !cell_begin || !cell_end || !f_contact)) return GIC_E_ARG;
     hipStream_t s = (hipStream_t)stream;
     if (n == 0) return GIC_OK;
-    if (brick_list(c, cell_begin, cell_end, s) != hipSuccess) return GIC_E_HIP;
+    if (brick_list(c, n, cell_begin, cell_end, s) != hipSuccess) return GIC_E_HIP;
     if (fp32(c))
         return hip_status(launch_contact<float>(c->dp, n, x, v, r, cell_begin, cell_end, c->bricks,
-                                                (const float *)sr, held, (float *)f_contact, n_contacts, c->err,
-                                                s, &c->shell));
+                                                (const float *)sr, held, (float *)f_contact, n_contacts, c->err, s, &c->shell));
     return hip_status(launch_contact<double>(c->dp, n, x, v, r, cell_begin, cell_end, c->bricks,
-                                             (const double *)sr, held, (double *)f_contact, n_contacts, c->err, s,
-                                             &c->shell));
+                                             (const double *)sr, held, (double *)f_contact, n_contacts, c->err, s, &c->shell));
 }
 
 gic_status gic_moisture_ratio(gic_ctx *c, int64_t n, const double *held, const void *alpha_f, void *sr,
@@ -729,7 +722,7 @@ gic_status gic_p2g(gic_ctx *c, int64_t n, const double *x, const double *v, cons
         if (e != hipSuccess) return GIC_E_HIP;
     }
     if (n == 0) return GIC_OK;
-    if (brick_list(c, cell_begin, cell_end, s) != hipSuccess) return GIC_E_HIP;
+    if (brick_list(c, n, cell_begin, cell_end, s) != hipSuccess) return GIC_E_HIP;
     return hip_status(
         launch_p2g_fixed(c->dp, n, c->K, x, v, r, cell_begin, cell_end, c->bricks, alpha_fx, mom_fx, c->err, s));
 }
@@ -741,7 +734,7 @@ gic_status gic_p2g_real(gic_ctx *c, int64_t n, const double *x, const double *v,
     if (!n_ok(c, n) || (!alpha && !mom)) return GIC_E_ARG;
     if (n > 0 && (!x || !r || !cell_begin || !cell_end || (mom && !v))) return GIC_E_ARG;
     hipStream_t s = (hipStream_t)stream;
-    if (n > 0 && brick_list(c, cell_begin, cell_end, s) != hipSuccess) return GIC_E_HIP;
+    if (n > 0 && brick_list(c, n, cell_begin, cell_end, s) != hipSuccess) return GIC_E_HIP;
     return hip_status(launch_p2g_real(c->dp, n, c->K, x, v, r, cell_begin, cell_end, c->bricks, alpha, mom,
                                       accumulate ? 1 : 0, c->fxs, c->fxp, s));
 }
@@ -757,12 +750,11 @@ gic_status gic_gather_g2p_drag(gic_ctx *c, int64_t n, const int32_t *order, cons
     if ((id == nullptr) != (id_out == nullptr) || (u_at == nullptr) != (alpha_f == nullptr)) return GIC_E_ARG;
     hipStream_t s = (hipStream_t)stream;
     if (n == 0) return GIC_OK;
-    if (brick_list(c, cell_begin, cell_end, s) != hipSuccess) return GIC_E_HIP;
+    if (brick_list(c, n, cell_begin, cell_end, s) != hipSuccess) return GIC_E_HIP;
     if (fp32(c))
         return hip_status(launch_gather_g2p_drag<float>(c->dp, n, c->K, order, x, v, r, id, x_out, v_out, r_out,
                                                         id_out, (const float *)u, alpha_fx, cell_begin, cell_end,
-                                                        c->bricks, (float *)f_drag, (float *)u_at, (float *)alpha_f,
-                                                        s));
+                                                        c->bricks, (float *)f_drag, (float *)u_at, (float *)alpha_f, s));
     return hip_status(launch_gather_g2p_drag<double>(c->dp, n, c->K, order, x, v, r, id, x_out, v_out, r_out, id_out,
                                                      (const double *)u, alpha_fx, cell_begin, cell_end, c->bricks,
                                                      (double *)f_drag, (double *)u_at, (double *)alpha_f, s));
@@ -784,7 +776,7 @@ static gic_status integrate_p2g_impl(gic_ctx *c, int64_t n, double *x, double *v
         if (e != hipSuccess) return GIC_E_HIP;
     }
     if (n == 0) return GIC_OK;
-    if (brick_list(c, cell_begin, cell_end, s) != hipSuccess) return GIC_E_HIP;
+    if (brick_list(c, n, cell_begin, cell_end, s) != hipSuccess) return GIC_E_HIP;
     if (fp32(c))
         return hip_status(launch_integrate_p2g<float>(c->dp, n, c->K, x, v, r, (const float *)f_contact,
                                                       (const float *)f_drag, cell_begin, cell_end, c->bricks,
@@ -835,7 +827,7 @@ static gic_status step_integrate_p2g(gic_ctx *c, int64_t n, double *x, double *v
         stage_mark(c, 6, s);
         return st;
     }
-    if (brick_list(c, cell_begin, cell_end, s) != hipSuccess) return GIC_E_HIP;
+    if (brick_list(c, n, cell_begin, cell_end, s) != hipSuccess) return GIC_E_HIP;
     stage_mark(c, 5, s);
     P2GStore st = c->p2gs;
     st.full = c->live_ok && c->live_a == alpha_fx && c->live_m == mom_fx ? 0 : 1;
@@ -845,12 +837,11 @@ static gic_status step_integrate_p2g(gic_ctx *c, int64_t n, double *x, double *v
     hipError_t e;
     if (fp32(c))
         e = launch_integrate_p2g_store<float>(c->dp, n, c->K, x, v, r, (const float *)f_contact,
-                                              (const float *)f_force, cell_begin, cell_end, c->bricks, c->err, s, st,
-                                              &c->brick_n);
+                                              (const float *)f_force, cell_begin, cell_end, c->bricks, c->err, s, st);
     else
         e = launch_integrate_p2g_store<double>(c->dp, n, c->K, x, v, r, (const double *)f_contact,
                                                (const double *)f_force, cell_begin, cell_end, c->bricks, c->err, s,
-                                               st, &c->brick_n);
+                                               st);
     if (e != hipSuccess) return hip_status(e);
     stage_mark(c, 6, s);
     e = launch_p2g_assemble(c->dp, n, x, v, r, c->bricks, alpha_fx, mom_fx, c->err, s, st, next);
@@ -971,16 +962,14 @@ gic_status gic_gather_g2p_fluid(gic_ctx *c, int64_t n, const int32_t *order, con
         return GIC_E_ARG;
     hipStream_t s = (hipStream_t)stream;
     if (n == 0) return GIC_OK;
-    if (brick_list(c, cell_begin, cell_end, s) != hipSuccess) return GIC_E_HIP;
+    if (brick_list(c, n, cell_begin, cell_end, s) != hipSuccess) return GIC_E_HIP;
     if (fp32(c))
         return hip_status(launch_gather_g2p_fluid<float>(
             c->dp, n, c->K, order, x, v, r, id, x_out, v_out, r_out, id_out, (const float *)u, alpha_fx,
-            (const float *)grad_p, (const float *)acc_f, cell_begin, cell_end, c->bricks, (float *)f_fluid, s, held,
-            held_out));
+            (const float *)grad_p, (const float *)acc_f, cell_begin, cell_end, c->bricks, (float *)f_fluid, s, held, held_out));
     return hip_status(launch_gather_g2p_fluid<double>(
         c->dp, n, c->K, order, x, v, r, id, x_out, v_out, r_out, id_out, (const double *)u, alpha_fx,
-        (const double *)grad_p, (const double *)acc_f, cell_begin, cell_end, c->bricks, (double *)f_fluid, s, held,
-        held_out));
+        (const double *)grad_p, (const double *)acc_f, cell_begin, cell_end, c->bricks, (double *)f_fluid, s, held, held_out));
 }
 
 gic_status gic_exchange_p2g(gic_ctx *c, int64_t n, const double *x, const double *r, const void *f_contact,
@@ -993,7 +982,7 @@ gic_status gic_exchange_p2g(gic_ctx *c, int64_t n, const double *x, const double
     hipStream_t s = (hipStream_t)stream;
     grids_written(c, fs_fx, 3 * c->dp.G);
     if (n == 0) return GIC_OK;
-    if (brick_list(c, cell_begin, cell_end, s) != hipSuccess) return GIC_E_HIP;
+    if (brick_list(c, n, cell_begin, cell_end, s) != hipSuccess) return GIC_E_HIP;
     const double exsc = -weight / c->p.f_unit;
     if (fp32(c))
         return hip_status(launch_exchange_p2g<float>(c->dp, n, c->K, x, r, (const float *)f_contact,
@@ -1107,7 +1096,7 @@ gic_status gic_g2p_vjp(gic_ctx *c, int64_t n, const double *x, const double *u, 
     if (!n_ok(c, n) || fp32(c)) return GIC_E_ARG;
     if (n > 0 && (!x || !u || !alpha_real || !g_u_at || !g_alpha_f || !g_x)) return GIC_E_ARG;
     if (n > 0 && g_alpha && (!cell_begin || !cell_end)) return GIC_E_ARG;
-    if (n > 0 && g_alpha && brick_list(c, cell_begin, cell_end, (hipStream_t)stream) != hipSuccess)
+    if (n > 0 && g_alpha && brick_list(c, n, cell_begin, cell_end, (hipStream_t)stream) != hipSuccess)
         return GIC_E_HIP;
     return hip_status(launch_g2p_vjp(c->dp, n, c->K, x, u, alpha_real, g_u_at, g_alpha_f, cell_begin, cell_end,
                                      c->bricks, g_x, g_alpha, c->fxs, c->fxp, (hipStream_t)stream));

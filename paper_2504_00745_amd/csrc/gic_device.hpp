@@ -61,6 +61,14 @@ __device__ inline int64_t brick_of_block(const int32_t *__restrict__ list, const
     return j < per && l < nocc ? list[l] : -1;
 }
 
+// One of two kernels that were both launched (see fill_mode) leaves at once:
+// only = 1 runs when an occupied brick holds at most `per` granules on
+// average, only = 2 when it holds more, only = 0 always.
+__device__ inline bool not_mine(int only, int64_t per, int64_t n, const int32_t *__restrict__ count)
+{
+    return only != 0 && (n <= per * (int64_t)*count) != (only == 1);
+}
+
 // Brick kernels that loop: workgroup b takes the entries j = b / kXcds +
 // it * (gridDim.x / kXcds), it = 0, 1, ..., of its XCD's eighth of the list
 // (the same split as brick_of_block); -1 when it has no more.  The grid is
@@ -434,6 +442,13 @@ __device__ inline uint64_t rint_biased(double v)
 #pragma clang fp contract(off)
     const double M = 6755399441055744.0;
     return (uint64_t)__double_as_longlong(v + M);
+}
+
+// The integer of such a pattern: the bias has no low word, so one 32-bit
+// subtraction from the high word.
+__device__ inline uint64_t unbiased(uint64_t b)
+{
+    return ((uint64_t)((uint32_t)(b >> 32) - (uint32_t)(kRintBias >> 32)) << 32) | (uint32_t)b;
 }
 
 // Bit pattern of the nearest integer (ties to even) to the exact product

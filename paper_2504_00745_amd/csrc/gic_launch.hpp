@@ -41,12 +41,17 @@ struct BrickList {
     uint32_t *sums;    // [<= 1024] block totals
     int32_t *slot_of;  // [nbricks] position of each brick in list, -1 if empty
     int64_t nbricks;
+    int32_t *seen;     // [1] pinned host: a copy of count (see brick_fill), of a list of seen_n granules
+    int64_t seen_n;
+    unsigned calls;
 };
 
 // skip (optional): the sort's control words; the list is kept when the sort
 // found no changed key (the caller checked that cb, ce are the tables the
 // list was built from).
-hipError_t launch_brick_list(const int32_t *cb, const int32_t *ce, BrickList &B, hipStream_t s,
+// n: granules of the tables, or -1 when the caller does not know (no copy of
+// the count to the host then).
+hipError_t launch_brick_list(const int32_t *cb, const int32_t *ce, BrickList &B, int64_t n, hipStream_t s,
                              const int32_t *skip = nullptr);
 
 // Persistent neighbour list of the contact stage (owned by a context): for
@@ -97,19 +102,14 @@ hipError_t launch_sort_cells(const DevParams &P, int64_t n, const double *x, uin
 hipError_t launch_reorder(int64_t n, const int32_t *order, const double *x, const double *v, const double *r,
                           const int32_t *id, double *xo, double *vo, double *ro, int32_t *ido, hipStream_t s);
 
-// The largest size a brick kernel met: dev[2][kRecSlots] (device,
-// alternating between recording calls: one records into dev[par] and clears
-// dev[par ^ 1]), host[kRecSlots] (pinned: a copy of the record, read by
-// later calls without waiting; zeros until the first copy lands).  Only
-// every 16th call records and copies (a copy costs a few microseconds of
-// the stream).  The direct contact kernel keeps the largest brick shell
-// (granule slots, pads included) in the first word (an atomic maximum,
-// taken only when the word is smaller); the P2G tile kernel keeps flags of
-// the granules of its bricks by steps of 64 (a brick of v granules sets
-// flag ceil(v / 64) with a plain store).  The next launches are shaped from
-// the record; a brick beyond the shape takes a slower path with the same
-// bits, and the calls after adapt.
-constexpr int kRecSlots = 64;  // flags of sizes up to 64 (kRecSlots - 1)
+// The largest brick shell (granule slots, pads included) that the direct
+// contact kernel met: dev[2] (device, alternating between recording calls: one
+// records into dev[par] and clears dev[par ^ 1]; an atomic maximum, taken only
+// when the word is smaller), host (pinned: a copy of the record, read by later
+// calls without waiting; 0 until the first copy lands).  Only every 16th call
+// records and copies (a copy costs a few microseconds of the stream).  The
+// next launches are shaped from the record; a brick beyond the shape takes a
+// slower path with the same bits, and the calls after adapt.
 struct SizeRecord {
     int32_t *dev;
     int32_t *host;
@@ -121,21 +121,43 @@ inline bool record_copy(SizeRecord *r)
 {
     return r && r->host && (r->calls++ & 15u) == 0u;
 }
-// An upper bound (a multiple of 64) of the largest size in the last copy
-// that reached the host (0: none yet).
-inline int32_t record_seen(const SizeRecord *r)
+
+// The granules that an occupied brick holds on average, for the shape of the
+// brick kernels: from the last count of occupied bricks that reached the host
+// (every 16th list of n granules copies it, read without waiting), or, before
+// the first (known false), the granules of radius r_max that its 64 cells hold
+// on a cubic lattice.
+struct BrickFill {
+    double avg;
+    bool known;
+};
+inline BrickFill brick_fill(const DevParams &P, int64_t n, const BrickList &B)
 {
-    if (!r || !r->host) return 0;
-    int32_t m = 0;
-    for (int i = 0; i < kRecSlots; ++i)
-        if (((volatile const int32_t *)r->host)[i]) m = 64 * i;
-    return m;
+    const int32_t seen = B.seen && B.seen_n == n ? *(volatile const int32_t *)B.seen : 0;
+    if (seen > 0) return {(double)n / seen, true};
+    const double e = 0.5 * P.cell / P.r_max;
+    return {kBrickCells * ((e * e) * e), false};
 }
-// The flag of size v (the last flag for sizes beyond the table).
-__host__ __device__ inline int record_flag(int32_t v)
+// Whether the gather, the direct contact and the direct P2G run one wave per
+// brick (workgroups of 64 threads) instead of 256 threads.  A 256-thread
+// workgroup leaves three of its four waves idle when a brick holds about one
+// granule per lane of a wave, and the chip holds a quarter of the bricks:
+// 16.8 million granules at 64 a brick take 0.89, 1.04 and 0.92 ms instead of
+// 1.25, 1.88 and 1.70 (gather, contact, P2G, FP32); at 205 a brick the wave
+// loops over its brick and takes 25 and 32 us instead of 19 and 26 (gather,
+// P2G).  With fewer bricks than the chip holds of the larger workgroups (1,024)
+// more threads per brick are faster (216 bricks: 7.8 and 7.2 against 6.4 and
+// 6.5 us; 1,728 bricks: 11.0 and 12.8 against 11.9 and 15.4).
+// kFillBoth: not known yet (a first call) and plausible: both kernels are
+// launched and the device's count of occupied bricks picks one.
+constexpr int64_t kWaveFill = 80;
+constexpr int64_t kWaveBricks = 1024;
+enum FillMode { kFillBlock = 0, kFillWave = 1, kFillBoth = 2 };
+inline FillMode fill_mode(const DevParams &P, int64_t n, const BrickList &B)
 {
-    const int32_t f = (v + 63) / 64;
-    return f < kRecSlots - 1 ? (f > 0 ? f : 0) : kRecSlots - 1;
+    const BrickFill f = brick_fill(P, n, B);
+    if (f.avg > kWaveFill || n < kWaveBricks * kBrickCells) return kFillBlock;
+    return f.known ? kFillWave : kFillBoth;
 }
 template <typename T>
 hipError_t launch_contact(const DevParams &P, int64_t n, const double *x, const double *v, const double *r,
@@ -179,9 +201,6 @@ struct P2GStore {
     // deposited there since; NULL: every node is written
     uint8_t *live;
     int full;  // 1: write every node (the grids hold no earlier assembly's values)
-    // the tile kernel's record of the most granules in a brick (max into
-    // nrec, clear nclr for the next call); NULL: none
-    int32_t *nrec, *nclr;
 };
 // The table P2GStore::cover for the parameters P (host; 4 (n0 + n1 + n2)
 // int32): for node i of axis a, at 4 (n0 + ... + n_{a-1} + i), the bricks
@@ -200,7 +219,7 @@ template <typename T>
 hipError_t launch_integrate_p2g_store(const DevParams &P, int64_t n, int64_t K, double *x, double *v,
                                       const double *r, const T *Fc, const T *Fd, const int32_t *cb,
                                       const int32_t *ce, const BrickList &B, int64_t *err, hipStream_t s,
-                                      const P2GStore &st, SizeRecord *rec = nullptr);
+                                      const P2GStore &st);
 hipError_t launch_p2g_assemble(const DevParams &P, int64_t n, const double *x, const double *v, const double *r,
                                const BrickList &B, int64_t *alpha, int64_t *mom, int64_t *err, hipStream_t s,
                                const P2GStore &st, uint32_t *esc_next);

@@ -637,7 +637,8 @@ hipError_t launch_sort_cells(const DevParams &P, int64_t n, const double *x, uin
     return hipGetLastError();
 }
 
-hipError_t launch_brick_list(const int32_t *cb, const int32_t *ce, BrickList &B, hipStream_t s, const int32_t *skip)
+hipError_t launch_brick_list(const int32_t *cb, const int32_t *ce, BrickList &B, int64_t n, hipStream_t s,
+                             const int32_t *skip)
 {
     const int64_t nb = B.nbricks;
     if (nb <= 0) return hipSuccess;
@@ -647,7 +648,13 @@ hipError_t launch_brick_list(const int32_t *cb, const int32_t *ce, BrickList &B,
     k_brick_count<<<blocks, 256, 0, s>>>(nb, per, cb, ce, B.sums, skip);
     k_brick_spine<<<1, kScanThreads, 0, s>>>(B.sums, blocks, B.count, skip);
     k_brick_scatter<<<blocks, 256, 0, s>>>(nb, per, cb, ce, B.sums, B.list, B.slot_of, skip);
-    return hipGetLastError();
+    hipError_t e = hipGetLastError();
+    if (n > 0 && B.seen && (B.calls++ & 15u) == 0u) {  // see brick_fill
+        if (e == hipSuccess) e = hipMemcpyAsync(B.seen, B.count, sizeof(int32_t), hipMemcpyDeviceToHost, s);
+        if (B.seen_n != n) *(volatile int32_t *)B.seen = 0;  // a copy of other tables until this one lands
+        B.seen_n = n;
+    }
+    return e;
 }
 
 hipError_t launch_reorder(int64_t n, const int32_t *order, const double *x, const double *v, const double *r,

@@ -97,10 +97,11 @@ __global__ void __launch_bounds__(NT) k_gather(DevParams P, int64_t n, const int
                                                const T *__restrict__ gp, const T *__restrict__ fa,
                                                const int32_t *__restrict__ cb, const int32_t *__restrict__ ce,
                                                T *__restrict__ Ff, T *__restrict__ uat, T *__restrict__ af,
-                                               const double *__restrict__ held, double *__restrict__ heldo)
+                                               const double *__restrict__ held, double *__restrict__ heldo, int only)
 {
     using V4 = typename Node4<T>::type;
     extern __shared__ double smem_d[];
+    if (not_mine(only, kWaveFill, n, bcnt)) return;
     const int64_t b = brick_of_block(bl, bcnt);
     if (b < 0) return;
     int32_t gb = cb[b * kBrickCells], ge = ce[b * kBrickCells + kBrickCells - 1];
@@ -234,6 +235,7 @@ __global__ void __launch_bounds__(NT) k_gather(DevParams P, int64_t n, const int
     }
 }
 
+// Threads per workgroup: see fill_mode.
 template <typename T, bool FLUID>
 hipError_t launch_gather(const DevParams &P, int64_t n, int64_t K, const int32_t *order, const double *x,
                          const double *v, const double *r, const int32_t *id, double *xo, double *vo, double *ro,
@@ -245,8 +247,13 @@ hipError_t launch_gather(const DevParams &P, int64_t n, int64_t K, const int32_t
     const unsigned grid = brick_grid(K / kBrickCells);
     const size_t E3 = (size_t)P.tile * P.tile * P.tile;
     const size_t lds = sizeof(T) * (FLUID ? 7 : 4) * E3;
-    k_gather<T, FLUID, 256><<<grid, 256, lds, s>>>(P, n, B.list, B.count, order, x, v, r, id, xo, vo, ro, ido, u, afx, gp,
-                                                   fa, cb, ce, Ff, uat, af, held, heldo);
+#define GIC_GATHER(NT, ONLY)                                                                                       \
+    k_gather<T, FLUID, NT><<<grid, NT, lds, s>>>(P, n, B.list, B.count, order, x, v, r, id, xo, vo, ro, ido, u, afx, \
+                                                 gp, fa, cb, ce, Ff, uat, af, held, heldo, ONLY)
+    const FillMode mode = fill_mode(P, n, B);
+    if (mode != kFillBlock) GIC_GATHER(64, mode == kFillBoth ? 1 : 0);
+    if (mode != kFillWave) GIC_GATHER(256, mode == kFillBoth ? 2 : 0);
+#undef GIC_GATHER
     return hipGetLastError();
 }
 

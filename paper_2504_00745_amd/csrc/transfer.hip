@@ -77,17 +77,9 @@ __device__ inline void tile_add(unsigned long long *tile, unsigned long long *gl
         __hip_atomic_fetch_add(&glob[gidx], (unsigned long long)val, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// One workgroup per brick, granules taken in batches.  Phase 1 (a thread per
-// granule) stores the stencil base, the offsets f of the 1-D weights and the
-// scaled totals S of each channel in LDS.  Consecutive sorted granules with
-// the same stencil base form a run; they share all 27 nodes.  Phase 2 (a
-// thread per run and channel) walks the run's granules, rounds each outer
-// contribution w S (once, from the exact product: one fused multiply-add)
-// and sums it in one of 26 register accumulators; the
-// centre node gets the run's sum of Q = rint(S) minus the 26 sums, which is
-// the sum over the run's granules of each granule's centre remainder (all
-// integer, so the regrouping is exact).  A run then costs 27 LDS atomics per
-// channel, not 27 per granule.
+// What a granule deposits: its position xa (after the move with INTEG) and
+// the scaled total S of each channel; a total out of range is latched and
+// deposited as zero.
 //
 // INTEG: the move of Sec. 4 is applied first, in place (x, v advanced with
 // the contact and drag forces Fc, Fd, as the integration kernel does), and
@@ -105,10 +97,86 @@ __device__ inline void tile_add(unsigned long long *tile, unsigned long long *gl
 // WET: granules hold water (held, per unit of their volume): the move takes
 // the wet mass of Eq. 19 (and the wet volume in the virtual mass), alpha
 // receives frac (1 + held) and momentum the wet mass's (Sec. 5.3).
-// NT: threads per workgroup (128 serves beds whose bricks hold few granules).
-template <bool MOM, typename T, bool INTEG, bool EXCH = false, bool WET = false, bool STORE = false,
-          int NT = kP2GThreads>
-__global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) k_p2g_fixed(DevParams P, int64_t n, const int32_t *__restrict__ bl,
+template <bool MOM, typename T, bool INTEG, bool EXCH, bool WET, int NCH>
+__device__ inline void granule_terms(const DevParams &P, int64_t n, int64_t q, double *x, double *v,
+                                     const double *__restrict__ r, const T *__restrict__ Fc,
+                                     const T *__restrict__ Fd, int64_t *err, double exsc,
+                                     const double *__restrict__ held, double xa[3], double S[NCH])
+{
+#pragma clang fp contract(off)
+    for (int a = 0; a < 3; ++a) xa[a] = x[a * n + q];
+    double va[3] = {0.0, 0.0, 0.0};
+    if (MOM || INTEG)
+        for (int a = 0; a < 3; ++a) va[a] = v[a * n + q];
+    if (INTEG) {
+        const T fc[3] = {Fc[q], Fc[n + q], Fc[2 * n + q]};
+        const T fd[3] = {Fd[q], Fd[n + q], Fd[2 * n + q]};
+        if (WET)
+            integrate_one_m<T>(P, wet_volume(r[q], held[q]), wet_mass(P, r[q], held[q]), fc, fd, xa, va);
+        else
+            integrate_one<T>(P, r[q], fc, fd, xa, va);
+        for (int a = 0; a < 3; ++a) {
+            x[a * n + q] = xa[a];
+            v[a * n + q] = va[a];
+        }
+    }
+    if constexpr (EXCH) {
+        // wet granules (held given): the wet mass of Eq. 19 and the
+        // volume with the held water (Sec. 5.3)
+        const double rq = r[q];
+        const double hq = held ? held[q] : 0.0;
+        const double m = held ? wet_mass(P, rq, hq) : mass_of(P, rq);
+        const double hv = P.half_rho_f * wet_volume(rq, hq);
+        const double me = m + hv;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            double f = (double)Fd[c * n + q];
+            if (P.vmass) {
+                const double as = (((double)Fc[c * n + q] + f) + m * P.g[c]) / me;
+                f = f - hv * as;
+            }
+            S[c] = (exsc * f) * GIC_TWO32;
+        }
+    } else {
+        const double frac = volume_of(r[q]) * P.inv_vcell;
+        // a wet granule's held water counts as volume in alpha_s
+        // (Sec. 5.3): frac (1 + held), frac exactly when held = 0
+        S[0] = (WET ? frac + frac * held[q] : frac) * GIC_TWO32;
+        // momentum in rho_s dx^3 units: a wet granule (Eq. 19) carries
+        // frac (rho_s + held rho_f) / rho_s = frac + frac held rho_f / rho_s
+        // per unit velocity (held = 0 gives frac exactly)
+        const double fm = WET ? frac + (frac * (held[q] * P.rho_f)) / P.rho_s : frac;
+        if (MOM)
+#pragma unroll
+            for (int c = 1; c < NCH; ++c) S[c] = (fm * va[c - 1]) * GIC_TWO32;
+    }
+    bool ok = true;
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) ok &= fabs(S[c]) < kFixLimit;
+    if (!ok) {
+        double sum = 0.0;
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) sum += S[c];
+        raise_error(err, isfinite(sum) ? kErrRange : kErrNonFinite, q);
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) S[c] = 0.0;
+    }
+}
+
+// One workgroup per brick, granules taken in batches.  Phase 1 (a thread per
+// granule) stores the stencil base, the offsets f of the 1-D weights and the
+// scaled totals S of each channel in LDS.  Consecutive sorted granules with
+// the same stencil base form a run; they share all 27 nodes.  Phase 2 (a
+// thread per run and channel) walks the run's granules, rounds each outer
+// contribution w S (once, from the exact product: one fused multiply-add)
+// and sums it in one of 26 register accumulators; the
+// centre node gets the run's sum of Q = rint(S) minus the 26 sums, which is
+// the sum over the run's granules of each granule's centre remainder (all
+// integer, so the regrouping is exact).  A run then costs 27 LDS atomics per
+// channel, not 27 per granule.
+//
+template <bool MOM, typename T, bool INTEG, bool EXCH, bool WET, bool STORE>
+__global__ void __launch_bounds__(kP2GThreads) __attribute__((amdgpu_waves_per_eu(4))) k_p2g_fixed(DevParams P, int64_t n, const int32_t *__restrict__ bl,
                                                            const int32_t *__restrict__ bcnt, int batch,
                                                            double *x, double *v, const double *__restrict__ r,
                                                            const T *__restrict__ Fc, const T *__restrict__ Fd,
@@ -122,18 +190,17 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) k_
 #pragma clang fp contract(off)
     static_assert(!(EXCH && (MOM || INTEG)), "the exchange deposit is a kind of its own");
     static_assert(!STORE || (MOM && !EXCH && !WET), "the stored tiles serve the dry alpha and momentum deposit");
+    constexpr int NT = kP2GThreads;
     constexpr int NCH = EXCH ? 3 : (MOM ? 4 : 1);
     extern __shared__ unsigned long long tile[];
     __shared__ int32_t s_range[2];
     __shared__ int32_t s_wave[NT / 64];
     int64_t slot;
-    if (STORE && st.nclr && blockIdx.x == 0 && threadIdx.x < kRecSlots) st.nclr[threadIdx.x] = 0;  // the next call's record
     const int64_t b = brick_slot_of_block(bl, bcnt, slot);
     if (b < 0) return;
     brick_range(n, b, cb, ce, s_range);
     __syncthreads();
     const int32_t beg = s_range[0], end = s_range[1];
-    if (STORE && st.nrec && threadIdx.x == 0) st.nrec[record_flag(end - beg)] = 1;  // the brick's granules
     if (end <= beg && !STORE) return;  // (a stored tile is written even if empty)
     const int E = P.tile;
     const int E3 = E * E * E;
@@ -155,22 +222,8 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) k_
         // ---- phase 1: per granule
         for (int i = tid; i < m; i += NT) {
             const int64_t q = b0 + i;
-            double xa[3] = {x[q], x[n + q], x[2 * n + q]};
-            double va[3] = {0.0, 0.0, 0.0};
-            if (MOM || INTEG)
-                for (int a = 0; a < 3; ++a) va[a] = v[a * n + q];
-            if (INTEG) {
-                const T fc[3] = {Fc[q], Fc[n + q], Fc[2 * n + q]};
-                const T fd[3] = {Fd[q], Fd[n + q], Fd[2 * n + q]};
-                if (WET)
-                    integrate_one_m<T>(P, wet_volume(r[q], held[q]), wet_mass(P, r[q], held[q]), fc, fd, xa, va);
-                else
-                    integrate_one<T>(P, r[q], fc, fd, xa, va);
-                for (int a = 0; a < 3; ++a) {
-                    x[a * n + q] = xa[a];
-                    v[a * n + q] = va[a];
-                }
-            }
+            double xa[3], S[NCH];
+            granule_terms<MOM, T, INTEG, EXCH, WET, NCH>(P, n, q, x, v, r, Fc, Fd, err, exsc, held, xa, S);
             bool inside = true;  // all 27 stencil nodes (folded onto the edge) in the tile
             for (int a = 0; a < 3; ++a) {
                 const double t = xa[a] * P.inv_dx;
@@ -190,48 +243,6 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) k_
                 const uint32_t k = atomicAdd(st.esc_n, 1u);
                 if (k < (uint32_t)n) st.esc[k] = (int32_t)q;
                 for (int a = 0; a < 3; ++a) sbase[a * bs + i] = (int16_t)(o[a] + 1);
-            }
-            double S[NCH];
-            if constexpr (EXCH) {
-                // wet granules (held given): the wet mass of Eq. 19 and the
-                // volume with the held water (Sec. 5.3)
-                const double rq = r[q];
-                const double hq = held ? held[q] : 0.0;
-                const double m = held ? wet_mass(P, rq, hq) : mass_of(P, rq);
-                const double hv = P.half_rho_f * wet_volume(rq, hq);
-                const double me = m + hv;
-#pragma unroll
-                for (int c = 0; c < 3; ++c) {
-                    double f = (double)Fd[c * n + q];
-                    if (P.vmass) {
-                        const double as = (((double)Fc[c * n + q] + f) + m * P.g[c]) / me;
-                        f = f - hv * as;
-                    }
-                    S[c] = (exsc * f) * GIC_TWO32;
-                }
-            } else {
-                const double frac = volume_of(r[q]) * P.inv_vcell;
-                // a wet granule's held water counts as volume in alpha_s
-                // (Sec. 5.3): frac (1 + held), frac exactly when held = 0
-                S[0] = (WET ? frac + frac * held[q] : frac) * GIC_TWO32;
-                // momentum in rho_s dx^3 units: a wet granule (Eq. 19) carries
-                // frac (rho_s + held rho_f) / rho_s = frac + frac held rho_f / rho_s
-                // per unit velocity (held = 0 gives frac exactly)
-                const double fm = WET ? frac + (frac * (held[q] * P.rho_f)) / P.rho_s : frac;
-                if (MOM)
-#pragma unroll
-                    for (int c = 1; c < NCH; ++c) S[c] = (fm * va[c - 1]) * GIC_TWO32;
-            }
-            bool ok = true;
-#pragma unroll
-            for (int c = 0; c < NCH; ++c) ok &= fabs(S[c]) < kFixLimit;
-            if (!ok) {
-                double sum = 0.0;
-#pragma unroll
-                for (int c = 0; c < NCH; ++c) sum += S[c];
-                raise_error(err, isfinite(sum) ? kErrRange : kErrNonFinite, q);
-#pragma unroll
-                for (int c = 0; c < NCH; ++c) S[c] = 0.0;
             }
 #pragma unroll
             for (int c = 0; c < NCH; ++c) sS[c * bs + i] = STORE && !inside ? 0.0 : S[c];
@@ -360,6 +371,111 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) k_
         const int32_t ni = o[0] + l % E, nj = o[1] + (l / E) % E, nk = o[2] + l / (E * E);
         atomicAdd(&glob_of(c)[node_index(P, ni, nj, nk)], val);
     }
+}
+
+// The moved and stored deposit for bricks whose granules seldom share a stencil
+// (fewer than about two per node): a thread per granule moves it, rounds all
+// its 26 outer contributions and the centre remainder of every channel and
+// adds them to the node tile, 27 LDS atomics per channel.  The 27 weights are
+// formed once for all channels (a run task of the kernel above forms them per
+// channel), nothing but the tile is held in LDS and there are no barriers
+// between batches; the sums are the same integers.  Bound by the LDS atomics
+// and the rounding (a fused multiply-add and two integer operations per node
+// and channel).  A stencil plane's products at a time are in registers (105,
+// four waves per SIMD; with all 27 nodes unrolled 191 and two).
+template <typename T, int NT>
+__global__ void __launch_bounds__(NT) k_p2g_direct(DevParams P, int64_t n, const int32_t *__restrict__ bl,
+                                                   const int32_t *__restrict__ bcnt, double *x, double *v,
+                                                   const double *__restrict__ r, const T *__restrict__ Fc,
+                                                   const T *__restrict__ Fd, const int32_t *__restrict__ cb,
+                                                   const int32_t *__restrict__ ce, int64_t *err, P2GStore st, int only)
+{
+#pragma clang fp contract(off)
+    constexpr int NCH = 4;
+    extern __shared__ unsigned long long tile[];
+    if (not_mine(only, kWaveFill, n, bcnt)) return;
+    int64_t slot;
+    const int64_t b = brick_slot_of_block(bl, bcnt, slot);
+    if (b < 0) return;
+    int32_t beg = cb[b * kBrickCells], end = ce[b * kBrickCells + kBrickCells - 1];
+    clip_range(n, beg, end);
+    const int E = P.tile;
+    const int E3 = E * E * E;
+    const int tid = threadIdx.x;
+    for (int k = tid; k < NCH * E3; k += NT) tile[k] = 0ull;
+    int32_t o[3];
+    tile_origin(P, b, o);
+    __syncthreads();
+    for (int64_t q = (int64_t)beg + tid; q < end; q += NT) {
+        double xa[3], S[NCH];
+        granule_terms<true, T, true, false, false, NCH>(P, n, q, x, v, r, Fc, Fd, err, 0.0, nullptr, xa, S);
+        double w[3][3];
+        int32_t l[3][3];  // tile coordinates of the stencil's nodes, folded onto the edge
+        bool inside = true;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            const double t = xa[a] * P.inv_dx;
+            double fb = floor(t - 1.0);
+            const double f = (t - fb) - 0.5;
+            if (!(fb >= -2.0)) fb = -2.0;
+            if (fb > (double)P.n[a]) fb = (double)P.n[a];
+            const double c0 = 1.5 - f, c1 = f - 1.0, c2 = f - 0.5;
+            w[a][0] = 0.5 * (c0 * c0);
+            w[a][1] = 0.75 - c1 * c1;
+            w[a][2] = 0.5 * (c2 * c2);
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                int32_t id = (int32_t)fb + k;
+                id = id < 0 ? 0 : id;
+                id = id > P.n[a] - 1 ? P.n[a] - 1 : id;
+                l[a][k] = id - o[a];
+                inside &= l[a][k] >= 0 && l[a][k] < E;
+            }
+        }
+        if (!inside) {  // deposited after the assembly (k_p2g_escapes)
+            const uint32_t k = atomicAdd(st.esc_n, 1u);
+            if (k < (uint32_t)n) st.esc[k] = (int32_t)q;
+            continue;
+        }
+        uint64_t rest[NCH];  // rint(S) minus the outer contributions: the centre's
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) rest[c] = unbiased(rint_biased(S[c]));
+        auto add = [&](int c, int li, uint64_t val) {
+            __hip_atomic_fetch_add(&tile[c * E3 + li], (unsigned long long)val, __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_WORKGROUP);
+        };
+        auto node = [&](double ww, int li) {
+#pragma unroll
+            for (int c = 0; c < NCH; ++c) {
+                const uint64_t val = unbiased(rint_product_biased(ww, S[c]));
+                rest[c] -= val;
+                add(c, li, val);
+            }
+        };
+        // the planes below and above the centre's, then its own
+        double wz = w[2][0];
+        int rz = l[2][0] * E * E;
+#pragma unroll 1
+        for (int cz = 0; cz < 2; ++cz) {
+#pragma unroll
+            for (int cy = 0; cy < 3; ++cy)
+#pragma unroll
+                for (int cx = 0; cx < 3; ++cx) node((w[0][cx] * w[1][cy]) * wz, rz + l[1][cy] * E + l[0][cx]);
+            wz = w[2][2];
+            rz = l[2][2] * E * E;
+        }
+        rz = l[2][1] * E * E;
+#pragma unroll
+        for (int cy = 0; cy < 3; ++cy)
+#pragma unroll
+            for (int cx = 0; cx < 3; ++cx)
+                if (cx != 1 || cy != 1) node((w[0][cx] * w[1][cy]) * w[2][1], rz + l[1][cy] * E + l[0][cx]);
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) add(c, rz + l[1][1] * E + l[0][1], rest[c]);
+    }
+    __syncthreads();
+    unsigned long long *dst = st.tiles + slot * (int64_t)(NCH * E3);
+    for (int k = tid; k < NCH * E3; k += NT) dst[k] = tile[k];
 }
 
 // Grid of the stored tiles (P2G in STORE mode): every node's alpha and
@@ -737,6 +853,22 @@ static size_t p2g_lds(int nch, int E3, int batch)
     return sizeof(unsigned long long) * (size_t)nch * E3 + (size_t)(batch + 1) * (3 * 8 + nch * 8 + 4 + 3 * 2);
 }
 
+// Launches the run kernel of one kind of deposit.
+template <bool MOM, typename T, bool INTEG, bool EXCH, bool WET, bool STORE>
+static void p2g_kernel(const DevParams &P, int64_t n, int64_t K, double *x, double *v, const double *r, const T *Fc,
+                       const T *Fd, const int32_t *cb, const int32_t *ce, const BrickList &B,
+                       unsigned long long *A, unsigned long long *M, int64_t *err, double exsc, const double *held,
+                       const P2GStore &st, hipStream_t s)
+{
+    constexpr int NCH = EXCH ? 3 : (MOM ? 4 : 1);
+    const int E3 = P.tile * P.tile * P.tile;
+    int batch = 512;  // a brick of 64 cells of 8 granules in one batch; 256 run-channel tasks
+    while (batch > 64 && p2g_lds(NCH, E3, batch) > 49152) batch /= 2;
+    k_p2g_fixed<MOM, T, INTEG, EXCH, WET, STORE>
+        <<<brick_grid(K / kBrickCells), kP2GThreads, p2g_lds(NCH, E3, batch), s>>>(
+            P, n, B.list, B.count, batch, x, v, r, Fc, Fd, cb, ce, A, M, err, exsc, held, st);
+}
+
 template <typename T, bool INTEG, bool WET = false>
 static hipError_t p2g_fixed_impl(const DevParams &P, int64_t n, int64_t K, double *x, double *v, const double *r,
                                  const T *Fc, const T *Fd, const int32_t *cb, const int32_t *ce, const BrickList &B,
@@ -744,20 +876,14 @@ static hipError_t p2g_fixed_impl(const DevParams &P, int64_t n, int64_t K, doubl
                                  const double *held = nullptr)
 {
     if (n == 0) return hipSuccess;
-    const int64_t bricks = K / kBrickCells;
-    const int E3 = P.tile * P.tile * P.tile;
-    const int nch = mom ? 4 : 1;
-    int batch = 512;  // a brick of 64 cells of 8 granules in one batch; 256 run-channel tasks
-    while (batch > 64 && p2g_lds(nch, E3, batch) > 49152) batch /= 2;
-    const size_t lds = p2g_lds(nch, E3, batch);
     unsigned long long *A = reinterpret_cast<unsigned long long *>(alpha);
     unsigned long long *M = reinterpret_cast<unsigned long long *>(mom);
     if (mom)
-        k_p2g_fixed<true, T, INTEG, false, WET><<<brick_grid(bricks), kP2GThreads, lds, s>>>(
-            P, n, B.list, B.count, batch, x, v, r, Fc, Fd, cb, ce, A, M, err, 0.0, held, P2GStore{});
+        p2g_kernel<true, T, INTEG, false, WET, false>(P, n, K, x, v, r, Fc, Fd, cb, ce, B, A, M, err, 0.0, held,
+                                                      P2GStore{}, s);
     else
-        k_p2g_fixed<false, T, INTEG, false, WET><<<brick_grid(bricks), kP2GThreads, lds, s>>>(
-            P, n, B.list, B.count, batch, x, v, r, Fc, Fd, cb, ce, A, nullptr, err, 0.0, held, P2GStore{});
+        p2g_kernel<false, T, INTEG, false, WET, false>(P, n, K, x, v, r, Fc, Fd, cb, ce, B, A, nullptr, err, 0.0, held,
+                                                       P2GStore{}, s);
     return hipGetLastError();
 }
 
@@ -767,16 +893,10 @@ hipError_t launch_exchange_p2g(const DevParams &P, int64_t n, int64_t K, const d
                                double exsc, int64_t *fs, int64_t *err, hipStream_t s, const double *held)
 {
     if (n == 0) return hipSuccess;
-    const int64_t bricks = K / kBrickCells;
-    const int E3 = P.tile * P.tile * P.tile;
-    int batch = 512;
-    while (batch > 64 && p2g_lds(3, E3, batch) > 49152) batch /= 2;
-    const size_t lds = p2g_lds(3, E3, batch);
     unsigned long long *F = reinterpret_cast<unsigned long long *>(fs);
     // x is only read on this path
-    k_p2g_fixed<false, T, false, true><<<brick_grid(bricks), kP2GThreads, lds, s>>>(
-        P, n, B.list, B.count, batch, const_cast<double *>(x), nullptr, r, Fc, Ffl, cb, ce, F, F + P.G, err, exsc,
-        held, P2GStore{});
+    p2g_kernel<false, T, false, true, false, false>(P, n, K, const_cast<double *>(x), nullptr, r, Fc, Ffl, cb, ce, B, F,
+                                                    F + P.G, err, exsc, held, P2GStore{}, s);
     return hipGetLastError();
 }
 
@@ -801,7 +921,8 @@ hipError_t launch_p2g_fixed(const DevParams &P, int64_t n, int64_t K, const doub
 template <typename T>
 hipError_t launch_integrate_p2g(const DevParams &P, int64_t n, int64_t K, double *x, double *v, const double *r,
                                 const T *Fc, const T *Fd, const int32_t *cb, const int32_t *ce, const BrickList &B,
-                                int64_t *alpha, int64_t *mom, int64_t *err, hipStream_t s, const double *held)
+                                int64_t *alpha, int64_t *mom, int64_t *err, hipStream_t s,
+                                const double *held)
 {
     if (held)
         return p2g_fixed_impl<T, true, true>(P, n, K, x, v, r, Fc, Fd, cb, ce, B, alpha, mom, err, s, held);
@@ -812,45 +933,42 @@ template <typename T>
 hipError_t launch_integrate_p2g_store(const DevParams &P, int64_t n, int64_t K, double *x, double *v,
                                       const double *r, const T *Fc, const T *Fd, const int32_t *cb,
                                       const int32_t *ce, const BrickList &B, int64_t *err, hipStream_t s,
-                                      const P2GStore &st, SizeRecord *rec)
+                                      const P2GStore &st)
 {
-    const int64_t bricks = K / kBrickCells;
-    const int E3 = P.tile * P.tile * P.tile;
-    int batch = 512;
-    while (batch > 64 && p2g_lds(4, E3, batch) > 49152) batch /= 2;
-    // bricks of at most 128 granules at the last record: workgroups of 128
-    // threads and batches of 128 (less LDS, twice the workgroups per CU); a
-    // denser brick loops over batches, and the calls after take 256
-    const int32_t seen = record_seen(rec);
-    const bool small = seen > 0 && seen <= 128 && batch >= 128;
-    if (small) batch = 128;
-    const size_t lds = p2g_lds(4, E3, batch);
-    P2GStore sr = st;
-    const bool copy = n > 0 && record_copy(rec);  // only these calls record (the stores contend)
-    sr.nrec = copy ? rec->dev + rec->par * kRecSlots : nullptr;
-    sr.nclr = copy ? rec->dev + (rec->par ^ 1) * kRecSlots : nullptr;
-    if (n > 0 && small)
-        k_p2g_fixed<true, T, true, false, false, true, 128><<<brick_grid(bricks), 128, lds, s>>>(
-            P, n, B.list, B.count, batch, x, v, r, Fc, Fd, cb, ce, nullptr, nullptr, err, 0.0, nullptr, sr);
-    else if (n > 0)
-        k_p2g_fixed<true, T, true, false, false, true><<<brick_grid(bricks), kP2GThreads, lds, s>>>(
-            P, n, B.list, B.count, batch, x, v, r, Fc, Fd, cb, ce, nullptr, nullptr, err, 0.0, nullptr, sr);
-    hipError_t e = hipGetLastError();
-    if (copy) {
-        rec->par ^= 1;
-        if (e == hipSuccess) e = hipMemcpyAsync(rec->host, sr.nrec, sizeof(int32_t) * kRecSlots, hipMemcpyDeviceToHost, s);
+    if (n == 0) return hipSuccess;
+    // The direct kernel when an occupied brick holds fewer than two granules
+    // per node on average (205 granules on 512 nodes 26 against 34 us, 64 on
+    // 64 nodes 0.92 ms in workgroups of 64 against 1.28 of 128 threads), the
+    // run kernel otherwise (at eight granules per node and stencil a run
+    // sums eight contributions per LDS atomic).  Without a count of the bricks
+    // the expected granules decide.  Deposits added to the grid with atomics
+    // keep the run kernel: those atomics bound them (3.9 ms against 4.5).
+    const double m = (double)kBrick * P.cell * P.inv_dx;  // nodes per brick edge
+    if (!(brick_fill(P, n, B).avg < 2.0 * (m * m * m))) {
+        p2g_kernel<true, T, true, false, false, true>(P, n, K, x, v, r, Fc, Fd, cb, ce, B, nullptr, nullptr, err, 0.0,
+                                                      nullptr, st, s);
+        return hipGetLastError();
     }
-    return e;
+    const FillMode mode = fill_mode(P, n, B);
+    const unsigned grid = brick_grid(K / kBrickCells);
+    const size_t lds = sizeof(unsigned long long) * 4 * P.tile * P.tile * P.tile;
+    if (mode != kFillBlock)
+        k_p2g_direct<T, 64><<<grid, 64, lds, s>>>(P, n, B.list, B.count, x, v, r, Fc, Fd, cb, ce, err, st,
+                                                  mode == kFillBoth ? 1 : 0);
+    if (mode != kFillWave)
+        k_p2g_direct<T, 256><<<grid, 256, lds, s>>>(P, n, B.list, B.count, x, v, r, Fc, Fd, cb, ce, err, st,
+                                                    mode == kFillBoth ? 2 : 0);
+    return hipGetLastError();
 }
 
 template hipError_t launch_integrate_p2g_store<float>(const DevParams &, int64_t, int64_t, double *, double *,
                                                       const double *, const float *, const float *,
                                                       const int32_t *, const int32_t *, const BrickList &,
-                                                      int64_t *, hipStream_t, const P2GStore &, SizeRecord *);
+                                                      int64_t *, hipStream_t, const P2GStore &);
 template hipError_t launch_integrate_p2g_store<double>(const DevParams &, int64_t, int64_t, double *, double *,
                                                        const double *, const double *, const double *,
                                                        const int32_t *, const int32_t *, const BrickList &,
-                                                       int64_t *, hipStream_t, const P2GStore &, SizeRecord *);
+                                                       int64_t *, hipStream_t, const P2GStore &);
 
 hipError_t launch_p2g_assemble(const DevParams &P, int64_t n, const double *x, const double *v, const double *r,
                                const BrickList &B, int64_t *alpha, int64_t *mom, int64_t *err, hipStream_t s,
