@@ -208,13 +208,6 @@ DevParams derive(const gic_params *p)
     return d;
 }
 
-int sort_passes(int64_t K)
-{
-    int bits = 1;
-    while (bits < 32 && ((int64_t)1 << bits) < K) ++bits;
-    return (bits + 7) / 8;
-}
-
 gic_status hip_status(hipError_t e) { return e == hipSuccess ? GIC_OK : GIC_E_HIP; }
 
 bool fp32(const gic_ctx *c) { return c->p.precision == GIC_FP32; }
@@ -245,8 +238,8 @@ hipError_t step_sort(gic_ctx *c, int64_t n, const double *x, uint32_t *key, int3
     const int keep = c->rng_ok && c->rng_cb == cb && c->rng_ce == ce && c->sort.last_n == n ? 1 : 0;
     c->rng_ok = false;
     c->bl_pin = false;
-    hipError_t e = launch_sort_cells(c->dp, n, x, key, order, cb, ce, c->K, c->sort, c->err, s, &c->nl, force, keep);
-    if (e == hipSuccess && n > 0) e = launch_brick_list(cb, ce, c->bricks, n, s, keep ? c->sort.ctl : nullptr);
+    const hipError_t e =
+        launch_sort_cells(c->dp, n, x, key, order, cb, ce, c->K, c->sort, c->bricks, c->err, s, &c->nl, force, keep);
     if (e == hipSuccess) {
         c->rng_ok = true;
         c->rng_cb = cb;
@@ -375,12 +368,8 @@ gic_status gic_create(const gic_params *p, int64_t n_max, gic_ctx **out)
         return GIC_E_HIP;
     }
     const int64_t nn = n_max > 0 ? n_max : 1;
-    const int64_t tiles = sort_tiles_max(nn);
-    c->sort.tiles_max = tiles;
-    c->sort.passes = sort_passes(c->K);
     bool ok = true;
-    ok &= hipMalloc(&c->sort.kA, sizeof(uint32_t) * nn) == hipSuccess;
-    ok &= hipMalloc(&c->sort.kB, sizeof(uint32_t) * nn) == hipSuccess;
+    ok &= hipMalloc(&c->sort.slot, sizeof(uint32_t) * nn) == hipSuccess;
     ok &= hipMalloc(&c->sort.skeys[0], sizeof(uint32_t) * nn) == hipSuccess;
     ok &= hipMalloc(&c->sort.skeys[1], sizeof(uint32_t) * nn) == hipSuccess;
     c->sort.cur = 0;
@@ -390,11 +379,9 @@ gic_status gic_create(const gic_params *p, int64_t n_max, gic_ctx **out)
     ok &= hipMalloc(&c->sort.chg_p, sizeof(uint32_t) * kChgCap) == hipSuccess;
     ok &= hipMalloc(&c->sort.ctl, sizeof(int32_t) * 4) == hipSuccess;
     if (ok) ok = hipMemset(c->sort.ctl, 0, sizeof(int32_t) * 4) == hipSuccess;
-    ok &= hipMalloc(&c->sort.vA, sizeof(int32_t) * nn) == hipSuccess;
-    ok &= hipMalloc(&c->sort.vB, sizeof(int32_t) * nn) == hipSuccess;
-    ok &= hipMalloc(&c->sort.rowtot, sizeof(uint32_t) * 256) == hipSuccess;
-    ok &= hipMalloc(&c->sort.tcnt, sizeof(uint32_t) * 256 * tiles) == hipSuccess;
-    ok &= hipMalloc(&c->sort.sums, sizeof(uint32_t) * 1024) == hipSuccess;
+    ok &= hipMalloc(&c->sort.tmp, sizeof(int32_t) * nn) == hipSuccess;
+    ok &= hipMalloc(&c->sort.tmp2, sizeof(int32_t) * nn) == hipSuccess;
+    ok &= hipMalloc(&c->sort.sums, sizeof(uint32_t) * 2048) == hipSuccess;
     ok &= hipMalloc(&c->sort.cnt, sizeof(uint32_t) * (c->K > 0 ? c->K : 1)) == hipSuccess;
     if (ok) ok = hipMemset(c->sort.cnt, 0, sizeof(uint32_t) * (c->K > 0 ? c->K : 1)) == hipSuccess;
     ok &= hipMalloc(&c->err, sizeof(int64_t) * 2) == hipSuccess;
@@ -482,18 +469,15 @@ gic_status gic_destroy(gic_ctx *c)
 {
     if (!c) return GIC_E_ARG;
     hipError_t e = hipDeviceSynchronize();
-    (void)hipFree(c->sort.kA);
-    (void)hipFree(c->sort.kB);
+    (void)hipFree(c->sort.slot);
     (void)hipFree(c->sort.skeys[0]);
     (void)hipFree(c->sort.skeys[1]);
     (void)hipFree(c->sort.chg);
     (void)hipFree(c->sort.chg_s);
     (void)hipFree(c->sort.chg_p);
     (void)hipFree(c->sort.ctl);
-    (void)hipFree(c->sort.vA);
-    (void)hipFree(c->sort.vB);
-    (void)hipFree(c->sort.rowtot);
-    (void)hipFree(c->sort.tcnt);
+    (void)hipFree(c->sort.tmp);
+    (void)hipFree(c->sort.tmp2);
     (void)hipFree(c->sort.sums);
     (void)hipFree(c->sort.cnt);
     (void)hipFree(c->err);
@@ -560,7 +544,7 @@ gic_status gic_sort_cells(gic_ctx *c, int64_t n, const double *x, uint32_t *key,
     c->nl_n = -1;  // the next gic_step cannot rely on this sort's keys for its neighbour list
     c->rng_ok = false;
     c->bl_pin = false;
-    return hip_status(launch_sort_cells(c->dp, n, x, key, order, cell_begin, cell_end, c->K, c->sort, c->err,
+    return hip_status(launch_sort_cells(c->dp, n, x, key, order, cell_begin, cell_end, c->K, c->sort, c->bricks, c->err,
                                         (hipStream_t)stream));
 }
 

@@ -15,22 +15,18 @@ constexpr int kChgCap = 4096;
 
 // Sort scratch owned by a context.
 struct SortScratch {
-    uint32_t *kA, *kB;
     uint32_t *skeys[2];  // sorted keys; skeys[cur] holds those of the last sort
     int cur;
     int64_t last_n;      // granules of the last sort, -1 before the first
-    int32_t *vA, *vB;
-    uint32_t *sums;      // 1024 chunk totals of the digit-offset scan
+    uint32_t *slot;      // [n] place of each granule in its cell, in order of arrival
+    int32_t *tmp, *tmp2; // [n] granules by cell, in order of arrival; second array of long cells
+    uint32_t *sums;      // [2 x 1024] granules and occupied bricks of the scan's chunks
     uint32_t *cnt;       // [K] granules per cell; zero between sorts
     uint64_t *chg;       // [kChgCap] changed granules as (key << 32 | position), in arrival order
     uint64_t *chg_s;     // [kChgCap] the same sorted
     uint32_t *chg_p;     // [kChgCap] their positions sorted
     int32_t *ctl;        // [4] changed count (zero between sorts), path of this sort (1 = incremental),
                          // no key changed (1: order, ranges and bricks of the last sort hold), spare
-    int64_t tiles_max;
-    int passes;          // 8-bit digit passes over the key bits
-    uint32_t *tcnt;      // [256][tiles_max] digit counts, then output offsets, of each tile in a digit pass
-    uint32_t *rowtot;    // [256] keys with each digit in a digit pass
 };
 
 // Occupied bricks of a set of cell ranges, in brick order (see
@@ -46,13 +42,9 @@ struct BrickList {
     unsigned calls;
 };
 
-// skip (optional): the sort's control words; the list is kept when the sort
-// found no changed key (the caller checked that cb, ce are the tables the
-// list was built from).
 // n: granules of the tables, or -1 when the caller does not know (no copy of
 // the count to the host then).
-hipError_t launch_brick_list(const int32_t *cb, const int32_t *ce, BrickList &B, int64_t n, hipStream_t s,
-                             const int32_t *skip = nullptr);
+hipError_t launch_brick_list(const int32_t *cb, const int32_t *ce, BrickList &B, int64_t n, hipStream_t s);
 
 // Persistent neighbour list of the contact stage (owned by a context): for
 // every granule (sorted position q) the sorted positions of the granules
@@ -73,32 +65,21 @@ struct NbrList {
     float thr2;     // squared displacement since the build that calls for a rebuild (< 0: every step)
 };
 
-constexpr int kSortThreads = 256;
-constexpr int kSortItems = 8;
-constexpr int kSortTile = kSortThreads * kSortItems;
-// Up to this many keys the digit passes take tiles of one key per thread,
-// so a small sort still spreads over many workgroups.
+// Up to this many keys a sort does not collect the changed ones: counting
+// everything again takes no longer than merging them in.
 constexpr int64_t kSmallSort = (int64_t)1 << 18;
-inline int sort_items(int64_t n) { return n <= kSmallSort ? 1 : kSortItems; }
-// Tiles of the digit passes for up to n_max keys (the larger of the two tilings).
-inline int64_t sort_tiles_max(int64_t n_max)
-{
-    const int64_t big = (n_max + kSortTile - 1) / kSortTile;
-    const int64_t m = n_max < kSmallSort ? n_max : kSmallSort;
-    const int64_t small = (m + kSortThreads - 1) / kSortThreads;
-    return big > small ? big : small;
-}
 
 // nl: the neighbour list of the stepping path, or NULL.  With nl, the key
 // kernel also measures every granule's displacement since the list's build
 // (x in the order of that build) and the sort decides nl->ctl[0]: rebuild
 // when force is set, when the sorted order changes, or when a granule moved
 // by more than the list's skin / 2.
+// B becomes the list of the tables' occupied bricks.
 // keep_ranges: cell_begin, cell_end hold the ranges of the last sort on S
-// (same n); they are then rewritten only if a key changed.
+// (same n) and B their bricks; they are then rewritten only if a key changed.
 hipError_t launch_sort_cells(const DevParams &P, int64_t n, const double *x, uint32_t *key, int32_t *order,
-                             int32_t *cell_begin, int32_t *cell_end, int64_t K, SortScratch &S, int64_t *err,
-                             hipStream_t s, const NbrList *nl = nullptr, int force = 1, int keep_ranges = 0);
+                             int32_t *cell_begin, int32_t *cell_end, int64_t K, SortScratch &S, BrickList &B,
+                             int64_t *err, hipStream_t s, const NbrList *nl = nullptr, int force = 1, int keep_ranges = 0);
 hipError_t launch_reorder(int64_t n, const int32_t *order, const double *x, const double *v, const double *r,
                           const int32_t *id, double *xo, double *vo, double *ro, int32_t *ido, hipStream_t s);
 

@@ -1,18 +1,24 @@
-// a1: cell binning, stable LSD radix sort of the cell keys, cell ranges and
-// the gather of granule arrays into sorted order (gfx950).
+// a1: cell binning, stable counting sort of the cell keys, cell ranges, the
+// list of occupied bricks and the gather of granule arrays into sorted order
+// (gfx950).
 //
 // The contact test of Sec. 3.1 only pairs granules closer than r_i + r_j;
 // binning granules into cells of edge >= 2 r_max and sorting them by cell
 // makes each granule's candidates the occupants of at most 27 cells, stored
 // contiguously so that later stages read them coalesced.
+//
+// The keys are cells, so the sort counts: every granule takes a place in its
+// cell with an atomic on the cell's counter, a scan of the counters gives the
+// cell ranges (needed in any case), and the granules of each cell are then
+// put in input order, which makes the sort stable whatever order the atomics
+// ran in.  Six launches for any number of cells (keys, counts, two scan
+// passes, places, order; one scan pass fewer for small tables); an 8-bit radix
+// sort takes three per digit besides the counts and scans.
 #include "gic_launch.hpp"
 
 namespace gic {
 
 namespace {
-
-constexpr int kRadix = 256;
-constexpr int64_t kRtsGrid = 1024;  // workgroups of the tile loops of the digit passes
 
 // Key of every granule; flags non-finite and out-of-box positions.  With
 // the previous sorted keys pk (same n), granules whose key differs from
@@ -20,12 +26,15 @@ constexpr int64_t kRtsGrid = 1024;  // workgroups of the tile loops of the digit
 // them all).  With xref (the positions of the neighbour list's build, same
 // order), each workgroup writes the largest squared displacement of its
 // granules since the build to dpart[block] (no atomics: one address hit by
-// every wave would serialise them).
+// every wave would serialise them).  With pk the order and the sorted keys of
+// an unchanged state (the identity and the keys themselves) are written here,
+// so that a sort that finds no changed key has nothing left to write.
 __global__ void __launch_bounds__(256) k_cell_keys(DevParams P, int64_t n, const double *__restrict__ x,
                                                    uint32_t *__restrict__ key, int64_t *err,
                                                    const uint32_t *__restrict__ pk, uint64_t *__restrict__ chg,
                                                    int32_t *__restrict__ ctl, const float *__restrict__ xref,
-                                                   float *__restrict__ dpart)
+                                                   float *__restrict__ dpart, int32_t *__restrict__ order,
+                                                   uint32_t *__restrict__ skeys)
 {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (xref) {
@@ -60,7 +69,11 @@ __global__ void __launch_bounds__(256) k_cell_keys(DevParams P, int64_t n, const
         else if (out) raise_error(err, kErrDomain, i);
         k = key_of_cell(P, c[0], c[1], c[2]);
         key[i] = k;
-        changed = pk && pk[i] != k;
+        if (pk) {
+            changed = pk[i] != k;
+            order[i] = (int32_t)i;
+            skeys[i] = k;
+        }
     }
     if (!pk) return;
     // changed keys appended with one counter atomic per workgroup that has
@@ -79,7 +92,7 @@ __global__ void __launch_bounds__(256) k_cell_keys(DevParams P, int64_t n, const
     if (changed) {
         int32_t slot = s_base + (int32_t)__popcll(mask & ((1ull << lane) - 1ull));
         for (int w = 0; w < wave; ++w) slot += s_cnt[w];
-        if (slot < kChgCap) chg[slot] = ((uint64_t)k << 32) | (uint64_t)i;
+        if (chg && slot < kChgCap) chg[slot] = ((uint64_t)k << 32) | (uint64_t)i;
     }
 }
 
@@ -129,44 +142,257 @@ __device__ inline uint32_t block_scan_inclusive(uint32_t v, uint32_t *lds, uint3
     return v + before;
 }
 
-// skip (optional): the sort's control words; skip[2] set means the cell
-// ranges of the last sort still hold (no key changed) and are kept.
+// The sum over t < m of a[t] (m <= kScanThreads), in every thread.
+__device__ inline uint32_t prefix_before(const uint32_t *__restrict__ a, int m, uint32_t *lds)
+{
+    __shared__ uint32_t s_sum;
+    const uint32_t v = block_reduce_sum((int)threadIdx.x < m ? a[threadIdx.x] : 0u, lds);
+    if (threadIdx.x == 0) s_sum = v;
+    __syncthreads();
+    const uint32_t r = s_sum;
+    __syncthreads();
+    return r;
+}
+
+// First scan pass over the cell counts: each chunk's granules (sums) and
+// occupied bricks (bsums).  A brick is 64 consecutive keys, four per lane of
+// sixteen lanes.  skip (optional): the sort's control words; skip[2] set means the cell
+// ranges and bricks of the last sort still hold (no key changed).
 __global__ void __launch_bounds__(kScanThreads) k_scan_reduce(const uint32_t *__restrict__ a, int64_t len,
                                                               int64_t chunk, uint32_t *__restrict__ sums,
+                                                              uint32_t *__restrict__ bsums,
                                                               const int32_t *__restrict__ skip)
 {
     if (skip && skip[2]) return;
     __shared__ uint32_t lds[kScanThreads / 64];
     const int64_t lo = (int64_t)blockIdx.x * chunk;
     const int64_t hi = lo + chunk < len ? lo + chunk : len;
-    uint32_t s = 0;
-    for (int64_t k = lo + threadIdx.x; k < hi; k += kScanThreads) s += a[k];
+    uint32_t s = 0, nb = 0;
+    const int lane = threadIdx.x & 63;
+    for (int64_t k = lo + 4 * (int64_t)threadIdx.x; k < hi; k += 4 * kScanThreads) {  // len: a multiple of 64
+        const uint4 v = *reinterpret_cast<const uint4 *>(a + k);
+        const uint32_t t = ((v.x + v.y) + v.z) + v.w;
+        s += t;
+        const uint64_t m = __ballot(t != 0u);
+        if ((lane & 15) == 0) nb += (m >> lane) & 0xFFFFull ? 1u : 0u;
+    }
     s = block_reduce_sum(s, lds);
     if (threadIdx.x == 0) sums[blockIdx.x] = s;
+    nb = block_reduce_sum(nb, lds);
+    if (threadIdx.x == 0) bsums[blockIdx.x] = nb;
 }
 
-__global__ void __launch_bounds__(kScanThreads) k_scan_spine(uint32_t *sums, int nb, const int32_t *__restrict__ skip)
+// Lanes of a wave from this one up to the next lane of `starts` (a run).
+__device__ inline int run_length(uint64_t starts)
 {
-    if (skip && skip[2]) return;
-    __shared__ uint32_t lds[kScanThreads / 64];
-    const uint32_t v = threadIdx.x < nb ? sums[threadIdx.x] : 0u;
-    uint32_t total;
-    const uint32_t inc = block_scan_inclusive(v, lds, &total);
-    if (threadIdx.x < nb) sums[threadIdx.x] = inc - v;
+    const int lane = threadIdx.x & 63;
+    const uint64_t above = lane == 63 ? 0ull : (starts >> (lane + 1)) << (lane + 1);
+    return (above ? __ffsll((unsigned long long)above) - 1 : 64) - lane;
 }
 
-// ---- digit passes (reduce, scan, scatter) --------------------------------
-//
-// Each 8-bit digit pass is three kernels with no waits between workgroups:
-// every tile of 2,048 keys (256 for sorts of at most 2^18 keys, so that a
-// small sort still spreads over many workgroups) counts its digits
-// (k_rts_count, into tcnt[digit][tile]); one workgroup per digit turns its
-// row into the exclusive prefix over the tiles and records the row's total
-// (k_rts_scan); every tile then scatters its keys stably (k_rts_scatter)
-// from the prefix
-// of its tile plus the keys of all smaller digits (a scan of the 256 row
-// totals).  The tile loops stride over the grid, so a launch needs no more
-// workgroups than it has tiles.
+__device__ inline int lower_bound_u64(const uint64_t *a, int m, uint64_t v)
+{
+    int lo = 0, hi = m;
+    while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (a[mid] < v) lo = mid + 1; else hi = mid;
+    }
+    return lo;
+}
+
+__device__ inline int lower_bound_u32(const uint32_t *a, int m, uint32_t v)
+{
+    int lo = 0, hi = m;
+    while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (a[mid] < v) lo = mid + 1; else hi = mid;
+    }
+    return lo;
+}
+
+// Counts of the cells, and each granule's place in its cell in order of
+// arrival (slot): one atomic per run of equal keys inside a wave.  After an
+// incremental sort (ctl[1]) no places are needed: the granules that kept
+// their key (U, see k_chg_sort) and are displaced by those that did not are
+// written to order and skeys instead.  Small sorts (one launch fewer: chg not
+// collected) decide here: the first workgroup writes ctl[2] (no key changed)
+// and, with nl, whether the neighbour list must be rebuilt.
+__global__ void __launch_bounds__(256) k_cell_count(const uint32_t *__restrict__ key, int64_t n,
+                                                    uint32_t *__restrict__ cnt, uint32_t *__restrict__ slot,
+                                                    const uint32_t *__restrict__ pk, const uint64_t *__restrict__ chg_s,
+                                                    const uint32_t *__restrict__ chg_p, uint32_t *__restrict__ skeys,
+                                                    int32_t *__restrict__ order, int32_t *__restrict__ ctl, int decide,
+                                                    int keep, uint32_t *__restrict__ nl, int force, float thr2,
+                                                    const float *__restrict__ dpart, int64_t nd)
+{
+    bool same = false, inc = false;
+    const int m = ctl ? ctl[0] : 0;
+    if (decide) {
+        same = m == 0;
+        if (blockIdx.x == 0) {
+            __shared__ float s_dm[4];
+            float dm = 0.0f;
+            if (dpart)
+                for (int64_t i = threadIdx.x; i < nd; i += 256) dm = fmaxf(dm, dpart[i]);
+            for (int off = 32; off > 0; off >>= 1) dm = fmaxf(dm, __shfl_xor(dm, off));
+            if ((threadIdx.x & 63) == 0) s_dm[threadIdx.x >> 6] = dm;
+            __syncthreads();
+            if (threadIdx.x == 0) {
+                const float d2 = fmaxf(fmaxf(s_dm[0], s_dm[1]), fmaxf(s_dm[2], s_dm[3]));
+                ctl[1] = 0;
+                ctl[2] = same ? 1 : 0;
+                if (nl) nl[0] = (force || m != 0 || !(d2 < thr2)) ? 1u : 0u;
+            }
+        }
+    } else if (ctl) {
+        inc = ctl[1] != 0;
+        same = ctl[2] != 0;
+    }
+    if (same && keep) return;
+    const int lane = threadIdx.x & 63;
+    for (int64_t q0 = (int64_t)blockIdx.x * 256; q0 < n; q0 += (int64_t)gridDim.x * 256) {
+        const int64_t q = q0 + threadIdx.x;
+        const bool valid = q < n;
+        const uint32_t k = valid ? key[q] : 0u;
+        const uint32_t before = __shfl_up(k, 1);
+        // run heads; invalid lanes end the last run
+        const uint64_t starts = __ballot(valid && (lane == 0 || before != k)) | (~__ballot(valid));
+        const bool first = valid && ((starts >> lane) & 1ull);
+        uint32_t at = 0;
+        if (first) at = atomicAdd(&cnt[k], (uint32_t)run_length(starts));
+        if (inc) {
+            if (same || !valid || k != pk[q]) continue;  // a changed element: placed by k_chg_sort
+            const int64_t place = q - lower_bound_u32(chg_p, m, (uint32_t)q) +
+                                  lower_bound_u64(chg_s, m, ((uint64_t)k << 32) | (uint64_t)q);
+            if (place == q) continue;  // written by the key kernel
+            order[place] = (int32_t)q;
+            skeys[place] = k;
+            continue;
+        }
+        const uint64_t upto = starts & (~0ull >> (63 - lane));  // run heads at or below this lane
+        const int head = upto ? 63 - __clzll((long long)upto) : 0;
+        at = __shfl(at, head) + (uint32_t)(lane - head);
+        if (valid) slot[q] = at;
+    }
+}
+
+// Second scan pass: begin = exclusive prefix, end = inclusive prefix of the
+// cell counts; the list of occupied bricks in brick order and each brick's
+// place in it.  A workgroup adds up what lies before its chunk itself: the
+// chunk sums of the first pass (at most 1,024 words), or, for tables of at
+// most kDirectScan cells, which then have no first pass, the counts (the
+// counts are reset to zero for the next sort by k_cell_order).
+constexpr int64_t kDirectScan = 32768;
+
+__global__ void __launch_bounds__(kScanThreads) k_scan_down_ranges(uint32_t *__restrict__ cnt,
+                                                                   uint32_t *__restrict__ begin,
+                                                                   uint32_t *__restrict__ end, int64_t len,
+                                                                   int64_t chunk, const uint32_t *__restrict__ sums,
+                                                                   const uint32_t *__restrict__ bsums,
+                                                                   int32_t *__restrict__ ctl, int keep,
+                                                                   int32_t *__restrict__ list,
+                                                                   int32_t *__restrict__ count,
+                                                                   int32_t *__restrict__ slot_of)
+{
+    if (keep && ctl[2]) return;  // ranges unchanged (and no changed granule to uncount)
+    if (blockIdx.x == 0 && threadIdx.x == 0) ctl[0] = 0;  // no changed granules counted for the next sort
+    __shared__ uint32_t lds[kScanThreads / 64];
+    __shared__ uint32_t s_occ[kScanThreads / 64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t lo = (int64_t)blockIdx.x * chunk;
+    const int64_t hi = lo + chunk < len ? lo + chunk : len;
+    uint32_t carry, nocc;
+    if (sums) {
+        carry = prefix_before(sums, (int)blockIdx.x, lds);
+        nocc = prefix_before(bsums, (int)blockIdx.x, lds);
+    } else {
+        // four cells per lane, sixteen lanes per brick, all loads in flight
+        constexpr int kBatch = (int)(kDirectScan / (4 * kScanThreads));
+        uint32_t a = 0, b = 0;
+        const uint4 *c4 = reinterpret_cast<const uint4 *>(cnt);
+        const int groups = (int)(lo / (4 * kScanThreads));  // chunks are whole groups
+        uint4 v[kBatch];
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u)
+            v[u] = u < groups ? c4[(int64_t)u * kScanThreads + threadIdx.x] : uint4{0u, 0u, 0u, 0u};
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) {
+            const uint32_t t = ((v[u].x + v[u].y) + v[u].z) + v[u].w;
+            a += t;
+            const uint64_t m = __ballot(t != 0u);
+            if ((lane & 15) == 0) b += (m >> lane) & 0xFFFFull ? 1u : 0u;
+        }
+        __shared__ uint32_t s_before[2];
+        a = block_reduce_sum(a, lds);
+        b = block_reduce_sum(b, lds);
+        if (threadIdx.x == 0) {
+            s_before[0] = a;
+            s_before[1] = b;
+        }
+        __syncthreads();
+        carry = s_before[0];
+        nocc = s_before[1];
+    }
+    // four cells per lane, so sixteen lanes per brick and four bricks per wave
+    for (int64_t base = lo; base < hi; base += 4 * kScanThreads) {
+        const int64_t k = base + 4 * (int64_t)threadIdx.x;
+        uint4 *c4 = reinterpret_cast<uint4 *>(cnt + k);
+        const uint4 v = k < hi ? *c4 : uint4{0u, 0u, 0u, 0u};
+        const uint32_t t = ((v.x + v.y) + v.z) + v.w;
+        const uint64_t m = __ballot(t != 0u);
+        const uint32_t occ = ((m & 0xFFFFull) ? 1u : 0u) | ((m & 0xFFFF0000ull) ? 2u : 0u) |
+                             ((m & 0xFFFF00000000ull) ? 4u : 0u) | ((m & 0xFFFF000000000000ull) ? 8u : 0u);
+        if (lane == 0) s_occ[wave] = __popc(occ);
+        uint32_t total;
+        const uint32_t before = carry + block_scan_inclusive(t, lds, &total) - t;  // (its barriers also publish s_occ)
+        uint32_t place = nocc;
+        for (int w = 0; w < kScanThreads / 64; ++w) {
+            if (w < wave) place += s_occ[w];
+            nocc += s_occ[w];
+        }
+        if (k < hi) {
+            const uint32_t e0 = before + v.x, e1 = e0 + v.y, e2 = e1 + v.z, e3 = e2 + v.w;
+            begin[k] = before;
+            begin[k + 1] = e0;
+            begin[k + 2] = e1;
+            begin[k + 3] = e2;
+            end[k] = e0;
+            end[k + 1] = e1;
+            end[k + 2] = e2;
+            end[k + 3] = e3;
+            if (sums && t != 0u) *c4 = uint4{0u, 0u, 0u, 0u};
+            if ((lane & 15) == 0) {
+                const int64_t b = k >> 6;
+                const int g = lane >> 4;
+                const uint32_t at = place + __popc(occ & ((1u << g) - 1u));
+                const bool mine = (occ >> g) & 1u;
+                if (mine) list[at] = (int32_t)b;
+                slot_of[b] = mine ? (int32_t)at : -1;
+            }
+        }
+        carry += total;
+        __syncthreads();  // s_occ is rewritten by the next round
+    }
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) *count = (int32_t)nocc;
+}
+
+// Granule i to its place in its cell, in order of arrival; the key of the
+// place is final.
+__global__ void __launch_bounds__(256) k_cell_place(const uint32_t *__restrict__ key, int64_t n,
+                                                    const uint32_t *__restrict__ begin,
+                                                    const uint32_t *__restrict__ slot, int32_t *__restrict__ tmp,
+                                                    uint32_t *__restrict__ skeys, const int32_t *__restrict__ ctl,
+                                                    int keep)
+{
+    if (ctl && (ctl[1] || (keep && ctl[2]))) return;
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
+        const uint32_t k = key[i];
+        const int64_t p = (int64_t)begin[k] + slot[i];
+        if (p >= n) continue;
+        tmp[p] = (int32_t)i;
+        skeys[p] = k;
+    }
+}
 
 // Rank of each lane's digit among the lanes of its wave with the same digit
 // (8 ballots), and the number of such lanes.
@@ -182,110 +408,34 @@ __device__ inline uint64_t digit_mask(uint32_t d, bool valid)
     return m;
 }
 
-// Mask of the lanes below this one in its wave.
-__device__ inline uint64_t lanes_below()
+// One workgroup sorts the distinct indices a[b..e) (all below n) into
+// out[b..e) by 8-bit digits, through t; a and t are overwritten.
+__device__ inline void sort_long_cell(int32_t *a, int32_t *t, int32_t *__restrict__ out, int64_t b, int64_t e,
+                                      int64_t n, uint32_t *s_base, uint32_t (*wcnt)[256], uint32_t *lds)
 {
-    const int lane = threadIdx.x & 63;
-    return lane == 0 ? 0ull : (~0ull >> (64 - lane));
-}
-
-// Digit counts of every tile of ITEMS x 256 keys: tcnt[d * tiles + t].
-template <int ITEMS>
-__global__ void __launch_bounds__(kSortThreads) k_rts_count(const uint32_t *__restrict__ kin, int64_t n, int pass,
-                                                            int64_t tiles, uint32_t *__restrict__ tcnt,
-                                                            const int32_t *__restrict__ skip)
-{
-    if (skip && skip[1]) return;  // the incremental path sorted this time
-    __shared__ uint32_t s_cnt[kRadix];
-    const int tid = threadIdx.x;
-    const int shift = 8 * pass;
-    const uint64_t lt = lanes_below();
-    for (int64_t t = blockIdx.x; t < tiles; t += gridDim.x) {
-        s_cnt[tid] = 0;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const uint64_t lt = lane == 0 ? 0ull : (~0ull >> (64 - lane));
+    int passes = 1;
+    while (passes < 4 && ((n - 1) >> (8 * passes)) != 0) ++passes;
+    for (int p = 0; p < passes; ++p) {
+        const int32_t *in = (p & 1) ? t : a;
+        int32_t *dst = p == passes - 1 ? out : ((p & 1) ? a : t);
+        const int shift = 8 * p;
+        s_base[tid] = 0;
+        for (int w = 0; w < 4; ++w) wcnt[w][tid] = 0;
         __syncthreads();
-        const int64_t tile0 = t * (kSortThreads * ITEMS);
-#pragma unroll
-        for (int it = 0; it < ITEMS; ++it) {
-            const int64_t p = tile0 + (int64_t)it * kSortThreads + tid;
-            const bool valid = p < n;
-            const uint32_t d = valid ? (kin[p] >> shift) & (kRadix - 1) : 0u;
-            const uint64_t m = digit_mask(d, valid);
-            if (valid && (m & lt) == 0) atomicAdd(&s_cnt[d], (uint32_t)__popcll(m));
-        }
+        for (int64_t i = b + tid; i < e; i += 256) atomicAdd(&s_base[((uint32_t)in[i] >> shift) & 255u], 1u);
         __syncthreads();
-        tcnt[(int64_t)tid * tiles + t] = s_cnt[tid];
+        const uint32_t g = s_base[tid];
+        uint32_t total;
+        const uint32_t ex = block_scan_inclusive(g, lds, &total) - g;
+        s_base[tid] = ex;
         __syncthreads();
-    }
-}
-
-// Workgroup d: tcnt[d][t] <- keys with digit d in tiles before t;
-// rowtot[d] <- keys with digit d.  Thread i takes a contiguous chunk of the
-// row, so the row is read in one sweep and scanned once.
-__global__ void __launch_bounds__(kSortThreads) k_rts_scan(uint32_t *__restrict__ tcnt, int64_t tiles,
-                                                           uint32_t *__restrict__ rowtot,
-                                                           const int32_t *__restrict__ skip)
-{
-    if (skip && skip[1]) return;
-    __shared__ uint32_t lds[kSortThreads / 64];
-    const int d = blockIdx.x;
-    uint32_t *row = tcnt + (int64_t)d * tiles;
-    const int64_t chunk = (tiles + kSortThreads - 1) / kSortThreads;
-    const int64_t lo = (int64_t)threadIdx.x * chunk;
-    const int64_t hi = lo + chunk < tiles ? lo + chunk : tiles;
-    uint32_t sum = 0;
-    for (int64_t t = lo; t < hi; ++t) sum += row[t];
-    uint32_t total;
-    uint32_t run = block_scan_inclusive(sum, lds, &total) - sum;
-    for (int64_t t = lo; t < hi; ++t) {
-        const uint32_t c = row[t];
-        row[t] = run;
-        run += c;
-    }
-    if (threadIdx.x == 0) rowtot[d] = total;
-}
-
-// Stable scatter of every tile's keys (and values: vin, or the positions)
-// from the offsets of k_rts_scan, in rounds of 256 keys in position order.
-template <int ITEMS>
-__global__ void __launch_bounds__(kSortThreads) k_rts_scatter(const uint32_t *__restrict__ kin,
-                                                              const int32_t *__restrict__ vin,
-                                                              uint32_t *__restrict__ kout, int32_t *__restrict__ vout,
-                                                              int64_t n, int pass, int64_t tiles,
-                                                              const uint32_t *__restrict__ tcnt,
-                                                              const uint32_t *__restrict__ rowtot,
-                                                              const int32_t *__restrict__ skip)
-{
-    if (skip && skip[1]) return;
-    __shared__ uint32_t s_base[kRadix];  // where this tile's next key of each digit goes
-    __shared__ uint32_t wcnt[kSortThreads / 64][kRadix];
-    __shared__ uint32_t lds[kSortThreads / 64];
-    const int tid = threadIdx.x;
-    const int wave = tid >> 6;
-    const int shift = 8 * pass;
-    const uint64_t lt = lanes_below();
-    for (int w = 0; w < kSortThreads / 64; ++w) wcnt[w][tid] = 0;
-    // keys of all smaller digits
-    const uint32_t g = rowtot[tid];
-    uint32_t total;
-    const uint32_t dbase = block_scan_inclusive(g, lds, &total) - g;
-    for (int64_t t = blockIdx.x; t < tiles; t += gridDim.x) {
-        const int64_t tile0 = t * (kSortThreads * ITEMS);
-        uint32_t k[ITEMS];
-        int32_t val[ITEMS];
-#pragma unroll
-        for (int it = 0; it < ITEMS; ++it) {
-            const int64_t p = tile0 + (int64_t)it * kSortThreads + tid;
-            const bool valid = p < n;
-            k[it] = valid ? kin[p] : 0xffffffffu;
-            val[it] = valid ? (vin ? vin[p] : (int32_t)p) : 0;
-        }
-        s_base[tid] = dbase + tcnt[(int64_t)tid * tiles + t];
-        __syncthreads();
-#pragma unroll
-        for (int it = 0; it < ITEMS; ++it) {
-            const int64_t p = tile0 + (int64_t)it * kSortThreads + tid;
-            const bool valid = p < n;
-            const uint32_t d = (k[it] >> shift) & (kRadix - 1);
+        for (int64_t i0 = b; i0 < e; i0 += 256) {
+            const int64_t i = i0 + tid;
+            const bool valid = i < e;
+            const int32_t v = valid ? in[i] : 0;
+            const uint32_t d = ((uint32_t)v >> shift) & 255u;
             const uint64_t m = digit_mask(d, valid);
             const uint32_t rank = (uint32_t)__popcll(m & lt);
             if (valid && rank == 0) wcnt[wave][d] = (uint32_t)__popcll(m);
@@ -293,14 +443,11 @@ __global__ void __launch_bounds__(kSortThreads) k_rts_scatter(const uint32_t *__
             if (valid) {
                 uint32_t pos = s_base[d] + rank;
                 for (int w = 0; w < wave; ++w) pos += wcnt[w][d];
-                if ((int64_t)pos < n) {
-                    kout[pos] = k[it];
-                    vout[pos] = val[it];
-                }
+                dst[b + pos] = v;
             }
             __syncthreads();
             uint32_t add = 0;
-            for (int w = 0; w < kSortThreads / 64; ++w) {
+            for (int w = 0; w < 4; ++w) {
                 add += wcnt[w][tid];
                 wcnt[w][tid] = 0;
             }
@@ -310,50 +457,45 @@ __global__ void __launch_bounds__(kSortThreads) k_rts_scatter(const uint32_t *__
     }
 }
 
-// Number of granules per cell key, from the sorted keys: the first lane of
-// each run of equal keys inside a wave adds the run's length.
-__global__ void __launch_bounds__(256) k_cell_count(const uint32_t *__restrict__ sk, int64_t n,
-                                                    uint32_t *__restrict__ cnt, const int32_t *__restrict__ skip)
-{
-    if (skip && skip[2]) return;
-    const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int lane = threadIdx.x & 63;
-    const bool valid = q < n;
-    const uint32_t k = valid ? sk[q] : 0u;
-    const bool start = valid && (lane == 0 || sk[q - 1] != k);
-    const uint64_t starts = __ballot(start) | (~__ballot(valid));  // invalid lanes end the last run
-    if (start) {
-        const uint64_t above = lane == 63 ? 0ull : (starts >> (lane + 1)) << (lane + 1);
-        const int next = above ? __ffsll((unsigned long long)above) - 1 : 64;
-        atomicAdd(&cnt[k], (uint32_t)(next - lane));
-    }
-}
+// The granules of every cell in input order: a granule's place is the number
+// of smaller indices in its cell (a cell's reads hit L1).  A cell of more than
+// kLongCell granules, where that would grow with the square of its size, is
+// sorted by digits by the workgroup that holds its first place.
+constexpr int kLongCell = 256;
 
-// Last phase of the scan of the per-cell counts: begin = exclusive prefix,
-// end = inclusive prefix; the counts are reset to zero for the next sort.
-__global__ void __launch_bounds__(kScanThreads) k_scan_down_ranges(uint32_t *__restrict__ cnt,
-                                                                   uint32_t *__restrict__ begin,
-                                                                   uint32_t *__restrict__ end, int64_t len,
-                                                                   int64_t chunk, const uint32_t *__restrict__ sums,
-                                                                   int32_t *__restrict__ ctl, int keep)
+__global__ void __launch_bounds__(256) k_cell_order(int64_t n, const uint32_t *__restrict__ skeys,
+                                                    const uint32_t *__restrict__ begin,
+                                                    const uint32_t *__restrict__ end, int32_t *tmp, int32_t *tmp2,
+                                                    int32_t *__restrict__ order, const int32_t *__restrict__ ctl,
+                                                    int keep, uint32_t *__restrict__ cnt, int64_t K)
 {
-    if (keep && ctl[2]) return;  // ranges unchanged (and no changed granule to uncount)
-    if (blockIdx.x == 0 && threadIdx.x == 0) ctl[0] = 0;  // no changed granules counted for the next sort
-    __shared__ uint32_t lds[kScanThreads / 64];
-    const int64_t lo = (int64_t)blockIdx.x * chunk;
-    const int64_t hi = lo + chunk < len ? lo + chunk : len;
-    uint32_t carry = sums[blockIdx.x];
-    for (int64_t base = lo; base < hi; base += kScanThreads) {
-        const int64_t k = base + threadIdx.x;
-        const uint32_t v = k < hi ? cnt[k] : 0u;
-        uint32_t total;
-        const uint32_t inc = block_scan_inclusive(v, lds, &total);
-        if (k < hi) {
-            begin[k] = carry + inc - v;
-            end[k] = carry + inc;
-            cnt[k] = 0u;
+    if (keep && ctl[2]) return;
+    if (cnt)  // the counts, for the next sort
+        for (int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x; k < K; k += (int64_t)gridDim.x * 256) cnt[k] = 0u;
+    if (ctl && ctl[1]) return;
+    __shared__ uint32_t s_base[256], wcnt[4][256], lds[4];
+    __shared__ int64_t s_long[2];
+    for (int64_t p0 = (int64_t)blockIdx.x * 256; p0 < n; p0 += (int64_t)gridDim.x * 256) {
+        if (threadIdx.x == 0) s_long[1] = 0;
+        __syncthreads();
+        const int64_t p = p0 + threadIdx.x;
+        if (p < n) {
+            const uint32_t k = skeys[p];
+            int64_t b = begin[k], e = end[k];
+            e = e < n ? e : n;
+            if (e - b <= kLongCell) {
+                const int32_t v = tmp[p];
+                int rank = 0;
+                for (int64_t j = b; j < e; ++j) rank += tmp[j] < v ? 1 : 0;
+                order[b + rank] = v;
+            } else if (p == b) {  // at most one such cell begins in 256 places
+                s_long[0] = b;
+                s_long[1] = e;
+            }
         }
-        carry += total;
+        __syncthreads();
+        if (s_long[1]) sort_long_cell(tmp, tmp2, order, s_long[0], s_long[1], n, s_base, wcnt, lds);
+        __syncthreads();
     }
 }
 
@@ -386,26 +528,6 @@ __global__ void __launch_bounds__(256) k_reorder(int64_t n, const int32_t *__res
 // that is (i - #C positions below i) + #C pairs below (key, i); for c in C
 // it is its rank in C plus #U pairs below (k_c, i_c) = L - #C positions
 // below L, with L the number of positions i with (pk[i], i) < (k_c, i_c).
-
-__device__ inline int lower_bound_u64(const uint64_t *a, int m, uint64_t v)
-{
-    int lo = 0, hi = m;
-    while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        if (a[mid] < v) lo = mid + 1; else hi = mid;
-    }
-    return lo;
-}
-
-__device__ inline int lower_bound_u32(const uint32_t *a, int m, uint32_t v)
-{
-    int lo = 0, hi = m;
-    while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        if (a[mid] < v) lo = mid + 1; else hi = mid;
-    }
-    return lo;
-}
 
 // One workgroup: decides the path, sorts C by (key, position) and by
 // position (bitonic, in LDS), and places the C elements.  With nl it also
@@ -486,26 +608,6 @@ __global__ void __launch_bounds__(1024) k_chg_sort(int64_t n, const uint32_t *__
     }
 }
 
-// Places the U elements (one thread per position).
-__global__ void __launch_bounds__(256) k_merge(int64_t n, const uint32_t *__restrict__ key,
-                                               const uint32_t *__restrict__ pk, const int32_t *__restrict__ ctl,
-                                               const uint64_t *__restrict__ chg_s, const uint32_t *__restrict__ chg_p,
-                                               uint32_t *__restrict__ skeys, int32_t *__restrict__ order)
-{
-    if (!ctl[1]) return;
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const uint32_t k = key[i];
-    if (k != pk[i]) return;  // an element of C, placed by k_chg_sort
-    const int m = ctl[0];
-    int64_t place = i;
-    if (m > 0)
-        place = i - lower_bound_u32(chg_p, m, (uint32_t)i) +
-                lower_bound_u64(chg_s, m, ((uint64_t)k << 32) | (uint64_t)i);
-    order[place] = (int32_t)i;
-    skeys[place] = k;
-}
-
 // ---- occupied bricks, in brick order (the schedule of the brick kernels) ----
 
 __device__ inline bool brick_occupied(int64_t b, const int32_t *__restrict__ cb, const int32_t *__restrict__ ce)
@@ -514,10 +616,8 @@ __device__ inline bool brick_occupied(int64_t b, const int32_t *__restrict__ cb,
 }
 
 __global__ void __launch_bounds__(256) k_brick_count(int64_t nbricks, int64_t per_block, const int32_t *__restrict__ cb,
-                                                     const int32_t *__restrict__ ce, uint32_t *__restrict__ sums,
-                                                     const int32_t *__restrict__ skip)
+                                                     const int32_t *__restrict__ ce, uint32_t *__restrict__ sums)
 {
-    if (skip && skip[2]) return;
     __shared__ uint32_t lds[4];
     const int64_t lo = (int64_t)blockIdx.x * per_block;
     const int64_t hi = lo + per_block < nbricks ? lo + per_block : nbricks;
@@ -527,29 +627,56 @@ __global__ void __launch_bounds__(256) k_brick_count(int64_t nbricks, int64_t pe
     if (threadIdx.x == 0) sums[blockIdx.x] = c;
 }
 
-// Exclusive scan of the block counts in place; the total is the list length.
-__global__ void __launch_bounds__(kScanThreads) k_brick_spine(uint32_t *sums, int nb, int32_t *count,
-                                                              const int32_t *__restrict__ skip)
+// The whole list in one workgroup, for few bricks.
+constexpr int64_t kBricksOneGroup = 2048;
+
+__global__ void __launch_bounds__(kScanThreads) k_brick_list(int nbricks, const int32_t *__restrict__ cb,
+                                                             const int32_t *__restrict__ ce,
+                                                             int32_t *__restrict__ list, int32_t *__restrict__ count,
+                                                             int32_t *__restrict__ slot_of)
 {
-    if (skip && skip[2]) return;
+    constexpr int kRounds = (int)(kBricksOneGroup / kScanThreads);
     __shared__ uint32_t lds[kScanThreads / 64];
-    const uint32_t v = threadIdx.x < nb ? sums[threadIdx.x] : 0u;
+    // thread t takes kRounds consecutive bricks (all loads in flight together)
+    const int b0 = (int)threadIdx.x * kRounds;
+    int32_t lo[kRounds], hi[kRounds];
+#pragma unroll
+    for (int u = 0; u < kRounds; ++u) {
+        const int b = b0 + u < nbricks ? b0 + u : nbricks - 1;
+        lo[u] = cb[(int64_t)b * kBrickCells];
+        hi[u] = ce[(int64_t)b * kBrickCells + kBrickCells - 1];
+    }
+    uint32_t f = 0;
+#pragma unroll
+    for (int u = 0; u < kRounds; ++u) f += b0 + u < nbricks && hi[u] > lo[u] ? 1u : 0u;
     uint32_t total;
-    const uint32_t inc = block_scan_inclusive(v, lds, &total);
-    if (threadIdx.x < nb) sums[threadIdx.x] = inc - v;
+    uint32_t at = block_scan_inclusive(f, lds, &total) - f;
+#pragma unroll
+    for (int u = 0; u < kRounds; ++u) {
+        if (b0 + u >= nbricks) break;
+        const bool occ = hi[u] > lo[u];
+        slot_of[b0 + u] = occ ? (int32_t)at : -1;
+        if (occ) list[at++] = b0 + u;
+    }
     if (threadIdx.x == 0) *count = (int32_t)total;
 }
 
+// Each workgroup sums the counts before its own (at most kScanThreads words).
 __global__ void __launch_bounds__(256) k_brick_scatter(int64_t nbricks, int64_t per_block,
                                                        const int32_t *__restrict__ cb, const int32_t *__restrict__ ce,
                                                        const uint32_t *__restrict__ sums, int32_t *__restrict__ list,
-                                                       int32_t *__restrict__ slot_of, const int32_t *__restrict__ skip)
+                                                       int32_t *__restrict__ count, int32_t *__restrict__ slot_of)
 {
-    if (skip && skip[2]) return;
     __shared__ uint32_t lds[4];
+    __shared__ uint32_t s_base;
     const int64_t lo = (int64_t)blockIdx.x * per_block;
     const int64_t hi = lo + per_block < nbricks ? lo + per_block : nbricks;
-    uint32_t base = sums[blockIdx.x];
+    uint32_t base = 0;
+    for (int t = threadIdx.x; t < (int)blockIdx.x; t += 256) base += sums[t];
+    base = block_reduce_sum(base, lds);
+    if (threadIdx.x == 0) s_base = base;
+    __syncthreads();
+    base = s_base;
     for (int64_t b0 = lo; b0 < hi; b0 += 256) {  // same trip count for the whole workgroup
         const int64_t b = b0 + threadIdx.x;
         const uint32_t f = b < hi && brick_occupied(b, cb, ce) ? 1u : 0u;
@@ -559,102 +686,106 @@ __global__ void __launch_bounds__(256) k_brick_scatter(int64_t nbricks, int64_t 
         if (b < hi) slot_of[b] = f ? (int32_t)(base + inc - 1) : -1;
         base += total;
     }
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) *count = (int32_t)base;
 }
 
 }  // namespace
 
 namespace {
 
+constexpr unsigned kLoopGrid = 2048;  // workgroups of 256 that the chip holds at once
+
+// Every 16th list of n granules leaves its count in pinned host memory (see
+// brick_fill); a change of n clears what a list of other granules left.
+hipError_t brick_count_copy(BrickList &B, int64_t n, hipStream_t s)
+{
+    hipError_t e = hipGetLastError();
+    if (n <= 0 || !B.seen) return e;
+    const bool copy = B.seen_n != n || (B.calls++ & 15u) == 0u;
+    if (B.seen_n != n) *(volatile int32_t *)B.seen = 0;
+    B.seen_n = n;
+    if (copy && e == hipSuccess) e = hipMemcpyAsync(B.seen, B.count, sizeof(int32_t), hipMemcpyDeviceToHost, s);
+    return e;
+}
+
 int64_t scan_chunk(int64_t len)
 {
-    int64_t chunk = (len + kScanThreads - 1) / kScanThreads;
-    return ((chunk + kScanThreads - 1) / kScanThreads) * kScanThreads;
+    const int64_t chunk = (len + kScanThreads - 1) / kScanThreads, unit = 4 * kScanThreads;
+    return (chunk + unit - 1) / unit * unit;
 }
 
 }  // namespace
 
 hipError_t launch_sort_cells(const DevParams &P, int64_t n, const double *x, uint32_t *key, int32_t *order,
-                             int32_t *cell_begin, int32_t *cell_end, int64_t K, SortScratch &S, int64_t *err,
-                             hipStream_t s, const NbrList *nl, int force, int keep_ranges)
+                             int32_t *cell_begin, int32_t *cell_end, int64_t K, SortScratch &S, BrickList &B,
+                             int64_t *err, hipStream_t s, const NbrList *nl, int force, int keep_ranges)
 {
     uint32_t *cnt = S.cnt;  // all zero between sorts
+    uint32_t *begin = reinterpret_cast<uint32_t *>(cell_begin), *end = reinterpret_cast<uint32_t *>(cell_end);
     // previous sorted keys: usable when the last sort had the same n
-    const bool inc = n > 0 && S.last_n == n;
+    const bool same_n = n > 0 && S.last_n == n;
+    const int keep = keep_ranges && same_n ? 1 : 0;
+    const bool small = n <= kSmallSort;
+    // a small sort compares with the previous keys only where an unchanged
+    // state saves the rest of it or the neighbour list
+    const bool inc = same_n && (!small || keep || (nl && !force));
     const uint32_t *pk = inc ? S.skeys[S.cur] : nullptr;
     uint32_t *skeys = S.skeys[S.cur ^ 1];
-    const int32_t *skip = inc ? S.ctl : nullptr;
+    int32_t *ctl = inc ? S.ctl : nullptr;
     // the displacement since the list's build is measured when the list may
     // be kept (its build had this sorted order: the caller checked that)
     const bool measure = nl && inc && !force && nl->thr2 > 0.0f;
+    const unsigned g = grid_for(n, 256);
+    // the passes that may have nothing to do loop over a resident grid: an idle
+    // launch of 65,536 workgroups took 15 us
+    const unsigned gl = g < kLoopGrid ? g : kLoopGrid;
+    uint32_t *nctl = nl ? nl->ctl : nullptr;
+    const float thr2 = nl ? nl->thr2 : 0.0f;
+    float *dpart = measure ? nl->dpart : nullptr;
     if (n > 0) {
-        k_cell_keys<<<grid_for(n, 256), 256, 0, s>>>(P, n, x, key, err, pk, S.chg, S.ctl,
-                                                     measure ? nl->xref : nullptr, measure ? nl->dpart : nullptr);
-        if (inc) {
-            k_chg_sort<<<1, 1024, 0, s>>>(n, pk, S.chg, S.ctl, S.chg_s, S.chg_p, skeys, order,
-                                          nl ? nl->ctl : nullptr, measure ? 0 : 1, nl ? nl->thr2 : 0.0f,
-                                          measure ? nl->dpart : nullptr, (int64_t)grid_for(n, 256));
-            k_merge<<<grid_for(n, 256), 256, 0, s>>>(n, key, pk, S.ctl, S.chg_s, S.chg_p, skeys, order);
-        }
-        // digit passes (skipped on the device when the incremental path sorted)
-        const int items = sort_items(n);
-        const int64_t tiles = (n + kSortThreads * items - 1) / (kSortThreads * items);
-        const unsigned tg = (unsigned)(tiles < kRtsGrid ? tiles : kRtsGrid);
-        const uint32_t *kin = key;
-        const int32_t *vin = nullptr;
-        for (int pass = 0; pass < S.passes; ++pass) {
-            const bool last = pass == S.passes - 1;
-            uint32_t *kout = last ? skeys : ((pass & 1) ? S.kB : S.kA);
-            int32_t *vout = last ? order : ((pass & 1) ? S.vB : S.vA);
-            if (items == 1)
-                k_rts_count<1><<<tg, kSortThreads, 0, s>>>(kin, n, pass, tiles, S.tcnt, skip);
-            else
-                k_rts_count<kSortItems><<<tg, kSortThreads, 0, s>>>(kin, n, pass, tiles, S.tcnt, skip);
-            k_rts_scan<<<kRadix, kSortThreads, 0, s>>>(S.tcnt, tiles, S.rowtot, skip);
-            if (items == 1)
-                k_rts_scatter<1><<<tg, kSortThreads, 0, s>>>(kin, vin, kout, vout, n, pass, tiles, S.tcnt,
-                                                             S.rowtot, skip);
-            else
-                k_rts_scatter<kSortItems><<<tg, kSortThreads, 0, s>>>(kin, vin, kout, vout, n, pass, tiles, S.tcnt,
-                                                                      S.rowtot, skip);
-            kin = kout;
-            vin = vout;
-        }
+        k_cell_keys<<<g, 256, 0, s>>>(P, n, x, key, err, pk, small ? nullptr : S.chg, S.ctl,
+                                      measure ? nl->xref : nullptr, dpart, order, skeys);
+        if (inc && !small)
+            k_chg_sort<<<1, 1024, 0, s>>>(n, pk, S.chg, S.ctl, S.chg_s, S.chg_p, skeys, order, nctl, measure ? 0 : 1,
+                                          thr2, dpart, (int64_t)g);
+        k_cell_count<<<gl, 256, 0, s>>>(key, n, cnt, S.slot, pk, S.chg_s, S.chg_p, skeys, order, ctl,
+                                        inc && small ? 1 : 0, keep, nctl, measure ? 0 : 1, thr2, dpart, (int64_t)g);
     }
-    // cell ranges: kept when the caller's tables hold the last sort's ranges
-    // and no key changed (decided on the device by k_chg_sort)
-    const int keep = keep_ranges && inc ? 1 : 0;
-    const int32_t *kskip = keep ? S.ctl : nullptr;
-    if (n > 0) k_cell_count<<<grid_for(n, 256), 256, 0, s>>>(skeys, n, cnt, kskip);
-    const int64_t chunk = scan_chunk(K);
+    // cell ranges and bricks: kept when the caller's tables hold the last
+    // sort's ranges and no key changed (decided on the device)
+    // (tables of one pass: chunks of 4,096 cells, so that 32 workgroups share them)
+    const bool direct = n > 0 && K <= kDirectScan;
+    const int64_t chunk = direct ? 4 * kScanThreads : scan_chunk(K);
     const int nb = (int)((K + chunk - 1) / chunk);
-    k_scan_reduce<<<nb, kScanThreads, 0, s>>>(cnt, K, chunk, S.sums, kskip);
-    k_scan_spine<<<1, kScanThreads, 0, s>>>(S.sums, nb, kskip);
-    k_scan_down_ranges<<<nb, kScanThreads, 0, s>>>(cnt, reinterpret_cast<uint32_t *>(cell_begin),
-                                                   reinterpret_cast<uint32_t *>(cell_end), K, chunk, S.sums, S.ctl,
-                                                   keep);
+    if (!direct)
+        k_scan_reduce<<<nb, kScanThreads, 0, s>>>(cnt, K, chunk, S.sums, S.sums + kScanThreads,
+                                                  keep ? S.ctl : nullptr);
+    k_scan_down_ranges<<<nb, kScanThreads, 0, s>>>(cnt, begin, end, K, chunk, direct ? nullptr : S.sums,
+                                                   S.sums + kScanThreads, S.ctl, keep, B.list, B.count, B.slot_of);
+    if (n > 0) {
+        k_cell_place<<<gl, 256, 0, s>>>(key, n, begin, S.slot, S.tmp, skeys, ctl, keep);
+        k_cell_order<<<gl, 256, 0, s>>>(n, skeys, begin, end, S.tmp, S.tmp2, order, ctl, keep, direct ? cnt : nullptr,
+                                        K);
+    }
     S.cur ^= 1;  // this sort's keys are the previous keys of the next
     S.last_n = n;
-    return hipGetLastError();
+    return brick_count_copy(B, n, s);
 }
 
-hipError_t launch_brick_list(const int32_t *cb, const int32_t *ce, BrickList &B, int64_t n, hipStream_t s,
-                             const int32_t *skip)
+hipError_t launch_brick_list(const int32_t *cb, const int32_t *ce, BrickList &B, int64_t n, hipStream_t s)
 {
     const int64_t nb = B.nbricks;
     if (nb <= 0) return hipSuccess;
+    if (nb <= kBricksOneGroup) {
+        k_brick_list<<<1, kScanThreads, 0, s>>>((int)nb, cb, ce, B.list, B.count, B.slot_of);
+        return brick_count_copy(B, n, s);
+    }
     int64_t per = 1024;
     while ((nb + per - 1) / per > kScanThreads) per *= 2;
     const int blocks = (int)((nb + per - 1) / per);
-    k_brick_count<<<blocks, 256, 0, s>>>(nb, per, cb, ce, B.sums, skip);
-    k_brick_spine<<<1, kScanThreads, 0, s>>>(B.sums, blocks, B.count, skip);
-    k_brick_scatter<<<blocks, 256, 0, s>>>(nb, per, cb, ce, B.sums, B.list, B.slot_of, skip);
-    hipError_t e = hipGetLastError();
-    if (n > 0 && B.seen && (B.calls++ & 15u) == 0u) {  // see brick_fill
-        if (e == hipSuccess) e = hipMemcpyAsync(B.seen, B.count, sizeof(int32_t), hipMemcpyDeviceToHost, s);
-        if (B.seen_n != n) *(volatile int32_t *)B.seen = 0;  // a copy of other tables until this one lands
-        B.seen_n = n;
-    }
-    return e;
+    k_brick_count<<<blocks, 256, 0, s>>>(nb, per, cb, ce, B.sums);
+    k_brick_scatter<<<blocks, 256, 0, s>>>(nb, per, cb, ce, B.sums, B.list, B.count, B.slot_of);
+    return brick_count_copy(B, n, s);
 }
 
 hipError_t launch_reorder(int64_t n, const int32_t *order, const double *x, const double *v, const double *r,
