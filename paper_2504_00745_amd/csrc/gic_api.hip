@@ -275,7 +275,7 @@ int64_t idp_work_bytes(const IdpDims &D0)
     const int L = idp_levels(D0, lv);
     int64_t b = 9 * idp_align(D0.G * 8) + idp_align(3 * kIdpMaxBlocks * 8) + idp_align(sizeof(CgState));
     for (int l = 1; l < L; ++l) b += 5 * idp_align(lv[l].G * 8);
-    return b;
+    return b + idp_align(lv[L - 1].G * lv[L - 1].G * 8);
 }
 
 // Carves the workspace: alpha_f' and s slots for gic_density_projection, the
@@ -318,6 +318,7 @@ IdpWork idp_carve(void *work, const IdpDims &D0, int precond, double **at, doubl
         p += 5 * g;
         W.lev[l] = m;
     }
+    W.coarse = (double *)p;
     return W;
 }
 

@@ -17,13 +17,16 @@
 // without atomics: each block writes one partial per quantity, and every
 // block of the consuming kernel sums all partials in the same fixed order,
 // so the iteration is deterministic and needs no clearing between launches.
+#include <string.h>
+
 #include "idp_launch.hpp"
 
 namespace gic {
 
 namespace {
 
-constexpr int kIdpThreads = 256;
+constexpr int kIdpThreads = 512;
+constexpr int kIdpWaves = kIdpThreads / 64;
 
 __device__ inline double block_sum(double v, double *red)
 {
@@ -32,7 +35,10 @@ __device__ inline double block_sum(double v, double *red)
     __syncthreads();
     if (l == 0) red[w] = v;
     __syncthreads();
-    return (red[0] + red[1]) + (red[2] + red[3]);
+    double t = red[0];
+#pragma unroll
+    for (int i = 1; i < kIdpWaves; ++i) t += red[i];
+    return t;
 }
 
 // Sum of the nb partials of a quantity, identical in every block.
@@ -41,6 +47,35 @@ __device__ inline double sum_partials(const double *__restrict__ part, int nb, d
     double v = 0.0;
     for (int i = threadIdx.x; i < nb; i += kIdpThreads) v += part[i];
     return block_sum(v, red);
+}
+
+// Two such sums at once.
+__device__ inline void sum_partials2(const double *__restrict__ p, const double *__restrict__ q, int nb, double *red,
+                                     double &s, double &t)
+{
+    double v = 0.0, u = 0.0;
+    for (int i = threadIdx.x; i < nb; i += kIdpThreads) {
+        v += p[i];
+        u += q[i];
+    }
+    for (int m = 32; m >= 1; m >>= 1) {
+        v += __shfl_xor(v, m);
+        u += __shfl_xor(u, m);
+    }
+    const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
+    __syncthreads();
+    if (l == 0) {
+        red[w] = v;
+        red[kIdpWaves + w] = u;
+    }
+    __syncthreads();
+    s = red[0];
+    t = red[kIdpWaves];
+#pragma unroll
+    for (int i = 1; i < kIdpWaves; ++i) {
+        s += red[i];
+        t += red[kIdpWaves + i];
+    }
 }
 
 struct Nbr {
@@ -184,19 +219,19 @@ __global__ void __launch_bounds__(kIdpThreads) k_idp_apply(IdpDims D, const doub
     }
 }
 
-// CG start: r = s - L q, z = r / diag, d = z, the signed coefficients ac
+// CG start: r = s - L q, z = r / diag (in the partials only), the signed coefficients ac
 // (alpha_f' on fluid cells, -alpha_f' on air cells, 0 on solid cells) that
 // the iteration kernels read instead of alpha_f' and the labels; partials of
 // s.s, r.z, r.r.
 __global__ void __launch_bounds__(kIdpThreads) k_cg_init(IdpDims D, const double *__restrict__ at,
                                                          const uint8_t *__restrict__ lab,
                                                          const double *__restrict__ s, const double *__restrict__ q,
-                                                         double *__restrict__ r, double *__restrict__ d,
-                                                         double *__restrict__ dinv, double *__restrict__ ac,
+                                                         double *__restrict__ r, double *__restrict__ dinv,
+                                                         double *__restrict__ ac,
                                                          double *__restrict__ part, CgState *__restrict__ st,
                                                          int64_t *err)
 {
-    __shared__ double red[4];
+    __shared__ double red[kIdpWaves];
     double rz = 0.0, rr = 0.0, ss = 0.0;
     for (int64_t c = (int64_t)blockIdx.x * kIdpThreads + threadIdx.x; c < D.G;
          c += (int64_t)gridDim.x * kIdpThreads) {
@@ -212,7 +247,6 @@ __global__ void __launch_bounds__(kIdpThreads) k_cg_init(IdpDims D, const double
         const double di = dg > 0.0 ? 1.0 / dg : 0.0;  // a fluid cell walled in on all sides: singular row
         const double zc = rc * di;
         r[c] = rc;
-        d[c] = zc;
         dinv[c] = di;
         rz += rc * zc;
         rr += rc * rc;
@@ -234,7 +268,7 @@ __global__ void __launch_bounds__(kIdpThreads) k_cg_init(IdpDims D, const double
 __global__ void __launch_bounds__(kIdpThreads) k_cg_start(int nb, const double *__restrict__ part, double tol,
                                                           CgState *__restrict__ st)
 {
-    __shared__ double red[4];
+    __shared__ double red[kIdpWaves];
     const double ss = sum_partials(part, nb, red);
     const double rz = sum_partials(part + nb, nb, red);
     const double rr = sum_partials(part + 2 * nb, nb, red);
@@ -249,48 +283,114 @@ __global__ void __launch_bounds__(kIdpThreads) k_cg_start(int nb, const double *
     }
 }
 
-// Stencil passes blocked in 2.5D.
-//   MODE 0, iteration k, part 1: w = L d, the partials of d.w in
-//     part[block].
-//   MODE 1, the multigrid post-sweep from the prolonged iterate d = u:
-//     w = e = u + omega D^-1 (b - A u) on fluid cells, b elsewhere; the
-//     partials of b.e in part[nblocks + block] when part is given.
-//   MODE 2, the residual after the pre-sweep from zero, e1 = omega D^-1 b
-//     (formed as each value is loaded): w = b - A e1 on fluid cells, 0
-//     elsewhere, for the restriction.
-// A block takes x-y tiles of kTileX x kTileY cells (each wave kTileRows rows)
-// and a run of zlen planes.  It keeps its columns' coefficients and values for
-// planes z - 1, z, z + 1 in registers and the tile of plane z with a one-cell
-// halo in LDS, so that each operand is read from memory about once instead of
-// once per neighbour; the next plane of each column and the next halo are
-// loaded one step ahead, within the run.  The face sum is face_sum_ac's, term
-// by term in the same order (cells outside the box hold coefficient 0 and
-// value 0).  Items (tile, run of planes) are dealt to the blocks; the block
-// count is the other iteration kernels', whose partial sums these kernels'
-// must match.
+// Stencil passes of a conjugate-gradient iteration, blocked in 2.5D; the
+// streaming passes around them are fused in, so that each vector is read and
+// written as seldom as the iteration allows.
+//   kApplyMg, kApplyJac, iteration k: the direction d = z + beta d_old (z from
+//     the V-cycle, or r / diag; beta = rz_k / rz_{k-1}, d = z at k = 0), formed
+//     as each value is loaded and stored in the other direction buffer (the
+//     halo reads d_old), and w = L d; partials of d.w.  Before that the
+//     stopping test on the last iteration's r.r.
+//   kUpdate, iteration k, multigrid: q += alpha d, r' = r - alpha w (stored in
+//     the buffer of z, which d has consumed; partials of r'.r'), the residual
+//     r' - A w D^-1 r' of the pre-sweep from zero and its restriction: the
+//     coarse right-hand side is the sum of the fluid children's residuals.
+//   kResidual: the last part of that, of a level's right-hand side b.
+//   kPost: u = w D^-1 b + P E (coarse correction, zero off the coarse fluid)
+//     and one sweep, e = u + w D^-1 (b - A u) on fluid cells, b elsewhere; on
+//     the finest level the partials of b.e (= r.z).
+// A block takes x-y tiles of kTileX x kTileY cells (each wave two adjacent
+// rows of 32, so that four lanes hold the four children of a coarse cell in a
+// plane) and a run of zlen planes (even).  It keeps its columns' coefficients
+// and values for planes z - 1, z, z + 1 in registers and the tile of plane z
+// with a one-cell halo in LDS, so that each operand is read from memory about
+// once instead of once per neighbour; the next plane of each column and the
+// next halo are loaded one step ahead, within the run.  (Tiles of 64 x 8 with
+// two rows per thread took 171 registers in kUpdate, two waves per SIMD, and
+// a larger halo.)  The face sum is face_sum_ac's, term by term in the same order
+// (cells outside the box hold coefficient 0 and value 0).  Items (tile, run of
+// planes) are dealt to the blocks; the block count is the other iteration
+// kernels', whose partial sums these kernels' must match.
+// Bound by HBM: on 4.2 M cells the apply pass takes 32 us (197 MB), the update
+// 51 (310 MB with the halo), the post pass 29 (about 160 MB), 6 TB/s each;
+// separate direction and product passes took 38, update, residual and
+// restriction 69, prolongation and sweep 54, and five more launches.
 constexpr double kOmega = 2.0 / 3.0;  // damping of the multigrid's Jacobi sweeps
-constexpr int kTileRows = 2;  // tile rows per wave (rows row and row + 4 of the tile)
-constexpr int kTileX = 64, kTileY = kIdpThreads / 64 * kTileRows;
+constexpr int kTileX = 32, kTileY = kIdpThreads / kTileX;
+enum StencilMode { kApplyMg, kApplyJac, kUpdate, kResidual, kPost };
 
-template <int MODE>
-__global__ void __launch_bounds__(kIdpThreads) k_stencil_tiled(IdpDims D, int ntx, int nty, int zlen,
-                                                               const double *__restrict__ ac,
-                                                               const double *__restrict__ d,
-                                                               const double *__restrict__ b,
-                                                               const double *__restrict__ dinv, double scale,
-                                                               double *__restrict__ w, double *__restrict__ part,
-                                                               const CgState *__restrict__ st)
+struct StencilArgs {
+    IdpDims D;
+    int ntx, nty, zlen, k;
+    double scale;
+    const double *ac, *dinv;
+    const double *p;       // kApplyMg: z; kApplyJac, kUpdate: r; else: b
+    const double *d;       // kApply: the old direction; kUpdate: the direction
+    const double *w;       // kUpdate: L d
+    const double *ec;      // kPost: the coarse correction
+    const double *acc;     // kUpdate, kResidual: the coarse coefficients
+    int64_t cnx, cny;      // coarse cells per row and rows per plane
+    double *o1, *o2;       // outputs: d, w | q, r' | - , - | e
+    double *bc;            // kUpdate, kResidual: the coarse right-hand side
+    double *part;
+    CgState *st;
+};
+
+// Off: byte offsets inside a plane, 32 bits where a plane is below 4 GiB (the
+// loads then take a scalar base and a 32-bit offset).
+template <int MODE, typename Off>
+__global__ void __launch_bounds__(kIdpThreads) __attribute__((amdgpu_waves_per_eu(4))) k_stencil(StencilArgs A)
 {
-    constexpr int kWaves = kIdpThreads / 64;
-    __shared__ double red[4];
+    constexpr bool kApply = MODE == kApplyMg || MODE == kApplyJac;
+    constexpr bool kRestrict = MODE == kUpdate || MODE == kResidual;
+    __shared__ double red[2 * kIdpWaves];
     __shared__ double sa[kTileY + 2][kTileX + 2], sv[kTileY + 2][kTileX + 2];
-    if (st->done >= 0) return;
-    // the value a cell contributes: d, or the pre-sweep iterate w D^-1 b of the residual pass
-    auto val = [&](int64_t n) { return MODE == 2 ? kOmega * dinv[n] * b[n] : d[n]; };
-    const int lane = threadIdx.x & 63, row = threadIdx.x >> 6, t = threadIdx.x;
+    __shared__ int64_t s_done;
+    // block 0 of an apply pass may set done while others start: read it once per block
+    if (threadIdx.x == 0) s_done = A.st->done;
+    __syncthreads();
+    if (s_done >= 0) return;
+    const IdpDims &D = A.D;
+    const int64_t nb = gridDim.x;
+    const bool first = kApply && A.k == 0;
+    double coef = 0.0;  // beta of the apply passes, alpha of the update
+    const int tx = threadIdx.x & (kTileX - 1), ty = threadIdx.x / kTileX, t = threadIdx.x;
     const int64_t nx = D.nx, ny = D.ny, nz = D.nz;
-    const int64_t tiles = (int64_t)ntx * nty, nzc = (nz + zlen - 1) / zlen, items = tiles * nzc;
-    // halo slot of this thread: rows below and above the tile (t < 128), columns left and right (t < 144)
+    const int64_t tiles = (int64_t)A.ntx * A.nty, nzc = (nz + A.zlen - 1) / A.zlen, items = tiles * nzc;
+    // what a cell's coefficient a, value v, right-hand side b and 1 / diag come from
+    struct Raw {
+        double a, p, s, q;
+    };
+    auto at = [](const double *base, Off off) {
+        return *reinterpret_cast<const double *>(reinterpret_cast<const char *>(base) + off);
+    };
+    auto put = [](double *base, Off off, double v) {
+        *reinterpret_cast<double *>(reinterpret_cast<char *>(base) + off) = v;
+    };
+    const int64_t csxy = A.cnx * A.cny;
+    // the cell at off in plane z; its coarse cell at coff in plane z / 2
+    auto load = [&](int64_t z, Off off, Off coff) {
+        const int64_t pz = z * D.sxy;
+        Raw r;
+        r.a = at(A.ac + pz, off);
+        r.p = at(A.p + pz, off);
+        r.s = MODE != kApplyMg ? at(A.dinv + pz, off) : 0.0;
+        r.q = 0.0;
+        if (kApply && !first) r.q = at(A.d + pz, off);
+        if (MODE == kUpdate) r.q = at(A.w + pz, off);
+        if (MODE == kPost) r.q = at(A.ec + (z >> 1) * csxy, coff);
+        return r;
+    };
+    const Raw none = {0.0, 0.0, 0.0, 0.0};
+    // (coef is set below, after the first loads are under way)
+    auto rhs = [&](const Raw &r) { return MODE == kUpdate ? r.p - coef * r.q : r.p; };
+    auto value = [&](const Raw &r) {
+        if (MODE == kApplyMg) return first ? r.p : r.p + coef * r.q;
+        if (MODE == kApplyJac) return first ? r.p * r.s : r.p * r.s + coef * r.q;
+        const double e1 = kOmega * r.s * rhs(r);
+        return MODE == kPost ? e1 + r.q : e1;
+    };
+    // halo slot of this thread: rows below and above the tile (t < 64), columns left and right (t < 96)
     int hr = -1, hc = -1, hdi = 0, hdj = 0;
     if (t < kTileX) { hr = 0; hc = t + 1; hdi = t; hdj = -1; }
     else if (t < 2 * kTileX) { hr = kTileY + 1; hc = t - kTileX + 1; hdi = t - kTileX; hdj = kTileY; }
@@ -299,110 +399,158 @@ __global__ void __launch_bounds__(kIdpThreads) k_stencil_tiled(IdpDims D, int nt
     // items in tile order within a run of planes; workgroups are dealt to the
     // eight XCDs in turn, so block b starts at item (b % 8) nb/8 + b/8 and each
     // XCD takes a contiguous eighth (y-adjacent tiles share its L2)
-    const int64_t nb = gridDim.x;
-    const int64_t first = nb % 8 ? (int64_t)blockIdx.x : (blockIdx.x % 8) * (nb / 8) + blockIdx.x / 8;
-    double dw = 0.0;
-    for (int64_t it = first; it < items; it += nb) {
-        const int64_t tile = it % tiles, z0 = (it / tiles) * zlen;
-        const int64_t z1 = z0 + zlen < nz ? z0 + zlen : nz;
-        const int64_t i0 = (tile % ntx) * kTileX, j0 = (tile / ntx) * kTileY;
-        const int64_t i = i0 + lane;
-        bool own[kTileRows];
-        int64_t col[kTileRows];  // cell index of (i, j, 0) for the thread's rows
-#pragma unroll
-        for (int q = 0; q < kTileRows; ++q) {
-            const int64_t j = j0 + row + q * kWaves;
-            own[q] = i < nx && j < ny;
-            col[q] = j * nx + i;
-        }
+    const int64_t it0 = nb % 8 ? (int64_t)blockIdx.x : (blockIdx.x % 8) * (nb / 8) + blockIdx.x / 8;
+    double dot = 0.0;
+    int64_t z0 = 0, z1 = 0, i = 0, j = 0;
+    bool own = false, hown = false;
+    Off col = 0, ccol = 0, hcol = 0, hccol = 0;
+    Raw rm = none, r0 = none, rp = none, h = none;
+    auto plane = [&](int64_t z) { return own && z >= 0 && z < nz ? load(z, col, ccol) : none; };
+    auto begin = [&](int64_t it) {  // an item's place and its first loads
+        const int64_t tile = it % tiles;
+        z0 = (it / tiles) * A.zlen;
+        z1 = z0 + A.zlen < nz ? z0 + A.zlen : nz;
+        const int64_t i0 = (tile % A.ntx) * kTileX, j0 = (tile / A.ntx) * kTileY;
+        i = i0 + tx;
+        j = j0 + ty;
+        own = i < nx && j < ny;
+        col = own ? (Off)(j * nx + i) * 8 : 0;
+        ccol = own ? (Off)((j >> 1) * A.cnx + (i >> 1)) * 8 : 0;
         const int64_t hi = i0 + hdi, hj = j0 + hdj;
-        const bool hown = hr >= 0 && hi >= 0 && hi < nx && hj >= 0 && hj < ny;
-        const int64_t hcol = hj * nx + hi;
-        // columns: m = z - 1, 0 = z, p = z + 1; halo of plane z
-        double am[kTileRows], vm[kTileRows], a0[kTileRows], v0[kTileRows], ap[kTileRows], vp[kTileRows];
-        double b0[kTileRows], di0[kTileRows];  // right-hand side and 1/diag of plane z (sweep)
-        double ha = 0.0, hv = 0.0;
-#pragma unroll
-        for (int q = 0; q < kTileRows; ++q) {
-            am[q] = vm[q] = a0[q] = v0[q] = ap[q] = vp[q] = b0[q] = di0[q] = 0.0;
-            if (MODE != 0 && own[q]) b0[q] = b[col[q] + z0 * D.sxy];
-            if (MODE == 1 && own[q]) di0[q] = dinv[col[q] + z0 * D.sxy];
-            if (own[q] && z0 > 0) { am[q] = ac[col[q] + (z0 - 1) * D.sxy]; vm[q] = val(col[q] + (z0 - 1) * D.sxy); }
-            if (own[q]) { a0[q] = ac[col[q] + z0 * D.sxy]; v0[q] = val(col[q] + z0 * D.sxy); }
-            if (own[q] && z0 + 1 < nz) { ap[q] = ac[col[q] + (z0 + 1) * D.sxy]; vp[q] = val(col[q] + (z0 + 1) * D.sxy); }
+        hown = hr >= 0 && hi >= 0 && hi < nx && hj >= 0 && hj < ny;
+        hcol = hown ? (Off)(hj * nx + hi) * 8 : 0;
+        hccol = hown ? (Off)((hj >> 1) * A.cnx + (hi >> 1)) * 8 : 0;
+        rm = plane(z0 - 1);
+        r0 = plane(z0);
+        rp = plane(z0 + 1);
+        h = hown ? load(z0, hcol, hccol) : none;
+    };
+    // (kUpdate begins after alpha is known: held over the sum, its first loads
+    // cost registers beyond 128 and 7 us of 51)
+    if (MODE != kUpdate && it0 < items) begin(it0);
+    if (kApply && !first) {
+        const double thr = A.st->thr, rz0 = A.st->rz[(A.k + 1) & 1];
+        double rz1, rr;
+        sum_partials2(A.part + nb, A.part + 2 * nb, (int)nb, red, rz1, rr);
+        const bool conv = rr <= thr;
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            A.st->rz[A.k & 1] = rz1;
+            A.st->rr = rr;
+            A.st->iters = A.k;
+            if (conv) A.st->done = A.k;
         }
-        if (hown) { ha = ac[hcol + z0 * D.sxy]; hv = val(hcol + z0 * D.sxy); }
+        if (conv) return;
+        coef = rz1 / rz0;
+    }
+    if (MODE == kUpdate) {
+        const double rz = A.st->rz[A.k & 1];
+        coef = rz / sum_partials(A.part, (int)nb, red);
+    }
+    for (int64_t it = it0; it < items; it += nb) {
+        if (MODE == kUpdate || it != it0) begin(it);
+        // the column: m = z - 1, 0 = z, p = z + 1; halo of plane z
+        double am = rm.a, vm = value(rm), a0 = r0.a, v0 = value(r0), ap = rp.a, vp = value(rp);
+        double b0 = rhs(r0), bp = rhs(rp), s0 = r0.s, sp = rp.s;  // right-hand side, 1 / diag
+        double half = 0.0;                                        // kRestrict: the even plane's children
         for (int64_t z = z0; z < z1; ++z) {
-            // one step ahead: the columns' plane z + 2 and the halo of plane z + 1
-            double a2[kTileRows], v2[kTileRows], b1[kTileRows], di1[kTileRows], ha1 = 0.0, hv1 = 0.0;
-#pragma unroll
-            for (int q = 0; q < kTileRows; ++q) {
-                a2[q] = v2[q] = b1[q] = di1[q] = 0.0;
-                if (MODE != 0 && own[q] && z + 1 < z1) b1[q] = b[col[q] + (z + 1) * D.sxy];
-                if (MODE == 1 && own[q] && z + 1 < z1) di1[q] = dinv[col[q] + (z + 1) * D.sxy];
-                // plane z1 is the last one the run reads (the +z neighbour of its last plane)
-                if (own[q] && z + 2 <= z1 && z + 2 < nz) {
-                    a2[q] = ac[col[q] + (z + 2) * D.sxy];
-                    v2[q] = val(col[q] + (z + 2) * D.sxy);
-                }
+            // one step ahead: the column's plane z + 2 and the halo of plane z + 1
+            // (plane z1 is the last one the run reads, the +z neighbour of its last plane)
+            const Raw r2 = z + 2 <= z1 ? plane(z + 2) : none;
+            Raw h1 = none;
+            if (hown && z + 1 < z1) h1 = load(z + 1, hcol, hccol);
+            double q0 = 0.0, d0 = 0.0;
+            if (MODE == kUpdate && own) {
+                q0 = at(A.o1 + z * D.sxy, col);
+                d0 = at(A.d + z * D.sxy, col);
             }
-            if (hown && z + 1 < z1) { ha1 = ac[hcol + (z + 1) * D.sxy]; hv1 = val(hcol + (z + 1) * D.sxy); }
             __syncthreads();  // the previous plane's reads of the tile are done
-#pragma unroll
-            for (int q = 0; q < kTileRows; ++q) {
-                sa[row + q * kWaves + 1][lane + 1] = a0[q];
-                sv[row + q * kWaves + 1][lane + 1] = v0[q];
+            sa[ty + 1][tx + 1] = a0;
+            sv[ty + 1][tx + 1] = v0;
+            if (hr >= 0) {
+                sa[hr][hc] = h.a;
+                sv[hr][hc] = value(h);
             }
-            if (hr >= 0) { sa[hr][hc] = ha; sv[hr][hc] = hv; }
             __syncthreads();
-#pragma unroll
-            for (int q = 0; q < kTileRows; ++q) {
-                if (!own[q]) continue;
-                const int r = row + q * kWaves + 1;  // the cell's row in the tile
-                const double an[6] = {sa[r][lane], sa[r][lane + 2], sa[r - 1][lane + 1], sa[r + 1][lane + 1], am[q], ap[q]};
-                const double vn[6] = {sv[r][lane], sv[r][lane + 2], sv[r - 1][lane + 1], sv[r + 1][lane + 1], vm[q], vp[q]};
+            double res = 0.0;
+            if (own) {
+                const int r = ty + 1, c = tx + 1;
+                const double an[6] = {sa[r][c - 1], sa[r][c + 1], sa[r - 1][c], sa[r + 1][c], am, ap};
+                const double vn[6] = {sv[r][c - 1], sv[r][c + 1], sv[r - 1][c], sv[r + 1][c], vm, vp};
                 double acc = 0.0;
 #pragma unroll
                 for (int f = 0; f < 6; ++f) {
-                    const double beta = an[f] != 0.0 ? (a0[q] + fabs(an[f])) * 0.5 : 0.0;
+                    const double beta = an[f] != 0.0 ? (a0 + fabs(an[f])) * 0.5 : 0.0;
                     const double v = an[f] > 0.0 ? vn[f] : 0.0;
-                    acc += beta * (v0[q] - v);
+                    acc += beta * (v0 - v);
                 }
-                if (MODE == 2) {
-                    w[col[q] + z * D.sxy] = a0[q] > 0.0 ? b0[q] - scale * acc : 0.0;
-                } else if (MODE == 1) {
-                    const double Au = scale * acc;
-                    const double e = a0[q] > 0.0 ? v0[q] + kOmega * di0[q] * (b0[q] - Au) : b0[q];
-                    w[col[q] + z * D.sxy] = e;
-                    dw += b0[q] * e;
+                double *const o1 = A.o1 + z * D.sxy, *const o2 = A.o2 + z * D.sxy;
+                if (kApply) {
+                    const double Lv = a0 > 0.0 ? acc : v0;  // identity row off the fluid
+                    put(o1, col, v0);
+                    put(o2, col, Lv);
+                    dot += v0 * Lv;
+                } else if (MODE == kPost) {
+                    const double Au = A.scale * acc;
+                    const double e = a0 > 0.0 ? v0 + kOmega * s0 * (b0 - Au) : b0;
+                    put(o1, col, e);
+                    dot += b0 * e;
                 } else {
-                    const double Lv = a0[q] > 0.0 ? acc : v0[q];  // identity row off the fluid
-                    w[col[q] + z * D.sxy] = Lv;
-                    dw += v0[q] * Lv;
+                    res = a0 > 0.0 ? b0 - A.scale * acc : 0.0;
+                    if (MODE == kUpdate) {
+                        put(o1, col, q0 + coef * d0);
+                        put(o2, col, b0);
+                        dot += b0 * b0;
+                    }
                 }
             }
-#pragma unroll
-            for (int q = 0; q < kTileRows; ++q) {
-                am[q] = a0[q]; vm[q] = v0[q]; a0[q] = ap[q]; v0[q] = vp[q]; ap[q] = a2[q]; vp[q] = v2[q];
-                b0[q] = b1[q]; di0[q] = di1[q];
+            if (kRestrict) {
+                // children (x, y, z): ((c0 + c1) + (c2 + c3)) + ((c4 + c5) + (c6 + c7)),
+                // x on the neighbour lane, y 32 lanes on
+                double quad = res + __shfl_xor(res, 1);
+                quad += __shfl_xor(quad, kTileX);
+                if ((z & 1) == 0) half = quad;
+                if (((z & 1) || z == nz - 1) && own && ((i | j) & 1) == 0) {
+                    const double sum = (z & 1) ? half + quad : half;
+                    const int64_t pz = (z >> 1) * csxy;
+                    put(A.bc + pz, ccol, at(A.acc + pz, ccol) > 0.0 ? sum : 0.0);
+                }
             }
-            ha = ha1; hv = hv1;
+            am = a0; vm = v0; a0 = ap; v0 = vp; b0 = bp; s0 = sp;
+            ap = r2.a; vp = value(r2); bp = rhs(r2); sp = r2.s;
+            h = h1;
         }
     }
-    if (MODE == 0 || (MODE == 1 && part)) {
-        dw = block_sum(dw, red);
-        if (threadIdx.x == 0) part[(MODE == 1 ? nb : 0) + blockIdx.x] = dw;
+    if (kApply || MODE == kUpdate || (MODE == kPost && A.part)) {
+        dot = block_sum(dot, red);
+        const int64_t slot = kApply ? 0 : (MODE == kUpdate ? 2 : 1);
+        if (threadIdx.x == 0) A.part[slot * nb + blockIdx.x] = dot;
     }
 }
 
-template <bool JAC>
+// After the last of a chunk of iterations: its r.r and the stopping test (one
+// block), so that the host reads the state of all iterations run.
+__global__ void __launch_bounds__(kIdpThreads) k_cg_check(int nb, int k, const double *__restrict__ part,
+                                                          CgState *__restrict__ st)
+{
+    __shared__ double red[kIdpWaves];
+    if (st->done >= 0) return;
+    const double rr = sum_partials(part + 2 * nb, nb, red);
+    if (threadIdx.x == 0) {
+        st->rr = rr;
+        st->iters = k;
+        if (rr <= st->thr) st->done = k;
+    }
+}
+
+// Iteration k with the Jacobi preconditioner: q += alpha d, r -= alpha w; the
+// partials of r.z and r.r.
 __global__ void __launch_bounds__(kIdpThreads) k_cg_update(IdpDims D, int k, const double *__restrict__ d,
                                                            const double *__restrict__ w,
                                                            const double *__restrict__ dinv, double *__restrict__ q,
                                                            double *__restrict__ r, double *__restrict__ part,
                                                            const CgState *__restrict__ st)
 {
-    __shared__ double red[4];
+    __shared__ double red[kIdpWaves];
     if (st->done >= 0) return;
     const int nb = gridDim.x;
     const double dw = sum_partials(part, nb, red);
@@ -413,48 +561,15 @@ __global__ void __launch_bounds__(kIdpThreads) k_cg_update(IdpDims D, int k, con
         q[c] += alpha * d[c];
         const double rc = r[c] - alpha * w[c];
         r[c] = rc;
-        if (JAC) rz += rc * (rc * dinv[c]);
+        rz += rc * (rc * dinv[c]);
         rr += rc * rc;
     }
-    if (JAC) rz = block_sum(rz, red);
+    rz = block_sum(rz, red);
     rr = block_sum(rr, red);
     if (threadIdx.x == 0) {
-        if (JAC) part[nb + blockIdx.x] = rz;  // with multigrid the V-cycle writes r.z
+        part[nb + blockIdx.x] = rz;
         part[2 * nb + blockIdx.x] = rr;
     }
-}
-
-// Iteration k, part 3: rz_{k+1}, r.r; stop at r.r <= tol^2 s.s, else
-// d = z + (rz_{k+1} / rz_k) d.  Block 0 records the state for iteration k + 1
-// in the other rz slot (the current one is still read by other blocks).
-template <bool JAC>
-__global__ void __launch_bounds__(kIdpThreads) k_cg_direction(IdpDims D, int k, const double *__restrict__ r,
-                                                              const double *__restrict__ dinv,
-                                                              const double *__restrict__ z, double *__restrict__ d,
-                                                              const double *__restrict__ part,
-                                                              CgState *__restrict__ st)
-{
-    __shared__ double red[4];
-    __shared__ int64_t s_done;
-    // block 0 of this kernel may set done while others start: read it once per block
-    if (threadIdx.x == 0) s_done = st->done;
-    __syncthreads();
-    if (s_done >= 0) return;
-    const int nb = gridDim.x;
-    const double rz1 = sum_partials(part + nb, nb, red);
-    const double rr = sum_partials(part + 2 * nb, nb, red);
-    const bool conv = rr <= st->thr;
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        st->rz[(k + 1) & 1] = rz1;
-        st->rr = rr;
-        st->iters = k + 1;
-        if (conv) st->done = k + 1;
-    }
-    if (conv) return;
-    const double beta = rz1 / st->rz[k & 1];
-    for (int64_t c = (int64_t)blockIdx.x * kIdpThreads + threadIdx.x; c < D.G;
-         c += (int64_t)gridDim.x * kIdpThreads)
-        d[c] = (JAC ? r[c] * dinv[c] : z[c]) + beta * d[c];
 }
 
 // Face displacements (Eq. 13): for the face from cell c to its +axis
@@ -512,10 +627,12 @@ __global__ void __launch_bounds__(kIdpThreads) k_idp_faces(IdpDims D, double dx,
 // children) and R = P^T (the sum of the fluid children's residuals).
 // Smoothing: one damped Jacobi sweep (omega = 2/3) before and one after the
 // coarse correction; the pre-sweep from zero, w D^-1 b, is formed on the fly
-// where it is used.  A small level costs two passes (restriction; correction
-// and post-sweep); a level of at least kMgSplitCells cells four (residual into
-// t, restriction of t, prolongation into t, post-sweep).  The coarsest level (at most 256 cells) takes 48 sweeps in
-// LDS.  Equal pre- and post-sweeps and R = P^T keep the preconditioner
+// where it is used.  A level costs two passes (restriction; correction and
+// post-sweep): the finest and levels of at least kMgTiledCells cells blocked
+// in 2.5D (k_stencil), the smaller ones a thread per cell; the levels of at
+// most kTailTop cells run in one workgroup and one launch (k_mg_tail).
+// The coarsest level (at most 256 cells) takes 48 sweeps, as a product with
+// their matrix.  Equal pre- and post-sweeps and R = P^T keep the preconditioner
 // symmetric.  Non-fluid rows of the finest level are identity rows and get
 // z = r.  Levels carry the signed coefficients (see face_sum_ac).
 constexpr int kCoarseSweeps = 48;
@@ -578,8 +695,7 @@ __global__ void __launch_bounds__(kIdpThreads) k_mg_diag(MgLevel L)
 // residuals b - A e1.  Eight adjacent lanes take the eight children of one
 // coarse cell (lane bits: x, y, z offset) and add their residuals with three
 // butterfly shuffles, the same order in every group.
-__global__ void __launch_bounds__(kIdpThreads) k_mg_restrict(MgLevel F, MgLevel Cl, const double *__restrict__ r1,
-                                                            const CgState *__restrict__ st)
+__global__ void __launch_bounds__(kIdpThreads) k_mg_restrict(MgLevel F, MgLevel Cl, const CgState *__restrict__ st)
 {
     if (cg_done(st)) return;
     auto e1 = [&](int64_t n, int64_t, int64_t, int64_t) { return kOmega * F.dinv[n] * F.b[n]; };
@@ -595,9 +711,7 @@ __global__ void __launch_bounds__(kIdpThreads) k_mg_restrict(MgLevel F, MgLevel 
             const int64_t i = 2 * I + (ch & 1), j = 2 * J + ((ch >> 1) & 1), k = 2 * K + (ch >> 2);
             if (i < F.D.nx && j < F.D.ny && k < F.D.nz) {
                 const int64_t f = (k * F.D.ny + j) * F.D.nx + i;
-                if (r1)
-                    v = r1[f];  // the residual pass's value: zero off the fluid
-                else if (F.ac[f] > 0.0)
+                if (F.ac[f] > 0.0)
                     v = F.b[f] - F.scale * face_sum_ac(F.D, f, i, j, k, F.ac, e1);
             }
         }
@@ -608,67 +722,15 @@ __global__ void __launch_bounds__(kIdpThreads) k_mg_restrict(MgLevel F, MgLevel 
     }
 }
 
-// Restriction of stored residuals r1 (zero off the fluid): one thread per
-// coarse cell adds its eight children in the order of k_mg_restrict's
-// butterfly, ((c0 + c1) + (c2 + c3)) + ((c4 + c5) + (c6 + c7)) with child
-// bits (x, y, z), so the coarse right-hand side is the same bit for bit.
-__global__ void __launch_bounds__(kIdpThreads) k_mg_restrict_sum(MgLevel F, MgLevel Cl,
-                                                                const double *__restrict__ r1,
-                                                                const CgState *__restrict__ st)
-{
-    if (cg_done(st)) return;
-    for (int64_t C = (int64_t)blockIdx.x * kIdpThreads + threadIdx.x; C < Cl.D.G;
-         C += (int64_t)gridDim.x * kIdpThreads) {
-        double v = 0.0;
-        if (Cl.ac[C] > 0.0) {
-            int64_t I, J, K;
-            coords(Cl.D, C, I, J, K);
-            double c[8];
-#pragma unroll
-            for (int ch = 0; ch < 8; ++ch) {
-                const int64_t i = 2 * I + (ch & 1), j = 2 * J + ((ch >> 1) & 1), k = 2 * K + (ch >> 2);
-                c[ch] = i < F.D.nx && j < F.D.ny && k < F.D.nz ? r1[(k * F.D.ny + j) * F.D.nx + i] : 0.0;
-            }
-            v = ((c[0] + c[1]) + (c[2] + c[3])) + ((c[4] + c[5]) + (c[6] + c[7]));
-        }
-        Cl.b[C] = v;
-    }
-}
-
-// Coarse correction alone: u = e1 + P E on fluid cells (0 elsewhere) into t,
-// for the larger levels, where the post-sweep then reads u once per
-// neighbour.
-__global__ void __launch_bounds__(kIdpThreads) k_mg_prolong(MgLevel F, MgLevel Cl, const CgState *__restrict__ st)
-{
-    if (cg_done(st)) return;
-    for (int64_t c = (int64_t)blockIdx.x * kIdpThreads + threadIdx.x; c < F.D.G;
-         c += (int64_t)gridDim.x * kIdpThreads) {
-        double u = 0.0;
-        if (F.ac[c] > 0.0) {
-            int64_t i, j, k;
-            coords(F.D, c, i, j, k);
-            const int64_t p = ((k >> 1) * Cl.D.ny + (j >> 1)) * Cl.D.nx + (i >> 1);
-            u = kOmega * F.dinv[c] * F.b[c];
-            if (Cl.ac[p] > 0.0) u += Cl.e[p];
-        }
-        F.t[c] = u;
-    }
-}
-
 // Coarse correction and one post-smoothing sweep: u = e1 + P E, e = u + w D^-1
-// (b - A u) (e = b on non-fluid rows); on the finest level also the partials
-// of b.e (= r.z of the CG iteration).
-__global__ void __launch_bounds__(kIdpThreads) k_mg_post(MgLevel F, MgLevel Cl, double *__restrict__ part,
-                                                         const CgState *__restrict__ st)
+// (b - A u) (e = b on non-fluid rows).
+__global__ void __launch_bounds__(kIdpThreads) k_mg_post(MgLevel F, MgLevel Cl, const CgState *__restrict__ st)
 {
-    __shared__ double red[4];
     if (cg_done(st)) return;
     auto u = [&](int64_t n, int64_t i, int64_t j, int64_t k) {
         const int64_t p = ((k >> 1) * Cl.D.ny + (j >> 1)) * Cl.D.nx + (i >> 1);
-        const double e1 = kOmega * F.dinv[n] * F.b[n];
-        return Cl.ac[p] > 0.0 ? e1 + Cl.e[p] : e1;
+        return kOmega * F.dinv[n] * F.b[n] + Cl.e[p];  // E is zero off the coarse fluid
     };
-    double rz = 0.0;
     for (int64_t c = (int64_t)blockIdx.x * kIdpThreads + threadIdx.x; c < F.D.G;
          c += (int64_t)gridDim.x * kIdpThreads) {
         double z = F.b[c];
@@ -679,46 +741,226 @@ __global__ void __launch_bounds__(kIdpThreads) k_mg_post(MgLevel F, MgLevel Cl, 
             z = u(c, i, j, k) + kOmega * F.dinv[c] * (F.b[c] - Au);
         }
         F.e[c] = z;
-        rz += F.b[c] * z;
-    }
-    if (part) {
-        rz = block_sum(rz, red);
-        if (threadIdx.x == 0) part[gridDim.x + blockIdx.x] = rz;
     }
 }
 
-// The coarsest level (at most 256 cells) in one block: kCoarseSweeps damped
-// Jacobi sweeps from zero, in LDS.
-__global__ void __launch_bounds__(kIdpThreads) k_mg_coarsest(MgLevel L, const CgState *__restrict__ st)
+// The operator of the coarsest level's kCoarseSweeps damped Jacobi sweeps from
+// zero as a dense matrix, one column per workgroup (the sweeps of a unit
+// right-hand side): it depends on the coefficients only, and a product with
+// it takes about 1.5 us where the sweeps took 9 to 16 in every cycle.
+__global__ void __launch_bounds__(kMgCoarsest) k_mg_coarse_matrix(MgLevel L, double *__restrict__ M)
 {
-    __shared__ double se[2][kIdpThreads], sb[kIdpThreads], sdi[kIdpThreads], sac[kIdpThreads];
-    if (cg_done(st)) return;
-    const int c = threadIdx.x;
-    const bool live = c < L.D.G;
-    sb[c] = live ? L.b[c] : 0.0;
-    sdi[c] = live ? L.dinv[c] : 0.0;
-    sac[c] = live ? L.ac[c] : 0.0;
+    constexpr int kZero = kMgCoarsest;  // slot that holds zero: neighbours that are no fluid
+    __shared__ double sa[kMgCoarsest], se[2][kMgCoarsest + 1];
+    const int c = threadIdx.x, n = (int)L.D.G;
+    const bool live = c < n;
+    sa[c] = live ? L.ac[c] : 0.0;
     se[0][c] = 0.0;
-    int64_t i = 0, j = 0, k = 0;
-    if (live) coords(L.D, c, i, j, k);
+    if (c < 2) se[c][kZero] = 0.0;
     __syncthreads();
+    const double a = sa[c];
+    double beta[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0}, di = 0.0;
+    int slot[6] = {kZero, kZero, kZero, kZero, kZero, kZero};
+    if (a > 0.0) {
+        int64_t i, j, k;
+        coords(L.D, c, i, j, k);
+        Nbr nb[6];
+        neighbours(L.D, i, j, k, nb);
+        di = L.dinv[c];
+#pragma unroll
+        for (int f = 0; f < 6; ++f) {
+            const double an = nb[f].inside ? sa[c + nb[f].off] : 0.0;
+            beta[f] = an != 0.0 ? (a + fabs(an)) * 0.5 : 0.0;
+            if (an > 0.0) slot[f] = (int)(c + nb[f].off);
+        }
+    }
+    const double b = c == (int)blockIdx.x ? 1.0 : 0.0;
+    double v = 0.0;
     for (int s = 0; s < kCoarseSweeps; ++s) {
         const int cur = s & 1;
-        double v = 0.0;
-        if (live && sac[c] > 0.0) {
-            const double Ae = L.scale * face_sum_ac(L.D, (int64_t)c, i, j, k, sac,
-                                                    [&](int64_t n, int64_t, int64_t, int64_t) { return se[cur][n]; });
-            v = se[cur][c] + kOmega * sdi[c] * (sb[c] - Ae);
+        if (a > 0.0) {
+            double acc = 0.0;
+#pragma unroll
+            for (int f = 0; f < 6; ++f) acc += beta[f] * (v - se[cur][slot[f]]);
+            v = v + kOmega * di * (b - L.scale * acc);
         }
-        se[cur ^ 1][c] = v;
+        if (live) se[cur ^ 1][c] = v;
         __syncthreads();
     }
-    if (live) L.e[c] = se[kCoarseSweeps & 1][c];
+    if (live) M[(int64_t)blockIdx.x * n + c] = v;
+}
+
+// The V-cycle's small levels in one workgroup and one launch: the first of at
+// most kTailTop cells, all below it of at most one cell per thread.  Their
+// coefficients and values are held in LDS, the first level's right-hand side
+// and 1 / diag in registers, so that between the first loads and the last
+// stores there are only LDS passes and barriers: restriction (residual, then
+// the sums of the children in k_mg_restrict's order), the coarsest matrix,
+// correction and sweep (k_mg_post).  Levels of 1,024 and 128 cells take 10.8
+// us, 4,096 to 64 cells 15.6; the same levels in launches of their own took
+// 4.5 to 5.2 us a pass and the coarsest sweeps 17.
+constexpr int kTailThreads = 1024;
+constexpr int kTailTop = 4096, kTailBelow = 2048;  // cells of the first level and of all below
+constexpr int kTailCells = kTailTop / kTailThreads;
+constexpr int kTailLevels = 8;
+
+struct MgTail {
+    int n;
+    MgLevel lev[kTailLevels];
+    const double *M;  // the coarsest level's matrix
+};
+
+__global__ void __launch_bounds__(kTailThreads) k_mg_tail(MgTail T, const CgState *__restrict__ st)
+{
+    __shared__ double sa[kTailTop + kTailBelow], sv[kTailTop + kTailBelow], sb[kTailBelow], sd[kTailBelow];
+    if (cg_done(st)) return;
+    const int tid = threadIdx.x;
+    const MgLevel &F0 = T.lev[0];
+    const int G0 = (int)F0.D.G;
+    double b0[kTailCells], d0[kTailCells];
+#pragma unroll
+    for (int u = 0; u < kTailCells; ++u) {
+        const int c = tid + u * kTailThreads;
+        b0[u] = d0[u] = 0.0;
+        if (c < G0) {
+            b0[u] = F0.b[c];
+            d0[u] = F0.dinv[c];
+            sa[c] = F0.ac[c];
+            sv[c] = kOmega * d0[u] * b0[u];
+        }
+    }
+    int below = 0;  // first slot of level l in sb, sd; level l > 0 has kTailTop + below in sa, sv
+    for (int l = 1; l < T.n; ++l) {
+        const int G = (int)T.lev[l].D.G;
+        if (tid < G) {
+            sa[kTailTop + below + tid] = T.lev[l].ac[tid];
+            sd[below + tid] = T.lev[l].dinv[tid];
+        }
+        below += G;
+    }
+    __syncthreads();
+    // residual of the cell c after the pre-sweep, or the post-sweep's result
+    auto face = [&](const MgLevel &L, int base, int c) {
+        int64_t i, j, k;
+        coords(L.D, c, i, j, k);
+        return L.scale * face_sum_ac(L.D, (int64_t)c, i, j, k, sa + base,
+                                     [&](int64_t n, int64_t, int64_t, int64_t) { return sv[base + n]; });
+    };
+    int at = 0, off = 0;  // this level's slots in sa, sv and in sb, sd
+    for (int l = 0; l + 1 < T.n; ++l) {
+        const MgLevel &F = T.lev[l], &C = T.lev[l + 1];
+        const int G = (int)F.D.G, cat = l == 0 ? kTailTop : at + G, coff = l == 0 ? 0 : off + G;
+        double r[kTailCells];
+#pragma unroll
+        for (int u = 0; u < kTailCells; ++u) {
+            const int c = tid + u * kTailThreads;
+            r[u] = 0.0;
+            if (c < G && sa[at + c] > 0.0) r[u] = (l == 0 ? b0[u] : sb[off + c]) - face(F, at, c);
+            if (l > 0) break;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < kTailCells; ++u) {
+            const int c = tid + u * kTailThreads;
+            if (c < G) sv[at + c] = r[u];
+            if (l > 0) break;
+        }
+        __syncthreads();
+        if (tid < (int)C.D.G) {
+            int64_t I, J, K;
+            coords(C.D, tid, I, J, K);
+            double c[8];
+#pragma unroll
+            for (int ch = 0; ch < 8; ++ch) {
+                const int64_t i = 2 * I + (ch & 1), j = 2 * J + ((ch >> 1) & 1), k = 2 * K + (ch >> 2);
+                c[ch] = i < F.D.nx && j < F.D.ny && k < F.D.nz ? sv[at + (k * F.D.ny + j) * F.D.nx + i] : 0.0;
+            }
+            const double sum = ((c[0] + c[1]) + (c[2] + c[3])) + ((c[4] + c[5]) + (c[6] + c[7]));
+            const double b = sa[cat + tid] > 0.0 ? sum : 0.0;
+            sb[coff + tid] = b;
+            sv[cat + tid] = kOmega * sd[coff + tid] * b;
+        }
+        __syncthreads();
+        at = cat;
+        off = coff;
+    }
+    {  // the coarsest level: its matrix times b, the columns shared by the waves
+        const int n = (int)T.lev[T.n - 1].D.G;
+        if (T.n == 1) {
+            if (tid < n) sb[tid] = b0[0];
+            __syncthreads();
+        }
+        const int pad = n <= 64 ? 64 : (n <= 128 ? 128 : 256), parts = kTailThreads / pad;
+        const int c = tid & (pad - 1), p = tid / pad, per = (n + parts - 1) / parts;
+        double sum = 0.0;
+        if (c < n) {
+            const int j1 = (p + 1) * per < n ? (p + 1) * per : n;
+#pragma unroll 4
+            for (int j = p * per; j < j1; ++j) sum += T.M[(int64_t)j * n + c] * sb[off + j];
+        }
+        // the partial sums take the first level's last coefficient slots for a
+        // moment (nothing reads them here; they are put back)
+        __syncthreads();
+        double *part = sa + kTailTop - kTailThreads;
+        const double keep = part[tid];
+        part[tid] = sum;
+        __syncthreads();
+        double e = 0.0;
+        if (tid < n) {
+            for (int q = 0; q < parts; ++q) e += part[q * pad + tid];
+            sv[at + tid] = e;
+        }
+        __syncthreads();
+        part[tid] = keep;
+        if (T.n == 1 && tid < n) T.lev[0].e[tid] = e;
+        __syncthreads();
+    }
+    for (int l = T.n - 2; l >= 0; --l) {
+        const MgLevel &F = T.lev[l], &C = T.lev[l + 1];
+        const int G = (int)F.D.G, cat = at;
+        at = l == 0 ? 0 : cat - G;
+        off = l == 0 ? 0 : off - G;
+        double e[kTailCells];
+#pragma unroll
+        for (int u = 0; u < kTailCells; ++u) {
+            const int c = tid + u * kTailThreads;
+            if (c < G) {
+                int64_t i, j, k;
+                coords(F.D, c, i, j, k);
+                const int64_t p = ((k >> 1) * C.D.ny + (j >> 1)) * C.D.nx + (i >> 1);
+                sv[at + c] = kOmega * (l == 0 ? d0[u] : sd[off + c]) * (l == 0 ? b0[u] : sb[off + c]) + sv[cat + p];
+            }
+            if (l > 0) break;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < kTailCells; ++u) {
+            const int c = tid + u * kTailThreads;
+            const double b = l == 0 ? b0[u] : (c < G ? sb[off + c] : 0.0);
+            e[u] = b;
+            if (c < G && sa[at + c] > 0.0)
+                e[u] = sv[at + c] + kOmega * (l == 0 ? d0[u] : sd[off + c]) * (b - face(F, at, c));
+            if (l > 0) break;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < kTailCells; ++u) {
+            const int c = tid + u * kTailThreads;
+            if (c < G) {
+                if (l == 0)
+                    F.e[c] = e[u];
+                else
+                    sv[at + c] = e[u];
+            }
+            if (l > 0) break;
+        }
+        __syncthreads();
+    }
 }
 
 unsigned idp_blocks(int64_t G)
 {
-    const int64_t b = (G + kIdpThreads - 1) / kIdpThreads;
+    const int64_t b = (G + 127) / 128;  // small grids: short runs of planes in more blocks
     return (unsigned)(b < 1 ? 1 : (b > kIdpMaxBlocks ? kIdpMaxBlocks : b));
 }
 
@@ -787,56 +1029,118 @@ hipError_t launch_idp_faces(const IdpDims &D, double dx, const double *q, const 
     return hipGetLastError();
 }
 
-// z = M^-1 r by one V-cycle over the levels of W (level 0 works on r and z).
-// Levels with at least this many cells prolong in a pass of their own and
-// then sweep; smaller levels do both in one pass (launch latency dominates).
-constexpr int64_t kMgSplitCells = 1 << 18;
+// Levels with at least this many cells take the passes blocked in 2.5D (the
+// finest always does); on smaller ones a thread per cell is faster, the grid
+// being too small for runs of planes.
+constexpr int64_t kMgTiledCells = 1 << 18;
 
-// Tiles of a blocked stencil pass over D and the planes per item: about one
-// item per block of nb.
-static void stencil_items(const IdpDims &D, unsigned nb, int &ntx, int &nty, int &zlen)
+// Tiles of a blocked stencil pass over D and the planes per item (even, so
+// that a coarse cell's children lie in one run): about one item per block of
+// nb.
+static void stencil_items(const IdpDims &D, unsigned nb, StencilArgs &A)
 {
-    ntx = (int)((D.nx + kTileX - 1) / kTileX);
-    nty = (int)((D.ny + kTileY - 1) / kTileY);
-    const int64_t zl = (D.nz * ntx * nty + nb - 1) / nb;
-    zlen = (int)(zl < 1 ? 1 : (zl > D.nz ? D.nz : zl));
+    A.D = D;
+    A.ntx = (int)((D.nx + kTileX - 1) / kTileX);
+    A.nty = (int)((D.ny + kTileY - 1) / kTileY);
+    int64_t zl = (D.nz * A.ntx * A.nty + nb - 1) / nb;
+    zl = (zl + 1) / 2 * 2;
+    A.zlen = (int)(zl > D.nz + 1 ? D.nz + 1 : zl);
+    if (A.zlen & 1) ++A.zlen;
 }
 
-static void launch_vcycle(const IdpWork &W, hipStream_t st)
+template <int MODE>
+static void launch_stencil(const StencilArgs &A, unsigned nb, hipStream_t st)
 {
-    const int L = W.nlev;
-    for (int l = 0; l + 1 < L; ++l) {
-        const MgLevel &F = W.lev[l];
-        const double *r1 = nullptr;
-        if (F.D.G >= kMgSplitCells) {  // the fine residual by the blocked pass, into t (free until prolongation)
-            const unsigned nb = idp_blocks(F.D.G);
-            int ntx, nty, zlen;
-            stencil_items(F.D, nb, ntx, nty, zlen);
-            k_stencil_tiled<2><<<nb, kIdpThreads, 0, st>>>(F.D, ntx, nty, zlen, F.ac, nullptr, F.b, F.dinv, F.scale,
-                                                           F.t, nullptr, W.state);
-            r1 = F.t;
+    if (A.D.sxy < (int64_t)1 << 29)
+        k_stencil<MODE, uint32_t><<<nb, kIdpThreads, 0, st>>>(A);
+    else
+        k_stencil<MODE, uint64_t><<<nb, kIdpThreads, 0, st>>>(A);
+}
+
+static StencilArgs stencil_args(const IdpDims &D, const IdpWork &W, unsigned nb)
+{
+    StencilArgs A;
+    memset(&A, 0, sizeof(A));
+    stencil_items(D, nb, A);
+    A.scale = 1.0;
+    A.ac = W.lev[0].ac;
+    A.dinv = W.dinv;
+    A.part = W.part;
+    A.st = W.state;
+    return A;
+}
+
+// The finest level's r and z and the directions live in two buffers each that
+// change places every iteration (see k_stencil): r of iteration k in
+// rbuf(k), z in rbuf(k + 1), d in dbuf(k).
+static double *rbuf(const IdpWork &W, int k) { return (k & 1) ? W.lev[0].e : W.r; }
+static double *dbuf(const IdpWork &W, int k) { return (k & 1) ? W.lev[0].t : W.d; }
+
+static void residual_pass(const MgLevel &F, const MgLevel &C, const double *b, const IdpWork &W, hipStream_t st)
+{
+    const unsigned nb = idp_blocks(F.D.G);
+    StencilArgs A = stencil_args(F.D, W, nb);
+    A.scale = F.scale;
+    A.ac = F.ac;
+    A.dinv = F.dinv;
+    A.p = b;
+    A.acc = C.ac;
+    A.cnx = C.D.nx;
+    A.cny = C.D.ny;
+    A.bc = C.b;
+    launch_stencil<kResidual>(A, nb, st);
+}
+
+static void post_pass(const MgLevel &F, const MgLevel &C, const double *b, double *e, double *part, const IdpWork &W,
+                      hipStream_t st)
+{
+    const unsigned nb = idp_blocks(F.D.G);
+    StencilArgs A = stencil_args(F.D, W, nb);
+    A.scale = F.scale;
+    A.ac = F.ac;
+    A.dinv = F.dinv;
+    A.p = b;
+    A.ec = C.e;
+    A.cnx = C.D.nx;
+    A.cny = C.D.ny;
+    A.o1 = e;
+    A.part = part;
+    launch_stencil<kPost>(A, nb, st);
+}
+
+// The V-cycle below the finest level: from level 1's right-hand side to its
+// correction.
+static void launch_coarse(const IdpWork &W, hipStream_t st)
+{
+    // the first level that, with all below it, fits one workgroup
+    auto fits = [&](int l) {
+        int64_t below = 0;
+        for (int m = l + 1; m < W.nlev; ++m) {
+            if (W.lev[m].D.G > kTailThreads) return false;
+            below += W.lev[m].D.G;
         }
-        if (r1)
-            k_mg_restrict_sum<<<idp_blocks_full(W.lev[l + 1].D.G), kIdpThreads, 0, st>>>(F, W.lev[l + 1], r1,
-                                                                                      W.state);
+        return W.lev[l].D.G <= kTailTop && below <= kTailBelow && W.nlev - l <= kTailLevels;
+    };
+    int tail = 1;
+    while (!fits(tail)) ++tail;
+    for (int l = 1; l < tail; ++l) {
+        const MgLevel &F = W.lev[l], &C = W.lev[l + 1];
+        if (F.D.G >= kMgTiledCells)
+            residual_pass(F, C, F.b, W, st);
         else
-            k_mg_restrict<<<idp_blocks_full(8 * W.lev[l + 1].D.G), kIdpThreads, 0, st>>>(F, W.lev[l + 1], nullptr,
-                                                                                         W.state);
+            k_mg_restrict<<<idp_blocks_full(8 * C.D.G), kIdpThreads, 0, st>>>(F, C, W.state);
     }
-    k_mg_coarsest<<<1, kIdpThreads, 0, st>>>(W.lev[L - 1], W.state);
-    for (int l = L - 2; l >= 0; --l) {
-        const unsigned nb = idp_blocks(W.lev[l].D.G);
-        double *part = l == 0 ? W.part : nullptr;
-        if (W.lev[l].D.G >= kMgSplitCells) {
-            k_mg_prolong<<<idp_blocks_full(W.lev[l].D.G), kIdpThreads, 0, st>>>(W.lev[l], W.lev[l + 1], W.state);
-            const MgLevel &F = W.lev[l];
-            int ntx, nty, zlen;
-            stencil_items(F.D, nb, ntx, nty, zlen);
-            k_stencil_tiled<1><<<nb, kIdpThreads, 0, st>>>(F.D, ntx, nty, zlen, F.ac, F.t, F.b, F.dinv, F.scale,
-                                                               F.e, part, W.state);
-        } else {
-            k_mg_post<<<nb, kIdpThreads, 0, st>>>(W.lev[l], W.lev[l + 1], part, W.state);
-        }
+    MgTail T;
+    T.n = W.nlev - tail;
+    for (int l = 0; l < T.n; ++l) T.lev[l] = W.lev[tail + l];
+    T.M = W.coarse;
+    k_mg_tail<<<1, kTailThreads, 0, st>>>(T, W.state);
+    for (int l = tail - 1; l >= 1; --l) {
+        const MgLevel &F = W.lev[l], &C = W.lev[l + 1];
+        if (F.D.G >= kMgTiledCells)
+            post_pass(F, C, F.b, F.e, nullptr, W, st);
+        else
+            k_mg_post<<<idp_blocks(F.D.G), kIdpThreads, 0, st>>>(F, C, W.state);
     }
 }
 
@@ -844,15 +1148,17 @@ hipError_t launch_cg_start(const IdpDims &D, const double *at, const uint8_t *la
                            const IdpWork &W, double tol, int64_t *err, hipStream_t st)
 {
     const unsigned nb = idp_blocks(D.G);
-    k_cg_init<<<nb, kIdpThreads, 0, st>>>(D, at, lab, s, q, W.r, W.d, W.dinv, W.lev[0].ac, W.part, W.state, err);
+    k_cg_init<<<nb, kIdpThreads, 0, st>>>(D, at, lab, s, q, W.r, W.dinv, W.lev[0].ac, W.part, W.state, err);
     if (W.nlev > 1) {
         for (int l = 0; l + 1 < W.nlev; ++l) {
             k_mg_coarsen<<<idp_blocks(W.lev[l + 1].D.G), kIdpThreads, 0, st>>>(W.lev[l], W.lev[l + 1]);
             k_mg_diag<<<idp_blocks(W.lev[l + 1].D.G), kIdpThreads, 0, st>>>(W.lev[l + 1]);
         }
-        launch_vcycle(W, st);
-        hipError_t e = hipMemcpyAsync(W.d, W.lev[0].e, sizeof(double) * D.G, hipMemcpyDeviceToDevice, st);
-        if (e != hipSuccess) return e;
+        const MgLevel &L = W.lev[W.nlev - 1];
+        k_mg_coarse_matrix<<<(unsigned)L.D.G, (unsigned)kMgCoarsest, 0, st>>>(L, W.coarse);
+        residual_pass(W.lev[0], W.lev[1], rbuf(W, 0), W, st);
+        launch_coarse(W, st);
+        post_pass(W.lev[0], W.lev[1], rbuf(W, 0), rbuf(W, 1), W.part, W, st);
     }
     k_cg_start<<<1, kIdpThreads, 0, st>>>((int)nb, W.part, tol, W.state);
     return hipGetLastError();
@@ -863,20 +1169,33 @@ hipError_t launch_cg_iterations(const IdpDims &D, const double *at, const uint8_
 {
     const unsigned nb = idp_blocks(D.G);
     const bool mg = W.nlev > 1;
-    int ntx, nty, zlen;
-    stencil_items(D, nb, ntx, nty, zlen);
     for (int k = k0; k < k0 + count; ++k) {
-        k_stencil_tiled<0><<<nb, kIdpThreads, 0, st>>>(D, ntx, nty, zlen, W.lev[0].ac, W.d, nullptr, nullptr,
-                                                            1.0, W.w, W.part, W.state);
-        if (mg) {
-            k_cg_update<false><<<nb, kIdpThreads, 0, st>>>(D, k, W.d, W.w, W.dinv, q, W.r, W.part, W.state);
-            launch_vcycle(W, st);
-            k_cg_direction<false><<<nb, kIdpThreads, 0, st>>>(D, k, W.r, W.dinv, W.lev[0].e, W.d, W.part, W.state);
-        } else {
-            k_cg_update<true><<<nb, kIdpThreads, 0, st>>>(D, k, W.d, W.w, W.dinv, q, W.r, W.part, W.state);
-            k_cg_direction<true><<<nb, kIdpThreads, 0, st>>>(D, k, W.r, W.dinv, nullptr, W.d, W.part, W.state);
+        StencilArgs A = stencil_args(D, W, nb);
+        A.k = k;
+        A.d = dbuf(W, k + 1);
+        A.o1 = dbuf(W, k);
+        A.o2 = W.w;
+        A.p = mg ? rbuf(W, k + 1) : W.r;
+        if (!mg) {
+            launch_stencil<kApplyJac>(A, nb, st);
+            k_cg_update<<<nb, kIdpThreads, 0, st>>>(D, k, dbuf(W, k), W.w, W.dinv, q, W.r, W.part, W.state);
+            continue;
         }
+        launch_stencil<kApplyMg>(A, nb, st);
+        A.p = rbuf(W, k);
+        A.d = dbuf(W, k);
+        A.w = W.w;
+        A.acc = W.lev[1].ac;
+        A.cnx = W.lev[1].D.nx;
+        A.cny = W.lev[1].D.ny;
+        A.bc = W.lev[1].b;
+        A.o1 = q;
+        A.o2 = rbuf(W, k + 1);
+        launch_stencil<kUpdate>(A, nb, st);
+        launch_coarse(W, st);
+        post_pass(W.lev[0], W.lev[1], rbuf(W, k + 1), rbuf(W, k + 2), W.part, W, st);
     }
+    k_cg_check<<<1, kIdpThreads, 0, st>>>((int)nb, k0 + count, W.part, W.state);
     return hipGetLastError();
 }
 

@@ -8,7 +8,7 @@
 namespace gic {
 
 constexpr uint8_t kIdpFluid = 0, kIdpAir = 1, kIdpSolid = 2;  // cell labels
-constexpr int kIdpMaxBlocks = 1024;  // partial sums per reduced quantity
+constexpr int kIdpMaxBlocks = 512;  // partial sums per reduced quantity
 
 struct IdpDims {
     int64_t nx, ny, nz, sxy, G;
@@ -50,6 +50,7 @@ struct IdpWork {
     CgState *state;
     int nlev;
     MgLevel lev[kMgMaxLevels];
+    double *coarse;  // the coarsest level's sweeps as a matrix (its cells squared)
 };
 
 IdpDims idp_dims(const DevParams &P);
