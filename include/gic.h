@@ -557,6 +557,28 @@ gic_status gic_sum_noalloc(int64_t n, const double *a, const double *b, double *
 gic_status gic_scale(gic_ctx *ctx, int64_t n, const double *a, const double *s, double factor, double *out,
                      void *stream);
 
+/* One step of the differentiable rollout, state in input order (xv: x then v,
+ * 6n doubles): sort, alpha deposit (unquantised transfers), G2P, drag,
+ * contact, move; the advanced state goes to xv_out (another array).  The same
+ * kernels' arithmetic as the stages
+ *     gic_sort_cells -> gic_reorder -> gic_p2g_real -> gic_g2p -> gic_drag ->
+ *     gic_contact_forces -> gic_integrate -> gic_permute
+ * in eight launches, same bits.  Plain form (GIC_FP64) and linear drag only.
+ * key, order (n int32), cell_begin, cell_end, xv_sorted (6n), r_sorted (n):
+ * scratch; the sort's outputs and the sorted state are left in them. */
+gic_status gic_rollout_step(gic_ctx *ctx, int64_t n, const double *xv, const double *r, const double *u,
+                            double *xv_out, uint32_t *key, int32_t *order, int32_t *cell_begin, int32_t *cell_end,
+                            double *xv_sorted, double *r_sorted, void *stream);
+
+/* Its reverse: g_xv (6n, input order) holds the adjoint of the step's result
+ * and receives that of xv; dL/dmu and dL/dC_d are added to g_mu[0] and
+ * g_cdrag[0].  The step's intermediate values are formed again from xv.
+ * Scratch besides the step's: g_sorted (6n), g_f (3n), g_af (n). */
+gic_status gic_rollout_step_vjp(gic_ctx *ctx, int64_t n, const double *xv, const double *r, const double *u,
+                                double *g_xv, double *g_mu, double *g_cdrag, uint32_t *key, int32_t *order,
+                                int32_t *cell_begin, int32_t *cell_end, double *xv_sorted, double *r_sorted,
+                                double *g_sorted, double *g_f, double *g_af, void *stream);
+
 /* Permute comps (1..6) planes of n doubles (six: positions and velocities
  * held as one array, x then v): scatter = 0: out[c n + q] =
  * in[c n + order[q]];  scatter = 1: out[c n + order[q]] = in[c n + q]. */

@@ -274,6 +274,181 @@ __device__ inline int exact_pair(const DevParams &P, const double xi[3], const d
     return 0;
 }
 
+// What the direct contact kernel does with each granule's partners.
+//   kForce    the contact force (dry)
+//   kBridge   the contact force and the liquid bridges
+//   kPull     the pullback of the contact force (double), added to gx and gv
+//   kMove     the differentiable step: contact force, G2P and drag at the
+//             granule, the move of Sec. 4, (x, v) written in input order
+//   kReverse  its reverse: the pullbacks of the contact force, the drag and
+//             the granule part of the G2P, added to the adjoint gs; the
+//             cotangent of the fluid fraction; the brick's sums of dL/dmu and
+//             dL/dC_d
+// The pullbacks search the same partners as the force, so they share its
+// brick shell in LDS: a pullback that gathered its partners from global memory
+// took 61 us on a bed of 65,536 granules, with the drag and G2P stages and
+// their pullbacks 103; kReverse takes 40 for all of them.  kMove takes 35 where
+// the force, the G2P, the drag, the move and the scatter took 22 + 15 + 5 + 5
+// + 6.
+enum ContactKind { kForce, kBridge, kPull, kMove, kReverse };
+constexpr bool pulls(int kind) { return kind == kPull || kind == kReverse; }
+constexpr int sums_of(int kind) { return pulls(kind) ? 7 : 3; }  // g_x, g_v, g_mu | F
+
+// A partner's cotangent of the force (pullbacks).
+struct Cotangent {
+    double g[3];
+};
+
+__device__ inline Cotangent fetch_cotangent(int64_t n, const double *__restrict__ gF, int64_t j)
+{
+    return {{gF[j], gF[n + j], gF[2 * n + j]}};
+}
+
+// Pullback of the pair force with partner p (cotangent cj) at granule i
+// (cotangent gi): the pair term with cotangent g_i - g_j, added to acc.
+__device__ inline int pull_pair(const DevParams &P, const double xi[3], const double vi[3], double ri, double mi,
+                                int64_t q, int32_t j, const Partner &p, const double gi[3], const Cotangent &cj,
+                                double acc[7])
+{
+    if (j == q) return 0;
+    const double d0 = xi[0] - p.x[0], d1 = xi[1] - p.x[1], d2c = xi[2] - p.x[2];
+    double d2;
+    if (!touching(d0, d1, d2c, ri + p.r, d2) || d2 == 0.0) return 0;
+    const double d = sqrt(d2);
+    const double nh[3] = {d0 / d, d1 / d, d2c / d};
+    const double delta = (ri + p.r) - d;
+    const double w[3] = {vi[0] - p.v[0], vi[1] - p.v[1], vi[2] - p.v[2]};
+    const double mj = mass_of(P, p.r);
+    const double meff = (mi * mj) / (mi + mj);
+    const double gbar[3] = {gi[0] - cj.g[0], gi[1] - cj.g[1], gi[2] - cj.g[2]};
+    double nbar[3] = {0, 0, 0}, wbar[3] = {0, 0, 0}, dbar = 0.0;
+    pair_force_vjp(P, nh, delta, w, meff, gbar, gi, nbar, dbar, wbar, acc[6]);
+    const double nn = (nbar[0] * nh[0] + nbar[1] * nh[1]) + nbar[2] * nh[2];
+    for (int a = 0; a < 3; ++a) {
+        acc[a] += (nbar[a] - nn * nh[a]) / d - dbar * nh[a];
+        acc[3 + a] += wbar[a];
+    }
+    return 1;
+}
+
+// Pullback of the wall forces at granule i.
+__device__ inline void pull_walls(const DevParams &P, const double xi[3], const double vi[3], double ri, double mi,
+                                  const double gi[3], double acc[7])
+{
+    if (!P.walls) return;
+    for (int a = 0; a < 3; ++a)
+        for (int side = 0; side < 2; ++side) {
+            if (!(P.walls & (1u << (2 * a + side)))) continue;
+            const double dist = side == 0 ? xi[a] : P.L[a] - xi[a];
+            const double delta = ri - dist;
+            if (!(delta > 0.0)) continue;
+            double nh[3] = {0.0, 0.0, 0.0};
+            nh[a] = side == 0 ? 1.0 : -1.0;
+            double nbar[3] = {0, 0, 0}, wbar[3] = {0, 0, 0}, dbar = 0.0;
+            pair_force_vjp(P, nh, delta, vi, mi, gi, gi, nbar, dbar, wbar, acc[6]);
+            acc[a] += side == 0 ? -dbar : dbar;
+            for (int b = 0; b < 3; ++b) acc[3 + b] += wbar[b];
+        }
+}
+
+// Ends granule q: its walls, then what the kind does with the sums.  tot: the
+// thread's dL/dmu, dL/dC_d and largest |g_alpha_f| (kReverse).
+template <typename T, int KIND>
+__device__ inline void finish_granule(const DevParams &P, int64_t n, int64_t q, const double xi[3], const double vi[3],
+                                      double ri, double mi, const double gi[3], T acc[], int32_t nc,
+                                      T *__restrict__ F, int32_t *__restrict__ ncont, const AdjArgs &A, double tot[3])
+{
+    if constexpr (pulls(KIND))
+        pull_walls(P, xi, vi, ri, mi, gi, acc);
+    else
+        add_walls<T>(P, xi, vi, ri, mi, acc, nc);
+    if constexpr (KIND == kForce || KIND == kBridge) {
+        F[q] = acc[0];
+        F[n + q] = acc[1];
+        F[2 * n + q] = acc[2];
+        if (ncont) ncont[q] = nc;
+    }
+    if constexpr (KIND == kPull) {
+        for (int a = 0; a < 3; ++a) {
+            A.gx[a * n + q] += acc[a];
+            A.gv[a * n + q] += acc[3 + a];
+        }
+        A.gmu[q] = acc[6];
+    }
+    if constexpr (KIND == kMove) {
+        const double inv = *A.inv;
+        const int64_t G = P.G;
+        double ua[3], a, fd[3];
+        g2p_sample<double>(P, xi, [&](int32_t i, int32_t j, int32_t k, double uu[3], double &al) {
+            const int64_t idx = node_index(P, i, j, k);
+            uu[0] = A.u[idx];
+            uu[1] = A.u[G + idx];
+            uu[2] = A.u[2 * G + idx];
+            al = node_alpha_real(P, (double)A.fx[idx] * inv);
+        }, ua, a);
+        drag_one<double>(P, ri, vi, ua, a, fd);
+        double x[3] = {xi[0], xi[1], xi[2]}, v[3] = {vi[0], vi[1], vi[2]};
+        integrate_one<double>(P, ri, acc, fd, x, v);
+        const int64_t s = A.order[q];
+        if ((uint64_t)s < (uint64_t)n)
+            for (int c = 0; c < 3; ++c) {
+                A.out[c * n + s] = x[c];
+                A.out[(3 + c) * n + s] = v[c];
+            }
+    }
+    if constexpr (KIND == kReverse) {
+        // u and alpha at the granule and their gradients in one pass over its nodes
+        const double inv = *A.inv;
+        const int64_t G = P.G;
+        Stencil st;
+        stencil_of(P, xi, st);
+        double dw[3][3];
+        stencil_dw(P, xi, dw);
+        double val[4] = {0, 0, 0, 0}, gr[3][4] = {{0, 0, 0, 0}, {0, 0, 0, 0}, {0, 0, 0, 0}};
+        double wz = st.w[2][0], wz1 = st.w[2][1], wz2 = st.w[2][2], ez = dw[2][0], ez1 = dw[2][1], ez2 = dw[2][2];
+        int32_t nz = st.node[2][0], nz1 = st.node[2][1], nz2 = st.node[2][2];
+#pragma unroll 1
+        for (int cz = 0; cz < 3; ++cz) {  // planes rotate through registers (see g2p_sample_st)
+#pragma unroll
+            for (int cy = 0; cy < 3; ++cy)
+#pragma unroll
+                for (int cx = 0; cx < 3; ++cx) {
+                    const int64_t k = node_index(P, st.node[0][cx], st.node[1][cy], nz);
+                    const double al = (double)A.fx[k] * inv;
+                    const double f[4] = {A.u[k], A.u[G + k], A.u[2 * G + k], al < P.alpha_max ? al : P.alpha_max};
+                    const double w = (st.w[0][cx] * st.w[1][cy]) * wz;
+                    const double g[3] = {(dw[0][cx] * st.w[1][cy]) * wz, (st.w[0][cx] * dw[1][cy]) * wz,
+                                         (st.w[0][cx] * st.w[1][cy]) * ez};
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) {
+                        val[c] += w * f[c];
+                        for (int a = 0; a < 3; ++a) gr[a][c] += g[a] * f[c];
+                    }
+                }
+            wz = wz1; wz1 = wz2;
+            ez = ez1; ez1 = ez2;
+            nz = nz1; nz1 = nz2;
+        }
+        const double af = 1.0 - val[3];
+        const double c6 = P.cdrag_unit * ri;  // 6 pi eta r
+        const double beta = P.c_drag * c6;
+        double s = 0.0;
+        for (int a = 0; a < 3; ++a) s += (val[a] - vi[a]) * gi[a];
+        const double gaf = beta * s;
+        for (int a = 0; a < 3; ++a) {
+            double gx = 0.0;
+            for (int c = 0; c < 3; ++c) gx += gr[a][c] * (beta * af * gi[c]);
+            gx -= gr[a][3] * gaf;
+            A.gs[a * n + q] += acc[a] + gx;
+            A.gs[(3 + a) * n + q] += acc[3 + a] - beta * af * gi[a];
+        }
+        A.gaf[q] = gaf;
+        tot[0] += acc[6];
+        tot[1] += c6 * af * s;
+        tot[2] = fmax(tot[2], fabs(gaf));
+    }
+}
+
 // Contact force on granule q reading its candidates from global memory, in
 // two passes: the candidate pass runs only the double contact test and lists
 // touching partners in `plist` (kMaxPartners x NT ints in LDS, column tid);
@@ -282,25 +457,36 @@ __device__ inline int exact_pair(const DevParams &P, const double xi[3], const d
 // positions, so evaluating forces inside the candidate loop would run the
 // expensive branch for almost every candidate.  A granule with more
 // partners than the list holds walks its candidates in canonical order.
-template <typename T, bool CAP, int NT>
+template <typename T, int KIND, int NT>
 __device__ inline void contact_global(const DevParams &P, int64_t n, const double *__restrict__ x,
                                       const double *__restrict__ v, const double *__restrict__ r,
                                       const int32_t *__restrict__ cb, const int32_t *__restrict__ ce, int64_t q,
                                       int32_t *plist, int tid, const T *__restrict__ sr,
                                       const double *__restrict__ held, T *__restrict__ F,
-                                      int32_t *__restrict__ ncont, int64_t *err)
+                                      int32_t *__restrict__ ncont, int64_t *err, const AdjArgs &A, double tot[3])
 {
+    constexpr bool CAP = KIND == kBridge;
     const double xi[3] = {x[q], x[n + q], x[2 * n + q]};
     const double vi[3] = {v[q], v[n + q], v[2 * n + q]};
     const double ri = r[q];
-    if (ri > P.r_max) raise_error(err, kErrRange, q);
+    if (!pulls(KIND) && ri > P.r_max) raise_error(err, kErrRange, q);
     const double mi = (CAP && held) ? wet_mass(P, ri, held[q]) : mass_of(P, ri);
     const double reach = CAP ? P.dr_max : 0.0;  // liquid bridges reach beyond contact
     const T sri = CAP ? sr[q] : (T)0;
     const double Rs = (ri + P.r_max + reach) * P.search_scale;
     int32_t lo[3], hi[3];
     for (int a = 0; a < 3; ++a) search_range(P, xi[a], Rs, P.nc[a], lo[a], hi[a]);
-    T acc[3] = {(T)0, (T)0, (T)0};
+    T acc[sums_of(KIND)] = {};
+    double gi[3] = {0.0, 0.0, 0.0};
+    if constexpr (pulls(KIND))
+        for (int a = 0; a < 3; ++a) gi[a] = A.gF[a * n + q];
+    auto take = [&](int32_t j) {
+        const Partner p = fetch_partner(n, x, v, r, j);
+        if constexpr (pulls(KIND))
+            return pull_pair(P, xi, vi, ri, mi, q, j, p, gi, fetch_cotangent(n, A.gF, j), acc);
+        else
+            return exact_pair<T, CAP>(P, xi, vi, ri, mi, q, j, p, sri, sr, held, acc);
+    };
     int32_t cnt = 0, nc = 0;
     for_each_run(P, n, lo, hi, cb, ce, [&](int32_t jb, int32_t je) {
         for (int32_t j0 = jb; j0 < je; j0 += kUnroll) {
@@ -327,20 +513,11 @@ __device__ inline void contact_global(const DevParams &P, int64_t n, const doubl
     });
     if (cnt <= kMaxPartners) {
         canon_sort(plist + tid, NT, cnt, q, [](int32_t j) { return (int64_t)j; });
-        for (int k = 0; k < cnt; ++k) {
-            const int32_t j = plist[k * NT + tid];
-            nc += exact_pair<T, CAP>(P, xi, vi, ri, mi, q, j, fetch_partner(n, x, v, r, j), sri, sr, held, acc);
-        }
+        for (int k = 0; k < cnt; ++k) nc += take(plist[k * NT + tid]);
     } else {  // rare: more partners than the list holds
-        for_each_canonical(P, n, q, lo, hi, cb, ce, [&](int32_t j) {
-            nc += exact_pair<T, CAP>(P, xi, vi, ri, mi, q, j, fetch_partner(n, x, v, r, j), sri, sr, held, acc);
-        });
+        for_each_canonical(P, n, q, lo, hi, cb, ce, [&](int32_t j) { nc += take(j); });
     }
-    add_walls<T>(P, xi, vi, ri, mi, acc, nc);
-    F[q] = acc[0];
-    F[n + q] = acc[1];
-    F[2 * n + q] = acc[2];
-    if (ncont) ncont[q] = nc;
+    finish_granule<T, KIND>(P, n, q, xi, vi, ri, mi, gi, acc, nc, F, ncont, A, tot);
 }
 
 // ---------------------------------------------------------------------------
@@ -458,8 +635,8 @@ __device__ inline bool near_slot(float4 p, float mx, float my, float mz, float t
 // NT: threads per workgroup; 64 serves beds whose bricks hold at most one
 // granule per lane (no empty slots after the cells there: the lanes of one
 // wave read a slot each).
-template <typename T, bool CAP, int NT>
-__global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(CAP ? 4 : 1)))
+template <typename T, int KIND, int NT>
+__global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(KIND == kBridge ? 4 : 1)))
 k_contact_lds(DevParams P, int64_t n, const int32_t *__restrict__ bl,
                                                      const int32_t *__restrict__ bcnt, int cap,
                                                      const double *__restrict__ x, const double *__restrict__ v,
@@ -467,8 +644,10 @@ k_contact_lds(DevParams P, int64_t n, const int32_t *__restrict__ bl,
                                                      const int32_t *__restrict__ ce, const T *__restrict__ sr,
                                                      const double *__restrict__ held, T *__restrict__ F,
                                                      int32_t *__restrict__ ncont, int64_t *err,
-                                                     int32_t *__restrict__ hmax, int32_t *__restrict__ hclr, int only)
+                                                     int32_t *__restrict__ hmax, int32_t *__restrict__ hclr, int only,
+                                                     AdjArgs A)
 {
+    constexpr bool CAP = KIND == kBridge;
     extern __shared__ float4 smem4[];
     float4 *spos = smem4;                                        // [cap + kCand] (p, Q), see above
     constexpr int kPad = shell_pad(NT);
@@ -481,14 +660,44 @@ k_contact_lds(DevParams P, int64_t n, const int32_t *__restrict__ bl,
     const int tid = threadIdx.x;
     if (hclr && blockIdx.x == 0 && tid == 0) *hclr = 0;  // the next recording call's record
     if (not_mine(only, kWaveFill, n, bcnt)) return;
-    const int64_t b = brick_of_block(bl, bcnt);
+    int64_t slot;
+    const int64_t b = brick_slot_of_block(bl, bcnt, slot);
     if (b < 0) return;
+    double tot[3] = {0.0, 0.0, 0.0};  // kReverse: dL/dmu, dL/dC_d, largest |g_alpha_f| of the thread
+    auto leave = [&]() {              // kReverse: those of the brick
+        if constexpr (KIND == kReverse) {
+            __shared__ double s_tot[3][NT / 64];
+            for (int off = 32; off > 0; off >>= 1) {
+                tot[0] += __shfl_xor(tot[0], off);
+                tot[1] += __shfl_xor(tot[1], off);
+                tot[2] = fmax(tot[2], __shfl_xor(tot[2], off));
+            }
+            if ((tid & 63) == 0)
+                for (int c = 0; c < 3; ++c) s_tot[c][tid >> 6] = tot[c];
+            __syncthreads();
+            if (tid == 0) {
+                double m = s_tot[0][0], d = s_tot[1][0], g = s_tot[2][0];
+                for (int w = 1; w < NT / 64; ++w) {
+                    m += s_tot[0][w];
+                    d += s_tot[1][w];
+                    g = fmax(g, s_tot[2][w]);
+                }
+                A.psum[2 * slot] = m;
+                A.psum[2 * slot + 1] = d;
+                // the bits of non-negative doubles order as the doubles do
+                atomicMax(A.gmax, (unsigned long long)__double_as_longlong(g));
+            }
+        }
+    };
     const int32_t bc[3] = {(int32_t)(b % P.nb[0]), (int32_t)((b / P.nb[0]) % P.nb[1]),
                            (int32_t)(b / ((int64_t)P.nb[0] * P.nb[1]))};
     const int32_t c0[3] = {bc[0] * kBrick - 1, bc[1] * kBrick - 1, bc[2] * kBrick - 1};  // shell origin cell
     int32_t gb = cb[b * kBrickCells], ge = ce[b * kBrickCells + kBrickCells - 1];
     clip_range(n, gb, ge);
-    if (ge <= gb) return;
+    if (ge <= gb) {
+        leave();
+        return;
+    }
     const double o[3] = {(c0[0] + 3) * P.cell, (c0[1] + 3) * P.cell, (c0[2] + 3) * P.cell};  // brick centre
     // ---- shell cells: counts, then slots (count + kPad each) by a scan;
     // thread t takes cells t, t + NT, ...
@@ -541,7 +750,8 @@ k_contact_lds(DevParams P, int64_t n, const int32_t *__restrict__ bl,
         __syncthreads();  // every thread has read s_wave (the slots alias nothing else in use)
         int32_t *glist = reinterpret_cast<int32_t *>(smem4);  // the slot arrays are unused on this path
         for (int64_t q = gb + tid; q < ge; q += NT)
-            contact_global<T, CAP, NT>(P, n, x, v, r, cb, ce, q, glist, tid, sr, held, F, ncont, err);
+            contact_global<T, KIND, NT>(P, n, x, v, r, cb, ce, q, glist, tid, sr, held, F, ncont, err, A, tot);
+        leave();
         return;
     }
     // ---- slot -> shell cell map (pads take their cell's number too)
@@ -608,7 +818,8 @@ k_contact_lds(DevParams P, int64_t n, const int32_t *__restrict__ bl,
     for (int64_t qb = gb; qb < ge; qb += NT) {  // same trip count in every lane
         const int64_t q = qb + tid;
         const bool live = q < ge;
-        T acc[3] = {(T)0, (T)0, (T)0};
+        T acc[sums_of(KIND)] = {};
+        double gi[3] = {0.0, 0.0, 0.0};
         int32_t nc = 0;
         bool bad = false;
         double xi[3] = {0.0, 0.0, 0.0}, vi[3] = {0.0, 0.0, 0.0}, ri = 0.0, mi = 0.0;
@@ -617,7 +828,7 @@ k_contact_lds(DevParams P, int64_t n, const int32_t *__restrict__ bl,
             xi[1] = x[n + q];
             xi[2] = x[2 * n + q];
             ri = r[q];
-            if (ri > P.r_max) raise_error(err, kErrRange, q);
+            if (!pulls(KIND) && ri > P.r_max) raise_error(err, kErrRange, q);
             const float ax = (float)(xi[0] - o[0]), ay = (float)(xi[1] - o[1]), az = (float)(xi[2] - o[2]);
             const float rf = (float)ri + hreach;
             const float thr = M - (((ax * ax + ay * ay) + az * az) - 2.0f * (rf * rf));
@@ -632,7 +843,23 @@ k_contact_lds(DevParams P, int64_t n, const int32_t *__restrict__ bl,
             }
             // the cell ranges do not match the positions (not the ranges of this state's sort)
             bad = ca[0] < 1 || ca[0] > 4 || ca[1] < 1 || ca[1] > 4 || ca[2] < 1 || ca[2] > 4;
-            if (bad) {
+            if constexpr (pulls(KIND))
+                for (int a = 0; a < 3; ++a) gi[a] = A.gF[a * n + q];
+            if (bad && pulls(KIND)) {
+                // every granule of the search box around the position
+                for (int a = 0; a < 3; ++a) {
+                    lo[a] += c0[a];
+                    hi[a] += c0[a];
+                    vi[a] = v[a * n + q];
+                }
+                mi = mass_of(P, ri);
+                if constexpr (pulls(KIND))
+                    for_each_canonical(P, n, q, lo, hi, cb, ce, [&](int32_t j) {
+                        pull_pair(P, xi, vi, ri, mi, q, j, fetch_partner(n, x, v, r, j), gi,
+                                  fetch_cotangent(n, A.gF, j), acc);
+                    });
+                bad = false;
+            } else if (bad) {
                 raise_error(err, kErrRange, q);
             } else {
                 // slot of q itself, skipped by the candidate pass (the exact test skips q too)
@@ -686,8 +913,14 @@ k_contact_lds(DevParams P, int64_t n, const int32_t *__restrict__ bl,
                         const int32_t j1 = two ? (int32_t)global_of(plist[(i + 1) * NT + tid]) : j0;
                         const Partner p0 = fetch_partner(n, x, v, r, j0);
                         const Partner p1 = fetch_partner(n, x, v, r, j1);
-                        nc += exact_pair<T, CAP>(P, xi, vi, ri, mi, q, j0, p0, sri, sr, held, acc);
-                        if (two) nc += exact_pair<T, CAP>(P, xi, vi, ri, mi, q, j1, p1, sri, sr, held, acc);
+                        if constexpr (pulls(KIND)) {
+                            const Cotangent c0 = fetch_cotangent(n, A.gF, j0), c1 = fetch_cotangent(n, A.gF, j1);
+                            pull_pair(P, xi, vi, ri, mi, q, j0, p0, gi, c0, acc);
+                            if (two) pull_pair(P, xi, vi, ri, mi, q, j1, p1, gi, c1, acc);
+                        } else {
+                            nc += exact_pair<T, CAP>(P, xi, vi, ri, mi, q, j0, p0, sri, sr, held, acc);
+                            if (two) nc += exact_pair<T, CAP>(P, xi, vi, ri, mi, q, j1, p1, sri, sr, held, acc);
+                        }
                     }
                 } else {
                     // more candidates than listed (rare): every granule of the
@@ -698,20 +931,25 @@ k_contact_lds(DevParams P, int64_t n, const int32_t *__restrict__ bl,
                         ghi[a] = hi[a] + c0[a];
                     }
                     for_each_canonical(P, n, q, glo, ghi, cb, ce, [&](int32_t j) {
-                        nc += exact_pair<T, CAP>(P, xi, vi, ri, mi, q, j, fetch_partner(n, x, v, r, j), sri, sr,
-                                                 held, acc);
+                        const Partner p = fetch_partner(n, x, v, r, j);
+                        if constexpr (pulls(KIND))
+                            pull_pair(P, xi, vi, ri, mi, q, j, p, gi, fetch_cotangent(n, A.gF, j), acc);
+                        else
+                            nc += exact_pair<T, CAP>(P, xi, vi, ri, mi, q, j, p, sri, sr, held, acc);
                     });
                 }
             }
         }
         if (live) {
-            if (!bad) add_walls<T>(P, xi, vi, ri, mi, acc, nc);
-            F[q] = acc[0];
-            F[n + q] = acc[1];
-            F[2 * n + q] = acc[2];
-            if (ncont) ncont[q] = nc;
+            if (bad && (KIND == kForce || KIND == kBridge)) {  // no walls either
+                F[q] = F[n + q] = F[2 * n + q] = (T)0;
+                if (ncont) ncont[q] = 0;
+                continue;
+            }
+            finish_granule<T, KIND>(P, n, q, xi, vi, ri, mi, gi, acc, nc, F, ncont, A, tot);
         }
     }
+    leave();
 }
 
 // ---------------------------------------------------------------------------
@@ -1073,20 +1311,22 @@ static int shell_cap(const SizeRecord *ss)
     return want < kShellCapMax ? (int)want : kShellCapMax;
 }
 
-template <typename T, bool CAP, int NT>
+template <typename T, int KIND, int NT>
 static void contact_kernel(const DevParams &P, int64_t n, const double *x, const double *v, const double *r,
                            const int32_t *cb, const int32_t *ce, const BrickList &B, const T *sr, const double *held,
-                           T *F, int32_t *ncont, int64_t *err, hipStream_t s, int cap, int32_t *hm, int32_t *hc, int only)
+                           T *F, int32_t *ncont, int64_t *err, hipStream_t s, int cap, int32_t *hm, int32_t *hc, int only,
+                           const AdjArgs &A)
 {
     const int64_t nbricks = (int64_t)P.nb[0] * P.nb[1] * P.nb[2];
-    k_contact_lds<T, CAP, NT><<<brick_grid(nbricks), NT, contact_lds_bytes(cap, NT), s>>>(
-        P, n, B.list, B.count, cap, x, v, r, cb, ce, sr, held, F, ncont, err, hm, hc, only);
+    k_contact_lds<T, KIND, NT><<<brick_grid(nbricks), NT, contact_lds_bytes(cap, NT), s>>>(
+        P, n, B.list, B.count, cap, x, v, r, cb, ce, sr, held, F, ncont, err, hm, hc, only, A);
 }
 
-template <typename T>
-hipError_t launch_contact(const DevParams &P, int64_t n, const double *x, const double *v, const double *r,
-                          const int32_t *cb, const int32_t *ce, const BrickList &B, const T *sr, const double *held,
-                          T *F, int32_t *ncont, int64_t *err, hipStream_t s, SizeRecord *ss)
+template <typename T, int KIND>
+static hipError_t contact_launch(const DevParams &P, int64_t n, const double *x, const double *v, const double *r,
+                                 const int32_t *cb, const int32_t *ce, const BrickList &B, const T *sr,
+                                 const double *held, T *F, int32_t *ncont, int64_t *err, hipStream_t s, SizeRecord *ss,
+                                 const AdjArgs &A)
 {
     if (n == 0) return hipSuccess;
     const int cap = shell_cap(ss);
@@ -1099,25 +1339,45 @@ hipError_t launch_contact(const DevParams &P, int64_t n, const double *x, const 
         // 216 cells of a shell at 1.7 granules each
         const int wc = cap == kShellCapMax ? 368 : cap - kHaloCells * kPad;
         const int wcap = wc < kCopyRounds * 64 ? wc : kCopyRounds * 64;
-        const int only = mode == kFillBoth ? 1 : 0;
-        if (sr)
-            contact_kernel<T, true, 64>(P, n, x, v, r, cb, ce, B, sr, held, F, ncont, err, s, wcap, hm, hc, only);
-        else
-            contact_kernel<T, false, 64>(P, n, x, v, r, cb, ce, B, sr, held, F, ncont, err, s, wcap, hm, hc, only);
+        contact_kernel<T, KIND, 64>(P, n, x, v, r, cb, ce, B, sr, held, F, ncont, err, s, wcap, hm, hc,
+                                    mode == kFillBoth ? 1 : 0, A);
     }
-    if (mode != kFillWave) {
-        const int only = mode == kFillBoth ? 2 : 0;
-        if (sr)
-            contact_kernel<T, true, 256>(P, n, x, v, r, cb, ce, B, sr, held, F, ncont, err, s, cap, hm, hc, only);
-        else
-            contact_kernel<T, false, 256>(P, n, x, v, r, cb, ce, B, sr, held, F, ncont, err, s, cap, hm, hc, only);
-    }
+    if (mode != kFillWave)
+        contact_kernel<T, KIND, 256>(P, n, x, v, r, cb, ce, B, sr, held, F, ncont, err, s, cap, hm, hc,
+                                     mode == kFillBoth ? 2 : 0, A);
     hipError_t e = hipGetLastError();
     if (copy) {
         ss->par ^= 1;
         if (e == hipSuccess) e = hipMemcpyAsync(ss->host, hm, sizeof(int32_t), hipMemcpyDeviceToHost, s);
     }
     return e;
+}
+
+template <typename T>
+hipError_t launch_contact(const DevParams &P, int64_t n, const double *x, const double *v, const double *r,
+                          const int32_t *cb, const int32_t *ce, const BrickList &B, const T *sr, const double *held,
+                          T *F, int32_t *ncont, int64_t *err, hipStream_t s, SizeRecord *ss)
+{
+    if (sr)
+        return contact_launch<T, kBridge>(P, n, x, v, r, cb, ce, B, sr, held, F, ncont, err, s, ss, AdjArgs{});
+    return contact_launch<T, kForce>(P, n, x, v, r, cb, ce, B, nullptr, nullptr, F, ncont, err, s, ss, AdjArgs{});
+}
+
+hipError_t launch_contact_vjp(const DevParams &P, int64_t n, const double *x, const double *v, const double *r,
+                              const int32_t *cb, const int32_t *ce, const BrickList &B, const AdjArgs &A, int64_t *err,
+                              hipStream_t s, SizeRecord *ss)
+{
+    return contact_launch<double, kPull>(P, n, x, v, r, cb, ce, B, nullptr, nullptr, nullptr, nullptr, err, s, ss, A);
+}
+
+hipError_t launch_rollout_contact(const DevParams &P, int64_t n, const double *x, const double *v, const double *r,
+                                  const int32_t *cb, const int32_t *ce, const BrickList &B, const AdjArgs &A,
+                                  bool reverse, int64_t *err, hipStream_t s, SizeRecord *ss)
+{
+    if (reverse)
+        return contact_launch<double, kReverse>(P, n, x, v, r, cb, ce, B, nullptr, nullptr, nullptr, nullptr, err, s, ss,
+                                                A);
+    return contact_launch<double, kMove>(P, n, x, v, r, cb, ce, B, nullptr, nullptr, nullptr, nullptr, err, s, ss, A);
 }
 
 template hipError_t launch_contact<float>(const DevParams &, int64_t, const double *, const double *,

@@ -23,6 +23,8 @@ struct gic_ctx {
     bool in_step;      // inside gic_step, which builds the brick list once
     int device;
     int64_t *fxs;      // device: 4 G int64, integer sums of the unquantised transfers
+    double *psum;      // device: 2 per brick, partial sums of the rollout's parameter gradients (FP64 form)
+    unsigned long long *gmax;  // device: [1] bits of a reverse step's largest cotangent of the fluid fraction
     double *fxp;       // device: 4 x 1024 partial maxima, then the 4 scales and their inverses
     NbrList nl;        // device: neighbour list of the stepping path
     // device: tiles and escape list of the stepping path's assembled P2G
@@ -434,6 +436,9 @@ gic_status gic_create(const gic_params *p, int64_t n_max, gic_ctx **out)
     }
     ok &= hipMalloc(&c->fxs, sizeof(int64_t) * 4 * (size_t)(c->dp.G > 0 ? c->dp.G : 1)) == hipSuccess;
     ok &= hipMalloc(&c->fxp, sizeof(double) * (4 * 1024 + 8)) == hipSuccess;
+    ok &= hipMalloc(&c->gmax, sizeof(unsigned long long)) == hipSuccess;
+    if (!fp32(c))
+        ok &= hipMalloc(&c->psum, sizeof(double) * 2 * (c->bricks.nbricks > 0 ? c->bricks.nbricks : 1)) == hipSuccess;
     ok &= hipMalloc(&c->nl.nbr, sizeof(int32_t) * kNbrCap * nn) == hipSuccess;
     ok &= hipMalloc(&c->nl.cnt, sizeof(int32_t) * nn) == hipSuccess;
     ok &= hipMalloc(&c->nl.xref, sizeof(float) * 3 * nn) == hipSuccess;
@@ -500,6 +505,8 @@ gic_status gic_destroy(gic_ctx *c)
     }
     (void)hipFree(c->fxs);
     (void)hipFree(c->fxp);
+    (void)hipFree(c->psum);
+    (void)hipFree(c->gmax);
     (void)hipFree(c->nl.nbr);
     (void)hipFree(c->nl.cnt);
     (void)hipFree(c->nl.xref);
@@ -1048,8 +1055,92 @@ gic_status gic_contact_forces_vjp(gic_ctx *c, int64_t n, const double *x, const 
     if (c && (c->p.drag_model != 0 || c->p.vmass != 0)) return GIC_E_ARG;  // the adjoint covers the linear drag only
     if (!n_ok(c, n) || fp32(c)) return GIC_E_ARG;
     if (n > 0 && (!x || !v || !r || !cell_begin || !cell_end || !g_f || !g_x || !g_v || !g_mu)) return GIC_E_ARG;
-    return hip_status(launch_contact_vjp(c->dp, n, x, v, r, cell_begin, cell_end, g_f, g_x, g_v, g_mu,
-                                         (hipStream_t)stream));
+    if (n == 0) return GIC_OK;
+    if (brick_list(c, n, cell_begin, cell_end, (hipStream_t)stream) != hipSuccess) return GIC_E_HIP;
+    AdjArgs A = {};
+    A.gF = g_f;
+    A.gx = g_x;
+    A.gv = g_v;
+    A.gmu = g_mu;
+    return hip_status(
+        launch_contact_vjp(c->dp, n, x, v, r, cell_begin, cell_end, c->bricks, A, c->err, (hipStream_t)stream, &c->shell));
+}
+
+static bool rollout_ok(const gic_ctx *c, int64_t n)
+{
+    return n_ok(c, n) && !fp32(c) && c->p.drag_model == 0 && c->p.vmass == 0;
+}
+
+// Sort, state in sorted order and the alpha deposit of a rollout step.
+static hipError_t rollout_begin(gic_ctx *c, int64_t n, const double *xv, const double *r, uint32_t *key, int32_t *order,
+                                int32_t *cb, int32_t *ce, double *xvs, double *rs, int64_t len, const double *gxv,
+                                double *gs, double *gF, hipStream_t s)
+{
+    c->nl_n = -1;  // as gic_sort_cells
+    c->rng_ok = false;
+    c->bl_pin = false;
+    int nb = 0;
+    hipError_t e = launch_rollout_sort(c->dp, n, xv, r, key, order, cb, ce, c->K, c->sort, c->bricks, c->err, xvs, rs,
+                                       c->fxs, len, c->fxp, &nb, gxv, gs, gF, c->gmax, s);
+    if (e == hipSuccess) e = launch_rollout_p2g(c->dp, n, c->K, xvs, rs, cb, ce, c->bricks, c->fxs, c->fxp, nb, s);
+    return e;
+}
+
+gic_status gic_rollout_step(gic_ctx *c, int64_t n, const double *xv, const double *r, const double *u, double *xv_out,
+                            uint32_t *key, int32_t *order, int32_t *cell_begin, int32_t *cell_end, double *xv_sorted,
+                            double *r_sorted, void *stream)
+{
+    if (!rollout_ok(c, n) || !cell_begin || !cell_end) return GIC_E_ARG;
+    if (n == 0) return GIC_OK;
+    if (!xv || !r || !u || !xv_out || xv_out == xv || !key || !order || !xv_sorted || !r_sorted) return GIC_E_ARG;
+    hipStream_t s = (hipStream_t)stream;
+    hipError_t e = rollout_begin(c, n, xv, r, key, order, cell_begin, cell_end, xv_sorted, r_sorted, c->dp.G, nullptr,
+                                 nullptr, nullptr, s);
+    AdjArgs A = {};
+    A.u = u;
+    A.inv = rollout_scale(c->fxp);
+    A.fx = c->fxs;
+    A.order = order;
+    A.out = xv_out;
+    if (e == hipSuccess)
+        e = launch_rollout_contact(c->dp, n, xv_sorted, xv_sorted + 3 * n, r_sorted, cell_begin, cell_end, c->bricks, A,
+                                   false, c->err, s, &c->shell);
+    return hip_status(e);
+}
+
+gic_status gic_rollout_step_vjp(gic_ctx *c, int64_t n, const double *xv, const double *r, const double *u,
+                                double *g_xv, double *g_mu, double *g_cdrag, uint32_t *key, int32_t *order,
+                                int32_t *cell_begin, int32_t *cell_end, double *xv_sorted, double *r_sorted,
+                                double *g_sorted, double *g_f, double *g_af, void *stream)
+{
+    if (!rollout_ok(c, n) || !cell_begin || !cell_end) return GIC_E_ARG;
+    if (n == 0) return GIC_OK;
+    if (!xv || !r || !u || !g_xv || !g_mu || !g_cdrag || !key || !order || !xv_sorted || !r_sorted || !g_sorted || !g_f ||
+        !g_af)
+        return GIC_E_ARG;
+    hipStream_t s = (hipStream_t)stream;
+    const int64_t G = c->dp.G;
+    hipError_t e = rollout_begin(c, n, xv, r, key, order, cell_begin, cell_end, xv_sorted, r_sorted, 2 * G, g_xv,
+                                 g_sorted, g_f, s);
+    AdjArgs A = {};
+    A.gF = g_f;
+    A.u = u;
+    A.inv = rollout_scale(c->fxp);
+    A.fx = c->fxs;
+    A.gs = g_sorted;
+    A.gaf = g_af;
+    A.gmax = c->gmax;
+    A.psum = c->psum;
+    if (e == hipSuccess)
+        e = launch_rollout_contact(c->dp, n, xv_sorted, xv_sorted + 3 * n, r_sorted, cell_begin, cell_end, c->bricks, A,
+                                   true, c->err, s, &c->shell);
+    if (e == hipSuccess)
+        e = launch_rollout_galpha(c->dp, n, c->K, xv_sorted, g_af, cell_begin, cell_end, c->bricks, c->fxs, c->fxs + G,
+                                  c->fxp, c->gmax, s);
+    if (e == hipSuccess)
+        e = launch_rollout_pull(c->dp, n, order, xv_sorted, r_sorted, c->fxs + G, c->gmax, g_sorted, g_xv, c->psum,
+                                c->bricks, g_mu, g_cdrag, s);
+    return hip_status(e);
 }
 
 gic_status gic_drag_vjp(gic_ctx *c, int64_t n, const double *r, const double *v, const double *u_at,

@@ -491,4 +491,59 @@ __device__ inline int pair_force(const DevParams &P, const T nh[3], T delta, con
     return slide;
 }
 
+// Reverse of pair_force in double.  gbar: cotangent of the force on the
+// first partner; gmu: cotangent used for the derivative in mu.  Adds to
+// nbar, *dbar (overlap), wbar (relative velocity), *mubar.
+__device__ inline void pair_force_vjp(const DevParams &P, const double nh[3], double delta, const double w[3],
+                                      double meff, const double gbar[3], const double gmu[3], double nbar[3],
+                                      double &dbar, double wbar[3], double &mubar)
+{
+    const double gam = 2.0 * P.zeta * sqrt(meff * P.kn);
+    const double kt = P.kt_ratio * gam;
+    const double vn = (w[0] * nh[0] + w[1] * nh[1]) + w[2] * nh[2];
+    const double fn = P.kn * delta - gam * vn;
+    double ft[3];
+    for (int a = 0; a < 3; ++a) ft[a] = -kt * (w[a] - vn * nh[a]);
+    const double s = sqrt((ft[0] * ft[0] + ft[1] * ft[1]) + ft[2] * ft[2]);
+    const double cap = P.mu * (P.kn * delta);
+    const bool slide = s > cap;
+    const double fnbar = (gbar[0] * nh[0] + gbar[1] * nh[1]) + gbar[2] * nh[2];
+    for (int a = 0; a < 3; ++a) nbar[a] += fn * gbar[a];
+    double ftbar[3];
+    if (slide) {
+        const double fh[3] = {ft[0] / s, ft[1] / s, ft[2] / s};
+        const double gdotf = (gbar[0] * fh[0] + gbar[1] * fh[1]) + gbar[2] * fh[2];
+        for (int a = 0; a < 3; ++a) ftbar[a] = (cap / s) * (gbar[a] - gdotf * fh[a]);
+        dbar += gdotf * P.mu * P.kn;
+        const double gmudotf = (gmu[0] * fh[0] + gmu[1] * fh[1]) + gmu[2] * fh[2];
+        mubar += gmudotf * P.kn * delta;
+    } else {
+        for (int a = 0; a < 3; ++a) ftbar[a] = gbar[a];
+    }
+    double tbar[3];
+    for (int a = 0; a < 3; ++a) tbar[a] = -kt * ftbar[a];
+    double vnbar = -((tbar[0] * nh[0] + tbar[1] * nh[1]) + tbar[2] * nh[2]);
+    for (int a = 0; a < 3; ++a) {
+        wbar[a] += tbar[a];
+        nbar[a] += -vn * tbar[a];
+    }
+    dbar += P.kn * fnbar;
+    vnbar += -gam * fnbar;
+    for (int a = 0; a < 3; ++a) {
+        wbar[a] += vnbar * nh[a];
+        nbar[a] += vnbar * w[a];
+    }
+}
+
+// Scale of the integer sums of the unquantised transfers: 2^(50 - e), 2^e the
+// power of two above the largest contribution bound M (1 when it is zero), so
+// that contributions times it stay below 2^50.
+__device__ inline double fix_scale(double M)
+{
+    if (!(M > 0.0)) return 1.0;
+    int e;
+    (void)frexp(M, &e);  // M = f 2^e, f in [0.5, 1)
+    return ldexp(1.0, 50 - e);
+}
+
 }  // namespace gic

@@ -80,6 +80,26 @@ constexpr int64_t kSmallSort = (int64_t)1 << 18;
 hipError_t launch_sort_cells(const DevParams &P, int64_t n, const double *x, uint32_t *key, int32_t *order,
                              int32_t *cell_begin, int32_t *cell_end, int64_t K, SortScratch &S, BrickList &B,
                              int64_t *err, hipStream_t s, const NbrList *nl = nullptr, int force = 1, int keep_ranges = 0);
+// Sort of a rollout step (n > 0): xv holds x then v (6 n) in input order; the
+// state goes to xvs and rs in sorted order, fx (len int64) is cleared and the
+// largest granule fractions of *nb workgroups go to part; with gxv (the reverse
+// step) the adjoint of the state goes to gs, moved through the integration, that
+// of the force to gF, and gmax is cleared.
+hipError_t launch_rollout_sort(const DevParams &P, int64_t n, const double *xv, const double *r, uint32_t *key,
+                               int32_t *order, int32_t *cell_begin, int32_t *cell_end, int64_t K, SortScratch &S,
+                               BrickList &B, int64_t *err, double *xvs, double *rs, int64_t *fx, int64_t len,
+                               double *part, int *nb, const double *gxv, double *gs, double *gF,
+                               unsigned long long *gmax, hipStream_t s);
+hipError_t launch_rollout_p2g(const DevParams &P, int64_t n, int64_t K, const double *x, const double *r,
+                              const int32_t *cb, const int32_t *ce, const BrickList &B, int64_t *fx, double *part, int nb,
+                              hipStream_t s);
+const double *rollout_scale(const double *part);  // the inverse scale of its sums (device)
+hipError_t launch_rollout_galpha(const DevParams &P, int64_t n, int64_t K, const double *x, const double *gaf,
+                                 const int32_t *cb, const int32_t *ce, const BrickList &B, const int64_t *fx,
+                                 int64_t *fx2, double *part, const unsigned long long *gmax, hipStream_t s);
+hipError_t launch_rollout_pull(const DevParams &P, int64_t n, const int32_t *order, const double *x, const double *r,
+                               const int64_t *fx2, const unsigned long long *gmax, const double *gs, double *gxv,
+                               const double *psum, const BrickList &B, double *gmu, double *gcd, hipStream_t s);
 hipError_t launch_reorder(int64_t n, const int32_t *order, const double *x, const double *v, const double *r,
                           const int32_t *id, double *xo, double *vo, double *ro, int32_t *ido, hipStream_t s);
 
@@ -242,9 +262,26 @@ hipError_t launch_g2p_vjp_grid(const DevParams &P, int64_t n, int64_t K, const d
                                const double *gaf, const int32_t *cb, const int32_t *ce, const BrickList &B,
                                double *gA, int64_t *fx, double *part, hipStream_t s);
 
+// What the differentiable form's kinds of the direct contact kernel (see
+// ContactKind in contact.hip) read and write besides the contact's arrays.
+struct AdjArgs {
+    const double *gF;            // pullbacks: cotangent of the force
+    double *gx, *gv, *gmu;       // gic_contact_forces_vjp: added to, added to, written
+    const double *u, *inv;       // rollout: fluid velocity; inverse scale of fx
+    const int64_t *fx;           // rollout: the alpha deposit's integer sums
+    const int32_t *order;        // forward step: sorted position to input index
+    double *out;                 // forward step: (x, v) advanced, input order
+    double *gs;                  // reverse step: adjoint of (x, v), sorted, in and out
+    double *gaf;                 // reverse step: cotangent of the fluid fraction
+    unsigned long long *gmax;    // reverse step: bits of the largest |gaf|
+    double *psum;                // reverse step: per brick, the sums of dL/dmu and dL/dC_d
+};
 hipError_t launch_contact_vjp(const DevParams &P, int64_t n, const double *x, const double *v, const double *r,
-                              const int32_t *cb, const int32_t *ce, const double *gF, double *gx, double *gv,
-                              double *gmu, hipStream_t s);
+                              const int32_t *cb, const int32_t *ce, const BrickList &B, const AdjArgs &A, int64_t *err,
+                              hipStream_t s, SizeRecord *ss);
+hipError_t launch_rollout_contact(const DevParams &P, int64_t n, const double *x, const double *v, const double *r,
+                                  const int32_t *cb, const int32_t *ce, const BrickList &B, const AdjArgs &A,
+                                  bool reverse, int64_t *err, hipStream_t s, SizeRecord *ss);
 hipError_t launch_drag_vjp(const DevParams &P, int64_t n, const double *r, const double *v, const double *uat,
                            const double *af, const double *gF, double *gv, double *guat, double *gaf, double *gcd,
                            hipStream_t s);

@@ -499,6 +499,86 @@ __global__ void __launch_bounds__(256) k_cell_order(int64_t n, const uint32_t *_
     }
 }
 
+// The last pass of a rollout step's sort: the order of k_cell_order, and with it
+// the state in sorted order (xv: x then v in input order), the grid sums fx
+// (len int64) cleared, and each workgroup's largest granule fraction in part.
+// REV (the reverse step): also the adjoint of the state in sorted order, moved
+// through the integration: v^{n+1} feeds x^{n+1}, so its adjoint, which is also
+// that of v^n through the identity term, is g_v + dt g_x, and the adjoint of
+// the force is dt / m of it.
+template <bool REV>
+__global__ void __launch_bounds__(256) k_rollout_order(DevParams P, int64_t n, const uint32_t *__restrict__ skeys,
+                                                       const uint32_t *__restrict__ begin,
+                                                       const uint32_t *__restrict__ end, int32_t *tmp, int32_t *tmp2,
+                                                       int32_t *__restrict__ order, uint32_t *__restrict__ cnt, int64_t K,
+                                                       const double *__restrict__ xv, const double *__restrict__ r,
+                                                       double *__restrict__ xvs, double *__restrict__ rs,
+                                                       int64_t *__restrict__ fx, int64_t len, double *__restrict__ part,
+                                                       const double *__restrict__ gxv, double *__restrict__ gs,
+                                                       double *__restrict__ gF, unsigned long long *__restrict__ gmax)
+{
+    __shared__ uint32_t s_base[256], wcnt[4][256], lds[4];
+    __shared__ int64_t s_long[2];
+    __shared__ double s_m[4];
+    if (cnt)  // the counts, for the next sort
+        for (int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x; k < K; k += (int64_t)gridDim.x * 256) cnt[k] = 0u;
+    for (int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x; k < len; k += (int64_t)gridDim.x * 256) fx[k] = 0;
+    if (REV && blockIdx.x == 0 && threadIdx.x == 0) *gmax = 0ull;
+    double m = 0.0;
+    auto take = [&](int64_t q, int64_t i) {  // granule i at sorted position q
+        double s[6];
+#pragma unroll
+        for (int c = 0; c < 6; ++c) s[c] = xv[c * n + i];
+        const double ri = r[i];
+        if (REV) {
+            const double w = P.dt / mass_of(P, ri);
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                const double gx = gxv[a * n + i];
+                const double t = gxv[(3 + a) * n + i] + P.dt * gx;
+                gs[a * n + q] = gx;
+                gs[(3 + a) * n + q] = t;
+                gF[a * n + q] = w * t;
+            }
+        }
+#pragma unroll
+        for (int c = 0; c < 6; ++c) xvs[c * n + q] = s[c];
+        rs[q] = ri;
+        m = fmax(m, volume_of(ri) * P.inv_vcell);
+    };
+    for (int64_t p0 = (int64_t)blockIdx.x * 256; p0 < n; p0 += (int64_t)gridDim.x * 256) {
+        if (threadIdx.x == 0) s_long[1] = 0;
+        __syncthreads();
+        const int64_t p = p0 + threadIdx.x;
+        if (p < n) {
+            const uint32_t k = skeys[p];
+            int64_t b = begin[k], e = end[k];
+            e = e < n ? e : n;
+            if (e - b <= kLongCell) {
+                const int32_t v = tmp[p];
+                int rank = 0;
+                for (int64_t j = b; j < e; ++j) rank += tmp[j] < v ? 1 : 0;
+                order[b + rank] = v;
+                take(b + rank, v);
+            } else if (p == b) {  // at most one such cell begins in 256 places
+                s_long[0] = b;
+                s_long[1] = e;
+            }
+        }
+        __syncthreads();
+        if (s_long[1]) {
+            sort_long_cell(tmp, tmp2, order, s_long[0], s_long[1], n, s_base, wcnt, lds);
+            __syncthreads();
+            for (int64_t q = s_long[0] + threadIdx.x; q < s_long[1]; q += 256) take(q, order[q]);
+        }
+        __syncthreads();
+    }
+    for (int off = 32; off > 0; off >>= 1) m = fmax(m, __shfl_xor(m, off));
+    if ((threadIdx.x & 63) == 0) s_m[threadIdx.x >> 6] = m;
+    __syncthreads();
+    if (threadIdx.x == 0) part[blockIdx.x] = fmax(fmax(s_m[0], s_m[1]), fmax(s_m[2], s_m[3]));
+}
+
 __global__ void __launch_bounds__(256) k_reorder(int64_t n, const int32_t *__restrict__ order,
                                                  const double *__restrict__ x, const double *__restrict__ v,
                                                  const double *__restrict__ r, const int32_t *__restrict__ id,
@@ -768,6 +848,38 @@ hipError_t launch_sort_cells(const DevParams &P, int64_t n, const double *x, uin
                                         K);
     }
     S.cur ^= 1;  // this sort's keys are the previous keys of the next
+    S.last_n = n;
+    return brick_count_copy(B, n, s);
+}
+
+hipError_t launch_rollout_sort(const DevParams &P, int64_t n, const double *xv, const double *r, uint32_t *key,
+                               int32_t *order, int32_t *cell_begin, int32_t *cell_end, int64_t K, SortScratch &S,
+                               BrickList &B, int64_t *err, double *xvs, double *rs, int64_t *fx, int64_t len,
+                               double *part, int *nb, const double *gxv, double *gs, double *gF,
+                               unsigned long long *gmax, hipStream_t s)
+{
+    uint32_t *begin = reinterpret_cast<uint32_t *>(cell_begin), *end = reinterpret_cast<uint32_t *>(cell_end);
+    uint32_t *skeys = S.skeys[S.cur ^ 1];
+    const unsigned g = grid_for(n, 256), gl = g < kLoopGrid ? g : kLoopGrid, go = g < 1024u ? g : 1024u;
+    k_cell_keys<<<g, 256, 0, s>>>(P, n, xv, key, err, nullptr, nullptr, S.ctl, nullptr, nullptr, order, skeys);
+    k_cell_count<<<gl, 256, 0, s>>>(key, n, S.cnt, S.slot, nullptr, S.chg_s, S.chg_p, skeys, order, nullptr, 0, 0, nullptr,
+                                    1, 0.0f, nullptr, 0);
+    const bool direct = K <= kDirectScan;
+    const int64_t chunk = direct ? 4 * kScanThreads : scan_chunk(K);
+    const int nc = (int)((K + chunk - 1) / chunk);
+    if (!direct) k_scan_reduce<<<nc, kScanThreads, 0, s>>>(S.cnt, K, chunk, S.sums, S.sums + kScanThreads, nullptr);
+    k_scan_down_ranges<<<nc, kScanThreads, 0, s>>>(S.cnt, begin, end, K, chunk, direct ? nullptr : S.sums,
+                                                   S.sums + kScanThreads, S.ctl, 0, B.list, B.count, B.slot_of);
+    k_cell_place<<<gl, 256, 0, s>>>(key, n, begin, S.slot, S.tmp, skeys, nullptr, 0);
+    uint32_t *cnt = direct ? S.cnt : nullptr;
+    if (gxv)
+        k_rollout_order<true><<<go, 256, 0, s>>>(P, n, skeys, begin, end, S.tmp, S.tmp2, order, cnt, K, xv, r, xvs, rs,
+                                                 fx, len, part, gxv, gs, gF, gmax);
+    else
+        k_rollout_order<false><<<go, 256, 0, s>>>(P, n, skeys, begin, end, S.tmp, S.tmp2, order, cnt, K, xv, r, xvs, rs,
+                                                  fx, len, part, nullptr, nullptr, nullptr, nullptr);
+    *nb = (int)go;
+    S.cur ^= 1;
     S.last_n = n;
     return brick_count_copy(B, n, s);
 }

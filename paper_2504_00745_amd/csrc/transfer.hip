@@ -696,34 +696,35 @@ __global__ void __launch_bounds__(256) k_fix_prep(DevParams P, int64_t n, int64_
             fmax(fmax(wm[threadIdx.x][0], wm[threadIdx.x][1]), fmax(wm[threadIdx.x][2], wm[threadIdx.x][3]));
 }
 
-// The scales of a call, after its nb partial maxima per channel:
-// part[kFixScale + c] = 2^(50 - e), 2^e the power of two above channel c's
-// largest bound (1 when all are zero), so contributions times it stay below
-// 2^50; part[kFixScale + 4 + c] = its inverse.  One workgroup, once per call.
+// The scales of a call from its nb partial maxima per channel, in every
+// workgroup of the kernel that needs them; the first one leaves them and
+// their inverses in part[kFixScale + c], part[kFixScale + 4 + c] for the
+// kernels after.
 constexpr int kFixScale = 4 * kFixParts;
 
-__global__ void __launch_bounds__(256) k_fix_scale(double *__restrict__ part, int nb, int nch)
+__device__ inline void fix_scales(double *__restrict__ part, int nb, int nch, double sc[4])
 {
-    __shared__ double wm[4];
+    __shared__ double wm[4][4];
     for (int c = 0; c < nch; ++c) {
         double M = 0.0;
         for (int b = threadIdx.x; b < nb; b += 256) M = fmax(M, part[c * kFixParts + b]);
         for (int off = 32; off > 0; off >>= 1) M = fmax(M, __shfl_xor(M, off));
-        if ((threadIdx.x & 63) == 0) wm[threadIdx.x >> 6] = M;
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            M = fmax(fmax(wm[0], wm[1]), fmax(wm[2], wm[3]));
-            double sc = 1.0;
-            if (M > 0.0) {
-                int e;
-                (void)frexp(M, &e);  // M = f 2^e, f in [0.5, 1)
-                sc = ldexp(1.0, 50 - e);
-            }
-            part[kFixScale + c] = sc;
-            part[kFixScale + 4 + c] = 1.0 / sc;
-        }
-        __syncthreads();
+        if ((threadIdx.x & 63) == 0) wm[c][threadIdx.x >> 6] = M;
     }
+    __syncthreads();
+    for (int c = 0; c < nch; ++c) {
+        sc[c] = fix_scale(fmax(fmax(wm[c][0], wm[c][1]), fmax(wm[c][2], wm[c][3])));
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            part[kFixScale + c] = sc[c];
+            part[kFixScale + 4 + c] = 1.0 / sc[c];
+        }
+    }
+}
+
+__global__ void __launch_bounds__(256) k_fix_scale(double *__restrict__ part, int nb, int nch)
+{
+    double sc[4];
+    fix_scales(part, nb, nch, sc);
 }
 
 __global__ void __launch_bounds__(kP2GThreads) k_p2g_real(DevParams P, int64_t n, const int32_t *__restrict__ bl,
@@ -733,22 +734,22 @@ __global__ void __launch_bounds__(kP2GThreads) k_p2g_real(DevParams P, int64_t n
                                                           const double *__restrict__ r,
                                                           const int32_t *__restrict__ cb,
                                                           const int32_t *__restrict__ ce,
-                                                          const double *__restrict__ part, int nch,
+                                                          double *__restrict__ part, int nb, int nch,
                                                           unsigned long long *__restrict__ fx)
 {
     extern __shared__ unsigned long long itile[];
-    __shared__ int32_t s_range[2];
     const int64_t b = brick_of_block(bl, bcnt);
+    if (b < 0 && blockIdx.x != 0) return;
+    double sc[4];
+    fix_scales(part, nb, nch, sc);
     if (b < 0) return;
-    brick_range(n, b, cb, ce, s_range);
+    int32_t beg = cb[b * kBrickCells], end = ce[b * kBrickCells + kBrickCells - 1];
+    clip_range(n, beg, end);
     const int E = P.tile;
     const int E3 = E * E * E;
     for (int k = threadIdx.x; k < nch * E3; k += kP2GThreads) itile[k] = 0ull;
     __syncthreads();
-    const int32_t beg = s_range[0], end = s_range[1];
     if (end <= beg) return;
-    double sc[4];
-    for (int c = 0; c < nch; ++c) sc[c] = part[kFixScale + c];
     int32_t o[3];
     tile_origin(P, b, o);
     const int64_t G = P.G;
@@ -1026,13 +1027,14 @@ hipError_t launch_p2g_real(const DevParams &P, int64_t n, int64_t K, const doubl
     const int64_t per = n > 0 ? (n + kFixParts - 1) / kFixParts : 1;
     const int nb = (int)(n > 0 ? (n + per - 1) / per : 1);
     k_fix_prep<<<nb, 256, 0, s>>>(P, n, per, v, r, nullptr, fx, nch * G, part);
-    k_fix_scale<<<1, 256, 0, s>>>(part, nb, nch);
     if (n > 0) {
         const int64_t bricks = K / kBrickCells;
         const int E3 = P.tile * P.tile * P.tile;
         const size_t lds = sizeof(unsigned long long) * (size_t)nch * E3;
-        k_p2g_real<<<brick_grid(bricks), kP2GThreads, lds, s>>>(P, n, B.list, B.count, x, v, r, cb, ce, part, nch,
+        k_p2g_real<<<brick_grid(bricks), kP2GThreads, lds, s>>>(P, n, B.list, B.count, x, v, r, cb, ce, part, nb, nch,
                                                                  reinterpret_cast<unsigned long long *>(fx));
+    } else {
+        k_fix_scale<<<1, 256, 0, s>>>(part, nb, nch);
     }
     unsigned g = grid_for(nch * G, 256);
     if (g > 4096) g = 4096;
@@ -1042,27 +1044,38 @@ hipError_t launch_p2g_real(const DevParams &P, int64_t n, int64_t K, const doubl
 
 // Grid part of the G2P pullback, deterministic like k_p2g_real: g_alpha_k =
 // -sum_i w_ik gaf_i on nodes below the clamp, the contributions rounded to
-// integers at the scale of the largest |gaf_i|.
+// integers at the scale of the largest |gaf_i|.  FUSED (the rollout's reverse
+// step): A as its integer sums fxA and their inverse scale, the largest |gaf_i|
+// as a word of bits.
+template <bool FUSED>
 __global__ void __launch_bounds__(256) k_g2p_vjp_grid(DevParams P, int64_t n, const int32_t *__restrict__ bl,
                                                       const int32_t *__restrict__ bcnt,
                                                       const double *__restrict__ x, const double *__restrict__ A,
                                                       const double *__restrict__ gaf,
                                                       const int32_t *__restrict__ cb, const int32_t *__restrict__ ce,
-                                                      const double *__restrict__ part,
-                                                      unsigned long long *__restrict__ fx)
+                                                      double *__restrict__ part, int nb,
+                                                      unsigned long long *__restrict__ fx,
+                                                      const int64_t *__restrict__ fxA,
+                                                      const unsigned long long *__restrict__ gmax)
 {
     extern __shared__ unsigned long long itile[];
-    __shared__ int32_t s_range[2];
     const int64_t b = brick_of_block(bl, bcnt);
+    if (b < 0 && (FUSED || blockIdx.x != 0)) return;
+    double sc4[4];
+    if (FUSED)
+        sc4[0] = fix_scale(__longlong_as_double((long long)*gmax));
+    else
+        fix_scales(part, nb, 1, sc4);
     if (b < 0) return;
-    brick_range(n, b, cb, ce, s_range);
+    const double sc = sc4[0], invA = FUSED ? part[kFixScale + 4] : 0.0;
+    auto alpha = [&](int64_t k) { return FUSED ? (double)fxA[k] * invA : A[k]; };
+    int32_t beg = cb[b * kBrickCells], end = ce[b * kBrickCells + kBrickCells - 1];
+    clip_range(n, beg, end);
     const int E = P.tile;
     const int E3 = E * E * E;
     for (int k = threadIdx.x; k < E3; k += 256) itile[k] = 0ull;
     __syncthreads();
-    const int32_t beg = s_range[0], end = s_range[1];
     if (end <= beg) return;
-    const double sc = part[kFixScale];
     int32_t o[3];
     tile_origin(P, b, o);
     for (int64_t q = beg + (int64_t)threadIdx.x; q < end; q += 256) {
@@ -1075,7 +1088,7 @@ __global__ void __launch_bounds__(256) k_g2p_vjp_grid(DevParams P, int64_t n, co
                 for (int cx = 0; cx < 3; ++cx) {
                     const int32_t ni = s.node[0][cx], nj = s.node[1][cy], nk = s.node[2][cz];
                     const int64_t gidx = node_index(P, ni, nj, nk);
-                    if (!(A[gidx] < P.alpha_max)) continue;
+                    if (!(alpha(gidx) < P.alpha_max)) continue;
                     const int64_t val = rint_i64((((s.w[0][cx] * s.w[1][cy]) * s.w[2][cz]) * sg) * sc);
                     const int32_t li = ni - o[0], lj = nj - o[1], lk = nk - o[2];
                     const bool in = li >= 0 && lj >= 0 && lk >= 0 && li < E && lj < E && lk < E;
@@ -1099,16 +1112,45 @@ hipError_t launch_g2p_vjp_grid(const DevParams &P, int64_t n, int64_t K, const d
     const int64_t per = n > 0 ? (n + kFixParts - 1) / kFixParts : 1;
     const int nb = (int)(n > 0 ? (n + per - 1) / per : 1);
     k_fix_prep<<<nb, 256, 0, s>>>(P, n, per, nullptr, nullptr, gaf, fx, G, part);
-    k_fix_scale<<<1, 256, 0, s>>>(part, nb, 1);
     if (n > 0) {
         const int64_t bricks = K / kBrickCells;
         const size_t lds = sizeof(unsigned long long) * (size_t)P.tile * P.tile * P.tile;
-        k_g2p_vjp_grid<<<brick_grid(bricks), 256, lds, s>>>(P, n, B.list, B.count, x, A, gaf, cb, ce, part,
-                                                            reinterpret_cast<unsigned long long *>(fx));
+        k_g2p_vjp_grid<false><<<brick_grid(bricks), 256, lds, s>>>(P, n, B.list, B.count, x, A, gaf, cb, ce, part, nb,
+                                                                   reinterpret_cast<unsigned long long *>(fx),
+                                                                   nullptr, nullptr);
+    } else {
+        k_fix_scale<<<1, 256, 0, s>>>(part, nb, 1);
     }
     unsigned g = grid_for(G, 256);
     if (g > 4096) g = 4096;
     k_fix_finish<<<g, 256, 0, s>>>(G, 1, part, fx, gA, nullptr, 0);
+    return hipGetLastError();
+}
+
+// The unquantised alpha deposit and the G2P pullback's grid part of a rollout
+// step, without the passes that the stages need around them: the grids are
+// cleared, and the largest contributions found, by the sort's last pass.
+const double *rollout_scale(const double *part) { return part + kFixScale + 4; }
+
+hipError_t launch_rollout_p2g(const DevParams &P, int64_t n, int64_t K, const double *x, const double *r,
+                              const int32_t *cb, const int32_t *ce, const BrickList &B, int64_t *fx, double *part, int nb,
+                              hipStream_t s)
+{
+    const size_t lds = sizeof(unsigned long long) * (size_t)P.tile * P.tile * P.tile;
+    k_p2g_real<<<brick_grid(K / kBrickCells), kP2GThreads, lds, s>>>(P, n, B.list, B.count, x, nullptr, r, cb, ce, part,
+                                                                     nb, 1, reinterpret_cast<unsigned long long *>(fx));
+    return hipGetLastError();
+}
+
+hipError_t launch_rollout_galpha(const DevParams &P, int64_t n, int64_t K, const double *x, const double *gaf,
+                                 const int32_t *cb, const int32_t *ce, const BrickList &B, const int64_t *fx,
+                                 int64_t *fx2, double *part, const unsigned long long *gmax, hipStream_t s)
+{
+    const size_t lds = sizeof(unsigned long long) * (size_t)P.tile * P.tile * P.tile;
+    k_g2p_vjp_grid<true><<<brick_grid(K / kBrickCells), 256, lds, s>>>(P, n, B.list, B.count, x, nullptr, gaf, cb, ce,
+                                                                       part, 0,
+                                                                       reinterpret_cast<unsigned long long *>(fx2), fx,
+                                                                       gmax);
     return hipGetLastError();
 }
 

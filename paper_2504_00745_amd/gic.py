@@ -88,6 +88,8 @@ def lib():
             "gic_exchange_p2g": (C.c_int, [_V, _I64] + [_V] * 6 + [C.c_double, _V, _V, _V]),
             "gic_sand_step": (C.c_int, [_V, _I64, C.c_double] + [_V] * 23),
             "gic_contact_forces_vjp": (C.c_int, [_V, _I64] + [_V] * 10),
+            "gic_rollout_step": (C.c_int, [_V, _I64] + [_V] * 11),
+            "gic_rollout_step_vjp": (C.c_int, [_V, _I64] + [_V] * 16),
             "gic_drag_vjp": (C.c_int, [_V, _I64] + [_V] * 10),
             "gic_integrate_vjp": (C.c_int, [_V, _I64] + [_V] * 5),
             "gic_g2p_vjp": (C.c_int, [_V, _I64] + [_V] * 10),
@@ -489,6 +491,31 @@ def gic_contact_forces_vjp(ctx, x, v, r, cell_begin, cell_end, g_f, g_x, g_v, g_
                                         _ptr(cell_begin, torch.int32, ctx.K), _ptr(cell_end, torch.int32, ctx.K),
                                         _ptr(g_f, f64, 3 * n), _ptr(g_x, f64, 3 * n), _ptr(g_v, f64, 3 * n),
                                         _ptr(g_mu, f64, n), _stream()), "gic_contact_forces_vjp")
+
+
+def gic_rollout_step(ctx, xv, r, u, xv_out, key, order, cell_begin, cell_end, xv_sorted, r_sorted):
+    """One differentiable step of the state xv = (x, v) (6n, input order) into
+    xv_out."""
+    n = r.shape[-1]
+    f64, i32 = torch.float64, torch.int32
+    _check(lib().gic_rollout_step(ctx.handle, n, _ptr(xv, f64, 6 * n, "xv"), _ptr(r, f64, n), _ptr(u, f64, 3 * ctx.G),
+                                  _ptr(xv_out, f64, 6 * n, "xv_out"), _ptr(key, i32, n), _ptr(order, i32, n),
+                                  _ptr(cell_begin, i32, ctx.K), _ptr(cell_end, i32, ctx.K),
+                                  _ptr(xv_sorted, f64, 6 * n), _ptr(r_sorted, f64, n), _stream()), "gic_rollout_step")
+
+
+def gic_rollout_step_vjp(ctx, xv, r, u, g_xv, g_mu, g_cdrag, key, order, cell_begin, cell_end, xv_sorted, r_sorted,
+                         g_sorted, g_f, g_af):
+    """Its reverse: g_xv (6n, input order) in place, g_mu and g_cdrag (one
+    element each) added to."""
+    n = r.shape[-1]
+    f64, i32 = torch.float64, torch.int32
+    _check(lib().gic_rollout_step_vjp(ctx.handle, n, _ptr(xv, f64, 6 * n, "xv"), _ptr(r, f64, n),
+                                      _ptr(u, f64, 3 * ctx.G), _ptr(g_xv, f64, 6 * n, "g_xv"), _ptr(g_mu, f64, 1),
+                                      _ptr(g_cdrag, f64, 1), _ptr(key, i32, n), _ptr(order, i32, n),
+                                      _ptr(cell_begin, i32, ctx.K), _ptr(cell_end, i32, ctx.K),
+                                      _ptr(xv_sorted, f64, 6 * n), _ptr(r_sorted, f64, n), _ptr(g_sorted, f64, 6 * n),
+                                      _ptr(g_f, f64, 3 * n), _ptr(g_af, f64, n), _stream()), "gic_rollout_step_vjp")
 
 
 def gic_drag_vjp(ctx, r, v, u_at, alpha_f, g_f, g_v, g_u_at, g_alpha_f, g_cdrag):

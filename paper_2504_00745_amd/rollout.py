@@ -10,10 +10,10 @@ GICRollout is a torch.autograd.Function whose backward runs the adjoint
 kernels of the C ABI (gic_*_vjp): states are checkpointed every `ckpt`
 steps in the forward, each segment is recomputed in the backward and walked
 in reverse.  The granule state is kept in input order; each step sorts, works
-on a sorted copy and scatters the result back, so adjoints are gathered and
-scattered with the same permutations.  Positions and velocities (and their
-adjoints) share one buffer, x then v (6n doubles), so each gather or scatter
-of both is one gic_permute of six components.  PyTorch provides device memory and
+on a sorted copy and writes the result back in input order, and so do the
+adjoints.  Positions and velocities (and their adjoints) share one buffer, x
+then v (6n doubles).  A step is one call (gic_rollout_step), its reverse
+another (gic_rollout_step_vjp).  PyTorch provides device memory and
 the stream only: the loss cotangent is scaled on the device (gic_scale) and
 the parameters mu and c_drag, kernel arguments, are read from host tensors
 (or numbers), so neither pass reads the device back.
@@ -51,14 +51,17 @@ class Rollout:
         self.cb, self.ce = e(K, dt=torch.int32), e(K, dt=torch.int32)
         self.xvs, self.rs = e(6 * n), e(n)  # sorted x then v
         self.xs, self.vs = self.xvs[:3 * n], self.xvs[3 * n:]
-        self.A, self.gA = e(G), e(G)
         self.P = e(3 * G)
-        self.uat, self.af, self.Fd, self.Fc = e(3 * n), e(n), e(3 * n), e(3 * n)
         self.gxvs, self.gF = e(6 * n), e(3 * n)  # sorted adjoints of x then v
         self.gxs, self.gvs = self.gxvs[:3 * n], self.gxvs[3 * n:]
-        self.guat, self.gaf, self.gmu_i, self.gcd_i = e(3 * n), e(n), e(n), e(n)
+        self.gaf = e(n)
         self.scal = torch.zeros(4, dtype=f64, device=dev)  # L, dL/dmu, dL/dC_d, spare
         self.params = (float(cfg["mu"]), float(cfg["c_drag"]))
+        # the one-call step covers the linear drag without added mass; other
+        # forms run forward stage by stage (they have no reverse)
+        self.staged = bool(cfg.get("drag_model", 0) or cfg.get("vmass", 0))
+        if self.staged:
+            self.A, self.uat, self.af, self.Fd, self.Fc = e(G), e(3 * n), e(n), e(3 * n), e(3 * n)
 
     def set_params(self, mu, c_drag):
         self.params = (float(mu), float(c_drag))
@@ -72,24 +75,26 @@ class Rollout:
         gic.gic_brick_list(c, self.cb, self.ce)  # one brick schedule for the step's brick kernels
         gic.gic_reorder(c, self.order, x.view(3, -1), v, self.r, None, self.xs, self.vs, self.rs, None)
 
-    def _forces(self):
+    def _split(self, xv):
+        return xv[:3 * self.n], xv[3 * self.n:]
+
+    def _step_stages(self, xv, xv_out):
         c = self.ctx
+        self._sorted(*self._split(xv))
         xs = self.xs.view(3, -1)
         gic.gic_p2g_real(c, xs, self.vs, self.rs, self.cb, self.ce, self.A, None)
         gic.gic_g2p(c, xs, self.u, None, self.A, self.uat, self.af)
         gic.gic_drag(c, self.rs, self.vs, self.uat, self.af, self.Fd)
-
-    def _split(self, xv):
-        return xv[:3 * self.n], xv[3 * self.n:]
+        gic.gic_contact_forces(c, xs, self.vs, self.rs, self.cb, self.ce, self.Fc)
+        gic.gic_integrate(c, self.rs, self.Fc, self.Fd, self.xs, self.vs)
+        gic.gic_permute(c, self.order, self.xvs, xv_out, 6, True)
 
     def step(self, xv, xv_out):
         """One step from the state xv = (x, v) (input order) into xv_out."""
-        c = self.ctx
-        self._sorted(*self._split(xv))
-        self._forces()
-        gic.gic_contact_forces(c, self.xs.view(3, -1), self.vs, self.rs, self.cb, self.ce, self.Fc)
-        gic.gic_integrate(c, self.rs, self.Fc, self.Fd, self.xs, self.vs)
-        gic.gic_permute(c, self.order, self.xvs, xv_out, 6, True)
+        if self.staged:
+            return self._step_stages(xv, xv_out)
+        gic.gic_rollout_step(self.ctx, xv, self.r, self.u, xv_out, self.key, self.order, self.cb, self.ce, self.xvs,
+                             self.rs)
 
     def loss(self, xv):
         """L = sum |P|^2 of the momentum grid of the state xv, into self.scal[0]."""
@@ -185,20 +190,8 @@ class Rollout:
                 xs_list.append(xb)
                 xa = xb
             for s in reversed(range(s0, s1)):
-                self._sorted(*self._split(xs_list[s - s0]))
-                self._forces()
-                gic.gic_permute(c, self.order, gxv, self.gxvs, 6, False)
-                xs = self.xs.view(3, -1)
-                gic.gic_integrate_vjp(c, self.rs, self.gxs, self.gvs, self.gF)
-                gic.gic_contact_forces_vjp(c, xs, self.vs, self.rs, self.cb, self.ce, self.gF, self.gxs, self.gvs,
-                                           self.gmu_i)
-                gic.gic_sum(c, self.gmu_i, self.scal[1:2], accumulate=True)
-                gic.gic_drag_vjp(c, self.rs, self.vs, self.uat, self.af, self.gF, self.gvs, self.guat, self.gaf,
-                                 self.gcd_i)
-                gic.gic_sum(c, self.gcd_i, self.scal[2:3], accumulate=True)
-                gic.gic_g2p_vjp(c, xs, self.u, self.A, self.guat, self.gaf, self.cb, self.ce, self.gxs, self.gA)
-                gic.gic_p2g_vjp(c, xs, self.vs, self.rs, self.gA, None, self.gxs, self.gvs)
-                gic.gic_permute(c, self.order, self.gxvs, gxv, 6, True)
+                gic.gic_rollout_step_vjp(c, xs_list[s - s0], self.r, self.u, gxv, self.scal[1:2], self.scal[2:3], self.key,
+                                         self.order, self.cb, self.ce, self.xvs, self.rs, self.gxvs, self.gF, self.gaf)
         return gxv[3 * n:].view(3, n), self.scal[1:2].clone(), self.scal[2:3].clone()
 
 
