@@ -552,10 +552,12 @@ __device__ inline void contact_global(const DevParams &P, int64_t n, const doubl
 //
 // A brick whose shell does not fit in LDS takes the global path.
 constexpr int kHaloCells = 216;
+constexpr int kGroupHalo = (kBrick * kGroup + 2) * (kBrick * kGroup + 2) * (kBrick * kGroup + 2);  // a group's shell
 constexpr int kLdsPartners = 10;
 constexpr int kCand = 4;  // candidates read from LDS before they are tested
 constexpr int kPad = 1;   // empty slots after each cell (256 threads)
 constexpr int shell_pad(int nt) { return nt == 64 ? 0 : kPad; }
+constexpr int kCellMost = 4096;
 constexpr int kCopyRounds = 8;  // shell copy rounds of one slot per thread: cap <= 8 x threads
 
 // Fixed compare-exchange networks sorting 4, 6, 8 and 10 entries (5, 12,
@@ -621,6 +623,16 @@ __device__ inline void lds_list_canonical(uint16_t *col, int m, int64_t q, J &&j
         if (i < m) col[i * NT] = (uint16_t)sl[i];
 }
 
+// Number of a shell's cell (216 around a brick, 1,000 around a group).
+template <bool GROUP>
+struct ShellCell {
+    using type = uint8_t;
+};
+template <>
+struct ShellCell<true> {
+    using type = uint16_t;
+};
+
 // Candidate test of the LDS pass (see above): p = (p, Q) of a slot,
 // m = -2 a, thr = M - b_i.
 __device__ inline bool near_slot(float4 p, float mx, float my, float mz, float thr)
@@ -634,14 +646,19 @@ __device__ inline bool near_slot(float4 p, float mx, float my, float mz, float t
 // exactly 2 r_max), where building a list every step costs more.
 // NT: threads per workgroup; 64 serves beds whose bricks hold at most one
 // granule per lane (no empty slots after the cells there: the lanes of one
-// wave read a slot each).
+// wave read a slot each).  GROUP (dry, no empty slots either): one workgroup
+// per group of bricks and its shell of 10^3 cells, see fill_mode; relative
+// coordinates then lie within 5 cells of the centre (the own granule's within
+// 4), so Q is below 75 cell^2, the sums of the chain below 195, their roundings
+// sum to less than 2^-12.8 cell^2, rounding the positions moves the value by
+// less than 2^-15 and M is 2^-10 cell^2, six times the total.
 // The hits of four candidates are a mask that one loop empties: a branch per
 // candidate took 48 us instead of 44 on 262,144 granules of a wide size
 // distribution, 35 and 40 us instead of 32 and 36 in kMove and kReverse.
 // The wave form's shell array has 16 slots and a sixteenth more than the record
 // (an eighth and 64 of the 256-thread form left 14 waves per CU instead of 18:
-// 1.03 instead of 0.95 ms on 16.8 million granules).
-template <typename T, int KIND, int NT>
+// 1.03 instead of 0.95 ms).
+template <typename T, int KIND, int NT, bool GROUP>
 __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(KIND == kBridge ? 4 : 1)))
 k_contact_lds(DevParams P, int64_t n, const int32_t *__restrict__ bl,
                                                      const int32_t *__restrict__ bcnt, int cap,
@@ -654,21 +671,48 @@ k_contact_lds(DevParams P, int64_t n, const int32_t *__restrict__ bl,
                                                      AdjArgs A)
 {
     constexpr bool CAP = KIND == kBridge;
+    constexpr int kEdge = GROUP ? kBrick * kGroup : kBrick;  // cells of the brick or group along an axis
+    constexpr int S = kEdge + 2, kHaloCells = S * S * S;     // and of its shell
+    using Cell = typename ShellCell<GROUP>::type;
     extern __shared__ float4 smem4[];
     float4 *spos = smem4;                                        // [cap + kCand] (p, Q), see above
-    constexpr int kPad = shell_pad(NT);
+    constexpr int kPad = GROUP ? 0 : shell_pad(NT);
     uint16_t *plist = reinterpret_cast<uint16_t *>(spos + cap + kCand);  // [kLdsPartners][NT] partner slots
-    int32_t *cgb = reinterpret_cast<int32_t *>(plist + kLdsPartners * NT);  // [216] global begin of each shell cell
+    int32_t *cgb = reinterpret_cast<int32_t *>(plist + kLdsPartners * NT);  // [kHaloCells] global begin of each shell cell
     int32_t *s_wave = cgb + kHaloCells;                                    // [4]
-    uint16_t *clo = reinterpret_cast<uint16_t *>(s_wave + 4);              // [216] first slot of each cell
-    uint16_t *cnum = clo + kHaloCells;                                     // [216] granules of each shell cell
-    uint8_t *scell = reinterpret_cast<uint8_t *>(cnum + kHaloCells);         // [cap] shell cell of each slot
+    uint16_t *clo = reinterpret_cast<uint16_t *>(s_wave + 4);              // [kHaloCells] first slot of each cell
+    uint16_t *cnum = clo + kHaloCells;                                     // [kHaloCells] granules of each
+    Cell *scell = reinterpret_cast<Cell *>(cnum + kHaloCells);         // [cap] shell cell of each slot
     const int tid = threadIdx.x;
     if (hclr && blockIdx.x == 0 && tid == 0) *hclr = 0;  // the next recording call's record
     if (not_mine(only, kWaveFill, n, bcnt)) return;
-    int64_t slot;
-    const int64_t b = brick_slot_of_block(bl, bcnt, slot);
-    if (b < 0) return;
+    constexpr int kBricks = GROUP ? kGroup * kGroup * kGroup : 1;
+    __shared__ int32_t s_beg[kBricks], s_end[kBricks];  // granules of the bricks
+    int64_t slot = 0, b;  // the brick's place in the list, and the (first) brick
+    if constexpr (GROUP) {
+        static_assert(KIND == kForce, "leave() is of one brick");
+        const int64_t grp = group_of_block(P);
+        if (grp < 0) return;
+        b = brick_of_group(P, grp, 0);
+        const int64_t t = tid < kBricks ? brick_of_group(P, grp, tid) : -1;
+        int32_t beg = 0, end = 0;
+        if (t >= 0) {
+            beg = cb[t * kBrickCells];
+            end = ce[t * kBrickCells + kBrickCells - 1];
+            clip_range(n, beg, end);
+        }
+        if (tid < kBricks) {
+            s_beg[tid] = beg;
+            s_end[tid] = end;
+        }
+        if (!__syncthreads_or(beg < end)) return;
+    } else {
+        b = brick_slot_of_block(bl, bcnt, slot);
+        if (b < 0) return;
+    }
+    // the bricks of a group are dealt to the waves
+    constexpr int kStep = GROUP ? 64 : NT, kWaves = GROUP ? NT / 64 : 1;
+    const int w0 = GROUP ? tid >> 6 : 0;
     double tot[3] = {0.0, 0.0, 0.0};  // kReverse: dL/dmu, dL/dC_d, largest |g_alpha_f| of the thread
     auto leave = [&]() {              // kReverse: those of the brick
         if constexpr (KIND == kReverse) {
@@ -698,13 +742,17 @@ k_contact_lds(DevParams P, int64_t n, const int32_t *__restrict__ bl,
     const int32_t bc[3] = {(int32_t)(b % P.nb[0]), (int32_t)((b / P.nb[0]) % P.nb[1]),
                            (int32_t)(b / ((int64_t)P.nb[0] * P.nb[1]))};
     const int32_t c0[3] = {bc[0] * kBrick - 1, bc[1] * kBrick - 1, bc[2] * kBrick - 1};  // shell origin cell
-    int32_t gb = cb[b * kBrickCells], ge = ce[b * kBrickCells + kBrickCells - 1];
-    clip_range(n, gb, ge);
-    if (ge <= gb) {
-        leave();
-        return;
+    int32_t gb = 0, ge = 0;
+    if constexpr (!GROUP) {
+        gb = cb[b * kBrickCells];
+        ge = ce[b * kBrickCells + kBrickCells - 1];
+        clip_range(n, gb, ge);
+        if (ge <= gb) {
+            leave();
+            return;
+        }
     }
-    const double o[3] = {(c0[0] + 3) * P.cell, (c0[1] + 3) * P.cell, (c0[2] + 3) * P.cell};  // brick centre
+    const double o[3] = {(c0[0] + S / 2) * P.cell, (c0[1] + S / 2) * P.cell, (c0[2] + S / 2) * P.cell};  // its centre
     // ---- shell cells: counts, then slots (count + kPad each) by a scan;
     // thread t takes cells t, t + NT, ...
     constexpr int kCellRounds = (kHaloCells + NT - 1) / NT;
@@ -714,13 +762,13 @@ k_contact_lds(DevParams P, int64_t n, const int32_t *__restrict__ bl,
         const int c = tid + w * NT;
         num[w] = gbeg[w] = 0;
         if (c >= kHaloCells) continue;
-        const int32_t cx = c0[0] + c % 6, cy = c0[1] + (c / 6) % 6, cz = c0[2] + c / 36;
+        const int32_t cx = c0[0] + c % S, cy = c0[1] + (c / S) % S, cz = c0[2] + c / (S * S);
         if (cx >= 0 && cy >= 0 && cz >= 0 && cx < P.nc[0] && cy < P.nc[1] && cz < P.nc[2]) {
             const uint32_t k = key_of_cell(P, cx, cy, cz);
             int32_t e = ce[k];
             gbeg[w] = cb[k];
             clip_range(n, gbeg[w], e);
-            num[w] = e - gbeg[w];
+            num[w] = e - gbeg[w] < kCellMost ? e - gbeg[w] : kCellMost;  // past every capacity: the sum cannot wrap
         }
     }
     int32_t H = 0;  // slots of the shell
@@ -745,18 +793,21 @@ k_contact_lds(DevParams P, int64_t n, const int32_t *__restrict__ bl,
                 if (t < wave) first[w] += s_wave[t];
                 H += s_wave[t];
             }
+            if (kCellRounds > 1) __syncthreads();
         }
     }
     // the largest shell (an atomic only when this one is larger than the record)
     if (hmax && tid == 0) {
-        const int32_t Hr = H + (1 - kPad) * kHaloCells;  // recorded with the pads of the 256-thread form
+        // recorded as a brick's shell with the pads of the 256-thread form
+        const int32_t Hr = GROUP ? (H * 216 + kHaloCells - 1) / kHaloCells + 216 : H + (1 - kPad) * kHaloCells;
         if (Hr > __hip_atomic_load(hmax, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(hmax, Hr);
     }
     if (H > cap) {  // shell too large for LDS: global candidate path for this brick
         __syncthreads();  // every thread has read s_wave (the slots alias nothing else in use)
         int32_t *glist = reinterpret_cast<int32_t *>(smem4);  // the slot arrays are unused on this path
-        for (int64_t q = gb + tid; q < ge; q += NT)
-            contact_global<T, KIND, NT>(P, n, x, v, r, cb, ce, q, glist, tid, sr, held, F, ncont, err, A, tot);
+        for (int w = w0; w < kBricks; w += kWaves)
+            for (int64_t q = (int64_t)(GROUP ? s_beg[w] : gb) + tid % kStep; q < (GROUP ? s_end[w] : ge); q += kStep)
+                contact_global<T, KIND, NT>(P, n, x, v, r, cb, ce, q, glist, tid, sr, held, F, ncont, err, A, tot);
         leave();
         return;
     }
@@ -768,7 +819,7 @@ k_contact_lds(DevParams P, int64_t n, const int32_t *__restrict__ bl,
         clo[c] = (uint16_t)first[w];
         cnum[c] = (uint16_t)num[w];
         cgb[c] = gbeg[w];
-        for (int32_t k = first[w]; k < first[w] + num[w] + kPad; ++k) scell[k] = (uint8_t)c;
+        for (int32_t k = first[w]; k < first[w] + num[w] + kPad; ++k) scell[k] = (Cell)c;
     }
     __syncthreads();
     // with liquid bridges the candidate pass looks d_r further: each radius
@@ -815,14 +866,14 @@ k_contact_lds(DevParams P, int64_t n, const int32_t *__restrict__ bl,
         }
     }
     __syncthreads();
-    const float M = (float)(P.cell * P.cell * (1.0 / 4096.0));
+    const float M = (float)(P.cell * P.cell * (GROUP ? 1.0 / 1024.0 : 1.0 / 4096.0));
     // ---- granules of the brick, one thread each: the listed partners are
     // evaluated in canonical order, the order of the dry contact's
     // neighbour list, so a bed without bridges gives the dry contact's bits
     constexpr int L = 1;
     constexpr int sub = 0;
-    for (int64_t qb = gb; qb < ge; qb += NT) {  // same trip count in every lane
-        const int64_t q = qb + tid;
+    auto granules = [&](int64_t qb, int32_t ge) {  // called by whole waves
+        const int64_t q = qb + tid % kStep;
         const bool live = q < ge;
         T acc[sums_of(KIND)] = {};
         double gi[3] = {0.0, 0.0, 0.0};
@@ -842,13 +893,13 @@ k_contact_lds(DevParams P, int64_t n, const int32_t *__restrict__ bl,
             const double Rs = (ri + P.r_max + (CAP ? P.dr_max : 0.0)) * P.search_scale;
             int32_t lo[3], hi[3], ca[3];
             for (int a = 0; a < 3; ++a) {
-                ca[a] = cell_coord(xi[a], P.inv_cell, P.nc[a]) - c0[a];  // in [1, 4]: q lies in the brick
+                ca[a] = cell_coord(xi[a], P.inv_cell, P.nc[a]) - c0[a];  // in [1, kEdge]: q lies in the brick
                 search_range(P, xi[a], Rs, P.nc[a], lo[a], hi[a]);
                 lo[a] -= c0[a];
                 hi[a] -= c0[a];
             }
             // the cell ranges do not match the positions (not the ranges of this state's sort)
-            bad = ca[0] < 1 || ca[0] > 4 || ca[1] < 1 || ca[1] > 4 || ca[2] < 1 || ca[2] > 4;
+            bad = ca[0] < 1 || ca[0] > kEdge || ca[1] < 1 || ca[1] > kEdge || ca[2] < 1 || ca[2] > kEdge;
             if constexpr (pulls(KIND))
                 for (int a = 0; a < 3; ++a) gi[a] = A.gF[a * n + q];
             if (bad && pulls(KIND)) {
@@ -869,7 +920,7 @@ k_contact_lds(DevParams P, int64_t n, const int32_t *__restrict__ bl,
                 raise_error(err, kErrRange, q);
             } else {
                 // slot of q itself, skipped by the candidate pass (the exact test skips q too)
-                const int own = (ca[2] * 6 + ca[1]) * 6 + ca[0];
+                const int own = (ca[2] * S + ca[1]) * S + ca[0];
                 const int32_t qoff = (int32_t)(q - cgb[own]);
                 const int32_t kself = qoff >= 0 && qoff < cnum[own] ? clo[own] + qoff : -1;
                 // this lane's rows (hz, hy) of the search box, f(first cell of the row)
@@ -880,7 +931,7 @@ k_contact_lds(DevParams P, int64_t n, const int32_t *__restrict__ bl,
                     int hz = lo[2], hy = lo[1] + sub;
                     while (hy > hi[1]) { hy -= ny; ++hz; }
                     for (int row = sub; row < nrow; row += L) {
-                        f((hz * 6 + hy) * 6);
+                        f((hz * S + hy) * S);
                         hy += L;
                         while (hy > hi[1]) { hy -= ny; ++hz; }
                     }
@@ -952,10 +1003,17 @@ k_contact_lds(DevParams P, int64_t n, const int32_t *__restrict__ bl,
             if (bad && (KIND == kForce || KIND == kBridge)) {  // no walls either
                 F[q] = F[n + q] = F[2 * n + q] = (T)0;
                 if (ncont) ncont[q] = 0;
-                continue;
+                return;
             }
             finish_granule<T, KIND>(P, n, q, xi, vi, ri, mi, gi, acc, nc, F, ncont, A, tot);
         }
+    };
+    for (int w = w0; w < kBricks; w += kWaves) {
+        if constexpr (GROUP) {
+            gb = s_beg[w];
+            ge = s_end[w];
+        }
+        for (int64_t qb = gb; qb < ge; qb += kStep) granules(qb, ge);
     }
     leave();
 }
@@ -1296,10 +1354,12 @@ __global__ void __launch_bounds__(kListThreads) k_contact_list(DevParams P, int6
 
 // LDS bytes of the staged contact kernel of nt threads for a shell capacity of
 // cap granules.
-static size_t contact_lds_bytes(int cap, int nt)
+static size_t contact_lds_bytes(int cap, int nt, bool group = false)
 {
-    const size_t b = (size_t)(cap + kCand) * sizeof(float4) + (size_t)cap + sizeof(uint16_t) * kLdsPartners * nt +
-                     (sizeof(int32_t) + 2 * sizeof(uint16_t)) * kHaloCells + 4 * sizeof(int32_t);
+    const size_t cells = group ? kGroupHalo : kHaloCells;
+    const size_t b = (size_t)(cap + kCand) * sizeof(float4) + (size_t)cap * (group ? 2 : 1) +
+                     sizeof(uint16_t) * kLdsPartners * nt + (sizeof(int32_t) + 2 * sizeof(uint16_t)) * cells +
+                     4 * sizeof(int32_t);
     const size_t fallback = sizeof(int32_t) * kMaxPartners * nt;  // list of the global path, aliasing the slots
     return b > fallback ? b : fallback;
 }
@@ -1326,7 +1386,7 @@ static void contact_kernel(const DevParams &P, int64_t n, const double *x, const
                            const AdjArgs &A)
 {
     const int64_t nbricks = (int64_t)P.nb[0] * P.nb[1] * P.nb[2];
-    k_contact_lds<T, KIND, NT><<<brick_grid(nbricks), NT, contact_lds_bytes(cap, NT), s>>>(
+    k_contact_lds<T, KIND, NT, false><<<brick_grid(nbricks), NT, contact_lds_bytes(cap, NT), s>>>(
         P, n, B.list, B.count, cap, x, v, r, cb, ce, sr, held, F, ncont, err, hm, hc, only, A);
 }
 
@@ -1341,8 +1401,22 @@ static hipError_t contact_launch(const DevParams &P, int64_t n, const double *x,
     const bool copy = record_copy(ss);  // only these calls record (the stores contend)
     int32_t *hm = copy ? ss->dev + ss->par : nullptr;
     int32_t *hc = copy ? ss->dev + (ss->par ^ 1) : nullptr;
-    const FillMode mode = fill_mode(P, n, B);
-    if (mode != kFillBlock) {
+    FillMode mode = fill_mode(P, n, B, kGroupShells);
+    if (mode == kFillGroup) {
+        // the recorded shell granules, for the cells of a group's shell
+        const int seen = ss && ss->host ? *(volatile const int32_t *)ss->host - kHaloCells * kPad : 0;
+        const int64_t all = ((int64_t)seen * kGroupHalo + kHaloCells - 1) / kHaloCells;
+        const int64_t want = seen <= 0 ? kCopyRounds * kGroupNT : (all + all / 16 + 32 + 7) / 8 * 8;
+        const size_t lds = contact_lds_bytes((int)want, kGroupNT, true);
+        mode = kFillWave;
+        if constexpr (KIND == kForce)
+            if (want <= kCopyRounds * kGroupNT) {
+                mode = kFillGroup;
+                k_contact_lds<T, KIND, kGroupNT, true><<<group_grid(P), kGroupNT, lds, s>>>(
+                    P, n, B.list, B.count, (int)want, x, v, r, cb, ce, sr, held, F, ncont, err, hm, hc, 0, A);
+            }
+    }
+    if (mode == kFillWave || mode == kFillBoth) {
         // no empty slots in the wave's shell; without a record, room for the
         // 216 cells of a shell at 1.7 granules each
         const int seen = ss && ss->host ? *(volatile const int32_t *)ss->host - kHaloCells * kPad : 0;

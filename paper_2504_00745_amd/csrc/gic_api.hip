@@ -158,9 +158,9 @@ bool tiles_assemble(const gic_params *p)
     return m4 > 4.0;
 }
 
-int tile_edge(const gic_params *p)
+int tile_edge(const gic_params *p, int bricks = 1)
 {
-    const double m4 = (double)kBrick * p->cell / p->dx;
+    const double m4 = (double)(kBrick * bricks) * p->cell / p->dx;
     const double r = floor(m4 + 0.5);
     if (fabs(m4 - r) < 1e-9 * (r > 1.0 ? r : 1.0)) return (int)r + 2;
     return (int)ceil(m4) + 3;
@@ -174,10 +174,12 @@ DevParams derive(const gic_params *p)
         d.n[a] = p->n[a];
         d.nc[a] = p->nc[a];
         d.nb[a] = (p->nc[a] + kBrick - 1) / kBrick;
+        d.ng[a] = (d.nb[a] + kGroup - 1) / kGroup;
         d.L[a] = (double)p->n[a] * p->dx;
         d.g[a] = p->g[a];
     }
     d.tile = tile_edge(p);
+    d.gtile = tile_edge(p, kGroup);
     d.G = (int64_t)p->n[0] * p->n[1] * p->n[2];
     d.dx = p->dx;
     d.inv_dx = 1.0 / p->dx;
@@ -413,14 +415,22 @@ gic_status gic_create(const gic_params *p, int64_t n_max, gic_ctx **out)
         const int64_t slots = c->bricks.nbricks < nn ? c->bricks.nbricks : nn;
         const size_t bytes = (size_t)(slots > 0 ? slots : 1) * 4 * E * E * E * sizeof(unsigned long long);
         const size_t ncov = 4 * ((size_t)p->n[0] + p->n[1] + p->n[2]);
+        // the tiles of the brick groups take the same room, if they fit
+        const int64_t F = c->dp.gtile, groups = (int64_t)c->dp.ng[0] * c->dp.ng[1] * c->dp.ng[2];
+        const bool grouped = F * F * F * 4 * (int64_t)sizeof(double) <= 65536 && groups * F * F * F <= slots * E * E * E;
         int32_t *cov = nullptr;
         if (bytes <= ((size_t)8 << 30) && hipMalloc(&c->p2gs.tiles, bytes) == hipSuccess &&
-            hipMalloc(&cov, sizeof(int32_t) * ncov) == hipSuccess) {
-            int32_t *h = new int32_t[ncov];
-            p2g_cover_table(c->dp, h);
-            ok &= hipMemcpy(cov, h, sizeof(int32_t) * ncov, hipMemcpyHostToDevice) == hipSuccess;
+            hipMalloc(&cov, sizeof(int32_t) * 2 * ncov) == hipSuccess) {
+            int32_t *h = new int32_t[2 * ncov];
+            p2g_cover_table(c->dp, 1, h);
+            p2g_cover_table(c->dp, kGroup, h + ncov);
+            ok &= hipMemcpy(cov, h, sizeof(int32_t) * 2 * ncov, hipMemcpyHostToDevice) == hipSuccess;
             delete[] h;
             c->p2gs.cover = cov;
+            if (grouped && hipMalloc(&c->p2gs.gslot, sizeof(int32_t) * groups) == hipSuccess)
+                c->p2gs.gcover = cov + ncov;
+            else
+                (void)hipGetLastError();
             // live flags: without them every assembly writes every node
             const size_t nlive = (size_t)p->n[1] * p->n[2] * (((size_t)p->n[0] + 3) / 4);
             if (hipMalloc(&c->p2gs.live, nlive) != hipSuccess || hipMemset(c->p2gs.live, 0, nlive) != hipSuccess) {
@@ -496,6 +506,7 @@ gic_status gic_destroy(gic_ctx *c)
     (void)hipFree(c->p2gs.tiles);
     (void)hipFree(const_cast<int32_t *>(c->p2gs.cover));
     (void)hipFree(c->p2gs.live);
+    (void)hipFree(c->p2gs.gslot);
     (void)hipFree(c->esc_n2);
     (void)hipFree(c->shell.dev);
     (void)hipHostFree(c->shell.host);
@@ -822,6 +833,7 @@ static gic_status step_integrate_p2g(gic_ctx *c, int64_t n, double *x, double *v
     if (brick_list(c, n, cell_begin, cell_end, s) != hipSuccess) return GIC_E_HIP;
     stage_mark(c, 5, s);
     P2GStore st = c->p2gs;
+    p2g_store_mode(c->dp, n, c->bricks, st);
     st.full = c->live_ok && c->live_a == alpha_fx && c->live_m == mom_fx ? 0 : 1;
     st.esc_n = c->esc_n2 + c->esc_par;
     uint32_t *next = c->esc_n2 + (c->esc_par ^ 1);

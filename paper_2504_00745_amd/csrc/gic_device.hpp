@@ -123,6 +123,8 @@ struct DevParams {
     int32_t nc[3];      // neighbour cells per axis
     int32_t nb[3];      // bricks per axis
     int32_t tile;       // P2G LDS tile edge (nodes)
+    int32_t ng[3];      // brick groups (kGroup^3 bricks) per axis
+    int32_t gtile;      // node tile edge of a group
     int64_t G;          // nodes
     double dx, inv_dx, inv_vcell;
     double cell, inv_cell;
@@ -143,6 +145,32 @@ struct DevParams {
     double sigma, vbridge, sr_peak;  // surface tension, bridge volume / granule volume, peak of Gamma
     double dr_max;                   // rupture distance of the largest pair (search reach)
 };
+
+// Kernels over groups of kGroup^3 bricks, one workgroup per group of the box:
+// the XCDs take the groups' x-rows in turn (a bed fills part of the box, so
+// contiguous eighths would leave XCDs idle; the groups of a row, neighbours in
+// the grid, share an L2).  group_grid(P) workgroups; group_of_block gives the
+// group or -1.
+constexpr int kGroup = 2;
+
+inline unsigned group_grid(const DevParams &P) { return xcd_grid((int64_t)P.ng[1] * P.ng[2]) * (unsigned)P.ng[0]; }
+
+__device__ inline int64_t group_of_block(const DevParams &P)
+{
+    const uint32_t j = blockIdx.x / kXcds;  // in the XCD's order
+    const int64_t row = (int64_t)(j / P.ng[0]) * kXcds + blockIdx.x % kXcds;
+    return row < (int64_t)P.ng[1] * P.ng[2] ? row * P.ng[0] + j % P.ng[0] : -1;
+}
+
+// Brick w (0 .. kGroup^3 - 1) of a group, or -1 outside the box.
+__device__ inline int64_t brick_of_group(const DevParams &P, int64_t g, int w)
+{
+    const int32_t bx = (int32_t)(g % P.ng[0]) * kGroup + w % kGroup;
+    const int32_t by = (int32_t)((g / P.ng[0]) % P.ng[1]) * kGroup + (w / kGroup) % kGroup;
+    const int32_t bz = (int32_t)(g / ((int64_t)P.ng[0] * P.ng[1])) * kGroup + w / (kGroup * kGroup);
+    if (bx >= P.nb[0] || by >= P.nb[1] || bz >= P.nb[2]) return -1;
+    return ((int64_t)bz * P.nb[1] + by) * P.nb[0] + bx;
+}
 
 // Latch the first error: code and granule index.
 __device__ inline void raise_error(int64_t *err, int code, int64_t idx)

@@ -139,26 +139,47 @@ inline BrickFill brick_fill(const DevParams &P, int64_t n, const BrickList &B)
     const double e = 0.5 * P.cell / P.r_max;
     return {kBrickCells * ((e * e) * e), false};
 }
-// Whether the gather, the direct contact and the direct P2G run one wave per
-// brick (workgroups of 64 threads) instead of 256 threads.  A 256-thread
-// workgroup leaves three of its four waves idle when a brick holds about one
-// granule per lane of a wave, and the chip holds a quarter of the bricks:
-// 16.8 million granules at 64 a brick take 0.89, 1.04 and 0.92 ms instead of
-// 1.25, 1.88 and 1.70 (gather, contact, P2G, FP32); at 205 a brick the wave
-// loops over its brick and takes 25 and 32 us instead of 19 and 26 (gather,
-// P2G).  With fewer bricks than the chip holds of the larger workgroups (1,024)
-// more threads per brick are faster (216 bricks: 7.8 and 7.2 against 6.4 and
-// 6.5 us; 1,728 bricks: 11.0 and 12.8 against 11.9 and 15.4).
+// How the gather, the direct contact and the direct P2G run.
+//
+// One wave per brick (workgroups of 64 threads) instead of 256 threads: a
+// 256-thread workgroup leaves three of its four waves idle when a brick holds
+// about one granule per lane of a wave, and the chip holds a quarter of the
+// bricks: 16.8 million granules at 64 a brick take 0.88, 1.04 and 0.92 ms
+// instead of 1.25, 1.88 and 1.70 (gather, contact, P2G, FP32); at 205 a brick
+// the wave loops over its brick and takes 25 and 32 us instead of 19 and 26
+// (gather, P2G).  With fewer bricks than the chip holds of the larger workgroups
+// (1,024) more threads per brick are faster (216 bricks: 7.8 and 7.2 against
+// 6.4 and 6.5 us; 1,728 bricks: 11.0 and 12.8 against 11.9 and 15.4).
+//
+// A workgroup of kGroupNT threads per group of 2x2x2 bricks, a wave per brick
+// and two bricks per wave, when there are many more bricks: eight tiles share
+// their halos (10^3 nodes instead of 8 x 6^3 at a cell of one node spacing), so
+// the tiles take 0.58 of the bytes, and so do the cells of eight shells.  The
+// same bed, one wave per brick against groups: gather 0.88 and 0.62 ms, contact
+// 0.94 and 0.87, P2G 0.90 and 0.68, assembly of the tiles 0.96 and 0.47.  (A
+// wave per brick, groups of 512 threads: 0.79, 1.08, 0.91, 0.46: two such
+// workgroups fill a CU and wait for each other's loads.)  From 4,096 bricks for
+// the node tiles (gather, P2G and assembly there: 15.2 + 17.8 + 10.6 against
+// 15.8 + 17.7 + 14.7 us); the contact and the FP64 gather, whose workgroups
+// hold more registers and LDS, from 16,384 (8,820 bricks: 42 against 35 us and
+// 40 against 34; 13,824: 50 against 51; 18,432: 78.4 against 78.0; 65,536: 231
+// against 261 and 226 against 257).
+//
 // kFillBoth: not known yet (a first call) and plausible: both kernels are
 // launched and the device's count of occupied bricks picks one.
 constexpr int64_t kWaveFill = 80;
 constexpr int64_t kWaveBricks = 1024;
-enum FillMode { kFillBlock = 0, kFillWave = 1, kFillBoth = 2 };
-inline FillMode fill_mode(const DevParams &P, int64_t n, const BrickList &B)
+constexpr int64_t kGroupBricks = 4096;
+constexpr int64_t kGroupShells = 16384;
+constexpr int kGroupNT = 256;
+enum FillMode { kFillBlock = 0, kFillWave = 1, kFillBoth = 2, kFillGroup = 3 };
+// least: occupied bricks from which the caller takes groups.
+inline FillMode fill_mode(const DevParams &P, int64_t n, const BrickList &B, int64_t least)
 {
     const BrickFill f = brick_fill(P, n, B);
     if (f.avg > kWaveFill || n < kWaveBricks * kBrickCells) return kFillBlock;
-    return f.known ? kFillWave : kFillBoth;
+    if (!f.known) return kFillBoth;
+    return (double)n >= (double)least * f.avg ? kFillGroup : kFillWave;
 }
 template <typename T>
 hipError_t launch_contact(const DevParams &P, int64_t n, const double *x, const double *v, const double *r,
@@ -201,12 +222,18 @@ struct P2GStore {
     // tile reached the segment at the last assembly or a listed granule was
     // deposited there since; NULL: every node is written
     uint8_t *live;
+    const int32_t *gcover;  // cover of the brick groups' tiles, NULL: no room for those
+    int32_t *gslot;         // [groups] the group's tile (its number), -1: no granules
+    // set by p2g_store_mode for both launches of a call:
+    bool direct;            // the direct kernel, in mode (kFillGroup: the tiles are the groups'), or the run kernel
+    FillMode mode;
     int full;  // 1: write every node (the grids hold no earlier assembly's values)
 };
 // The table P2GStore::cover for the parameters P (host; 4 (n0 + n1 + n2)
 // int32): for node i of axis a, at 4 (n0 + ... + n_{a-1} + i), the bricks
 // along the axis whose tile holds the node, with the node's offset in it.
-void p2g_cover_table(const DevParams &P, int32_t *out);
+// (edge kGroup: of the brick groups and their tiles.)
+void p2g_cover_table(const DevParams &P, int edge, int32_t *out);
 // Integrate + P2G of the stepping path (dry, alpha and momentum) in two
 // launches: launch_integrate_p2g_store moves the granules and stores each
 // occupied brick's tile (listing the granules whose stencil left it);
@@ -216,6 +243,7 @@ void p2g_cover_table(const DevParams &P, int32_t *out);
 // With st.live and !st.full the grids hold the previous assembly's result
 // (and its deposits): segments that no tile reaches now and that were not
 // live are zero already and are not written again.
+void p2g_store_mode(const DevParams &P, int64_t n, const BrickList &B, P2GStore &st);
 template <typename T>
 hipError_t launch_integrate_p2g_store(const DevParams &P, int64_t n, int64_t K, double *x, double *v,
                                       const double *r, const T *Fc, const T *Fd, const int32_t *cb,

@@ -86,7 +86,7 @@ __device__ inline void g2p_sample_tile(const Stencil &s, const V4 *__restrict__ 
 // The second record is read in place of seven scalar reads per node, and the
 // first granule's state is fetched before the tile: a 1.05 million granule
 // column 73 -> 50 us (FP32), 0.52 million wet granules 48 -> 29 us.
-template <typename T, bool FLUID, int NT>
+template <typename T, bool FLUID, int NT, bool GROUP>
 __global__ void __launch_bounds__(NT) k_gather(DevParams P, int64_t n, const int32_t *__restrict__ bl,
                                                const int32_t *__restrict__ bcnt, const int32_t *__restrict__ order,
                                                const double *__restrict__ x, const double *__restrict__ v,
@@ -102,12 +102,39 @@ __global__ void __launch_bounds__(NT) k_gather(DevParams P, int64_t n, const int
     using V4 = typename Node4<T>::type;
     extern __shared__ double smem_d[];
     if (not_mine(only, kWaveFill, n, bcnt)) return;
-    const int64_t b = brick_of_block(bl, bcnt);
-    if (b < 0) return;
-    int32_t gb = cb[b * kBrickCells], ge = ce[b * kBrickCells + kBrickCells - 1];
-    clip_range(n, gb, ge);
-    if (ge <= gb) return;
-    const int E = P.tile, E3 = E * E * E;
+    constexpr int kBricks = GROUP ? kGroup * kGroup * kGroup : 1;
+    __shared__ int32_t s_beg[kBricks], s_end[kBricks];  // GROUP: its bricks' granules
+    const int tid = threadIdx.x;
+    int64_t b;             // the tile's (first) brick
+    int32_t gb = 0, ge = 0;
+    if (GROUP) {
+        const int64_t grp = group_of_block(P);
+        if (grp < 0) return;
+        b = brick_of_group(P, grp, 0);
+        const int64_t t = tid < kBricks ? brick_of_group(P, grp, tid) : -1;
+        if (t >= 0) {
+            gb = cb[t * kBrickCells];
+            ge = ce[t * kBrickCells + kBrickCells - 1];
+            clip_range(n, gb, ge);
+        }
+        if (tid < kBricks) {
+            s_beg[tid] = gb;
+            s_end[tid] = ge;
+        }
+        if (!__syncthreads_or(gb < ge)) return;
+        gb = s_beg[tid >> 6];
+        ge = s_end[tid >> 6];
+    } else {
+        b = brick_of_block(bl, bcnt);
+        if (b < 0) return;
+        gb = cb[b * kBrickCells];
+        ge = ce[b * kBrickCells + kBrickCells - 1];
+        clip_range(n, gb, ge);
+        if (ge <= gb) return;
+    }
+    constexpr int kStep = GROUP ? 64 : NT;  // threads on a brick
+    const int64_t q0 = (int64_t)gb + tid % kStep;  // the thread's first granule
+    const int E = GROUP ? P.gtile : P.tile, E3 = E * E * E;
     const int64_t G = P.G;
     V4 *su = reinterpret_cast<V4 *>(smem_d);                   // [E3]: u_x, u_y, u_z, clamped alpha
     Node3<T> *se = reinterpret_cast<Node3<T> *>(su + E3);      // [E3]: e (FLUID)
@@ -138,7 +165,6 @@ __global__ void __launch_bounds__(NT) k_gather(DevParams P, int64_t n, const int
         if (ido) idq = id[s];
         if (FLUID && held) hq = held[s];
     };
-    const int64_t q0 = gb + threadIdx.x;
     if (q0 < ge) fetch(q0);
     for (int k = threadIdx.x; k < E3; k += NT) {
         const int32_t i = o[0] + k % E, j = o[1] + (k / E) % E, l = o[2] + k / (E * E);
@@ -159,9 +185,9 @@ __global__ void __launch_bounds__(NT) k_gather(DevParams P, int64_t n, const int
         }
     }
     __syncthreads();
-    for (int64_t q = q0; q < ge; q += NT) {
+    auto gather = [&](int64_t q) {
         if (q != q0) fetch(q);
-        if ((uint64_t)s >= (uint64_t)n) continue;  // not a permutation of [0, n): position q left untouched
+        if ((uint64_t)s >= (uint64_t)n) return;  // not a permutation of [0, n): position q left untouched
         for (int a = 0; a < 3; ++a) {
             xo[a * n + q] = xa[a];
             vo[a * n + q] = va[a];
@@ -232,7 +258,11 @@ __global__ void __launch_bounds__(NT) k_gather(DevParams P, int64_t n, const int
             uat[2 * n + q] = ua[2];
         }
         if (af) af[q] = a;
-    }
+    };
+    for (int64_t q = q0; q < ge; q += kStep) gather(q);
+    if (GROUP)
+        for (int w = (tid >> 6) + NT / 64; w < kBricks; w += NT / 64)
+            for (int64_t q = (int64_t)s_beg[w] + (tid & 63); q < s_end[w]; q += 64) gather(q);
 }
 
 // Threads per workgroup: see fill_mode.
@@ -245,14 +275,18 @@ hipError_t launch_gather(const DevParams &P, int64_t n, int64_t K, const int32_t
 {
     if (n == 0) return hipSuccess;
     const unsigned grid = brick_grid(K / kBrickCells);
-    const size_t E3 = (size_t)P.tile * P.tile * P.tile;
-    const size_t lds = sizeof(T) * (FLUID ? 7 : 4) * E3;
-#define GIC_GATHER(NT, ONLY)                                                                                       \
-    k_gather<T, FLUID, NT><<<grid, NT, lds, s>>>(P, n, B.list, B.count, order, x, v, r, id, xo, vo, ro, ido, u, afx, \
+    const size_t node = sizeof(T) * (FLUID ? 7 : 4);
+    const size_t lds = node * P.tile * P.tile * P.tile, glds = node * P.gtile * P.gtile * P.gtile;
+    constexpr int kGatherNT = sizeof(T) == 4 ? kGroupNT : 128;
+    FillMode mode = fill_mode(P, n, B, sizeof(T) == 4 ? kGroupBricks : kGroupShells);
+    // the FP64 fluid tile of a group leaves a CU two workgroups
+    if (mode == kFillGroup && ((FLUID && sizeof(T) == 8) || glds > 65536)) mode = kFillWave;
+#define GIC_GATHER(NT, GROUP, ONLY)                                                                                  \
+    k_gather<T, FLUID, NT, GROUP><<<GROUP ? group_grid(P) : grid, NT, GROUP ? glds : lds, s>>>(P, n, B.list, B.count, order, x, v, r, id, xo, vo, ro, ido, u, afx, \
                                                  gp, fa, cb, ce, Ff, uat, af, held, heldo, ONLY)
-    const FillMode mode = fill_mode(P, n, B);
-    if (mode != kFillBlock) GIC_GATHER(64, mode == kFillBoth ? 1 : 0);
-    if (mode != kFillWave) GIC_GATHER(256, mode == kFillBoth ? 2 : 0);
+    if (mode == kFillGroup) GIC_GATHER(kGatherNT, true, 0);
+    if (mode == kFillWave || mode == kFillBoth) GIC_GATHER(64, false, mode == kFillBoth ? 1 : 0);
+    if (mode == kFillBlock || mode == kFillBoth) GIC_GATHER(256, false, mode == kFillBoth ? 2 : 0);
 #undef GIC_GATHER
     return hipGetLastError();
 }

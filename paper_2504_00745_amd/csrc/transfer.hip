@@ -383,7 +383,9 @@ __global__ void __launch_bounds__(kP2GThreads) __attribute__((amdgpu_waves_per_e
 // and the rounding (a fused multiply-add and two integer operations per node
 // and channel).  A stencil plane's products at a time are in registers (105,
 // four waves per SIMD; with all 27 nodes unrolled 191 and two).
-template <typename T, int NT>
+// GROUP: one tile for a group of bricks (see fill_mode), a wave per brick and
+// two bricks per wave.
+template <typename T, int NT, bool GROUP>
 __global__ void __launch_bounds__(NT) k_p2g_direct(DevParams P, int64_t n, const int32_t *__restrict__ bl,
                                                    const int32_t *__restrict__ bcnt, double *x, double *v,
                                                    const double *__restrict__ r, const T *__restrict__ Fc,
@@ -393,20 +395,39 @@ __global__ void __launch_bounds__(NT) k_p2g_direct(DevParams P, int64_t n, const
 #pragma clang fp contract(off)
     constexpr int NCH = 4;
     extern __shared__ unsigned long long tile[];
+    __shared__ int32_t s_beg[kGroup * kGroup * kGroup], s_end[kGroup * kGroup * kGroup];  // GROUP: its bricks' granules
     if (not_mine(only, kWaveFill, n, bcnt)) return;
-    int64_t slot;
-    const int64_t b = brick_slot_of_block(bl, bcnt, slot);
-    if (b < 0) return;
-    int32_t beg = cb[b * kBrickCells], end = ce[b * kBrickCells + kBrickCells - 1];
-    clip_range(n, beg, end);
-    const int E = P.tile;
-    const int E3 = E * E * E;
     const int tid = threadIdx.x;
+    int64_t slot, b;  // the tile's, and its (first) brick
+    if (GROUP) {
+        slot = group_of_block(P);
+        if (slot < 0) return;
+        b = brick_of_group(P, slot, 0);
+        int32_t beg = 0, end = 0;
+        const int64_t t = tid < kGroup * kGroup * kGroup ? brick_of_group(P, slot, tid) : -1;
+        if (t >= 0) {
+            beg = cb[t * kBrickCells];
+            end = ce[t * kBrickCells + kBrickCells - 1];
+            clip_range(n, beg, end);
+        }
+        if (tid < kGroup * kGroup * kGroup) {
+            s_beg[tid] = beg;
+            s_end[tid] = end;
+        }
+        const int any = __syncthreads_or(beg < end);
+        if (tid == 0) st.gslot[slot] = any ? (int32_t)slot : -1;
+        if (!any) return;
+    } else {
+        b = brick_slot_of_block(bl, bcnt, slot);
+        if (b < 0) return;
+    }
+    const int E = GROUP ? P.gtile : P.tile;
+    const int E3 = E * E * E;
     for (int k = tid; k < NCH * E3; k += NT) tile[k] = 0ull;
     int32_t o[3];
     tile_origin(P, b, o);
     __syncthreads();
-    for (int64_t q = (int64_t)beg + tid; q < end; q += NT) {
+    auto deposit = [&](int64_t q) {
         double xa[3], S[NCH];
         granule_terms<true, T, true, false, false, NCH>(P, n, q, x, v, r, Fc, Fd, err, 0.0, nullptr, xa, S);
         double w[3][3];
@@ -435,7 +456,7 @@ __global__ void __launch_bounds__(NT) k_p2g_direct(DevParams P, int64_t n, const
         if (!inside) {  // deposited after the assembly (k_p2g_escapes)
             const uint32_t k = atomicAdd(st.esc_n, 1u);
             if (k < (uint32_t)n) st.esc[k] = (int32_t)q;
-            continue;
+            return;
         }
         uint64_t rest[NCH];  // rint(S) minus the outer contributions: the centre's
 #pragma unroll
@@ -472,6 +493,14 @@ __global__ void __launch_bounds__(NT) k_p2g_direct(DevParams P, int64_t n, const
                 if (cx != 1 || cy != 1) node((w[0][cx] * w[1][cy]) * w[2][1], rz + l[1][cy] * E + l[0][cx]);
 #pragma unroll
         for (int c = 0; c < NCH; ++c) add(c, rz + l[1][1] * E + l[0][1], rest[c]);
+    };
+    if (GROUP) {
+        for (int w = tid >> 6; w < kGroup * kGroup * kGroup; w += NT / 64)
+            for (int64_t q = (int64_t)s_beg[w] + (tid & 63); q < s_end[w]; q += 64) deposit(q);
+    } else {
+        int32_t beg = cb[b * kBrickCells], end = ce[b * kBrickCells + kBrickCells - 1];
+        clip_range(n, beg, end);
+        for (int64_t q = (int64_t)beg + tid; q < end; q += NT) deposit(q);
     }
     __syncthreads();
     unsigned long long *dst = st.tiles + slot * (int64_t)(NCH * E3);
@@ -488,9 +517,14 @@ __global__ void __launch_bounds__(NT) k_p2g_direct(DevParams P, int64_t n, const
 // tile holds now and that was not live holds zeros from an earlier
 // assembly and is left as it is: a bed that fills part of the box writes
 // its own region (and the region it left) instead of the whole grids.
+// The tiles (edge E) are those of the bricks or of the brick groups: slot_of,
+// nbx, nby and the cover table are then the groups'.  Bound by the tile rows, of
+// which a brick's hold 48 bytes a line or more: 16.8 million granules 0.96 ms
+// from brick tiles, 0.47 from group tiles.
 // (Giving each XCD a contiguous eighth of the rows, so that the rows reading
 // one tile share an L2, was slower: a bed fills part of the box, so most
-// tile reads then fell to a few XCDs.)
+// tile reads then fell to a few XCDs.  So was giving the XCDs the rows of one
+// brick in turn, 1.05 ms.)
 constexpr int kAsmRows = 4;  // node rows per workgroup pass, one per wave
 
 __global__ void __launch_bounds__(256) k_p2g_assemble(DevParams P, const unsigned long long *__restrict__ tiles,
@@ -498,15 +532,15 @@ __global__ void __launch_bounds__(256) k_p2g_assemble(DevParams P, const unsigne
                                                       const int32_t *__restrict__ cover,
                                                       unsigned long long *__restrict__ alpha,
                                                       unsigned long long *__restrict__ mom,
-                                                      uint8_t *__restrict__ live, int full)
+                                                      uint8_t *__restrict__ live, int full, int E, int32_t nbx,
+                                                      int32_t nby)
 {
     extern __shared__ int32_t s_slot[];  // [kAsmRows][4][nb0]: slots of each row's (z, y) brick pairs along x
     __shared__ int32_t s_any[kAsmRows];
-    const int E = P.tile, E3 = E * E * E;
+    const int E3 = E * E * E;
     const int64_t G = P.G;
     const int64_t rows = (int64_t)P.n[1] * P.n[2];
     const int32_t *cx = cover, *cy = cover + 4 * P.n[0], *cz = cover + 4 * (P.n[0] + P.n[1]);
-    const int32_t nbx = P.nb[0];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     for (int64_t r0 = (int64_t)blockIdx.x * kAsmRows; r0 < rows; r0 += (int64_t)gridDim.x * kAsmRows) {
         // the brick slots of the pass's rows into LDS (all loads in flight
@@ -521,7 +555,7 @@ __global__ void __launch_bounds__(256) k_p2g_assemble(DevParams P, const unsigne
             if (row < rows) {
                 const int32_t j = (int32_t)(row % P.n[1]), k = (int32_t)(row / P.n[1]);
                 const int32_t by = cy[4 * j + 2 * (p & 1)], bz = cz[4 * k + 2 * (p >> 1)];
-                if (bz >= 0 && by >= 0) sl = slot_of[((int64_t)bz * P.nb[1] + by) * nbx + bx];
+                if (bz >= 0 && by >= 0) sl = slot_of[((int64_t)bz * nby + by) * nbx + bx];
             }
             s_slot[t] = sl;
             if (sl >= 0) s_any[rr] = 1;
@@ -930,13 +964,8 @@ hipError_t launch_integrate_p2g(const DevParams &P, int64_t n, int64_t K, double
     return p2g_fixed_impl<T, true>(P, n, K, x, v, r, Fc, Fd, cb, ce, B, alpha, mom, err, s);
 }
 
-template <typename T>
-hipError_t launch_integrate_p2g_store(const DevParams &P, int64_t n, int64_t K, double *x, double *v,
-                                      const double *r, const T *Fc, const T *Fd, const int32_t *cb,
-                                      const int32_t *ce, const BrickList &B, int64_t *err, hipStream_t s,
-                                      const P2GStore &st)
+void p2g_store_mode(const DevParams &P, int64_t n, const BrickList &B, P2GStore &st)
 {
-    if (n == 0) return hipSuccess;
     // The direct kernel when an occupied brick holds fewer than two granules
     // per node on average (205 granules on 512 nodes 26 against 34 us, 64 on
     // 64 nodes 0.92 ms in workgroups of 64 against 1.28 of 128 threads), the
@@ -945,20 +974,38 @@ hipError_t launch_integrate_p2g_store(const DevParams &P, int64_t n, int64_t K, 
     // the expected granules decide.  Deposits added to the grid with atomics
     // keep the run kernel: those atomics bound them (3.9 ms against 4.5).
     const double m = (double)kBrick * P.cell * P.inv_dx;  // nodes per brick edge
-    if (!(brick_fill(P, n, B).avg < 2.0 * (m * m * m))) {
+    st.direct = brick_fill(P, n, B).avg < 2.0 * (m * m * m);
+    st.mode = st.direct ? fill_mode(P, n, B, kGroupBricks) : kFillBlock;
+    if (st.mode == kFillGroup && !st.gcover) st.mode = kFillWave;
+}
+
+template <typename T>
+hipError_t launch_integrate_p2g_store(const DevParams &P, int64_t n, int64_t K, double *x, double *v,
+                                      const double *r, const T *Fc, const T *Fd, const int32_t *cb,
+                                      const int32_t *ce, const BrickList &B, int64_t *err, hipStream_t s,
+                                      const P2GStore &st)
+{
+    if (n == 0) return hipSuccess;
+    if (!st.direct) {
         p2g_kernel<true, T, true, false, false, true>(P, n, K, x, v, r, Fc, Fd, cb, ce, B, nullptr, nullptr, err, 0.0,
                                                       nullptr, st, s);
         return hipGetLastError();
     }
-    const FillMode mode = fill_mode(P, n, B);
+    const FillMode mode = st.mode;
     const unsigned grid = brick_grid(K / kBrickCells);
     const size_t lds = sizeof(unsigned long long) * 4 * P.tile * P.tile * P.tile;
+    if (mode == kFillGroup) {
+        const size_t glds = sizeof(unsigned long long) * 4 * P.gtile * P.gtile * P.gtile;
+        k_p2g_direct<T, kGroupNT, true><<<group_grid(P), kGroupNT, glds, s>>>(P, n, B.list, B.count, x, v, r, Fc, Fd, cb,
+                                                                              ce, err, st, 0);
+        return hipGetLastError();
+    }
     if (mode != kFillBlock)
-        k_p2g_direct<T, 64><<<grid, 64, lds, s>>>(P, n, B.list, B.count, x, v, r, Fc, Fd, cb, ce, err, st,
-                                                  mode == kFillBoth ? 1 : 0);
+        k_p2g_direct<T, 64, false><<<grid, 64, lds, s>>>(P, n, B.list, B.count, x, v, r, Fc, Fd, cb, ce, err, st,
+                                                         mode == kFillBoth ? 1 : 0);
     if (mode != kFillWave)
-        k_p2g_direct<T, 256><<<grid, 256, lds, s>>>(P, n, B.list, B.count, x, v, r, Fc, Fd, cb, ce, err, st,
-                                                    mode == kFillBoth ? 2 : 0);
+        k_p2g_direct<T, 256, false><<<grid, 256, lds, s>>>(P, n, B.list, B.count, x, v, r, Fc, Fd, cb, ce, err, st,
+                                                           mode == kFillBoth ? 2 : 0);
     return hipGetLastError();
 }
 
@@ -978,15 +1025,18 @@ hipError_t launch_p2g_assemble(const DevParams &P, int64_t n, const double *x, c
     unsigned long long *A = reinterpret_cast<unsigned long long *>(alpha);
     unsigned long long *M = reinterpret_cast<unsigned long long *>(mom);
     const int64_t passes = ((int64_t)P.n[1] * P.n[2] + kAsmRows - 1) / kAsmRows;
-    k_p2g_assemble<<<(unsigned)(passes < 16384 ? passes : 16384), 256, sizeof(int32_t) * kAsmRows * 4 * P.nb[0],
-                     s>>>(
-        P, st.tiles, B.slot_of, st.cover, A, M, st.live, st.live ? st.full : 1);
+    const bool grp = st.mode == kFillGroup;
+    const int32_t nbx = grp ? P.ng[0] : P.nb[0], nby = grp ? P.ng[1] : P.nb[1];
+    k_p2g_assemble<<<(unsigned)(passes < 16384 ? passes : 16384), 256, sizeof(int32_t) * kAsmRows * 4 * nbx, s>>>(
+        P, st.tiles, grp ? st.gslot : B.slot_of, grp ? st.gcover : st.cover, A, M, st.live, st.live ? st.full : 1,
+        grp ? P.gtile : P.tile, nbx, nby);
     k_p2g_escapes<<<256, 256, 0, s>>>(P, n, st.esc, st.esc_n, esc_next, x, v, r, A, M, st.live, err);
     return hipGetLastError();
 }
 
-void p2g_cover_table(const DevParams &P, int32_t *out)
+void p2g_cover_table(const DevParams &P, int edge, int32_t *out)
 {
+    const int32_t cells = kBrick * edge, E = edge == 1 ? P.tile : P.gtile;
     int32_t *t = out;
     for (int a = 0; a < 3; ++a) {
         for (int32_t i = 0; i < P.n[a]; ++i, t += 4) {
@@ -994,12 +1044,12 @@ void p2g_cover_table(const DevParams &P, int32_t *out)
             int k = 0;
             // tiles start about 4 cell/dx apart and reach about one node past
             // their brick: the bricks near the node's own are the candidates
-            const int32_t bc = (int32_t)floor((double)(i + 1) / ((double)kBrick * P.cell * P.inv_dx));
+            const int32_t bc = (int32_t)floor((double)(i + 1) / ((double)cells * P.cell * P.inv_dx));
             const int32_t b0 = bc - 2 > 0 ? bc - 2 : 0;
-            for (int32_t bx = b0; bx <= bc + 2 && bx < P.nb[a] && k < 2; ++bx) {
+            for (int32_t bx = b0; bx <= bc + 2 && bx < (edge == 1 ? P.nb[a] : P.ng[a]) && k < 2; ++bx) {
                 // the tile origin of tile_origin
-                const int32_t o = (int32_t)floor((double)(bx * kBrick) * P.cell * P.inv_dx + 1e-7) - 1;
-                if (i >= o && i < o + P.tile) {
+                const int32_t o = (int32_t)floor((double)(bx * cells) * P.cell * P.inv_dx + 1e-7) - 1;
+                if (i >= o && i < o + E) {
                     t[2 * k] = bx;
                     t[2 * k + 1] = i - o;
                     ++k;
