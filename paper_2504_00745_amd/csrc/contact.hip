@@ -351,12 +351,39 @@ __device__ inline void pull_walls(const DevParams &P, const double xi[3], const 
         }
 }
 
+// A brick's node tile in LDS (rollout kinds): its loads are in flight with the
+// shell's, and a granule's 27 nodes are read without three rounds of global
+// loads at the end of the chain (65,536 granules: kMove 34.4 -> 30.0 us, kReverse
+// 36.6 -> 31.3).  t NULL when the launch has none (no room in 64 KiB):
+// u and alpha (not clamped) of node (o0 + i, o1 + j, o2 + k) at
+// (k edge + j) edge + i.
+struct alignas(16) FluidNode {
+    double u[3], alpha;
+};
+struct FluidTile {
+    const FluidNode *t;
+    int32_t o[3], edge;
+    // entry of node (i, j, k), in the tile
+    __device__ const FluidNode &at(int32_t i, int32_t j, int32_t k) const
+    {
+        return t[((k - o[2]) * edge + (j - o[1])) * edge + (i - o[0])];
+    }
+    __device__ bool holds(const Stencil &st) const
+    {
+        bool in = t != nullptr;
+        for (int a = 0; a < 3; ++a)
+            for (int k = 0; k < 3; ++k) in &= st.node[a][k] >= o[a] && st.node[a][k] < o[a] + edge;
+        return in;
+    }
+};
+
 // Ends granule q: its walls, then what the kind does with the sums.  tot: the
 // thread's dL/dmu, dL/dC_d and largest |g_alpha_f| (kReverse).
 template <typename T, int KIND>
 __device__ inline void finish_granule(const DevParams &P, int64_t n, int64_t q, const double xi[3], const double vi[3],
                                       double ri, double mi, const double gi[3], T acc[], int32_t nc,
-                                      T *__restrict__ F, int32_t *__restrict__ ncont, const AdjArgs &A, double tot[3])
+                                      T *__restrict__ F, int32_t *__restrict__ ncont, const AdjArgs &A, double tot[3],
+                                      const FluidTile &tile)
 {
     if constexpr (pulls(KIND))
         pull_walls(P, xi, vi, ri, mi, gi, acc);
@@ -379,13 +406,22 @@ __device__ inline void finish_granule(const DevParams &P, int64_t n, int64_t q, 
         const double inv = *A.inv;
         const int64_t G = P.G;
         double ua[3], a, fd[3];
-        g2p_sample<double>(P, xi, [&](int32_t i, int32_t j, int32_t k, double uu[3], double &al) {
-            const int64_t idx = node_index(P, i, j, k);
-            uu[0] = A.u[idx];
-            uu[1] = A.u[G + idx];
-            uu[2] = A.u[2 * G + idx];
-            al = node_alpha_real(P, (double)A.fx[idx] * inv);
-        }, ua, a);
+        Stencil st;
+        stencil_of(P, xi, st);
+        if (tile.holds(st))
+            g2p_sample_st<double>(st, [&](int32_t i, int32_t j, int32_t k, double uu[3], double &al) {
+                const FluidNode &f = tile.at(i, j, k);
+                for (int c = 0; c < 3; ++c) uu[c] = f.u[c];
+                al = node_alpha_real(P, f.alpha);
+            }, ua, a);
+        else
+            g2p_sample_st<double>(st, [&](int32_t i, int32_t j, int32_t k, double uu[3], double &al) {
+                const int64_t idx = node_index(P, i, j, k);
+                uu[0] = A.u[idx];
+                uu[1] = A.u[G + idx];
+                uu[2] = A.u[2 * G + idx];
+                al = node_alpha_real(P, (double)A.fx[idx] * inv);
+            }, ua, a);
         drag_one<double>(P, ri, vi, ua, a, fd);
         double x[3] = {xi[0], xi[1], xi[2]}, v[3] = {vi[0], vi[1], vi[2]};
         integrate_one<double>(P, ri, acc, fd, x, v);
@@ -405,30 +441,44 @@ __device__ inline void finish_granule(const DevParams &P, int64_t n, int64_t q, 
         double dw[3][3];
         stencil_dw(P, xi, dw);
         double val[4] = {0, 0, 0, 0}, gr[3][4] = {{0, 0, 0, 0}, {0, 0, 0, 0}, {0, 0, 0, 0}};
-        double wz = st.w[2][0], wz1 = st.w[2][1], wz2 = st.w[2][2], ez = dw[2][0], ez1 = dw[2][1], ez2 = dw[2][2];
-        int32_t nz = st.node[2][0], nz1 = st.node[2][1], nz2 = st.node[2][2];
+        auto sweep = [&](auto &&fetch) {
+            double wz = st.w[2][0], wz1 = st.w[2][1], wz2 = st.w[2][2], ez = dw[2][0], ez1 = dw[2][1], ez2 = dw[2][2];
+            int32_t nz = st.node[2][0], nz1 = st.node[2][1], nz2 = st.node[2][2];
 #pragma unroll 1
-        for (int cz = 0; cz < 3; ++cz) {  // planes rotate through registers (see g2p_sample_st)
+            for (int cz = 0; cz < 3; ++cz) {  // planes rotate through registers (see g2p_sample_st)
 #pragma unroll
-            for (int cy = 0; cy < 3; ++cy)
+                for (int cy = 0; cy < 3; ++cy)
 #pragma unroll
-                for (int cx = 0; cx < 3; ++cx) {
-                    const int64_t k = node_index(P, st.node[0][cx], st.node[1][cy], nz);
-                    const double al = (double)A.fx[k] * inv;
-                    const double f[4] = {A.u[k], A.u[G + k], A.u[2 * G + k], al < P.alpha_max ? al : P.alpha_max};
-                    const double w = (st.w[0][cx] * st.w[1][cy]) * wz;
-                    const double g[3] = {(dw[0][cx] * st.w[1][cy]) * wz, (st.w[0][cx] * dw[1][cy]) * wz,
-                                         (st.w[0][cx] * st.w[1][cy]) * ez};
+                    for (int cx = 0; cx < 3; ++cx) {
+                        double f[4];
+                        fetch(st.node[0][cx], st.node[1][cy], nz, f);
+                        f[3] = f[3] < P.alpha_max ? f[3] : P.alpha_max;
+                        const double w = (st.w[0][cx] * st.w[1][cy]) * wz;
+                        const double g[3] = {(dw[0][cx] * st.w[1][cy]) * wz, (st.w[0][cx] * dw[1][cy]) * wz,
+                                             (st.w[0][cx] * st.w[1][cy]) * ez};
 #pragma unroll
-                    for (int c = 0; c < 4; ++c) {
-                        val[c] += w * f[c];
-                        for (int a = 0; a < 3; ++a) gr[a][c] += g[a] * f[c];
+                        for (int c = 0; c < 4; ++c) {
+                            val[c] += w * f[c];
+                            for (int a = 0; a < 3; ++a) gr[a][c] += g[a] * f[c];
+                        }
                     }
-                }
-            wz = wz1; wz1 = wz2;
-            ez = ez1; ez1 = ez2;
-            nz = nz1; nz1 = nz2;
-        }
+                wz = wz1; wz1 = wz2;
+                ez = ez1; ez1 = ez2;
+                nz = nz1; nz1 = nz2;
+            }
+        };
+        if (tile.holds(st))
+            sweep([&](int32_t i, int32_t j, int32_t k, double f[4]) {
+                const FluidNode &q = tile.at(i, j, k);
+                for (int c = 0; c < 3; ++c) f[c] = q.u[c];
+                f[3] = q.alpha;
+            });
+        else
+            sweep([&](int32_t i, int32_t j, int32_t kz, double f[4]) {
+                const int64_t k = node_index(P, i, j, kz);
+                for (int c = 0; c < 3; ++c) f[c] = A.u[c * G + k];
+                f[3] = (double)A.fx[k] * inv;
+            });
         const double af = 1.0 - val[3];
         const double c6 = P.cdrag_unit * ri;  // 6 pi eta r
         const double beta = P.c_drag * c6;
@@ -517,7 +567,7 @@ __device__ inline void contact_global(const DevParams &P, int64_t n, const doubl
     } else {  // rare: more partners than the list holds
         for_each_canonical(P, n, q, lo, hi, cb, ce, [&](int32_t j) { nc += take(j); });
     }
-    finish_granule<T, KIND>(P, n, q, xi, vi, ri, mi, gi, acc, nc, F, ncont, A, tot);
+    finish_granule<T, KIND>(P, n, q, xi, vi, ri, mi, gi, acc, nc, F, ncont, A, tot, FluidTile{});
 }
 
 // ---------------------------------------------------------------------------
@@ -825,6 +875,37 @@ k_contact_lds(DevParams P, int64_t n, const int32_t *__restrict__ bl,
     // with liquid bridges the candidate pass looks d_r further: each radius
     // grows by d_r / 2 in Q and b_i, so r_i + r_j grows by d_r
     const float hreach = CAP ? (float)(0.5 * P.dr_max) : 0.0f;
+    // ---- the rollout's node tile: its loads are in flight with the shell's
+    FluidTile tile = {};
+    FluidNode *tnode = nullptr;
+    constexpr int kNodeRounds = 4;  // nodes a thread holds; a tile of more ends below
+    double nu[kNodeRounds][3];
+    int64_t na[kNodeRounds];
+    auto node_at = [&](int k, int64_t &idx) {  // whether entry k lies on the grid
+        const int32_t i = tile.o[0] + k % tile.edge, j = tile.o[1] + (k / tile.edge) % tile.edge;
+        const int32_t l = tile.o[2] + k / (tile.edge * tile.edge);
+        idx = node_index(P, i, j, l);
+        return i >= 0 && j >= 0 && l >= 0 && i < P.n[0] && j < P.n[1] && l < P.n[2];
+    };
+    if constexpr (KIND == kMove || KIND == kReverse) {
+        if (A.tile_at > 0) {
+            tnode = reinterpret_cast<FluidNode *>(reinterpret_cast<char *>(smem4) + A.tile_at);
+            tile.t = tnode;
+            tile.edge = P.tile;
+            tile_origin(P, b, tile.o);
+#pragma unroll
+            for (int it = 0; it < kNodeRounds; ++it) {
+                const int k = tid + it * NT;
+                int64_t idx;
+                na[it] = 0;
+                for (int c = 0; c < 3; ++c) nu[it][c] = 0.0;
+                if (k < tile.edge * tile.edge * tile.edge && node_at(k, idx)) {
+                    for (int c = 0; c < 3; ++c) nu[it][c] = A.u[c * P.G + idx];
+                    na[it] = A.fx[idx];
+                }
+            }
+        }
+    }
     // ---- copy the shell's granules, relative to the centre, in single precision.
     // H <= cap <= kCopyRounds * NT: all loads of a thread are issued before
     // any of them is used, so they are in flight together.
@@ -863,6 +944,22 @@ k_contact_lds(DevParams P, int64_t n, const int32_t *__restrict__ bl,
                 p = make_float4(nan, nan, nan, nan);
             }
             spos[k] = p;
+        }
+    }
+    if constexpr (KIND == kMove || KIND == kReverse) {
+        if (A.tile_at > 0) {
+            const double inv = *A.inv;
+            const int E3 = tile.edge * tile.edge * tile.edge;
+#pragma unroll
+            for (int it = 0; it < kNodeRounds; ++it) {
+                const int k = tid + it * NT;
+                if (k < E3) tnode[k] = {{nu[it][0], nu[it][1], nu[it][2]}, (double)na[it] * inv};
+            }
+            for (int k = tid + kNodeRounds * NT; k < E3; k += NT) {
+                int64_t idx;
+                if (!node_at(k, idx)) continue;  // never referenced
+                tnode[k] = {{A.u[idx], A.u[P.G + idx], A.u[2 * P.G + idx]}, (double)A.fx[idx] * inv};
+            }
         }
     }
     __syncthreads();
@@ -1005,7 +1102,7 @@ k_contact_lds(DevParams P, int64_t n, const int32_t *__restrict__ bl,
                 if (ncont) ncont[q] = 0;
                 return;
             }
-            finish_granule<T, KIND>(P, n, q, xi, vi, ri, mi, gi, acc, nc, F, ncont, A, tot);
+            finish_granule<T, KIND>(P, n, q, xi, vi, ri, mi, gi, acc, nc, F, ncont, A, tot, tile);
         }
     };
     for (int w = w0; w < kBricks; w += kWaves) {
@@ -1386,8 +1483,16 @@ static void contact_kernel(const DevParams &P, int64_t n, const double *x, const
                            const AdjArgs &A)
 {
     const int64_t nbricks = (int64_t)P.nb[0] * P.nb[1] * P.nb[2];
-    k_contact_lds<T, KIND, NT, false><<<brick_grid(nbricks), NT, contact_lds_bytes(cap, NT), s>>>(
-        P, n, B.list, B.count, cap, x, v, r, cb, ce, sr, held, F, ncont, err, hm, hc, only, A);
+    size_t lds = contact_lds_bytes(cap, NT);
+    AdjArgs At = A;
+    if (KIND == kMove || KIND == kReverse) {
+        // the node tile after the other arrays, if it fits
+        const size_t at = (lds + 15) / 16 * 16, end = at + sizeof(FluidNode) * P.tile * P.tile * P.tile;
+        At.tile_at = end <= 65536 ? (int)at : 0;
+        if (At.tile_at) lds = end;
+    }
+    k_contact_lds<T, KIND, NT, false><<<brick_grid(nbricks), NT, lds, s>>>(
+        P, n, B.list, B.count, cap, x, v, r, cb, ce, sr, held, F, ncont, err, hm, hc, only, At);
 }
 
 template <typename T, int KIND>

@@ -303,6 +303,7 @@ struct AdjArgs {
     double *gaf;                 // reverse step: cotangent of the fluid fraction
     unsigned long long *gmax;    // reverse step: bits of the largest |gaf|
     double *psum;                // reverse step: per brick, the sums of dL/dmu and dL/dC_d
+    int tile_at;                 // rollout: where the brick's node tile lies in LDS (bytes), 0 for none (set at the launch)
 };
 hipError_t launch_contact_vjp(const DevParams &P, int64_t n, const double *x, const double *v, const double *r,
                               const int32_t *cb, const int32_t *ce, const BrickList &B, const AdjArgs &A, int64_t *err,

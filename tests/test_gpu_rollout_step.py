@@ -37,6 +37,12 @@ def bed(name):
         return dict(d, x=np.ascontiguousarray(x[:, q]), v=d["v"], r=r[q])
     d = wl.make("c4", n_override=1 if name == "one" else 4099)
     d["v"] = 20.0 * d["v"]
+    if name.startswith("fine"):  # node tiles of 11^3 (beyond four a thread) and 13^3 (beyond LDS)
+        p = dict(d["params"])
+        dx = p["cell"] / (1.9 if name == "fine" else 2.5)
+        n = [int(np.ceil(m * p["dx"] / dx)) for m in p["n"]]
+        p.update(dx=dx, n=n)
+        d.update(params=p, u=np.random.Generator(np.random.PCG64(7)).normal(0, 0.1, (3, int(np.prod(n)))))
     if name == "dense":  # 300 granules in one cell, the rest as they were
         rng = np.random.Generator(np.random.PCG64(6))
         x, r = d["x"].copy(), d["r"].copy()
@@ -46,7 +52,7 @@ def bed(name):
     return d
 
 
-@pytest.mark.parametrize("name", ["bidisperse", "dense", "sparse", "one"])
+@pytest.mark.parametrize("name", ["bidisperse", "dense", "sparse", "one", "fine", "finer"])
 def test_step_and_reverse_match_stages(T, name):
     import torch
     from paper_2504_00745_amd import gic
