@@ -224,10 +224,23 @@ constexpr int64_t kSumNoallocMax = (int64_t)kSumParts << 20;
 
 // The brick schedule of the cell ranges a call is given, built on the stream
 // before its brick kernel; gic_step builds it once after its sort.
-hipError_t brick_list(gic_ctx *c, int64_t n, const int32_t *cb, const int32_t *ce, hipStream_t s)
+// any: the kernel can also take every brick of the box, and does in boxes of at
+// most kBoxBricks, a quarter of them (but for 1,024) occupied, once a count of
+// those has reached the host: a list takes one or two launches (4,576 bricks, half of them
+// empty: 10.5 us), the workgroups of empty bricks leave after one load (a wet
+// step of three such calls 239 -> 209 us).
+constexpr int64_t kBoxBricks = 8192;
+hipError_t brick_list(gic_ctx *c, int64_t n, const int32_t *cb, const int32_t *ce, hipStream_t s, bool any = false)
 {
+    c->bricks.use = c->bricks.list;
     if (c->in_step) return hipSuccess;
     if (c->bl_pin && c->bl_cb == cb && c->bl_ce == ce) return hipSuccess;  // kept by gic_brick_list
+    const BrickFill f = brick_fill(c->dp, n, c->bricks);
+    const int64_t nb = c->bricks.nbricks;
+    if (any && f.known && nb <= kBoxBricks && (double)(nb - 1024) * f.avg <= 4.0 * (double)n) {
+        c->bricks.use = nullptr;
+        return hipSuccess;
+    }
     c->bl_pin = false;
     c->rng_ok = false;  // the brick list is now that of these tables
     return launch_brick_list(cb, ce, c->bricks, n, s);
@@ -626,7 +639,7 @@ gic_status gic_contact_forces(gic_ctx *c, int64_t n, const double *x, const doub
     if (n > 0 && (!x || !v || !r || !cell_begin || !cell_end || !f_contact)) return GIC_E_ARG;
     hipStream_t s = (hipStream_t)stream;
     if (n == 0) return GIC_OK;
-    if (brick_list(c, n, cell_begin, cell_end, s) != hipSuccess) return GIC_E_HIP;
+    if (brick_list(c, n, cell_begin, cell_end, s, pair_cap == 0) != hipSuccess) return GIC_E_HIP;
     c->nl_n = -1;  // the list now belongs to these arrays, not to the stepping path
     return contact_impl(c, n, x, v, r, cell_begin, cell_end, f_contact, n_contacts, pair_cap > 0 ? pair_ids : nullptr,
                         pair_cap, 1, s);
@@ -641,7 +654,7 @@ gic_status gic_contact_capillary_forces(gic_ctx *c, int64_t n, const double *x, 
     if (n > 0 && (!x || !v || !r || !sr || !cell_begin || !cell_end || !f_contact)) return GIC_E_ARG;
     hipStream_t s = (hipStream_t)stream;
     if (n == 0) return GIC_OK;
-    if (brick_list(c, n, cell_begin, cell_end, s) != hipSuccess) return GIC_E_HIP;
+    if (brick_list(c, n, cell_begin, cell_end, s, true) != hipSuccess) return GIC_E_HIP;
     if (fp32(c))
         return hip_status(launch_contact<float>(c->dp, n, x, v, r, cell_begin, cell_end, c->bricks,
                                                 (const float *)sr, held, (float *)f_contact, n_contacts, c->err, s, &c->shell));
@@ -725,7 +738,7 @@ gic_status gic_p2g(gic_ctx *c, int64_t n, const double *x, const double *v, cons
         if (e != hipSuccess) return GIC_E_HIP;
     }
     if (n == 0) return GIC_OK;
-    if (brick_list(c, n, cell_begin, cell_end, s) != hipSuccess) return GIC_E_HIP;
+    if (brick_list(c, n, cell_begin, cell_end, s, true) != hipSuccess) return GIC_E_HIP;
     return hip_status(
         launch_p2g_fixed(c->dp, n, c->K, x, v, r, cell_begin, cell_end, c->bricks, alpha_fx, mom_fx, c->err, s));
 }
@@ -737,7 +750,7 @@ gic_status gic_p2g_real(gic_ctx *c, int64_t n, const double *x, const double *v,
     if (!n_ok(c, n) || (!alpha && !mom)) return GIC_E_ARG;
     if (n > 0 && (!x || !r || !cell_begin || !cell_end || (mom && !v))) return GIC_E_ARG;
     hipStream_t s = (hipStream_t)stream;
-    if (n > 0 && brick_list(c, n, cell_begin, cell_end, s) != hipSuccess) return GIC_E_HIP;
+    if (n > 0 && brick_list(c, n, cell_begin, cell_end, s, true) != hipSuccess) return GIC_E_HIP;
     return hip_status(launch_p2g_real(c->dp, n, c->K, x, v, r, cell_begin, cell_end, c->bricks, alpha, mom,
                                       accumulate ? 1 : 0, c->fxs, c->fxp, s));
 }
@@ -753,7 +766,7 @@ gic_status gic_gather_g2p_drag(gic_ctx *c, int64_t n, const int32_t *order, cons
     if ((id == nullptr) != (id_out == nullptr) || (u_at == nullptr) != (alpha_f == nullptr)) return GIC_E_ARG;
     hipStream_t s = (hipStream_t)stream;
     if (n == 0) return GIC_OK;
-    if (brick_list(c, n, cell_begin, cell_end, s) != hipSuccess) return GIC_E_HIP;
+    if (brick_list(c, n, cell_begin, cell_end, s, true) != hipSuccess) return GIC_E_HIP;
     if (fp32(c))
         return hip_status(launch_gather_g2p_drag<float>(c->dp, n, c->K, order, x, v, r, id, x_out, v_out, r_out,
                                                         id_out, (const float *)u, alpha_fx, cell_begin, cell_end,
@@ -779,7 +792,7 @@ static gic_status integrate_p2g_impl(gic_ctx *c, int64_t n, double *x, double *v
         if (e != hipSuccess) return GIC_E_HIP;
     }
     if (n == 0) return GIC_OK;
-    if (brick_list(c, n, cell_begin, cell_end, s) != hipSuccess) return GIC_E_HIP;
+    if (brick_list(c, n, cell_begin, cell_end, s, true) != hipSuccess) return GIC_E_HIP;
     if (fp32(c))
         return hip_status(launch_integrate_p2g<float>(c->dp, n, c->K, x, v, r, (const float *)f_contact,
                                                       (const float *)f_drag, cell_begin, cell_end, c->bricks,
@@ -966,7 +979,7 @@ gic_status gic_gather_g2p_fluid(gic_ctx *c, int64_t n, const int32_t *order, con
         return GIC_E_ARG;
     hipStream_t s = (hipStream_t)stream;
     if (n == 0) return GIC_OK;
-    if (brick_list(c, n, cell_begin, cell_end, s) != hipSuccess) return GIC_E_HIP;
+    if (brick_list(c, n, cell_begin, cell_end, s, true) != hipSuccess) return GIC_E_HIP;
     if (fp32(c))
         return hip_status(launch_gather_g2p_fluid<float>(
             c->dp, n, c->K, order, x, v, r, id, x_out, v_out, r_out, id_out, (const float *)u, alpha_fx,
@@ -986,7 +999,7 @@ gic_status gic_exchange_p2g(gic_ctx *c, int64_t n, const double *x, const double
     hipStream_t s = (hipStream_t)stream;
     grids_written(c, fs_fx, 3 * c->dp.G);
     if (n == 0) return GIC_OK;
-    if (brick_list(c, n, cell_begin, cell_end, s) != hipSuccess) return GIC_E_HIP;
+    if (brick_list(c, n, cell_begin, cell_end, s, true) != hipSuccess) return GIC_E_HIP;
     const double exsc = -weight / c->p.f_unit;
     if (fp32(c))
         return hip_status(launch_exchange_p2g<float>(c->dp, n, c->K, x, r, (const float *)f_contact,
@@ -1068,7 +1081,7 @@ gic_status gic_contact_forces_vjp(gic_ctx *c, int64_t n, const double *x, const 
     if (!n_ok(c, n) || fp32(c)) return GIC_E_ARG;
     if (n > 0 && (!x || !v || !r || !cell_begin || !cell_end || !g_f || !g_x || !g_v || !g_mu)) return GIC_E_ARG;
     if (n == 0) return GIC_OK;
-    if (brick_list(c, n, cell_begin, cell_end, (hipStream_t)stream) != hipSuccess) return GIC_E_HIP;
+    if (brick_list(c, n, cell_begin, cell_end, (hipStream_t)stream, true) != hipSuccess) return GIC_E_HIP;
     AdjArgs A = {};
     A.gF = g_f;
     A.gx = g_x;
@@ -1184,7 +1197,7 @@ gic_status gic_g2p_vjp(gic_ctx *c, int64_t n, const double *x, const double *u, 
     if (!n_ok(c, n) || fp32(c)) return GIC_E_ARG;
     if (n > 0 && (!x || !u || !alpha_real || !g_u_at || !g_alpha_f || !g_x)) return GIC_E_ARG;
     if (n > 0 && g_alpha && (!cell_begin || !cell_end)) return GIC_E_ARG;
-    if (n > 0 && g_alpha && brick_list(c, n, cell_begin, cell_end, (hipStream_t)stream) != hipSuccess)
+    if (n > 0 && g_alpha && brick_list(c, n, cell_begin, cell_end, (hipStream_t)stream, true) != hipSuccess)
         return GIC_E_HIP;
     return hip_status(launch_g2p_vjp(c->dp, n, c->K, x, u, alpha_real, g_u_at, g_alpha_f, cell_begin, cell_end,
                                      c->bricks, g_x, g_alpha, c->fxs, c->fxp, (hipStream_t)stream));

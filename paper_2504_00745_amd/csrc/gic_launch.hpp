@@ -35,6 +35,7 @@ struct BrickList {
     int32_t *list;     // [nbricks]
     int32_t *count;    // [1]
     uint32_t *sums;    // [<= 1024] block totals
+    const int32_t *use;  // the list as the brick kernels take it: list, or NULL to take every brick of the box
     int32_t *slot_of;  // [nbricks] position of each brick in list, -1 if empty
     int64_t nbricks;
     int32_t *seen;     // [1] pinned host: a copy of count (see brick_fill), of a list of seen_n granules

@@ -800,6 +800,7 @@ hipError_t launch_sort_cells(const DevParams &P, int64_t n, const double *x, uin
                              int32_t *cell_begin, int32_t *cell_end, int64_t K, SortScratch &S, BrickList &B,
                              int64_t *err, hipStream_t s, const NbrList *nl, int force, int keep_ranges)
 {
+    B.use = B.list;
     uint32_t *cnt = S.cnt;  // all zero between sorts
     uint32_t *begin = reinterpret_cast<uint32_t *>(cell_begin), *end = reinterpret_cast<uint32_t *>(cell_end);
     // previous sorted keys: usable when the last sort had the same n
@@ -858,6 +859,7 @@ hipError_t launch_rollout_sort(const DevParams &P, int64_t n, const double *xv, 
                                double *part, int *nb, const double *gxv, double *gs, double *gF,
                                unsigned long long *gmax, hipStream_t s)
 {
+    B.use = B.list;
     uint32_t *begin = reinterpret_cast<uint32_t *>(cell_begin), *end = reinterpret_cast<uint32_t *>(cell_end);
     uint32_t *skeys = S.skeys[S.cur ^ 1];
     const unsigned g = grid_for(n, 256), gl = g < kLoopGrid ? g : kLoopGrid, go = g < 1024u ? g : 1024u;
@@ -886,6 +888,7 @@ hipError_t launch_rollout_sort(const DevParams &P, int64_t n, const double *xv, 
 
 hipError_t launch_brick_list(const int32_t *cb, const int32_t *ce, BrickList &B, int64_t n, hipStream_t s)
 {
+    B.use = B.list;
     const int64_t nb = B.nbricks;
     if (nb <= 0) return hipSuccess;
     if (nb <= kBricksOneGroup) {
