@@ -757,7 +757,7 @@ k_contact_lds(DevParams P, int64_t n, const int32_t *__restrict__ bl,
         }
         if (!__syncthreads_or(beg < end)) return;
     } else {
-        b = brick_slot_of_block(brick_count(P), bl, bcnt, slot);
+        b = brick_slot_of_block(bl, bcnt, slot);
         if (b < 0) return;
     }
     // the bricks of a group are dealt to the waves
@@ -1492,7 +1492,7 @@ static void contact_kernel(const DevParams &P, int64_t n, const double *x, const
         if (At.tile_at) lds = end;
     }
     k_contact_lds<T, KIND, NT, false><<<brick_grid(nbricks), NT, lds, s>>>(
-        P, n, B.use, B.count, cap, x, v, r, cb, ce, sr, held, F, ncont, err, hm, hc, only, At);
+        P, n, B.use, B.use_count, cap, x, v, r, cb, ce, sr, held, F, ncont, err, hm, hc, only, At);
 }
 
 template <typename T, int KIND>
@@ -1518,7 +1518,7 @@ static hipError_t contact_launch(const DevParams &P, int64_t n, const double *x,
             if (want <= kCopyRounds * kGroupNT) {
                 mode = kFillGroup;
                 k_contact_lds<T, KIND, kGroupNT, true><<<group_grid(P), kGroupNT, lds, s>>>(
-                    P, n, B.use, B.count, (int)want, x, v, r, cb, ce, sr, held, F, ncont, err, hm, hc, 0, A);
+                    P, n, B.use, B.use_count, (int)want, x, v, r, cb, ce, sr, held, F, ncont, err, hm, hc, 0, A);
             }
     }
     if (mode == kFillWave || mode == kFillBoth) {

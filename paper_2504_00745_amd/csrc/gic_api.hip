@@ -233,12 +233,14 @@ constexpr int64_t kBoxBricks = 8192;
 hipError_t brick_list(gic_ctx *c, int64_t n, const int32_t *cb, const int32_t *ce, hipStream_t s, bool any = false)
 {
     c->bricks.use = c->bricks.list;
+    c->bricks.use_count = c->bricks.count;
     if (c->in_step) return hipSuccess;
     if (c->bl_pin && c->bl_cb == cb && c->bl_ce == ce) return hipSuccess;  // kept by gic_brick_list
     const BrickFill f = brick_fill(c->dp, n, c->bricks);
     const int64_t nb = c->bricks.nbricks;
-    if (any && f.known && nb <= kBoxBricks && (double)(nb - 1024) * f.avg <= 4.0 * (double)n) {
-        c->bricks.use = nullptr;
+    if (any && f.known && c->bricks.box && (double)(nb - 1024) * f.avg <= 4.0 * (double)n) {
+        c->bricks.use = c->bricks.box;
+        c->bricks.use_count = c->bricks.box + nb;
         return hipSuccess;
     }
     c->bl_pin = false;
@@ -407,6 +409,13 @@ gic_status gic_create(const gic_params *p, int64_t n_max, gic_ctx **out)
     c->bricks.nbricks = c->K / kBrickCells;
     ok &= hipMalloc(&c->bricks.list, sizeof(int32_t) * (c->bricks.nbricks > 0 ? c->bricks.nbricks : 1)) == hipSuccess;
     ok &= hipMalloc(&c->bricks.count, sizeof(int32_t)) == hipSuccess;
+    if (ok && c->bricks.nbricks > 0 && c->bricks.nbricks <= kBoxBricks) {
+        int32_t h[kBoxBricks + 1];
+        const size_t bytes = sizeof(int32_t) * (size_t)(c->bricks.nbricks + 1);
+        box_list(c->bricks.nbricks, h);
+        ok &= hipMalloc(&c->bricks.box, bytes) == hipSuccess &&
+              hipMemcpy(c->bricks.box, h, bytes, hipMemcpyHostToDevice) == hipSuccess;
+    }
     ok &= hipMalloc(&c->bricks.sums, sizeof(uint32_t) * 1024) == hipSuccess;
     ok &= hipMalloc(&c->bricks.slot_of, sizeof(int32_t) * (c->bricks.nbricks > 0 ? c->bricks.nbricks : 1)) ==
           hipSuccess;
@@ -513,6 +522,7 @@ gic_status gic_destroy(gic_ctx *c)
     (void)hipFree(c->part);
     (void)hipFree(c->bricks.list);
     (void)hipFree(c->bricks.count);
+    (void)hipFree(c->bricks.box);
     (void)hipFree(c->bricks.sums);
     (void)hipFree(c->bricks.slot_of);
     (void)hipFree(c->p2gs.esc);

@@ -51,22 +51,8 @@ __device__ inline int64_t xcd_block(int64_t nlogical)
 // brick_of_block returns the brick or -1.
 inline unsigned brick_grid(int64_t nbricks) { return xcd_grid(nbricks); }
 
-// Without a list (list NULL) the workgroups take every brick of the box, empty
-// ones too: runs of 16 neighbouring bricks to the XCDs in turn (a bed fills part
-// of the box), the remainder brick by brick.
-constexpr int64_t kBrickRun = 16;
-__device__ inline int64_t brick_of_box(int64_t nbricks)
+__device__ inline int64_t brick_of_block(const int32_t *__restrict__ list, const int32_t *__restrict__ count)
 {
-    const int64_t per = (nbricks + kXcds - 1) / kXcds, full = per / kBrickRun * kBrickRun;
-    const int64_t j = (int64_t)blockIdx.x / kXcds, xcd = (int64_t)blockIdx.x % kXcds;
-    const int64_t l = j < full ? (j / kBrickRun * kXcds + xcd) * kBrickRun + j % kBrickRun : j * kXcds + xcd;
-    return j < per && l < nbricks ? l : -1;
-}
-
-__device__ inline int64_t brick_of_block(int64_t nbricks, const int32_t *__restrict__ list,
-                                         const int32_t *__restrict__ count)
-{
-    if (!list) return brick_of_box(nbricks);
     const int64_t nocc = *count;
     const int64_t per = (nocc + kXcds - 1) / kXcds;  // list entries per XCD
     const int64_t b = blockIdx.x;
@@ -103,12 +89,10 @@ __device__ inline int64_t brick_at(const int32_t *__restrict__ list, const int32
     return j < per && l < nocc ? list[l] : -1;
 }
 
-// brick_of_block that also gives the brick's position in the list (its number
-// without a list).
-__device__ inline int64_t brick_slot_of_block(int64_t nbricks, const int32_t *__restrict__ list,
-                                              const int32_t *__restrict__ count, int64_t &slot)
+// brick_of_block that also gives the brick's position in the list.
+__device__ inline int64_t brick_slot_of_block(const int32_t *__restrict__ list, const int32_t *__restrict__ count,
+                                              int64_t &slot)
 {
-    if (!list) return slot = brick_of_box(nbricks);
     const int64_t nocc = *count;
     const int64_t per = (nocc + kXcds - 1) / kXcds;
     const int64_t b = blockIdx.x;
@@ -187,8 +171,6 @@ __device__ inline int64_t brick_of_group(const DevParams &P, int64_t g, int w)
     if (bx >= P.nb[0] || by >= P.nb[1] || bz >= P.nb[2]) return -1;
     return ((int64_t)bz * P.nb[1] + by) * P.nb[0] + bx;
 }
-
-__host__ __device__ inline int64_t brick_count(const DevParams &P) { return (int64_t)P.nb[0] * P.nb[1] * P.nb[2]; }
 
 // Latch the first error: code and granule index.
 __device__ inline void raise_error(int64_t *err, int code, int64_t idx)

@@ -35,7 +35,8 @@ struct BrickList {
     int32_t *list;     // [nbricks]
     int32_t *count;    // [1]
     uint32_t *sums;    // [<= 1024] block totals
-    const int32_t *use;  // the list as the brick kernels take it: list, or NULL to take every brick of the box
+    int32_t *box;      // [nbricks + 1] every brick of the box and their number, or NULL (see box_list)
+    const int32_t *use, *use_count;  // what the brick kernels run over: list and count, or the box
     int32_t *slot_of;  // [nbricks] position of each brick in list, -1 if empty
     int64_t nbricks;
     int32_t *seen;     // [1] pinned host: a copy of count (see brick_fill), of a list of seen_n granules
@@ -43,6 +44,10 @@ struct BrickList {
     unsigned calls;
 };
 
+// Every brick of the box in the order of a brick list, runs of 16 neighbouring
+// bricks to the XCDs' eighths in turn (a bed fills part of the box); host, n + 1
+// int32, the last one n.
+void box_list(int64_t n, int32_t *out);
 // n: granules of the tables, or -1 when the caller does not know (no copy of
 // the count to the host then).
 hipError_t launch_brick_list(const int32_t *cb, const int32_t *ce, BrickList &B, int64_t n, hipStream_t s);

@@ -801,6 +801,7 @@ hipError_t launch_sort_cells(const DevParams &P, int64_t n, const double *x, uin
                              int64_t *err, hipStream_t s, const NbrList *nl, int force, int keep_ranges)
 {
     B.use = B.list;
+    B.use_count = B.count;
     uint32_t *cnt = S.cnt;  // all zero between sorts
     uint32_t *begin = reinterpret_cast<uint32_t *>(cell_begin), *end = reinterpret_cast<uint32_t *>(cell_end);
     // previous sorted keys: usable when the last sort had the same n
@@ -860,6 +861,7 @@ hipError_t launch_rollout_sort(const DevParams &P, int64_t n, const double *xv, 
                                unsigned long long *gmax, hipStream_t s)
 {
     B.use = B.list;
+    B.use_count = B.count;
     uint32_t *begin = reinterpret_cast<uint32_t *>(cell_begin), *end = reinterpret_cast<uint32_t *>(cell_end);
     uint32_t *skeys = S.skeys[S.cur ^ 1];
     const unsigned g = grid_for(n, 256), gl = g < kLoopGrid ? g : kLoopGrid, go = g < 1024u ? g : 1024u;
@@ -889,6 +891,7 @@ hipError_t launch_rollout_sort(const DevParams &P, int64_t n, const double *xv, 
 hipError_t launch_brick_list(const int32_t *cb, const int32_t *ce, BrickList &B, int64_t n, hipStream_t s)
 {
     B.use = B.list;
+    B.use_count = B.count;
     const int64_t nb = B.nbricks;
     if (nb <= 0) return hipSuccess;
     if (nb <= kBricksOneGroup) {
@@ -901,6 +904,21 @@ hipError_t launch_brick_list(const int32_t *cb, const int32_t *ce, BrickList &B,
     k_brick_count<<<blocks, 256, 0, s>>>(nb, per, cb, ce, B.sums);
     k_brick_scatter<<<blocks, 256, 0, s>>>(nb, per, cb, ce, B.sums, B.list, B.count, B.slot_of);
     return brick_count_copy(B, n, s);
+}
+
+void box_list(int64_t n, int32_t *out)
+{
+    const int64_t per = (n + kXcds - 1) / kXcds;
+    int64_t at[kXcds];  // next free entry of each eighth
+    for (int x = 0; x < kXcds; ++x) at[x] = x * per;
+    auto room = [&](int x) { return at[x] < (x + 1) * per && at[x] < n; };
+    int x = 0;
+    for (int64_t b = 0; b < n; ++b) {
+        if (b % 16 == 0) x = (int)(b / 16 % kXcds);
+        while (!room(x)) x = (x + 1) % kXcds;  // the eighths hold n entries in all
+        out[at[x]++] = (int32_t)b;
+    }
+    out[n] = (int32_t)n;
 }
 
 hipError_t launch_reorder(int64_t n, const int32_t *order, const double *x, const double *v, const double *r,

@@ -125,7 +125,7 @@ __global__ void __launch_bounds__(NT) k_gather(DevParams P, int64_t n, const int
         gb = s_beg[tid >> 6];
         ge = s_end[tid >> 6];
     } else {
-        b = brick_of_block(brick_count(P), bl, bcnt);
+        b = brick_of_block(bl, bcnt);
         if (b < 0) return;
         gb = cb[b * kBrickCells];
         ge = ce[b * kBrickCells + kBrickCells - 1];
@@ -282,7 +282,7 @@ hipError_t launch_gather(const DevParams &P, int64_t n, int64_t K, const int32_t
     // the FP64 fluid tile of a group leaves a CU two workgroups
     if (mode == kFillGroup && ((FLUID && sizeof(T) == 8) || glds > 65536)) mode = kFillWave;
 #define GIC_GATHER(NT, GROUP, ONLY)                                                                                  \
-    k_gather<T, FLUID, NT, GROUP><<<GROUP ? group_grid(P) : grid, NT, GROUP ? glds : lds, s>>>(P, n, B.use, B.count, order, x, v, r, id, xo, vo, ro, ido, u, afx, \
+    k_gather<T, FLUID, NT, GROUP><<<GROUP ? group_grid(P) : grid, NT, GROUP ? glds : lds, s>>>(P, n, B.use, B.use_count, order, x, v, r, id, xo, vo, ro, ido, u, afx, \
                                                  gp, fa, cb, ce, Ff, uat, af, held, heldo, ONLY)
     if (mode == kFillGroup) GIC_GATHER(kGatherNT, true, 0);
     if (mode == kFillWave || mode == kFillBoth) GIC_GATHER(64, false, mode == kFillBoth ? 1 : 0);

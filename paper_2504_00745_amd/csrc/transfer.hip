@@ -196,7 +196,7 @@ __global__ void __launch_bounds__(kP2GThreads) __attribute__((amdgpu_waves_per_e
     __shared__ int32_t s_range[2];
     __shared__ int32_t s_wave[NT / 64];
     int64_t slot;
-    const int64_t b = brick_slot_of_block(brick_count(P), bl, bcnt, slot);
+    const int64_t b = brick_slot_of_block(bl, bcnt, slot);
     if (b < 0) return;
     brick_range(n, b, cb, ce, s_range);
     __syncthreads();
@@ -418,7 +418,7 @@ __global__ void __launch_bounds__(NT) k_p2g_direct(DevParams P, int64_t n, const
         if (tid == 0) st.gslot[slot] = any ? (int32_t)slot : -1;
         if (!any) return;
     } else {
-        b = brick_slot_of_block(brick_count(P), bl, bcnt, slot);
+        b = brick_slot_of_block(bl, bcnt, slot);
         if (b < 0) return;
     }
     const int E = GROUP ? P.gtile : P.tile;
@@ -779,7 +779,7 @@ __global__ void __launch_bounds__(kP2GThreads) k_p2g_real(DevParams P, int64_t n
                                                           unsigned long long *__restrict__ fx)
 {
     extern __shared__ unsigned long long itile[];
-    const int64_t b = brick_of_block(brick_count(P), bl, bcnt);
+    const int64_t b = brick_of_block(bl, bcnt);
     if (b < 0 && blockIdx.x != 0) return;
     int32_t beg = 0, end = 0;
     if (b >= 0) {
@@ -944,7 +944,7 @@ static void p2g_kernel(const DevParams &P, int64_t n, int64_t K, double *x, doub
     while (batch > 64 && p2g_lds(NCH, E3, batch) > 49152) batch /= 2;
     k_p2g_fixed<MOM, T, INTEG, EXCH, WET, STORE>
         <<<brick_grid(K / kBrickCells), kP2GThreads, p2g_lds(NCH, E3, batch), s>>>(
-            P, n, B.use, B.count, batch, x, v, r, Fc, Fd, cb, ce, A, M, err, exsc, held, st);
+            P, n, B.use, B.use_count, batch, x, v, r, Fc, Fd, cb, ce, A, M, err, exsc, held, st);
 }
 
 template <typename T, bool INTEG, bool WET = false>
@@ -1039,15 +1039,15 @@ hipError_t launch_integrate_p2g_store(const DevParams &P, int64_t n, int64_t K, 
     const size_t lds = sizeof(unsigned long long) * 4 * P.tile * P.tile * P.tile;
     if (mode == kFillGroup) {
         const size_t glds = sizeof(unsigned long long) * 4 * P.gtile * P.gtile * P.gtile;
-        k_p2g_direct<T, kGroupNT, true><<<group_grid(P), kGroupNT, glds, s>>>(P, n, B.use, B.count, x, v, r, Fc, Fd, cb,
+        k_p2g_direct<T, kGroupNT, true><<<group_grid(P), kGroupNT, glds, s>>>(P, n, B.use, B.use_count, x, v, r, Fc, Fd, cb,
                                                                               ce, err, st, 0);
         return hipGetLastError();
     }
     if (mode != kFillBlock)
-        k_p2g_direct<T, 64, false><<<grid, 64, lds, s>>>(P, n, B.use, B.count, x, v, r, Fc, Fd, cb, ce, err, st,
+        k_p2g_direct<T, 64, false><<<grid, 64, lds, s>>>(P, n, B.use, B.use_count, x, v, r, Fc, Fd, cb, ce, err, st,
                                                          mode == kFillBoth ? 1 : 0);
     if (mode != kFillWave)
-        k_p2g_direct<T, 256, false><<<grid, 256, lds, s>>>(P, n, B.use, B.count, x, v, r, Fc, Fd, cb, ce, err, st,
+        k_p2g_direct<T, 256, false><<<grid, 256, lds, s>>>(P, n, B.use, B.use_count, x, v, r, Fc, Fd, cb, ce, err, st,
                                                            mode == kFillBoth ? 2 : 0);
     return hipGetLastError();
 }
@@ -1127,9 +1127,9 @@ hipError_t launch_p2g_real(const DevParams &P, int64_t n, int64_t K, const doubl
         unsigned long long *f = reinterpret_cast<unsigned long long *>(fx);
         const unsigned g = brick_grid(bricks);
         if (nch == 4)
-            k_p2g_real<4><<<g, kP2GThreads, lds, s>>>(P, n, B.use, B.count, x, v, r, cb, ce, part, nb, f);
+            k_p2g_real<4><<<g, kP2GThreads, lds, s>>>(P, n, B.use, B.use_count, x, v, r, cb, ce, part, nb, f);
         else
-            k_p2g_real<1><<<g, kP2GThreads, lds, s>>>(P, n, B.use, B.count, x, v, r, cb, ce, part, nb, f);
+            k_p2g_real<1><<<g, kP2GThreads, lds, s>>>(P, n, B.use, B.use_count, x, v, r, cb, ce, part, nb, f);
     } else {
         k_fix_scale<<<1, 256, 0, s>>>(part, nb, nch);
     }
@@ -1158,7 +1158,7 @@ __global__ void __launch_bounds__(256) k_g2p_vjp_grid(DevParams P, int64_t n, co
                                                       const unsigned long long *__restrict__ gmax)
 {
     extern __shared__ unsigned long long itile[];
-    const int64_t b = brick_of_block(brick_count(P), bl, bcnt);
+    const int64_t b = brick_of_block(bl, bcnt);
     if (b < 0 && (FUSED || blockIdx.x != 0)) return;
     double sc4[4];
     if (FUSED)
@@ -1232,7 +1232,7 @@ hipError_t launch_g2p_vjp_grid(const DevParams &P, int64_t n, int64_t K, const d
     if (n > 0) {
         const int64_t bricks = K / kBrickCells;
         const size_t lds = sizeof(unsigned long long) * (size_t)P.tile * P.tile * P.tile;
-        k_g2p_vjp_grid<false><<<brick_grid(bricks), 256, lds, s>>>(P, n, B.use, B.count, x, A, gaf, cb, ce, part, nb,
+        k_g2p_vjp_grid<false><<<brick_grid(bricks), 256, lds, s>>>(P, n, B.use, B.use_count, x, A, gaf, cb, ce, part, nb,
                                                                    reinterpret_cast<unsigned long long *>(fx),
                                                                    nullptr, nullptr);
     } else {
@@ -1254,7 +1254,7 @@ hipError_t launch_rollout_p2g(const DevParams &P, int64_t n, int64_t K, const do
                               hipStream_t s)
 {
     const size_t lds = sizeof(unsigned long long) * (size_t)P.tile * P.tile * P.tile;
-    k_p2g_real<1><<<brick_grid(K / kBrickCells), kP2GThreads, lds, s>>>(P, n, B.use, B.count, x, nullptr, r, cb, ce, part,
+    k_p2g_real<1><<<brick_grid(K / kBrickCells), kP2GThreads, lds, s>>>(P, n, B.use, B.use_count, x, nullptr, r, cb, ce, part,
                                                                         nb, reinterpret_cast<unsigned long long *>(fx));
     return hipGetLastError();
 }
@@ -1264,7 +1264,7 @@ hipError_t launch_rollout_galpha(const DevParams &P, int64_t n, int64_t K, const
                                  int64_t *fx2, double *part, const unsigned long long *gmax, hipStream_t s)
 {
     const size_t lds = sizeof(unsigned long long) * (size_t)P.tile * P.tile * P.tile;
-    k_g2p_vjp_grid<true><<<brick_grid(K / kBrickCells), 256, lds, s>>>(P, n, B.use, B.count, x, nullptr, gaf, cb, ce,
+    k_g2p_vjp_grid<true><<<brick_grid(K / kBrickCells), 256, lds, s>>>(P, n, B.use, B.use_count, x, nullptr, gaf, cb, ce,
                                                                        part, 0,
                                                                        reinterpret_cast<unsigned long long *>(fx2), fx,
                                                                        gmax);
