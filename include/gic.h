@@ -197,7 +197,7 @@ gic_status gic_destroy(gic_ctx *ctx);
  * clear != 0 resets the latch. */
 gic_status gic_get_error(gic_ctx *ctx, void *stream, int32_t *code, int64_t *index, int32_t clear);
 
-/* ---- a1: binning and stable radix sort -----------------------------------
+/* ---- a1: binning and stable counting sort ---------------------------------
  * Neighbour search support for the contact test of Sec. 3.1.
  *   x           3n positions (any order).
  *   key         out, n: cell key of granule i, cell coordinate per axis
@@ -218,7 +218,8 @@ gic_status gic_sort_cells(gic_ctx *ctx, int64_t n, const double *x, uint32_t *ke
  * same tables use it instead of building their own, until the next
  * gic_sort_cells, stepping call or gic_brick_list.  The caller must not
  * change the tables' contents meanwhile.  Without this call every brick
- * kernel call builds the list (three small kernels) itself. */
+ * kernel call takes every brick of the box if that is small, or builds the
+ * list (one or two small kernels) itself. */
 gic_status gic_brick_list(gic_ctx *ctx, const int32_t *cell_begin, const int32_t *cell_end, void *stream);
 
 /* Gather granule arrays into sorted order: out[q] = in[order[q]] for x, v

@@ -10,7 +10,7 @@
 namespace gic {
 
 // Granules whose key changed since the last sort that the incremental path
-// takes (more go through the radix passes).
+// takes (more: everything is counted again).
 constexpr int kChgCap = 4096;
 
 // Sort scratch owned by a context.
