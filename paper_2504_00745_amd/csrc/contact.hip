@@ -1486,9 +1486,10 @@ static void contact_kernel(const DevParams &P, int64_t n, const double *x, const
     size_t lds = contact_lds_bytes(cap, NT);
     AdjArgs At = A;
     if (KIND == kMove || KIND == kReverse) {
-        // the node tile after the other arrays, if it fits
+        // the node tile after the other arrays, if it fits (beside a wave's
+        // few kilobytes only a small one: 10^3 nodes would leave four waves per CU)
         const size_t at = (lds + 15) / 16 * 16, end = at + sizeof(FluidNode) * P.tile * P.tile * P.tile;
-        At.tile_at = end <= 65536 ? (int)at : 0;
+        At.tile_at = end <= (NT == 64 ? at + 8192 : 65536) ? (int)at : 0;
         if (At.tile_at) lds = end;
     }
     k_contact_lds<T, KIND, NT, false><<<brick_grid(nbricks), NT, lds, s>>>(
