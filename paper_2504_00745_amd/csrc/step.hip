@@ -185,8 +185,10 @@ __global__ void __launch_bounds__(NT) k_gather(DevParams P, int64_t n, const int
         }
     }
     __syncthreads();
-    auto gather = [&](int64_t q) {
-        if (q != q0) fetch(q);
+    // fetched: granule q's state is the one fetched before the tile.  Its place does
+    // not tell: an empty first brick begins where the wave's next brick does.
+    auto gather = [&](int64_t q, bool fetched) {
+        if (!fetched) fetch(q);
         if ((uint64_t)s >= (uint64_t)n) return;  // not a permutation of [0, n): position q left untouched
         for (int a = 0; a < 3; ++a) {
             xo[a * n + q] = xa[a];
@@ -259,10 +261,10 @@ __global__ void __launch_bounds__(NT) k_gather(DevParams P, int64_t n, const int
         }
         if (af) af[q] = a;
     };
-    for (int64_t q = q0; q < ge; q += kStep) gather(q);
+    for (int64_t q = q0; q < ge; q += kStep) gather(q, q == q0);
     if (GROUP)
         for (int w = (tid >> 6) + NT / 64; w < kBricks; w += NT / 64)
-            for (int64_t q = (int64_t)s_beg[w] + (tid & 63); q < s_end[w]; q += 64) gather(q);
+            for (int64_t q = (int64_t)s_beg[w] + (tid & 63); q < s_end[w]; q += 64) gather(q, false);
 }
 
 // Threads per workgroup: see fill_mode.
