@@ -741,8 +741,8 @@ k_contact_lds(DevParams P, int64_t n, const int32_t *__restrict__ bl,
     int64_t slot = 0, b;  // the brick's place in the list, and the (first) brick
     if constexpr (GROUP) {
         static_assert(KIND == kForce, "leave() is of one brick");
-        const int64_t grp = group_of_block(P);
-        if (grp < 0) return;
+        const Group grp = group_of_block(P);
+        if (grp.id < 0) return;
         b = brick_of_group(P, grp, 0);
         const int64_t t = tid < kBricks ? brick_of_group(P, grp, tid) : -1;
         int32_t beg = 0, end = 0;

@@ -149,25 +149,44 @@ struct DevParams {
 // Kernels over groups of kGroup^3 bricks, one workgroup per group of the box:
 // the XCDs take the groups' x-rows in turn (a bed fills part of the box, so
 // contiguous eighths would leave XCDs idle; the groups of a row, neighbours in
-// the grid, share an L2).  group_grid(P) workgroups; group_of_block gives the
-// group or -1.
+// the grid, share an L2).  Where a layer has an even number of rows, or a row an
+// even number of groups, each layer starts one further on: otherwise the groups
+// of an upright sheet lie whole eights of rows or whole fours of groups apart,
+// and all fall to one XCD or to one of the shader engines that its workgroups
+// go to in turn (2.1 million granules in a sheet two bricks thick: normal to y,
+// FP32 gather 427 -> 120, contact 751 -> 146, P2G 544 -> 134 us; normal to x
+// 255 -> 120, 395 -> 146, 290 -> 134).
+// group_grid(P) workgroups; group_of_block gives the group, its number -1 for
+// none.  (Its place rather than the number alone: 64-bit divisions by the box's
+// edges would be most of what a workgroup without granules does.)
 constexpr int kGroup = 2;
+
+struct Group {
+    int32_t x, y, z;
+    int64_t id;
+};
 
 inline unsigned group_grid(const DevParams &P) { return xcd_grid((int64_t)P.ng[1] * P.ng[2]) * (unsigned)P.ng[0]; }
 
-__device__ inline int64_t group_of_block(const DevParams &P)
+__host__ __device__ inline Group group_at(const int32_t ng[3], uint32_t block)
 {
-    const uint32_t j = blockIdx.x / kXcds;  // in the XCD's order
-    const int64_t row = (int64_t)(j / P.ng[0]) * kXcds + blockIdx.x % kXcds;
-    return row < (int64_t)P.ng[1] * P.ng[2] ? row * P.ng[0] + j % P.ng[0] : -1;
+    const uint32_t nx = (uint32_t)ng[0], ny = (uint32_t)ng[1];
+    const uint32_t j = block / kXcds, slot = j / nx, row = slot * kXcds + block % kXcds, z = row / ny;
+    uint32_t x = j - slot * nx, y = row - z * ny;
+    if (z >= (uint32_t)ng[2]) return {0, 0, 0, -1};
+    if ((nx & 1u) == 0u) x = (x + z) % nx;
+    if ((ny & 1u) == 0u) y = (y + z) % ny;
+    return {(int32_t)x, (int32_t)y, (int32_t)z, ((int64_t)z * ny + y) * nx + x};
 }
 
+__device__ inline Group group_of_block(const DevParams &P) { return group_at(P.ng, blockIdx.x); }
+
 // Brick w (0 .. kGroup^3 - 1) of a group, or -1 outside the box.
-__device__ inline int64_t brick_of_group(const DevParams &P, int64_t g, int w)
+__device__ inline int64_t brick_of_group(const DevParams &P, const Group &g, int w)
 {
-    const int32_t bx = (int32_t)(g % P.ng[0]) * kGroup + w % kGroup;
-    const int32_t by = (int32_t)((g / P.ng[0]) % P.ng[1]) * kGroup + (w / kGroup) % kGroup;
-    const int32_t bz = (int32_t)(g / ((int64_t)P.ng[0] * P.ng[1])) * kGroup + w / (kGroup * kGroup);
+    const int32_t bx = g.x * kGroup + w % kGroup;
+    const int32_t by = g.y * kGroup + (w / kGroup) % kGroup;
+    const int32_t bz = g.z * kGroup + w / (kGroup * kGroup);
     if (bx >= P.nb[0] || by >= P.nb[1] || bz >= P.nb[2]) return -1;
     return ((int64_t)bz * P.nb[1] + by) * P.nb[0] + bx;
 }

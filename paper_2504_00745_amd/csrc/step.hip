@@ -108,8 +108,8 @@ __global__ void __launch_bounds__(NT) k_gather(DevParams P, int64_t n, const int
     int64_t b;             // the tile's (first) brick
     int32_t gb = 0, ge = 0;
     if (GROUP) {
-        const int64_t grp = group_of_block(P);
-        if (grp < 0) return;
+        const Group grp = group_of_block(P);
+        if (grp.id < 0) return;
         b = brick_of_group(P, grp, 0);
         const int64_t t = tid < kBricks ? brick_of_group(P, grp, tid) : -1;
         if (t >= 0) {

@@ -400,11 +400,12 @@ __global__ void __launch_bounds__(NT) k_p2g_direct(DevParams P, int64_t n, const
     const int tid = threadIdx.x;
     int64_t slot, b;  // the tile's, and its (first) brick
     if (GROUP) {
-        slot = group_of_block(P);
-        if (slot < 0) return;
-        b = brick_of_group(P, slot, 0);
+        const Group grp = group_of_block(P);
+        if (grp.id < 0) return;
+        slot = grp.id;
+        b = brick_of_group(P, grp, 0);
         int32_t beg = 0, end = 0;
-        const int64_t t = tid < kGroup * kGroup * kGroup ? brick_of_group(P, slot, tid) : -1;
+        const int64_t t = tid < kGroup * kGroup * kGroup ? brick_of_group(P, grp, tid) : -1;
         if (t >= 0) {
             beg = cb[t * kBrickCells];
             end = ce[t * kBrickCells + kBrickCells - 1];
