@@ -155,7 +155,7 @@ struct DevParams {
 // and all fall to one XCD or to one of the shader engines that its workgroups
 // go to in turn (2.1 million granules in a sheet two bricks thick: normal to y,
 // FP32 gather 427 -> 120, contact 751 -> 146, P2G 544 -> 134 us; normal to x
-// 255 -> 120, 395 -> 146, 290 -> 134).
+// 256 -> 130, 395 -> 159, 301 -> 142).
 // group_grid(P) workgroups; group_of_block gives the group, its number -1 for
 // none.  (Its place rather than the number alone: 64-bit divisions by the box's
 // edges would be most of what a workgroup without granules does.)
