@@ -408,7 +408,7 @@ gic_status gic_create(const gic_params *p, int64_t n_max, gic_ctx **out)
     ok &= hipMalloc(&c->part, sizeof(double) * kSumParts) == hipSuccess;
     c->bricks.nbricks = c->K / kBrickCells;
     ok &= hipMalloc(&c->bricks.list, sizeof(int32_t) * (c->bricks.nbricks > 0 ? c->bricks.nbricks : 1)) == hipSuccess;
-    ok &= hipMalloc(&c->bricks.count, sizeof(int32_t)) == hipSuccess;
+    ok &= hipMalloc(&c->bricks.count, sizeof(BrickSeen)) == hipSuccess;
     if (ok && c->bricks.nbricks > 0 && c->bricks.nbricks <= kBoxBricks) {
         int32_t h[kBoxBricks + 1];
         const size_t bytes = sizeof(int32_t) * (size_t)(c->bricks.nbricks + 1);
@@ -425,11 +425,9 @@ gic_status gic_create(const gic_params *p, int64_t n_max, gic_ctx **out)
     ok &= hipMalloc(&c->shell.dev, sizeof(int32_t) * 2) == hipSuccess;
     if (ok) ok = hipMemset(c->shell.dev, 0, sizeof(int32_t) * 2) == hipSuccess;
     ok &= hipHostMalloc(&c->shell.host, sizeof(int32_t) * 2, hipHostMallocDefault) == hipSuccess;
-    if (ok) {
-        c->shell.host[0] = 0;  // no record yet: the largest shell array
-        c->shell.host[1] = 0;  // and no count of occupied bricks
-        c->bricks.seen = c->shell.host + 1;
-    }
+    if (ok) c->shell.host[0] = 0;  // no record yet: the largest shell array
+    ok &= hipHostMalloc(&c->bricks.seen, sizeof(BrickSeen), hipHostMallocDefault) == hipSuccess;
+    if (ok) *c->bricks.seen = {0, 0};  // nor a count of occupied bricks
     if (ok && tiles_assemble(p)) {
         // one 4-channel node tile per occupied brick (at most min(bricks, n));
         // beyond 8 GiB the stepping path keeps the cleared grids and atomics
@@ -525,6 +523,7 @@ gic_status gic_destroy(gic_ctx *c)
     (void)hipFree(c->bricks.box);
     (void)hipFree(c->bricks.sums);
     (void)hipFree(c->bricks.slot_of);
+    (void)hipHostFree(c->bricks.seen);
     (void)hipFree(c->p2gs.esc);
     (void)hipFree(c->p2gs.tiles);
     (void)hipFree(const_cast<int32_t *>(c->p2gs.cover));

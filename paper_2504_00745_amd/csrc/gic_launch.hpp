@@ -29,18 +29,25 @@ struct SortScratch {
                          // no key changed (1: order, ranges and bricks of the last sort hold), spare
 };
 
+// What the host learns of a brick list, without waiting: its occupied bricks and
+// the granules it was built for.  A record in flight when the next bed's list is
+// built names its own bed.
+struct BrickSeen {
+    int32_t count, n;
+};
+
 // Occupied bricks of a set of cell ranges, in brick order (see
 // brick_of_block), built by launch_brick_list before the brick kernels.
 struct BrickList {
     int32_t *list;     // [nbricks]
-    int32_t *count;    // [1]
+    int32_t *count;    // [2] their number, and the granules of the list (a BrickSeen)
     uint32_t *sums;    // [<= 1024] block totals
     int32_t *box;      // [nbricks + 1] every brick of the box and their number, or NULL (see box_list)
     const int32_t *use, *use_count;  // what the brick kernels run over: list and count, or the box
     int32_t *slot_of;  // [nbricks] position of each brick in list, -1 if empty
     int64_t nbricks;
-    int32_t *seen;     // [1] pinned host: a copy of count (see brick_fill), of a list of seen_n granules
-    int64_t seen_n;
+    BrickSeen *seen;   // pinned host: a copy of an earlier list's count (see brick_fill)
+    int64_t seen_n;    // granules of the last list
     unsigned calls;
 };
 
@@ -131,17 +138,18 @@ inline bool record_copy(SizeRecord *r)
 
 // The granules that an occupied brick holds on average, for the shape of the
 // brick kernels: from the last count of occupied bricks that reached the host
-// (every 16th list of n granules copies it, read without waiting), or, before
-// the first (known false), the granules of radius r_max that its 64 cells hold
-// on a cubic lattice.
+// (every 16th list copies it, and the first after one of another number of
+// granules; read without waiting), or, before the first of n granules (known
+// false), the granules of radius r_max that its 64 cells hold on a cubic lattice.
 struct BrickFill {
     double avg;
     bool known;
 };
 inline BrickFill brick_fill(const DevParams &P, int64_t n, const BrickList &B)
 {
-    const int32_t seen = B.seen && B.seen_n == n ? *(volatile const int32_t *)B.seen : 0;
-    if (seen > 0) return {(double)n / seen, true};
+    const volatile BrickSeen *seen = B.seen;
+    const int32_t count = seen && seen->n == n ? seen->count : 0;
+    if (count > 0) return {(double)n / count, true};
     const double e = 0.5 * P.cell / P.r_max;
     return {kBrickCells * ((e * e) * e), false};
 }

@@ -284,6 +284,13 @@ __global__ void __launch_bounds__(256) k_cell_count(const uint32_t *__restrict__
 // counts are reset to zero for the next sort by k_cell_order).
 constexpr int64_t kDirectScan = 32768;
 
+// A list's count and the granules it is of (BrickSeen).
+__device__ inline void put_count(int32_t *count, int32_t nocc, int32_t n)
+{
+    count[0] = nocc;
+    count[1] = n;
+}
+
 __global__ void __launch_bounds__(kScanThreads) k_scan_down_ranges(uint32_t *__restrict__ cnt,
                                                                    uint32_t *__restrict__ begin,
                                                                    uint32_t *__restrict__ end, int64_t len,
@@ -292,7 +299,7 @@ __global__ void __launch_bounds__(kScanThreads) k_scan_down_ranges(uint32_t *__r
                                                                    int32_t *__restrict__ ctl, int keep,
                                                                    int32_t *__restrict__ list,
                                                                    int32_t *__restrict__ count,
-                                                                   int32_t *__restrict__ slot_of)
+                                                                   int32_t *__restrict__ slot_of, int32_t n)
 {
     if (keep && ctl[2]) return;  // ranges unchanged (and no changed granule to uncount)
     if (blockIdx.x == 0 && threadIdx.x == 0) ctl[0] = 0;  // no changed granules counted for the next sort
@@ -373,7 +380,7 @@ __global__ void __launch_bounds__(kScanThreads) k_scan_down_ranges(uint32_t *__r
         carry += total;
         __syncthreads();  // s_occ is rewritten by the next round
     }
-    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) *count = (int32_t)nocc;
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) put_count(count, (int32_t)nocc, n);
 }
 
 // Granule i to its place in its cell, in order of arrival; the key of the
@@ -713,7 +720,7 @@ constexpr int64_t kBricksOneGroup = 2048;
 __global__ void __launch_bounds__(kScanThreads) k_brick_list(int nbricks, const int32_t *__restrict__ cb,
                                                              const int32_t *__restrict__ ce,
                                                              int32_t *__restrict__ list, int32_t *__restrict__ count,
-                                                             int32_t *__restrict__ slot_of)
+                                                             int32_t *__restrict__ slot_of, int32_t n)
 {
     constexpr int kRounds = (int)(kBricksOneGroup / kScanThreads);
     __shared__ uint32_t lds[kScanThreads / 64];
@@ -738,14 +745,15 @@ __global__ void __launch_bounds__(kScanThreads) k_brick_list(int nbricks, const 
         slot_of[b0 + u] = occ ? (int32_t)at : -1;
         if (occ) list[at++] = b0 + u;
     }
-    if (threadIdx.x == 0) *count = (int32_t)total;
+    if (threadIdx.x == 0) put_count(count, (int32_t)total, n);
 }
 
 // Each workgroup sums the counts before its own (at most kScanThreads words).
 __global__ void __launch_bounds__(256) k_brick_scatter(int64_t nbricks, int64_t per_block,
                                                        const int32_t *__restrict__ cb, const int32_t *__restrict__ ce,
                                                        const uint32_t *__restrict__ sums, int32_t *__restrict__ list,
-                                                       int32_t *__restrict__ count, int32_t *__restrict__ slot_of)
+                                                       int32_t *__restrict__ count, int32_t *__restrict__ slot_of,
+                                                       int32_t n)
 {
     __shared__ uint32_t lds[4];
     __shared__ uint32_t s_base;
@@ -766,7 +774,7 @@ __global__ void __launch_bounds__(256) k_brick_scatter(int64_t nbricks, int64_t 
         if (b < hi) slot_of[b] = f ? (int32_t)(base + inc - 1) : -1;
         base += total;
     }
-    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) *count = (int32_t)base;
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) put_count(count, (int32_t)base, n);
 }
 
 }  // namespace
@@ -775,16 +783,15 @@ namespace {
 
 constexpr unsigned kLoopGrid = 2048;  // workgroups of 256 that the chip holds at once
 
-// Every 16th list of n granules leaves its count in pinned host memory (see
-// brick_fill); a change of n clears what a list of other granules left.
+// Every 16th list, and the first of another number of granules, leaves its
+// record in pinned host memory (see brick_fill).
 hipError_t brick_count_copy(BrickList &B, int64_t n, hipStream_t s)
 {
     hipError_t e = hipGetLastError();
     if (n <= 0 || !B.seen) return e;
     const bool copy = B.seen_n != n || (B.calls++ & 15u) == 0u;
-    if (B.seen_n != n) *(volatile int32_t *)B.seen = 0;
     B.seen_n = n;
-    if (copy && e == hipSuccess) e = hipMemcpyAsync(B.seen, B.count, sizeof(int32_t), hipMemcpyDeviceToHost, s);
+    if (copy && e == hipSuccess) e = hipMemcpyAsync(B.seen, B.count, sizeof(BrickSeen), hipMemcpyDeviceToHost, s);
     return e;
 }
 
@@ -843,7 +850,7 @@ hipError_t launch_sort_cells(const DevParams &P, int64_t n, const double *x, uin
         k_scan_reduce<<<nb, kScanThreads, 0, s>>>(cnt, K, chunk, S.sums, S.sums + kScanThreads,
                                                   keep ? S.ctl : nullptr);
     k_scan_down_ranges<<<nb, kScanThreads, 0, s>>>(cnt, begin, end, K, chunk, direct ? nullptr : S.sums,
-                                                   S.sums + kScanThreads, S.ctl, keep, B.list, B.count, B.slot_of);
+                                                   S.sums + kScanThreads, S.ctl, keep, B.list, B.count, B.slot_of, (int32_t)n);
     if (n > 0) {
         k_cell_place<<<gl, 256, 0, s>>>(key, n, begin, S.slot, S.tmp, skeys, ctl, keep);
         k_cell_order<<<gl, 256, 0, s>>>(n, skeys, begin, end, S.tmp, S.tmp2, order, ctl, keep, direct ? cnt : nullptr,
@@ -873,7 +880,7 @@ hipError_t launch_rollout_sort(const DevParams &P, int64_t n, const double *xv, 
     const int nc = (int)((K + chunk - 1) / chunk);
     if (!direct) k_scan_reduce<<<nc, kScanThreads, 0, s>>>(S.cnt, K, chunk, S.sums, S.sums + kScanThreads, nullptr);
     k_scan_down_ranges<<<nc, kScanThreads, 0, s>>>(S.cnt, begin, end, K, chunk, direct ? nullptr : S.sums,
-                                                   S.sums + kScanThreads, S.ctl, 0, B.list, B.count, B.slot_of);
+                                                   S.sums + kScanThreads, S.ctl, 0, B.list, B.count, B.slot_of, (int32_t)n);
     k_cell_place<<<gl, 256, 0, s>>>(key, n, begin, S.slot, S.tmp, skeys, nullptr, 0);
     uint32_t *cnt = direct ? S.cnt : nullptr;
     if (gxv)
@@ -895,14 +902,14 @@ hipError_t launch_brick_list(const int32_t *cb, const int32_t *ce, BrickList &B,
     const int64_t nb = B.nbricks;
     if (nb <= 0) return hipSuccess;
     if (nb <= kBricksOneGroup) {
-        k_brick_list<<<1, kScanThreads, 0, s>>>((int)nb, cb, ce, B.list, B.count, B.slot_of);
+        k_brick_list<<<1, kScanThreads, 0, s>>>((int)nb, cb, ce, B.list, B.count, B.slot_of, (int32_t)n);
         return brick_count_copy(B, n, s);
     }
     int64_t per = 1024;
     while ((nb + per - 1) / per > kScanThreads) per *= 2;
     const int blocks = (int)((nb + per - 1) / per);
     k_brick_count<<<blocks, 256, 0, s>>>(nb, per, cb, ce, B.sums);
-    k_brick_scatter<<<blocks, 256, 0, s>>>(nb, per, cb, ce, B.sums, B.list, B.count, B.slot_of);
+    k_brick_scatter<<<blocks, 256, 0, s>>>(nb, per, cb, ce, B.sums, B.list, B.count, B.slot_of, (int32_t)n);
     return brick_count_copy(B, n, s);
 }
 
