@@ -245,7 +245,7 @@ hipError_t brick_list(gic_ctx *c, int64_t n, const int32_t *cb, const int32_t *c
     }
     c->bl_pin = false;
     c->rng_ok = false;  // the brick list is now that of these tables
-    return launch_brick_list(cb, ce, c->bricks, n, s);
+    return launch_brick_list(c->dp, cb, ce, c->bricks, n, s);
 }
 
 // Sort of a stepping call: keeps the neighbour list when the last step's
@@ -409,6 +409,7 @@ gic_status gic_create(const gic_params *p, int64_t n_max, gic_ctx **out)
     c->bricks.nbricks = c->K / kBrickCells;
     ok &= hipMalloc(&c->bricks.list, sizeof(int32_t) * (c->bricks.nbricks > 0 ? c->bricks.nbricks : 1)) == hipSuccess;
     ok &= hipMalloc(&c->bricks.count, sizeof(BrickSeen)) == hipSuccess;
+    if (ok) ok = hipMemset(c->bricks.count, 0, sizeof(BrickSeen)) == hipSuccess;
     if (ok && c->bricks.nbricks > 0 && c->bricks.nbricks <= kBoxBricks) {
         int32_t h[kBoxBricks + 1];
         const size_t bytes = sizeof(int32_t) * (size_t)(c->bricks.nbricks + 1);
@@ -427,7 +428,7 @@ gic_status gic_create(const gic_params *p, int64_t n_max, gic_ctx **out)
     ok &= hipHostMalloc(&c->shell.host, sizeof(int32_t) * 2, hipHostMallocDefault) == hipSuccess;
     if (ok) c->shell.host[0] = 0;  // no record yet: the largest shell array
     ok &= hipHostMalloc(&c->bricks.seen, sizeof(BrickSeen), hipHostMallocDefault) == hipSuccess;
-    if (ok) *c->bricks.seen = {0, 0};  // nor a count of occupied bricks
+    if (ok) *c->bricks.seen = {0, 0, 0, 0};  // nor a count of occupied bricks
     if (ok && tiles_assemble(p)) {
         // one 4-channel node tile per occupied brick (at most min(bricks, n));
         // beyond 8 GiB the stepping path keeps the cleared grids and atomics

@@ -30,17 +30,21 @@ struct SortScratch {
 };
 
 // What the host learns of a brick list, without waiting: its occupied bricks and
-// the granules it was built for.  A record in flight when the next bed's list is
-// built names its own bed.
+// the granules it was built for (a record in flight when the next bed's list is
+// built names its own bed), and, for beds large enough to be run by groups, the
+// groups of a sample that hold granules and their occupied bricks (0: none taken).
 struct BrickSeen {
     int32_t count, n;
+    int32_t groups, bricks;
 };
+// Groups of the sample; a fixed number, so that taking it costs the same in any box.
+constexpr int kGroupSample = 4096;
 
 // Occupied bricks of a set of cell ranges, in brick order (see
 // brick_of_block), built by launch_brick_list before the brick kernels.
 struct BrickList {
     int32_t *list;     // [nbricks]
-    int32_t *count;    // [2] their number, and the granules of the list (a BrickSeen)
+    int32_t *count;    // [4] their number, and the rest of a BrickSeen
     uint32_t *sums;    // [<= 1024] block totals
     int32_t *box;      // [nbricks + 1] every brick of the box and their number, or NULL (see box_list)
     const int32_t *use, *use_count;  // what the brick kernels run over: list and count, or the box
@@ -57,7 +61,8 @@ struct BrickList {
 void box_list(int64_t n, int32_t *out);
 // n: granules of the tables, or -1 when the caller does not know (no copy of
 // the count to the host then).
-hipError_t launch_brick_list(const int32_t *cb, const int32_t *ce, BrickList &B, int64_t n, hipStream_t s);
+hipError_t launch_brick_list(const DevParams &P, const int32_t *cb, const int32_t *ce, BrickList &B, int64_t n,
+                             hipStream_t s);
 
 // Persistent neighbour list of the contact stage (owned by a context): for
 // every granule (sorted position q) the sorted positions of the granules
@@ -144,14 +149,15 @@ inline bool record_copy(SizeRecord *r)
 struct BrickFill {
     double avg;
     bool known;
+    double full;  // occupied bricks of a group that holds granules, 0 where not known
 };
 inline BrickFill brick_fill(const DevParams &P, int64_t n, const BrickList &B)
 {
     const volatile BrickSeen *seen = B.seen;
     const int32_t count = seen && seen->n == n ? seen->count : 0;
-    if (count > 0) return {(double)n / count, true};
+    if (count > 0) return {(double)n / count, true, seen->groups > 0 ? (double)seen->bricks / seen->groups : 0.0};
     const double e = 0.5 * P.cell / P.r_max;
-    return {kBrickCells * ((e * e) * e), false};
+    return {kBrickCells * ((e * e) * e), false, 0.0};
 }
 // How the gather, the direct contact and the direct P2G run.
 //
@@ -177,7 +183,12 @@ inline BrickFill brick_fill(const DevParams &P, int64_t n, const BrickList &B)
 // 15.8 + 17.7 + 14.7 us); the contact and the FP64 gather, whose workgroups
 // hold more registers and LDS, from 16,384 (8,820 bricks: 42 against 35 us and
 // 40 against 34; 13,824: 50 against 51; 18,432: 78.4 against 78.0; 65,536: 231
-// against 261 and 226 against 257).
+// against 261 and 226 against 257).  And where a group that holds granules holds
+// five of its eight bricks or more: fewer do not share enough.  Steps in FP32 by
+// waves against groups: columns of single bricks (two of eight) 285 and 456 us,
+// bricks at random, a quarter of the box 292 and 375, 3/8 400 and 492, half 482
+// and 535, three quarters 671 and 612; sheets one brick thick (four of eight)
+// 398 and 392, 507 and 567, 638 and 606 us, normal to z, x and y.
 //
 // kFillBoth: not known yet (a first call) and plausible: both kernels are
 // launched and the device's count of occupied bricks picks one.
@@ -185,6 +196,7 @@ constexpr int64_t kWaveFill = 80;
 constexpr int64_t kWaveBricks = 1024;
 constexpr int64_t kGroupBricks = 4096;
 constexpr int64_t kGroupShells = 16384;
+constexpr double kGroupFull = 5.0;
 constexpr int kGroupNT = 256;
 enum FillMode { kFillBlock = 0, kFillWave = 1, kFillBoth = 2, kFillGroup = 3 };
 // least: occupied bricks from which the caller takes groups.
@@ -193,7 +205,7 @@ inline FillMode fill_mode(const DevParams &P, int64_t n, const BrickList &B, int
     const BrickFill f = brick_fill(P, n, B);
     if (f.avg > kWaveFill || n < kWaveBricks * kBrickCells) return kFillBlock;
     if (!f.known) return kFillBoth;
-    return (double)n >= (double)least * f.avg ? kFillGroup : kFillWave;
+    return (double)n >= (double)least * f.avg && f.full >= kGroupFull ? kFillGroup : kFillWave;
 }
 template <typename T>
 hipError_t launch_contact(const DevParams &P, int64_t n, const double *x, const double *v, const double *r,

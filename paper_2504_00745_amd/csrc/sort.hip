@@ -777,6 +777,43 @@ __global__ void __launch_bounds__(256) k_brick_scatter(int64_t nbricks, int64_t 
     if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) put_count(count, (int32_t)base, n);
 }
 
+// How full the groups are (see fill_mode), from kGroupSample groups spread over
+// the box, each at a place of its own in its share so that no bed's period falls
+// in with theirs.  One workgroup, on the lists whose record is copied only.
+__global__ void __launch_bounds__(1024) k_group_sample(int32_t nbx, int32_t nby, int32_t nbz,
+                                                       const int32_t *__restrict__ slot_of, int32_t *__restrict__ count)
+{
+    __shared__ uint32_t lds[1024 / 64];
+    const uint32_t ngx = (uint32_t)(nbx + kGroup - 1) / kGroup, ngy = (uint32_t)(nby + kGroup - 1) / kGroup;
+    const uint32_t groups = ngx * ngy * ((uint32_t)(nbz + kGroup - 1) / kGroup);  // below 2^31, as the bricks are
+    uint32_t held = 0, occ = 0;
+#pragma unroll
+    for (int u = 0; u < kGroupSample / 1024; ++u) {
+        const uint32_t t = threadIdx.x + u * 1024;
+        const uint32_t lo = (uint32_t)((uint64_t)t * groups / kGroupSample);
+        const uint32_t share = (uint32_t)((uint64_t)(t + 1) * groups / kGroupSample) - lo;
+        const uint32_t g = lo + (share > 1 ? (t * 2654435761u >> 8) % share : 0u);
+        const uint32_t gyz = g / ngx, gz = gyz / ngy;
+        const int32_t bx = (int32_t)(g - gyz * ngx) * kGroup, by = (int32_t)(gyz - gz * ngy) * kGroup;
+        const int32_t bz = (int32_t)gz * kGroup;
+        uint32_t c = 0;
+#pragma unroll
+        for (int w = 0; w < kGroup * kGroup * kGroup; ++w) {
+            const int32_t x = bx + w % kGroup, y = by + w / kGroup % kGroup, z = bz + w / (kGroup * kGroup);
+            if (share != 0u && x < nbx && y < nby && z < nbz)
+                c += slot_of[((int64_t)z * nby + y) * nbx + x] >= 0 ? 1u : 0u;
+        }
+        held += c != 0u ? 1u : 0u;
+        occ += c;
+    }
+    held = block_reduce_sum(held, lds);
+    occ = block_reduce_sum(occ, lds);
+    if (threadIdx.x == 0) {
+        count[2] = (int32_t)held;
+        count[3] = (int32_t)occ;
+    }
+}
+
 }  // namespace
 
 namespace {
@@ -785,12 +822,17 @@ constexpr unsigned kLoopGrid = 2048;  // workgroups of 256 that the chip holds a
 
 // Every 16th list, and the first of another number of granules, leaves its
 // record in pinned host memory (see brick_fill).
-hipError_t brick_count_copy(BrickList &B, int64_t n, hipStream_t s)
+hipError_t brick_count_copy(const DevParams &P, BrickList &B, int64_t n, hipStream_t s)
 {
     hipError_t e = hipGetLastError();
     if (n <= 0 || !B.seen) return e;
     const bool copy = B.seen_n != n || (B.calls++ & 15u) == 0u;
     B.seen_n = n;
+    // sampled where the bed may be run by groups, as far as is known
+    if (copy && n >= kWaveBricks * kBrickCells && B.nbricks >= kGroupBricks && brick_fill(P, n, B).avg <= kWaveFill) {
+        k_group_sample<<<1, 1024, 0, s>>>(P.nb[0], P.nb[1], P.nb[2], B.slot_of, B.count);
+        e = hipGetLastError();
+    }
     if (copy && e == hipSuccess) e = hipMemcpyAsync(B.seen, B.count, sizeof(BrickSeen), hipMemcpyDeviceToHost, s);
     return e;
 }
@@ -858,7 +900,7 @@ hipError_t launch_sort_cells(const DevParams &P, int64_t n, const double *x, uin
     }
     S.cur ^= 1;  // this sort's keys are the previous keys of the next
     S.last_n = n;
-    return brick_count_copy(B, n, s);
+    return brick_count_copy(P, B, n, s);
 }
 
 hipError_t launch_rollout_sort(const DevParams &P, int64_t n, const double *xv, const double *r, uint32_t *key,
@@ -892,10 +934,11 @@ hipError_t launch_rollout_sort(const DevParams &P, int64_t n, const double *xv, 
     *nb = (int)go;
     S.cur ^= 1;
     S.last_n = n;
-    return brick_count_copy(B, n, s);
+    return brick_count_copy(P, B, n, s);
 }
 
-hipError_t launch_brick_list(const int32_t *cb, const int32_t *ce, BrickList &B, int64_t n, hipStream_t s)
+hipError_t launch_brick_list(const DevParams &P, const int32_t *cb, const int32_t *ce, BrickList &B, int64_t n,
+                             hipStream_t s)
 {
     B.use = B.list;
     B.use_count = B.count;
@@ -903,14 +946,14 @@ hipError_t launch_brick_list(const int32_t *cb, const int32_t *ce, BrickList &B,
     if (nb <= 0) return hipSuccess;
     if (nb <= kBricksOneGroup) {
         k_brick_list<<<1, kScanThreads, 0, s>>>((int)nb, cb, ce, B.list, B.count, B.slot_of, (int32_t)n);
-        return brick_count_copy(B, n, s);
+        return brick_count_copy(P, B, n, s);
     }
     int64_t per = 1024;
     while ((nb + per - 1) / per > kScanThreads) per *= 2;
     const int blocks = (int)((nb + per - 1) / per);
     k_brick_count<<<blocks, 256, 0, s>>>(nb, per, cb, ce, B.sums);
     k_brick_scatter<<<blocks, 256, 0, s>>>(nb, per, cb, ce, B.sums, B.list, B.count, B.slot_of, (int32_t)n);
-    return brick_count_copy(B, n, s);
+    return brick_count_copy(P, B, n, s);
 }
 
 void box_list(int64_t n, int32_t *out)

@@ -1,6 +1,7 @@
 """What the host takes from the record of an earlier brick list (brick_fill,
 fill_mode), compiled for the host: a record counts for the number of granules
-that it names and for no other."""
+that it names and for no other, and groups of bricks are taken where they are
+full enough."""
 import os
 import subprocess
 
@@ -15,7 +16,7 @@ int main()
     DevParams P = {};
     P.cell = 2.0;
     P.r_max = 1.0;  // 64 granules a brick expected
-    BrickSeen seen = {100, 5000};
+    BrickSeen seen = {100, 5000, 0, 0};
     BrickList B = {};
     B.seen = &seen;
     B.seen_n = 7000;  // a list of 7,000 granules followed; its record has not arrived
@@ -42,3 +43,30 @@ def run(d, main, *args):
 
 def test_record_of_another_bed_is_not_taken(tmp_path):
     assert run(tmp_path, MAIN) == [[5000, 1, 50.0], [7000, 0, 64.0], [4999, 0, 64.0], [0, 0, 64.0]]
+
+
+MODES = r"""
+#include <cstdio>
+#include "gic_launch.hpp"
+using namespace gic;
+int main()
+{
+    DevParams P = {};
+    P.cell = 2.0;
+    P.r_max = 1.0;
+    BrickList B = {};
+    const int32_t rec[][4] = {{20000, 1000000, 4000, 8 * 4000}, {20000, 1000000, 4000, 5 * 4000}, {20000, 1000000, 4000, 19999},
+                              {20000, 1000000, 4000, 4000}, {20000, 1000000, 0, 0}, {4096, 300000, 700, 5000},
+                              {4095, 300000, 700, 5000}, {20000, 1000001, 4000, 8 * 4000}, {10000, 1000000, 4000, 8 * 4000}};
+    for (auto &r : rec) {
+        BrickSeen seen = {r[0], r[1], r[2], r[3]};
+        B.seen = &seen;
+        printf("%d\n", (int)fill_mode(P, r[1] == 1000001 ? 1000000 : r[1], B, kGroupBricks));
+    }
+}
+"""
+BLOCK, WAVE, BOTH, GROUP = range(4)
+
+
+def test_groups_where_they_are_full(tmp_path):
+    assert [m for m, in run(tmp_path, MODES)] == [GROUP, GROUP, WAVE, WAVE, WAVE, GROUP, WAVE, BOTH, BLOCK]
