@@ -401,6 +401,10 @@ gic_status gic_create(const gic_params *p, int64_t n_max, gic_ctx **out)
     if (ok) ok = hipMemset(c->sort.ctl, 0, sizeof(int32_t) * 4) == hipSuccess;
     ok &= hipMalloc(&c->sort.tmp, sizeof(int32_t) * nn) == hipSuccess;
     ok &= hipMalloc(&c->sort.tmp2, sizeof(int32_t) * nn) == hipSuccess;
+    c->sort.passes = sort_passes(c->K);
+    if (c->sort.passes > 2) ok &= hipMalloc(&c->sort.kB, sizeof(uint32_t) * nn) == hipSuccess;
+    ok &= hipMalloc(&c->sort.tcnt, sizeof(uint32_t) * 256 * sort_tiles_max(nn)) == hipSuccess;
+    ok &= hipMalloc(&c->sort.rowtot, sizeof(uint32_t) * 256) == hipSuccess;
     ok &= hipMalloc(&c->sort.sums, sizeof(uint32_t) * 2048) == hipSuccess;
     ok &= hipMalloc(&c->sort.cnt, sizeof(uint32_t) * (c->K > 0 ? c->K : 1)) == hipSuccess;
     if (ok) ok = hipMemset(c->sort.cnt, 0, sizeof(uint32_t) * (c->K > 0 ? c->K : 1)) == hipSuccess;
@@ -428,7 +432,7 @@ gic_status gic_create(const gic_params *p, int64_t n_max, gic_ctx **out)
     ok &= hipHostMalloc(&c->shell.host, sizeof(int32_t) * 2, hipHostMallocDefault) == hipSuccess;
     if (ok) c->shell.host[0] = 0;  // no record yet: the largest shell array
     ok &= hipHostMalloc(&c->bricks.seen, sizeof(BrickSeen), hipHostMallocDefault) == hipSuccess;
-    if (ok) *c->bricks.seen = {0, 0, 0, 0};  // nor a count of occupied bricks
+    if (ok) *c->bricks.seen = {};  // nor a count of occupied bricks
     if (ok && tiles_assemble(p)) {
         // one 4-channel node tile per occupied brick (at most min(bricks, n));
         // beyond 8 GiB the stepping path keeps the cleared grids and atomics
@@ -515,6 +519,9 @@ gic_status gic_destroy(gic_ctx *c)
     (void)hipFree(c->sort.ctl);
     (void)hipFree(c->sort.tmp);
     (void)hipFree(c->sort.tmp2);
+    (void)hipFree(c->sort.kB);
+    (void)hipFree(c->sort.tcnt);
+    (void)hipFree(c->sort.rowtot);
     (void)hipFree(c->sort.sums);
     (void)hipFree(c->sort.cnt);
     (void)hipFree(c->err);

@@ -20,6 +20,11 @@ struct SortScratch {
     int64_t last_n;      // granules of the last sort, -1 before the first
     uint32_t *slot;      // [n] place of each granule in its cell, in order of arrival
     int32_t *tmp, *tmp2; // [n] granules by cell, in order of arrival; second array of long cells
+                         // (digit passes: the values' buffers, and slot the keys' first)
+    uint32_t *kB;        // [n] the keys' second buffer (keys of more than two digits), or NULL
+    uint32_t *tcnt;      // [256][sort_tiles_max] digit counts, then output offsets, of each tile in a digit pass
+    uint32_t *rowtot;    // [256] keys with each digit in a digit pass
+    int passes;          // 8-bit digits of the keys
     uint32_t *sums;      // [2 x 1024] granules and occupied bricks of the scan's chunks
     uint32_t *cnt;       // [K] granules per cell; zero between sorts
     uint64_t *chg;       // [kChgCap] changed granules as (key << 32 | position), in arrival order
@@ -33,18 +38,24 @@ struct SortScratch {
 // the granules it was built for (a record in flight when the next bed's list is
 // built names its own bed), and, for beds large enough to be run by groups, the
 // groups of a sample that hold granules and their occupied bricks (0: none taken).
+// Of the last sort: the granules whose key had changed since the one before (all,
+// where they were not compared); of the last sampled, those in cells larger than
+// its sort_limit.
 struct BrickSeen {
     int32_t count, n;
     int32_t groups, bricks;
+    int32_t changed, dense;
 };
-// Groups of the sample; a fixed number, so that taking it costs the same in any box.
-constexpr int kGroupSample = 4096;
+// Groups and granules of the samples; fixed numbers, so that taking them costs the
+// same in any box.  Sorts of fewer than kDenseSorts granules are not sampled.
+constexpr int kGroupSample = 4096, kDenseSample = 4096;
+constexpr int64_t kDenseSorts = 8192;
 
 // Occupied bricks of a set of cell ranges, in brick order (see
 // brick_of_block), built by launch_brick_list before the brick kernels.
 struct BrickList {
     int32_t *list;     // [nbricks]
-    int32_t *count;    // [4] their number, and the rest of a BrickSeen
+    int32_t *count;    // [6] their number, and the rest of a BrickSeen
     uint32_t *sums;    // [<= 1024] block totals
     int32_t *box;      // [nbricks + 1] every brick of the box and their number, or NULL (see box_list)
     const int32_t *use, *use_count;  // what the brick kernels run over: list and count, or the box
@@ -53,6 +64,7 @@ struct BrickList {
     BrickSeen *seen;   // pinned host: a copy of an earlier list's count (see brick_fill)
     int64_t seen_n;    // granules of the last list
     unsigned calls;
+    bool again;        // the last list was the first of seen_n granules
 };
 
 // Every brick of the box in the order of a brick list, runs of 16 neighbouring
@@ -83,9 +95,57 @@ struct NbrList {
     float thr2;     // squared displacement since the build that calls for a rebuild (< 0: every step)
 };
 
-// Up to this many keys a sort does not collect the changed ones: counting
-// everything again takes no longer than merging them in.
+// Up to this many keys a counting sort does not collect the changed ones:
+// counting everything again takes no longer than merging them in.
 constexpr int64_t kSmallSort = (int64_t)1 << 18;
+
+// A sort counts, or passes over the keys' digits.  Counting places each granule
+// with an atomic on its cell and a store, both at random where the input is
+// shuffled, and puts a cell's granules in order at a cost that grows with the
+// cell; the digit passes cost the same for any input.  sort_limit: the granules
+// per cell from which the digits are faster, 0 for any; shuffled: most keys differ
+// from those of the last sort at their place.  Counting against digits, us:
+//   262,144, sorted 300 a cell 57 and 65; shuffled 96 60 and 65, 128 68 and 64
+//   524,288, sorted 128 78 and 78; shuffled 8 89 and 99, 32 93 and 79
+//   786,432, sorted 96 93 and 95, 128 101 and 96; shuffled 8 120 and 121, 32 126 and 100
+//   4.2 million, sorted 64 354 and 353, 128 424 and 308; shuffled 1 580 and 477
+//   16.8 million, sorted 32 1,228 and 1,344, 64 1,384 and 1,346; shuffled 1 2,493 and 1,947
+// and 16 cells of 262,144 granules each, shuffled, 18,300 and 1,000.
+inline int64_t sort_limit(int64_t n, bool shuffled)
+{
+    if (n <= kSmallSort) return 160;
+    if (shuffled) return n <= 2 * kSmallSort ? 32 : 0;
+    return n <= 2 * kSmallSort ? 128 : (n <= 4 * kSmallSort ? 96 : 64);
+}
+// Whether a sort of n granules in K cells takes the digit passes, from the record
+// of an earlier list of n granules or, before the first, from the mean of the box.
+inline bool sort_by_digits(int64_t n, int64_t K, const BrickList &B, int64_t limit)
+{
+    if (limit == 0) return true;
+    const volatile BrickSeen *seen = B.seen;
+    if (n >= kDenseSorts && seen && seen->n == n && seen->count > 0) return 2 * (int64_t)seen->dense > n;
+    return n > limit * K;
+}
+// Keys of a tile of a digit pass, in threads: small sorts take small tiles, to
+// spread over the chip.
+constexpr int kSortThreads = 256, kSortItems = 8;
+inline int sort_items(int64_t n) { return n <= kSmallSort ? 1 : kSortItems; }
+inline int64_t sort_tiles(int64_t n)
+{
+    const int64_t keys = (int64_t)kSortThreads * sort_items(n);
+    return (n + keys - 1) / keys;
+}
+inline int64_t sort_tiles_max(int64_t n_max)  // of any n up to n_max
+{
+    const int64_t a = sort_tiles(n_max), b = sort_tiles(n_max < kSmallSort ? n_max : kSmallSort);
+    return a > b ? a : b;
+}
+inline int sort_passes(int64_t K)
+{
+    int p = 1;
+    while (p < 4 && ((K - 1) >> (8 * p)) != 0) ++p;
+    return p;
+}
 
 // nl: the neighbour list of the stepping path, or NULL.  With nl, the key
 // kernel also measures every granule's displacement since the list's build

@@ -1,4 +1,4 @@
-// a1: cell binning, stable counting sort of the cell keys, cell ranges, the
+// a1: cell binning, stable sort of the cell keys, cell ranges, the
 // list of occupied bricks and the gather of granule arrays into sorted order
 // (gfx950).
 //
@@ -7,13 +7,14 @@
 // makes each granule's candidates the occupants of at most 27 cells, stored
 // contiguously so that later stages read them coalesced.
 //
-// The keys are cells, so the sort counts: every granule takes a place in its
+// The keys are cells, so most sorts count: every granule takes a place in its
 // cell with an atomic on the cell's counter, a scan of the counters gives the
 // cell ranges (needed in any case), and the granules of each cell are then
 // put in input order, which makes the sort stable whatever order the atomics
 // ran in.  Six launches for any number of cells (keys, counts, two scan
-// passes, places, order; one scan pass fewer for small tables); an 8-bit radix
-// sort takes three per digit besides the counts and scans.
+// passes, places, order; one scan pass fewer for small tables).  Cells of many
+// granules and large shuffled inputs are sorted by passes over 8-bit digits, three
+// launches each, whose cost does not depend on the input (see sort_limit).
 #include "gic_launch.hpp"
 
 namespace gic {
@@ -215,8 +216,9 @@ __device__ inline int lower_bound_u32(const uint32_t *a, int m, uint32_t v)
 // incremental sort (ctl[1]) no places are needed: the granules that kept
 // their key (U, see k_chg_sort) and are displaced by those that did not are
 // written to order and skeys instead.  Small sorts (one launch fewer: chg not
-// collected) decide here: the first workgroup writes ctl[2] (no key changed)
-// and, with nl, whether the neighbour list must be rebuilt.
+// collected) decide here (decide 1): the first workgroup writes ctl[2] (no key
+// changed) and, with nl, whether the neighbour list must be rebuilt.  Sorts by
+// digits (decide 2) count here after the incremental path only.
 __global__ void __launch_bounds__(256) k_cell_count(const uint32_t *__restrict__ key, int64_t n,
                                                     uint32_t *__restrict__ cnt, uint32_t *__restrict__ slot,
                                                     const uint32_t *__restrict__ pk, const uint64_t *__restrict__ chg_s,
@@ -227,7 +229,7 @@ __global__ void __launch_bounds__(256) k_cell_count(const uint32_t *__restrict__
 {
     bool same = false, inc = false;
     const int m = ctl ? ctl[0] : 0;
-    if (decide) {
+    if (decide == 1) {
         same = m == 0;
         if (blockIdx.x == 0) {
             __shared__ float s_dm[4];
@@ -248,7 +250,7 @@ __global__ void __launch_bounds__(256) k_cell_count(const uint32_t *__restrict__
         inc = ctl[1] != 0;
         same = ctl[2] != 0;
     }
-    if (same && keep) return;
+    if ((same && keep) || (decide == 2 && !inc)) return;
     const int lane = threadIdx.x & 63;
     for (int64_t q0 = (int64_t)blockIdx.x * 256; q0 < n; q0 += (int64_t)gridDim.x * 256) {
         const int64_t q = q0 + threadIdx.x;
@@ -299,10 +301,14 @@ __global__ void __launch_bounds__(kScanThreads) k_scan_down_ranges(uint32_t *__r
                                                                    int32_t *__restrict__ ctl, int keep,
                                                                    int32_t *__restrict__ list,
                                                                    int32_t *__restrict__ count,
-                                                                   int32_t *__restrict__ slot_of, int32_t n)
+                                                                   int32_t *__restrict__ slot_of, int32_t n,
+                                                                   int compared)
 {
     if (keep && ctl[2]) return;  // ranges unchanged (and no changed granule to uncount)
-    if (blockIdx.x == 0 && threadIdx.x == 0) ctl[0] = 0;  // no changed granules counted for the next sort
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        count[4] = compared ? ctl[0] : n;
+        ctl[0] = 0;  // no changed granules counted for the next sort
+    }
     __shared__ uint32_t lds[kScanThreads / 64];
     __shared__ uint32_t s_occ[kScanThreads / 64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -415,6 +421,146 @@ __device__ inline uint64_t digit_mask(uint32_t d, bool valid)
     return m;
 }
 
+// ---- digit passes (count, scan, scatter) ----------------------------------
+//
+// Each 8-bit digit pass is three kernels with no waits between workgroups: every
+// tile of keys counts its digits (k_digit_count, into tcnt[digit][tile]); one
+// workgroup per digit turns its row into the exclusive prefix over the tiles
+// and records the row's total (k_digit_scan); every tile then scatters its keys
+// stably (k_digit_scatter) from the prefix of its tile plus the keys of all
+// smaller digits (a scan of the 256 row totals).  skip (optional): the sort's
+// control words; skip[1] set means the incremental path sorted this time.
+constexpr int64_t kDigitGrid = 1024;  // workgroups of the tile loops
+
+template <int ITEMS>
+__global__ void __launch_bounds__(kSortThreads) k_digit_count(const uint32_t *__restrict__ kin, int64_t n, int pass,
+                                                              int64_t tiles, uint32_t *__restrict__ tcnt,
+                                                              const int32_t *__restrict__ skip)
+{
+    if (skip && skip[1]) return;
+    __shared__ uint32_t s_cnt[256];
+    const int tid = threadIdx.x, lane = tid & 63, shift = 8 * pass;
+    const uint64_t lt = lane == 0 ? 0ull : (~0ull >> (64 - lane));
+    for (int64_t t = blockIdx.x; t < tiles; t += gridDim.x) {
+        s_cnt[tid] = 0;
+        __syncthreads();
+        const int64_t tile0 = t * (kSortThreads * ITEMS);
+#pragma unroll
+        for (int it = 0; it < ITEMS; ++it) {
+            const int64_t p = tile0 + (int64_t)it * kSortThreads + tid;
+            const bool valid = p < n;
+            const uint32_t d = valid ? (kin[p] >> shift) & 255u : 0u;
+            const uint64_t m = digit_mask(d, valid);
+            if (valid && (m & lt) == 0) atomicAdd(&s_cnt[d], (uint32_t)__popcll(m));
+        }
+        __syncthreads();
+        tcnt[(int64_t)tid * tiles + t] = s_cnt[tid];
+        __syncthreads();
+    }
+}
+
+// Thread i of a row's workgroup takes a contiguous chunk, so the row is read in
+// one sweep and scanned once.
+__global__ void __launch_bounds__(kSortThreads) k_digit_scan(uint32_t *__restrict__ tcnt, int64_t tiles,
+                                                             uint32_t *__restrict__ rowtot,
+                                                             const int32_t *__restrict__ skip)
+{
+    if (skip && skip[1]) return;
+    __shared__ uint32_t lds[kSortThreads / 64];
+    uint32_t *row = tcnt + (int64_t)blockIdx.x * tiles;
+    const int64_t chunk = (tiles + kSortThreads - 1) / kSortThreads;
+    const int64_t lo = (int64_t)threadIdx.x * chunk, hi = lo + chunk < tiles ? lo + chunk : tiles;
+    uint32_t sum = 0;
+    for (int64_t t = lo; t < hi; ++t) sum += row[t];
+    uint32_t total;
+    uint32_t run = block_scan_inclusive(sum, lds, &total) - sum;
+    for (int64_t t = lo; t < hi; ++t) {
+        const uint32_t c = row[t];
+        row[t] = run;
+        run += c;
+    }
+    if (threadIdx.x == 0) rowtot[blockIdx.x] = total;
+}
+
+// Keys and values (vin, or the positions), in rounds of 256 in position order.
+template <int ITEMS>
+__global__ void __launch_bounds__(kSortThreads) k_digit_scatter(const uint32_t *__restrict__ kin,
+                                                                const int32_t *__restrict__ vin,
+                                                                uint32_t *__restrict__ kout, int32_t *__restrict__ vout,
+                                                                int64_t n, int pass, int64_t tiles,
+                                                                const uint32_t *__restrict__ tcnt,
+                                                                const uint32_t *__restrict__ rowtot,
+                                                                const int32_t *__restrict__ skip)
+{
+    if (skip && skip[1]) return;
+    __shared__ uint32_t s_base[256];  // where this tile's next key of each digit goes
+    __shared__ uint32_t wcnt[kSortThreads / 64][256];
+    __shared__ uint32_t lds[kSortThreads / 64];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, shift = 8 * pass;
+    const uint64_t lt = lane == 0 ? 0ull : (~0ull >> (64 - lane));
+    for (int w = 0; w < kSortThreads / 64; ++w) wcnt[w][tid] = 0;
+    const uint32_t g = rowtot[tid];
+    uint32_t total;
+    const uint32_t dbase = block_scan_inclusive(g, lds, &total) - g;  // keys of all smaller digits
+    for (int64_t t = blockIdx.x; t < tiles; t += gridDim.x) {
+        const int64_t tile0 = t * (kSortThreads * ITEMS);
+        uint32_t k[ITEMS];
+        int32_t val[ITEMS];
+#pragma unroll
+        for (int it = 0; it < ITEMS; ++it) {
+            const int64_t p = tile0 + (int64_t)it * kSortThreads + tid;
+            const bool valid = p < n;
+            k[it] = valid ? kin[p] : 0xffffffffu;
+            val[it] = valid ? (vin ? vin[p] : (int32_t)p) : 0;
+        }
+        s_base[tid] = dbase + tcnt[(int64_t)tid * tiles + t];
+        __syncthreads();
+#pragma unroll
+        for (int it = 0; it < ITEMS; ++it) {
+            const int64_t p = tile0 + (int64_t)it * kSortThreads + tid;
+            const bool valid = p < n;
+            const uint32_t d = (k[it] >> shift) & 255u;
+            const uint64_t m = digit_mask(d, valid);
+            const uint32_t rank = (uint32_t)__popcll(m & lt);
+            if (valid && rank == 0) wcnt[wave][d] = (uint32_t)__popcll(m);
+            __syncthreads();
+            if (valid) {
+                uint32_t pos = s_base[d] + rank;
+                for (int w = 0; w < wave; ++w) pos += wcnt[w][d];
+                if ((int64_t)pos < n) {
+                    kout[pos] = k[it];
+                    vout[pos] = val[it];
+                }
+            }
+            __syncthreads();
+            uint32_t add = 0;
+            for (int w = 0; w < kSortThreads / 64; ++w) {
+                add += wcnt[w][tid];
+                wcnt[w][tid] = 0;
+            }
+            s_base[tid] += add;
+            __syncthreads();
+        }
+    }
+}
+
+// Counts of the cells from the sorted keys, after the digit passes: one atomic per
+// run of equal keys inside a wave.
+__global__ void __launch_bounds__(256) k_run_count(const uint32_t *__restrict__ sk, int64_t n, uint32_t *__restrict__ cnt,
+                                                   const int32_t *__restrict__ skip)
+{
+    if (skip && skip[1]) return;
+    const int lane = threadIdx.x & 63;
+    for (int64_t q0 = (int64_t)blockIdx.x * 256; q0 < n; q0 += (int64_t)gridDim.x * 256) {
+        const int64_t q = q0 + threadIdx.x;
+        const bool valid = q < n;
+        const uint32_t k = valid ? sk[q] : 0u;
+        const uint32_t before = __shfl_up(k, 1);
+        const uint64_t starts = __ballot(valid && (lane == 0 || before != k)) | (~__ballot(valid));
+        if (valid && ((starts >> lane) & 1ull)) atomicAdd(&cnt[k], (uint32_t)run_length(starts));
+    }
+}
+
 // One workgroup sorts the distinct indices a[b..e) (all below n) into
 // out[b..e) by 8-bit digits, through t; a and t are overwritten.
 __device__ inline void sort_long_cell(int32_t *a, int32_t *t, int32_t *__restrict__ out, int64_t b, int64_t e,
@@ -512,8 +658,8 @@ __global__ void __launch_bounds__(256) k_cell_order(int64_t n, const uint32_t *_
 // REV (the reverse step): also the adjoint of the state in sorted order, moved
 // through the integration: v^{n+1} feeds x^{n+1}, so its adjoint, which is also
 // that of v^n through the identity term, is g_v + dt g_x, and the adjoint of
-// the force is dt / m of it.
-template <bool REV>
+// the force is dt / m of it.  ORDERED: the digit passes have left the order.
+template <bool REV, bool ORDERED>
 __global__ void __launch_bounds__(256) k_rollout_order(DevParams P, int64_t n, const uint32_t *__restrict__ skeys,
                                                        const uint32_t *__restrict__ begin,
                                                        const uint32_t *__restrict__ end, int32_t *tmp, int32_t *tmp2,
@@ -553,7 +699,9 @@ __global__ void __launch_bounds__(256) k_rollout_order(DevParams P, int64_t n, c
         rs[q] = ri;
         m = fmax(m, volume_of(ri) * P.inv_vcell);
     };
-    for (int64_t p0 = (int64_t)blockIdx.x * 256; p0 < n; p0 += (int64_t)gridDim.x * 256) {
+    if constexpr (ORDERED)
+        for (int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x; q < n; q += (int64_t)gridDim.x * 256) take(q, order[q]);
+    for (int64_t p0 = (int64_t)blockIdx.x * 256; !ORDERED && p0 < n; p0 += (int64_t)gridDim.x * 256) {
         if (threadIdx.x == 0) s_long[1] = 0;
         __syncthreads();
         const int64_t p = p0 + threadIdx.x;
@@ -777,13 +925,31 @@ __global__ void __launch_bounds__(256) k_brick_scatter(int64_t nbricks, int64_t 
     if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) put_count(count, (int32_t)base, n);
 }
 
-// How full the groups are (see fill_mode), from kGroupSample groups spread over
-// the box, each at a place of its own in its share so that no bed's period falls
-// in with theirs.  One workgroup, on the lists whose record is copied only.
-__global__ void __launch_bounds__(1024) k_group_sample(int32_t nbx, int32_t nby, int32_t nbz,
-                                                       const int32_t *__restrict__ slot_of, int32_t *__restrict__ count)
+// Samples of a bed for its record, one workgroup.
+//
+// How full the groups are (groups; see fill_mode), from kGroupSample groups spread
+// over the box, each at a place of its own in its share so that no bed's period
+// falls in with theirs.  And how many of kDenseSample sorted granules lie in cells
+// of more than limit (skeys given; see sort_by_digits), as a share of n.
+__global__ void __launch_bounds__(1024) k_bed_sample(int32_t nbx, int32_t nby, int32_t nbz, int64_t n, int groups_too,
+                                                     uint32_t limit, const int32_t *__restrict__ slot_of,
+                                                     const uint32_t *__restrict__ skeys,
+                                                     const uint32_t *__restrict__ begin, const uint32_t *__restrict__ end,
+                                                     int32_t *__restrict__ count)
 {
     __shared__ uint32_t lds[1024 / 64];
+    if (skeys) {
+        uint32_t dense = 0;
+#pragma unroll
+        for (int u = 0; u < kDenseSample / 1024; ++u) {
+            const int64_t p = (threadIdx.x + u * 1024) * n / kDenseSample;
+            const uint32_t k = skeys[p];
+            dense += end[k] - begin[k] > limit ? 1u : 0u;
+        }
+        dense = block_reduce_sum(dense, lds);
+        if (threadIdx.x == 0) count[5] = (int32_t)((int64_t)dense * n / kDenseSample);
+    }
+    if (!groups_too) return;
     const uint32_t ngx = (uint32_t)(nbx + kGroup - 1) / kGroup, ngy = (uint32_t)(nby + kGroup - 1) / kGroup;
     const uint32_t groups = ngx * ngy * ((uint32_t)(nbz + kGroup - 1) / kGroup);  // below 2^31, as the bricks are
     uint32_t held = 0, occ = 0;
@@ -820,20 +986,36 @@ namespace {
 
 constexpr unsigned kLoopGrid = 2048;  // workgroups of 256 that the chip holds at once
 
-// Every 16th list, and the first of another number of granules, leaves its
-// record in pinned host memory (see brick_fill).
-hipError_t brick_count_copy(const DevParams &P, BrickList &B, int64_t n, hipStream_t s)
+// A sort's keys and ranges, for its record.
+struct Sorted {
+    const uint32_t *skeys, *begin, *end;
+    int64_t limit;
+    bool asks;  // the next sort's form depends on whether this one's input was shuffled
+};
+
+// Every 16th list, and the first of another number of granules, leaves its record
+// in pinned host memory (see brick_fill); so does the second where a sort asks for
+// what changed (it is the first that can be compared).  Samples are taken of those
+// two and of every 64th list.
+hipError_t brick_count_copy(const DevParams &P, BrickList &B, int64_t n, hipStream_t s, const Sorted &S = Sorted{})
 {
     hipError_t e = hipGetLastError();
     if (n <= 0 || !B.seen) return e;
-    const bool copy = B.seen_n != n || (B.calls++ & 15u) == 0u;
+    const bool first = B.seen_n != n, fresh = first || (B.again && S.asks);
+    if (first) B.calls = 0;
+    const unsigned call = B.calls++;
+    B.again = first;
     B.seen_n = n;
-    // sampled where the bed may be run by groups, as far as is known
-    if (copy && n >= kWaveBricks * kBrickCells && B.nbricks >= kGroupBricks && brick_fill(P, n, B).avg <= kWaveFill) {
-        k_group_sample<<<1, 1024, 0, s>>>(P.nb[0], P.nb[1], P.nb[2], B.slot_of, B.count);
+    if (!fresh && (call & 15u) != 0u) return e;
+    // (groups: where the bed may be run by them, as far as is known)
+    const bool groups = n >= kWaveBricks * kBrickCells && B.nbricks >= kGroupBricks && brick_fill(P, n, B).avg <= kWaveFill;
+    if ((fresh || (call & 63u) == 0u) && (groups || (S.skeys && n >= kDenseSorts))) {
+        k_bed_sample<<<1, 1024, 0, s>>>(P.nb[0], P.nb[1], P.nb[2], n, groups ? 1 : 0,
+                                        (uint32_t)(S.limit ? S.limit : sort_limit(n, false)), B.slot_of, S.skeys, S.begin,
+                                        S.end, B.count);
         e = hipGetLastError();
     }
-    if (copy && e == hipSuccess) e = hipMemcpyAsync(B.seen, B.count, sizeof(BrickSeen), hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess) e = hipMemcpyAsync(B.seen, B.count, sizeof(BrickSeen), hipMemcpyDeviceToHost, s);
     return e;
 }
 
@@ -841,6 +1023,37 @@ int64_t scan_chunk(int64_t len)
 {
     const int64_t chunk = (len + kScanThreads - 1) / kScanThreads, unit = 4 * kScanThreads;
     return (chunk + unit - 1) / unit * unit;
+}
+
+}  // namespace
+
+namespace {
+
+// The digit passes of a sort: skeys and order from key.
+void digit_passes(int64_t n, const uint32_t *key, uint32_t *skeys, int32_t *order, SortScratch &S, const int32_t *skip,
+                  hipStream_t s)
+{
+    const int64_t tiles = sort_tiles(n);
+    const unsigned tg = (unsigned)(tiles < kDigitGrid ? tiles : kDigitGrid);
+    const uint32_t *kin = key;
+    const int32_t *vin = nullptr;
+    for (int pass = 0; pass < S.passes; ++pass) {
+        const bool last = pass == S.passes - 1;
+        uint32_t *kout = last ? skeys : ((pass & 1) ? S.kB : S.slot);
+        int32_t *vout = last ? order : ((pass & 1) ? S.tmp2 : S.tmp);
+        if (sort_items(n) == 1)
+            k_digit_count<1><<<tg, kSortThreads, 0, s>>>(kin, n, pass, tiles, S.tcnt, skip);
+        else
+            k_digit_count<kSortItems><<<tg, kSortThreads, 0, s>>>(kin, n, pass, tiles, S.tcnt, skip);
+        k_digit_scan<<<256, kSortThreads, 0, s>>>(S.tcnt, tiles, S.rowtot, skip);
+        if (sort_items(n) == 1)
+            k_digit_scatter<1><<<tg, kSortThreads, 0, s>>>(kin, vin, kout, vout, n, pass, tiles, S.tcnt, S.rowtot, skip);
+        else
+            k_digit_scatter<kSortItems>
+                <<<tg, kSortThreads, 0, s>>>(kin, vin, kout, vout, n, pass, tiles, S.tcnt, S.rowtot, skip);
+        kin = kout;
+        vin = vout;
+    }
 }
 
 }  // namespace
@@ -856,7 +1069,13 @@ hipError_t launch_sort_cells(const DevParams &P, int64_t n, const double *x, uin
     // previous sorted keys: usable when the last sort had the same n
     const bool same_n = n > 0 && S.last_n == n;
     const int keep = keep_ranges && same_n ? 1 : 0;
-    const bool small = n <= kSmallSort;
+    // a stepping call continues a sorted state; what a stage call sorts, the
+    // record of its last sorts says
+    const volatile BrickSeen *seen = B.seen;
+    const bool shuffled = !same_n || (!nl && !(seen && seen->n == n && 2 * (int64_t)seen->changed <= n));
+    const int64_t limit = sort_limit(n, shuffled);
+    const bool digits = n > 0 && sort_by_digits(n, K, B, limit);
+    const bool small = n <= kSmallSort && !digits;
     // a small sort compares with the previous keys only where an unchanged
     // state saves the rest of it or the neighbour list
     const bool inc = same_n && (!small || keep || (nl && !force));
@@ -879,28 +1098,35 @@ hipError_t launch_sort_cells(const DevParams &P, int64_t n, const double *x, uin
         if (inc && !small)
             k_chg_sort<<<1, 1024, 0, s>>>(n, pk, S.chg, S.ctl, S.chg_s, S.chg_p, skeys, order, nctl, measure ? 0 : 1,
                                           thr2, dpart, (int64_t)g);
-        k_cell_count<<<gl, 256, 0, s>>>(key, n, cnt, S.slot, pk, S.chg_s, S.chg_p, skeys, order, ctl,
-                                        inc && small ? 1 : 0, keep, nctl, measure ? 0 : 1, thr2, dpart, (int64_t)g);
+        if (inc || !digits)
+            k_cell_count<<<gl, 256, 0, s>>>(key, n, cnt, S.slot, pk, S.chg_s, S.chg_p, skeys, order, ctl,
+                                            digits ? 2 : (inc && small ? 1 : 0), keep, nctl, measure ? 0 : 1, thr2,
+                                            dpart, (int64_t)g);
+        if (digits) {
+            digit_passes(n, key, skeys, order, S, ctl, s);
+            k_run_count<<<gl, 256, 0, s>>>(skeys, n, cnt, ctl);
+        }
     }
     // cell ranges and bricks: kept when the caller's tables hold the last
     // sort's ranges and no key changed (decided on the device)
     // (tables of one pass: chunks of 4,096 cells, so that 32 workgroups share them)
-    const bool direct = n > 0 && K <= kDirectScan;
+    const bool direct = n > 0 && K <= kDirectScan && !digits;
     const int64_t chunk = direct ? 4 * kScanThreads : scan_chunk(K);
     const int nb = (int)((K + chunk - 1) / chunk);
     if (!direct)
         k_scan_reduce<<<nb, kScanThreads, 0, s>>>(cnt, K, chunk, S.sums, S.sums + kScanThreads,
                                                   keep ? S.ctl : nullptr);
     k_scan_down_ranges<<<nb, kScanThreads, 0, s>>>(cnt, begin, end, K, chunk, direct ? nullptr : S.sums,
-                                                   S.sums + kScanThreads, S.ctl, keep, B.list, B.count, B.slot_of, (int32_t)n);
-    if (n > 0) {
+                                                   S.sums + kScanThreads, S.ctl, keep, B.list, B.count, B.slot_of,
+                                                   (int32_t)n, inc ? 1 : 0);
+    if (n > 0 && !digits) {
         k_cell_place<<<gl, 256, 0, s>>>(key, n, begin, S.slot, S.tmp, skeys, ctl, keep);
         k_cell_order<<<gl, 256, 0, s>>>(n, skeys, begin, end, S.tmp, S.tmp2, order, ctl, keep, direct ? cnt : nullptr,
                                         K);
     }
     S.cur ^= 1;  // this sort's keys are the previous keys of the next
     S.last_n = n;
-    return brick_count_copy(P, B, n, s);
+    return brick_count_copy(P, B, n, s, Sorted{skeys, begin, end, limit, !nl && n > kSmallSort});
 }
 
 hipError_t launch_rollout_sort(const DevParams &P, int64_t n, const double *xv, const double *r, uint32_t *key,
@@ -913,28 +1139,46 @@ hipError_t launch_rollout_sort(const DevParams &P, int64_t n, const double *xv, 
     B.use_count = B.count;
     uint32_t *begin = reinterpret_cast<uint32_t *>(cell_begin), *end = reinterpret_cast<uint32_t *>(cell_end);
     uint32_t *skeys = S.skeys[S.cur ^ 1];
+    const int64_t limit = sort_limit(n, true);  // input order
+    const bool digits = sort_by_digits(n, K, B, limit);
     const unsigned g = grid_for(n, 256), gl = g < kLoopGrid ? g : kLoopGrid, go = g < 1024u ? g : 1024u;
     k_cell_keys<<<g, 256, 0, s>>>(P, n, xv, key, err, nullptr, nullptr, S.ctl, nullptr, nullptr, order, skeys);
-    k_cell_count<<<gl, 256, 0, s>>>(key, n, S.cnt, S.slot, nullptr, S.chg_s, S.chg_p, skeys, order, nullptr, 0, 0, nullptr,
-                                    1, 0.0f, nullptr, 0);
-    const bool direct = K <= kDirectScan;
+    if (digits) {
+        digit_passes(n, key, skeys, order, S, nullptr, s);
+        k_run_count<<<gl, 256, 0, s>>>(skeys, n, S.cnt, nullptr);
+    } else {
+        k_cell_count<<<gl, 256, 0, s>>>(key, n, S.cnt, S.slot, nullptr, S.chg_s, S.chg_p, skeys, order, nullptr, 0, 0,
+                                        nullptr, 1, 0.0f, nullptr, 0);
+    }
+    const bool direct = K <= kDirectScan && !digits;
     const int64_t chunk = direct ? 4 * kScanThreads : scan_chunk(K);
     const int nc = (int)((K + chunk - 1) / chunk);
-    if (!direct) k_scan_reduce<<<nc, kScanThreads, 0, s>>>(S.cnt, K, chunk, S.sums, S.sums + kScanThreads, nullptr);
+    if (!direct)
+        k_scan_reduce<<<nc, kScanThreads, 0, s>>>(S.cnt, K, chunk, S.sums, S.sums + kScanThreads, nullptr);
     k_scan_down_ranges<<<nc, kScanThreads, 0, s>>>(S.cnt, begin, end, K, chunk, direct ? nullptr : S.sums,
-                                                   S.sums + kScanThreads, S.ctl, 0, B.list, B.count, B.slot_of, (int32_t)n);
-    k_cell_place<<<gl, 256, 0, s>>>(key, n, begin, S.slot, S.tmp, skeys, nullptr, 0);
+                                                   S.sums + kScanThreads, S.ctl, 0, B.list, B.count, B.slot_of, (int32_t)n,
+                                                   0);
+    if (!digits) k_cell_place<<<gl, 256, 0, s>>>(key, n, begin, S.slot, S.tmp, skeys, nullptr, 0);
     uint32_t *cnt = direct ? S.cnt : nullptr;
-    if (gxv)
-        k_rollout_order<true><<<go, 256, 0, s>>>(P, n, skeys, begin, end, S.tmp, S.tmp2, order, cnt, K, xv, r, xvs, rs,
-                                                 fx, len, part, gxv, gs, gF, gmax);
-    else
-        k_rollout_order<false><<<go, 256, 0, s>>>(P, n, skeys, begin, end, S.tmp, S.tmp2, order, cnt, K, xv, r, xvs, rs,
-                                                  fx, len, part, nullptr, nullptr, nullptr, nullptr);
+#define GIC_ROLLOUT_ORDER(REV, ORDERED)                                                                                \
+    k_rollout_order<REV, ORDERED><<<go, 256, 0, s>>>(P, n, skeys, begin, end, S.tmp, S.tmp2, order, cnt, K, xv, r,     \
+                                                     xvs, rs, fx, len, part, gxv, gs, gF, gmax)
+    if (gxv) {
+        if (digits)
+            GIC_ROLLOUT_ORDER(true, true);
+        else
+            GIC_ROLLOUT_ORDER(true, false);
+    } else {
+        if (digits)
+            GIC_ROLLOUT_ORDER(false, true);
+        else
+            GIC_ROLLOUT_ORDER(false, false);
+    }
+#undef GIC_ROLLOUT_ORDER
     *nb = (int)go;
     S.cur ^= 1;
     S.last_n = n;
-    return brick_count_copy(P, B, n, s);
+    return brick_count_copy(P, B, n, s, Sorted{skeys, begin, end, limit, false});
 }
 
 hipError_t launch_brick_list(const DevParams &P, const int32_t *cb, const int32_t *ce, BrickList &B, int64_t n,

@@ -16,7 +16,7 @@ int main()
     DevParams P = {};
     P.cell = 2.0;
     P.r_max = 1.0;  // 64 granules a brick expected
-    BrickSeen seen = {100, 5000, 0, 0};
+    BrickSeen seen = {100, 5000};
     BrickList B = {};
     B.seen = &seen;
     B.seen_n = 7000;  // a list of 7,000 granules followed; its record has not arrived
@@ -59,7 +59,7 @@ int main()
                               {20000, 1000000, 4000, 4000}, {20000, 1000000, 0, 0}, {4096, 300000, 700, 5000},
                               {4095, 300000, 700, 5000}, {20000, 1000001, 4000, 8 * 4000}, {10000, 1000000, 4000, 8 * 4000}};
     for (auto &r : rec) {
-        BrickSeen seen = {r[0], r[1], r[2], r[3]};
+        BrickSeen seen = {r[0], r[1], r[2], r[3], 0, 0};
         B.seen = &seen;
         printf("%d\n", (int)fill_mode(P, r[1] == 1000001 ? 1000000 : r[1], B, kGroupBricks));
     }
@@ -70,3 +70,32 @@ BLOCK, WAVE, BOTH, GROUP = range(4)
 
 def test_groups_where_they_are_full(tmp_path):
     assert [m for m, in run(tmp_path, MODES)] == [GROUP, GROUP, WAVE, WAVE, WAVE, GROUP, WAVE, BOTH, BLOCK]
+
+
+SORTS = r"""
+#include <cstdio>
+#include "gic_launch.hpp"
+using namespace gic;
+int main()
+{
+    BrickSeen seen = {};
+    BrickList B = {};
+    B.seen = &seen;
+    auto form = [&](int64_t n, int64_t K, bool shuffled) { return sort_by_digits(n, K, B, sort_limit(n, shuffled)) ? 1 : 0; };
+    // nothing known: from the mean of the box, and a large bed is taken to be shuffled
+    printf("%d %d %d %d %d\n", form(4096, 4096, true), form(70001, 64, true), form(524288, 65536, true),
+           form(524289, 1 << 20, true), form(524289, 1 << 20, false));
+    // known: half of the granules in cells beyond the limit
+    seen = {1000, 200000, 0, 0, 200000, 100000};
+    printf("%d %d", form(200000, 64000, true), form(200001, 64000, true));
+    seen.dense = 100001;
+    printf(" %d %d\n", form(200000, 64000, true), form(200000, 64000, false));
+    // buffers: tiles and digits
+    printf("%lld %lld %lld %d %d %d %d\n", (long long)sort_tiles_max(1), (long long)sort_tiles_max(262144),
+           (long long)sort_tiles_max(16777216), sort_passes(64), sort_passes(257), sort_passes(65537), sort_passes(16777217));
+}
+"""
+
+
+def test_sorts_by_digits_where_faster(tmp_path):
+    assert run(tmp_path, SORTS) == [[0, 1, 0, 1, 0], [0, 0, 1, 1], [1, 1024, 8192, 1, 2, 3, 4]]
