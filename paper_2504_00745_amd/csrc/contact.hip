@@ -600,7 +600,12 @@ __device__ inline void contact_global(const DevParams &P, int64_t n, const doubl
 // positions outside the box, which the key kernel reports as a domain
 // error, the bound does not hold and the step's result is unspecified.)
 //
-// A brick whose shell does not fit in LDS takes the global path.
+// A brick whose shell does not fit in LDS takes the global path.  So does, in the
+// pullbacks, which answer for any positions, a brick with a granule in its shell
+// whose |p|^2 + 2 r^2 is beyond kFarCells cells^2 (far outside the box, in the
+// clamped cell, or larger than any cell): the roundings grow with that sum, 27.5
+// cells^2 inside the box, and at 64 are less than half of M.
+constexpr float kFarCells = 64.0f;
 constexpr int kHaloCells = 216;
 constexpr int kGroupHalo = (kBrick * kGroup + 2) * (kBrick * kGroup + 2) * (kBrick * kGroup + 2);  // a group's shell
 constexpr int kLdsPartners = 10;
@@ -909,6 +914,7 @@ k_contact_lds(DevParams P, int64_t n, const int32_t *__restrict__ bl,
     // ---- copy the shell's granules, relative to the centre, in single precision.
     // H <= cap <= kCopyRounds * NT: all loads of a thread are issued before
     // any of them is used, so they are in flight together.
+    bool far = false;  // a granule whose prefilter has no margin (see kFarCells)
     {
         double gx[kCopyRounds], gy[kCopyRounds], gz[kCopyRounds], gr[kCopyRounds];
         bool real[kCopyRounds];
@@ -938,7 +944,9 @@ k_contact_lds(DevParams P, int64_t n, const int32_t *__restrict__ bl,
             if (real[it]) {
                 const float px = (float)(gx[it] - o[0]), py = (float)(gy[it] - o[1]), pz = (float)(gz[it] - o[2]);
                 const float rg = (float)gr[it] + hreach;
-                p = make_float4(px, py, pz, ((px * px + py * py) + pz * pz) - 2.0f * (rg * rg));
+                const float p2 = (px * px + py * py) + pz * pz, r2 = 2.0f * (rg * rg);
+                far |= !(p2 + r2 <= kFarCells * (float)(P.cell * P.cell));
+                p = make_float4(px, py, pz, p2 - r2);
             } else {
                 const float nan = __builtin_nanf("");
                 p = make_float4(nan, nan, nan, nan);
@@ -962,7 +970,17 @@ k_contact_lds(DevParams P, int64_t n, const int32_t *__restrict__ bl,
             }
         }
     }
-    __syncthreads();
+    if constexpr (pulls(KIND)) {
+        if (__syncthreads_or(far)) {
+            int32_t *glist = reinterpret_cast<int32_t *>(smem4);  // over the slots
+            for (int64_t q = (int64_t)gb + tid; q < ge; q += NT)
+                contact_global<T, KIND, NT>(P, n, x, v, r, cb, ce, q, glist, tid, sr, held, F, ncont, err, A, tot);
+            leave();
+            return;
+        }
+    } else {
+        __syncthreads();
+    }
     const float M = (float)(P.cell * P.cell * (GROUP ? 1.0 / 1024.0 : 1.0 / 4096.0));
     // ---- granules of the brick, one thread each: the listed partners are
     // evaluated in canonical order, the order of the dry contact's
