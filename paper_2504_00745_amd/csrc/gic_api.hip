@@ -347,7 +347,7 @@ gic_status idp_cg(const gic_ctx *c, const double *at, const uint8_t *label, cons
                   const IdpWork &W, int32_t max_iter, double tol, int32_t check_every, int32_t *iters,
                   double *relres, hipStream_t st)
 {
-    const IdpDims D = idp_dims(c->dp);
+    const IdpDims D = idp_solve_dims(c->dp);
     hipError_t e = launch_cg_start(D, at, label, s, q, W, tol, c->err, st);
     CgState h;
     int k = 0;
@@ -1290,7 +1290,7 @@ gic_status gic_permute(gic_ctx *c, int64_t n, int32_t comps, const int32_t *orde
 int64_t gic_idp_workspace_bytes(const gic_ctx *c)
 {
     if (!c) return -1;
-    return idp_work_bytes(idp_dims(c->dp));
+    return idp_work_bytes(idp_solve_dims(c->dp));
 }
 
 gic_status gic_idp_setup(gic_ctx *c, const int64_t *alpha_fx, const double *alpha_star, const uint8_t *label,
@@ -1315,7 +1315,7 @@ gic_status gic_idp_solve(gic_ctx *c, const double *alpha_t, const uint8_t *label
     if (!c || !alpha_t || !label || !rhs || !q || !work || max_iter < 0 || check_every < 1) return GIC_E_ARG;
     if (!(tol >= 0.0) || !isfinite(tol) || (precond != 0 && precond != 1)) return GIC_E_ARG;
     double *at_w, *s_w;
-    const IdpWork W = idp_carve(work, idp_dims(c->dp), precond, &at_w, &s_w);
+    const IdpWork W = idp_carve(work, idp_solve_dims(c->dp), precond, &at_w, &s_w);
     return idp_cg(c, alpha_t, label, rhs, q, W, max_iter, tol, check_every, iters, relres, (hipStream_t)stream);
 }
 
@@ -1337,7 +1337,7 @@ gic_status gic_density_projection(gic_ctx *c, const int64_t *alpha_fx, const dou
     const IdpDims D = idp_dims(c->dp);
     hipStream_t s = (hipStream_t)stream;
     double *at, *rhs;
-    const IdpWork W = idp_carve(work, D, precond, &at, &rhs);
+    const IdpWork W = idp_carve(work, idp_solve_dims(c->dp), precond, &at, &rhs);
     if (launch_idp_setup(D, c->dp.alpha_max, alpha_fx, alpha_star, label, at, rhs, c->err, s) != hipSuccess)
         return GIC_E_HIP;
     const gic_status st = idp_cg(c, at, label, rhs, q, W, max_iter, tol, check_every, iters, relres, s);

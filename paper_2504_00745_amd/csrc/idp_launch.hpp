@@ -54,6 +54,7 @@ struct IdpWork {
 };
 
 IdpDims idp_dims(const DevParams &P);
+IdpDims idp_solve_dims(const DevParams &P);  // the solver's: axes of one cell last
 // Fills sxy, G and the division constants from nx, ny, nz.
 void idp_dims_finish(IdpDims &D);
 hipError_t launch_idp_setup(const IdpDims &D, double alpha_max, const int64_t *afx, const double *astar,
