@@ -308,7 +308,8 @@ __global__ void __launch_bounds__(kIdpThreads) k_cg_start(int nb, const double *
 // next halo are loaded one step ahead, within the run.  (Tiles of 64 x 8 with
 // two rows per thread took 171 registers in kUpdate, two waves per SIMD, and
 // a larger halo.)  The face sum is face_sum_ac's, term by term in the same order
-// (cells outside the box hold coefficient 0 and value 0).  Items (tile, run of
+// (but for z before y where those are exchanged; cells outside the box hold
+// coefficient 0 and value 0).  Items (tile, run of
 // planes) are dealt to the blocks; the block count is the other iteration
 // kernels', whose partial sums these kernels' must match.
 // Bound by HBM: on 4.2 M cells the apply pass takes 32 us (197 MB), the update
@@ -319,8 +320,11 @@ constexpr double kOmega = 2.0 / 3.0;  // damping of the multigrid's Jacobi sweep
 constexpr int kTileX = 32, kTileY = kIdpThreads / kTileX;
 enum StencilMode { kApplyMg, kApplyJac, kUpdate, kResidual, kPost };
 
+// (x, y, z of the pass: the grid's, or with y and z exchanged, see stencil_items)
 struct StencilArgs {
-    IdpDims D;
+    int64_t nx, ny, nz, ry, rz;  // cells per axis; distance of rows and of planes
+    int64_t cry, crz;            // of the coarse rows and planes
+    int exchanged;
     int ntx, nty, zlen, k;
     double scale;
     const double *ac, *dinv;
@@ -329,14 +333,13 @@ struct StencilArgs {
     const double *w;       // kUpdate: L d
     const double *ec;      // kPost: the coarse correction
     const double *acc;     // kUpdate, kResidual: the coarse coefficients
-    int64_t cnx, cny;      // coarse cells per row and rows per plane
     double *o1, *o2;       // outputs: d, w | q, r' | - , - | e
     double *bc;            // kUpdate, kResidual: the coarse right-hand side
     double *part;
     CgState *st;
 };
 
-// Off: byte offsets inside a plane, 32 bits where a plane is below 4 GiB (the
+// Off: byte offsets inside a plane, 32 bits where it reaches below 4 GiB (the
 // loads then take a scalar base and a 32-bit offset).
 template <int MODE, typename Off>
 __global__ void __launch_bounds__(kIdpThreads) __attribute__((amdgpu_waves_per_eu(4))) k_stencil(StencilArgs A)
@@ -350,12 +353,11 @@ __global__ void __launch_bounds__(kIdpThreads) __attribute__((amdgpu_waves_per_e
     if (threadIdx.x == 0) s_done = A.st->done;
     __syncthreads();
     if (s_done >= 0) return;
-    const IdpDims &D = A.D;
     const int64_t nb = gridDim.x;
     const bool first = kApply && A.k == 0;
     double coef = 0.0;  // beta of the apply passes, alpha of the update
     const int tx = threadIdx.x & (kTileX - 1), ty = threadIdx.x / kTileX, t = threadIdx.x;
-    const int64_t nx = D.nx, ny = D.ny, nz = D.nz;
+    const int64_t nx = A.nx, ny = A.ny, nz = A.nz;
     const int64_t tiles = (int64_t)A.ntx * A.nty, nzc = (nz + A.zlen - 1) / A.zlen, items = tiles * nzc;
     // what a cell's coefficient a, value v, right-hand side b and 1 / diag come from
     struct Raw {
@@ -367,10 +369,9 @@ __global__ void __launch_bounds__(kIdpThreads) __attribute__((amdgpu_waves_per_e
     auto put = [](double *base, Off off, double v) {
         *reinterpret_cast<double *>(reinterpret_cast<char *>(base) + off) = v;
     };
-    const int64_t csxy = A.cnx * A.cny;
     // the cell at off in plane z; its coarse cell at coff in plane z / 2
     auto load = [&](int64_t z, Off off, Off coff) {
-        const int64_t pz = z * D.sxy;
+        const int64_t pz = z * A.rz;
         Raw r;
         r.a = at(A.ac + pz, off);
         r.p = at(A.p + pz, off);
@@ -378,7 +379,7 @@ __global__ void __launch_bounds__(kIdpThreads) __attribute__((amdgpu_waves_per_e
         r.q = 0.0;
         if (kApply && !first) r.q = at(A.d + pz, off);
         if (MODE == kUpdate) r.q = at(A.w + pz, off);
-        if (MODE == kPost) r.q = at(A.ec + (z >> 1) * csxy, coff);
+        if (MODE == kPost) r.q = at(A.ec + (z >> 1) * A.crz, coff);
         return r;
     };
     const Raw none = {0.0, 0.0, 0.0, 0.0};
@@ -414,12 +415,12 @@ __global__ void __launch_bounds__(kIdpThreads) __attribute__((amdgpu_waves_per_e
         i = i0 + tx;
         j = j0 + ty;
         own = i < nx && j < ny;
-        col = own ? (Off)(j * nx + i) * 8 : 0;
-        ccol = own ? (Off)((j >> 1) * A.cnx + (i >> 1)) * 8 : 0;
+        col = own ? (Off)(j * A.ry + i) * 8 : 0;
+        ccol = own ? (Off)((j >> 1) * A.cry + (i >> 1)) * 8 : 0;
         const int64_t hi = i0 + hdi, hj = j0 + hdj;
         hown = hr >= 0 && hi >= 0 && hi < nx && hj >= 0 && hj < ny;
-        hcol = hown ? (Off)(hj * nx + hi) * 8 : 0;
-        hccol = hown ? (Off)((hj >> 1) * A.cnx + (hi >> 1)) * 8 : 0;
+        hcol = hown ? (Off)(hj * A.ry + hi) * 8 : 0;
+        hccol = hown ? (Off)((hj >> 1) * A.cry + (hi >> 1)) * 8 : 0;
         rm = plane(z0 - 1);
         r0 = plane(z0);
         rp = plane(z0 + 1);
@@ -460,8 +461,8 @@ __global__ void __launch_bounds__(kIdpThreads) __attribute__((amdgpu_waves_per_e
             if (hown && z + 1 < z1) h1 = load(z + 1, hcol, hccol);
             double q0 = 0.0, d0 = 0.0;
             if (MODE == kUpdate && own) {
-                q0 = at(A.o1 + z * D.sxy, col);
-                d0 = at(A.d + z * D.sxy, col);
+                q0 = at(A.o1 + z * A.rz, col);
+                d0 = at(A.d + z * A.rz, col);
             }
             __syncthreads();  // the previous plane's reads of the tile are done
             sa[ty + 1][tx + 1] = a0;
@@ -483,7 +484,7 @@ __global__ void __launch_bounds__(kIdpThreads) __attribute__((amdgpu_waves_per_e
                     const double v = an[f] > 0.0 ? vn[f] : 0.0;
                     acc += beta * (v0 - v);
                 }
-                double *const o1 = A.o1 + z * D.sxy, *const o2 = A.o2 + z * D.sxy;
+                double *const o1 = A.o1 + z * A.rz, *const o2 = A.o2 + z * A.rz;
                 if (kApply) {
                     const double Lv = a0 > 0.0 ? acc : v0;  // identity row off the fluid
                     put(o1, col, v0);
@@ -511,7 +512,7 @@ __global__ void __launch_bounds__(kIdpThreads) __attribute__((amdgpu_waves_per_e
                 if ((z & 1) == 0) half = quad;
                 if (((z & 1) || z == nz - 1) && own && ((i | j) & 1) == 0) {
                     const double sum = (z & 1) ? half + quad : half;
-                    const int64_t pz = (z >> 1) * csxy;
+                    const int64_t pz = (z >> 1) * A.crz;
                     put(A.bc + pz, ccol, at(A.acc + pz, ccol) > 0.0 ? sum : 0.0);
                 }
             }
@@ -1053,24 +1054,39 @@ hipError_t launch_idp_faces(const IdpDims &D, double dx, const double *q, const 
 // being too small for runs of planes.
 constexpr int64_t kMgTiledCells = 1 << 18;
 
-// Tiles of a blocked stencil pass over D and the planes per item (even, so
-// that a coarse cell's children lie in one run): about one item per block of
-// nb.
+// Axes of a blocked stencil pass over D: with fewer rows than half a tile's and
+// more planes, the tiles lie in x and z and the runs go along y, so that the tiles
+// are full and the runs short (1,024 x 4 x 1,024 cells, multigrid 140 -> 84 ms,
+// Jacobi 197 -> 155; at 8 rows no difference with 256 planes, 12 % slower with 300
+// planes of 8 x 8).
+// Then its tiles, and the planes per item (even, so that a coarse cell's children
+// lie in one run): about one item per block of nb.
 static void stencil_items(const IdpDims &D, unsigned nb, StencilArgs &A)
 {
-    A.D = D;
-    A.ntx = (int)((D.nx + kTileX - 1) / kTileX);
-    A.nty = (int)((D.ny + kTileY - 1) / kTileY);
-    int64_t zl = (D.nz * A.ntx * A.nty + nb - 1) / nb;
+    A.exchanged = 2 * D.ny < kTileY && D.nz > D.ny;
+    A.nx = D.nx;
+    A.ny = A.exchanged ? D.nz : D.ny;
+    A.nz = A.exchanged ? D.ny : D.nz;
+    A.ry = A.exchanged ? D.sxy : D.nx;
+    A.rz = A.exchanged ? D.nx : D.sxy;
+    A.ntx = (int)((A.nx + kTileX - 1) / kTileX);
+    A.nty = (int)((A.ny + kTileY - 1) / kTileY);
+    int64_t zl = (A.nz * A.ntx * A.nty + nb - 1) / nb;
     zl = (zl + 1) / 2 * 2;
-    A.zlen = (int)(zl > D.nz + 1 ? D.nz + 1 : zl);
+    A.zlen = (int)(zl > A.nz + 1 ? A.nz + 1 : zl);
     if (A.zlen & 1) ++A.zlen;
+}
+
+static void stencil_coarse(const IdpDims &C, StencilArgs &A)
+{
+    A.cry = A.exchanged ? C.sxy : C.nx;
+    A.crz = A.exchanged ? C.nx : C.sxy;
 }
 
 template <int MODE>
 static void launch_stencil(const StencilArgs &A, unsigned nb, hipStream_t st)
 {
-    if (A.D.sxy < (int64_t)1 << 29)
+    if (A.ny * A.ry < (int64_t)1 << 29)
         k_stencil<MODE, uint32_t><<<nb, kIdpThreads, 0, st>>>(A);
     else
         k_stencil<MODE, uint64_t><<<nb, kIdpThreads, 0, st>>>(A);
@@ -1104,8 +1120,7 @@ static void residual_pass(const MgLevel &F, const MgLevel &C, const double *b, c
     A.dinv = F.dinv;
     A.p = b;
     A.acc = C.ac;
-    A.cnx = C.D.nx;
-    A.cny = C.D.ny;
+    stencil_coarse(C.D, A);
     A.bc = C.b;
     launch_stencil<kResidual>(A, nb, st);
 }
@@ -1120,8 +1135,7 @@ static void post_pass(const MgLevel &F, const MgLevel &C, const double *b, doubl
     A.dinv = F.dinv;
     A.p = b;
     A.ec = C.e;
-    A.cnx = C.D.nx;
-    A.cny = C.D.ny;
+    stencil_coarse(C.D, A);
     A.o1 = e;
     A.part = part;
     launch_stencil<kPost>(A, nb, st);
@@ -1205,8 +1219,7 @@ hipError_t launch_cg_iterations(const IdpDims &D, const double *at, const uint8_
         A.d = dbuf(W, k);
         A.w = W.w;
         A.acc = W.lev[1].ac;
-        A.cnx = W.lev[1].D.nx;
-        A.cny = W.lev[1].D.ny;
+        stencil_coarse(W.lev[1].D, A);
         A.bc = W.lev[1].b;
         A.o1 = q;
         A.o2 = rbuf(W, k + 1);

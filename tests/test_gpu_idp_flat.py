@@ -1,5 +1,6 @@
 """The projection's iterates on flat and narrow grids, whose axes the solver may
-take in another order: axes of one cell in every place, against the numpy
+take in another order: axes of one cell in every place, few rows and many planes
+(the tiles then lie in x and z; also on a coarser level), against the numpy
 conjugate gradients of the iterates' test, to its 1e-10; the whole projection with
 its face displacements on a flat grid and on the same grid lying in x and y."""
 import numpy as np
@@ -12,7 +13,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("precond", [1, 0])
-@pytest.mark.parametrize("shape", [(40, 1, 90), (90, 40, 1), (1, 40, 90), (1, 1, 700), (1, 700, 1), (700, 1, 1), (530, 1, 520)])
+@pytest.mark.parametrize("shape", [(40, 1, 90), (90, 40, 1), (1, 40, 90), (1, 1, 700), (1, 700, 1), (700, 1, 1), (530, 1, 520),
+                                   (300, 2, 50), (271, 3, 341), (90, 7, 33), (1030, 5, 520), (9, 7, 40), (7, 7, 100)])
 def test_iterates(G, shape, precond):  # noqa: F811
     import torch
     from paper_2504_00745_amd import gic
@@ -27,7 +29,8 @@ def test_iterates(G, shape, precond):  # noqa: F811
     s = np.where(lab == 0, rng.normal(0, 0.1, shape), 0.0)
     ctx = gic.Context(wl._params((nx, ny, nz), 0.01, 0.01, 1e-4, (0.0, 0.0, 0.0)), 1, "fp64", r_max=0.0025)
     work = gic.idp_workspace(ctx)
-    for m in (7, 8):  # an odd and an even count: the buffers change places
+    iters = 4 if at.size > 1 << 20 else 7
+    for m in (iters, iters + 1):  # an odd and an even count: the buffers change places
         q = torch.zeros(ctx.G, dtype=torch.float64, device="cuda")
         it, rel = gic.gic_idp_solve(ctx, G.dev(at.reshape(-1)), torch.as_tensor(lab.reshape(-1)).to("cuda"),
                                     G.dev(s.reshape(-1)), q, work, max_iter=m, tol=0.0, check_every=3, precond=precond)
