@@ -241,20 +241,24 @@ namespace {
 
 // Last pass of a reverse step: the P2G pullback of g_alpha (held as integer
 // sums fx2 at the scale of the largest |g_alpha_f| bits), and the adjoint of
-// (x, v) back in input order.  The first workgroup adds the bricks' partial
-// sums of dL/dmu and dL/dC_d to the scalars, in brick order.
+// (x, v) back in input order.  The first workgroup adds the bricks' (or
+// workgroups') partial sums of dL/dmu and dL/dC_d to the scalars, in their order.
 __global__ void __launch_bounds__(256) k_rollout_pull(DevParams P, int64_t n, const int32_t *__restrict__ order,
                                                       const double *__restrict__ x, const double *__restrict__ r,
                                                       const int64_t *__restrict__ fx2,
                                                       const unsigned long long *__restrict__ gmax,
                                                       const double *__restrict__ gs, double *__restrict__ gxv,
                                                       const double *__restrict__ psum, const int32_t *__restrict__ count,
+                                                      int parts,
                                                       double *__restrict__ gmu, double *__restrict__ gcd)
 {
     if (blockIdx.x == 0) {
         __shared__ double w[2][4];
         double m = 0.0, c = 0.0;
-        for (int i = threadIdx.x; i < *count; i += 256) {
+        int np = parts;  // per workgroup of granules or per brick, see launch_rollout_contact
+        if (np < 0) np = pull_granules(n, *count) ? -np : 0;
+        if (np == 0) np = *count;
+        for (int i = threadIdx.x; i < np; i += 256) {
             m += psum[2 * i];
             c += psum[2 * i + 1];
         }
@@ -303,10 +307,11 @@ __global__ void __launch_bounds__(256) k_rollout_pull(DevParams P, int64_t n, co
 
 hipError_t launch_rollout_pull(const DevParams &P, int64_t n, const int32_t *order, const double *x, const double *r,
                                const int64_t *fx2, const unsigned long long *gmax, const double *gs, double *gxv,
-                               const double *psum, const BrickList &B, double *gmu, double *gcd, hipStream_t s)
+                               const double *psum, const BrickList &B, int parts, double *gmu, double *gcd, hipStream_t s)
 {
     if (n == 0) return hipSuccess;
-    k_rollout_pull<<<grid_for(n, 256), 256, 0, s>>>(P, n, order, x, r, fx2, gmax, gs, gxv, psum, B.count, gmu, gcd);
+    k_rollout_pull<<<grid_for(n, 256), 256, 0, s>>>(P, n, order, x, r, fx2, gmax, gs, gxv, psum, B.count, parts, gmu,
+                                                    gcd);
     return hipGetLastError();
 }
 

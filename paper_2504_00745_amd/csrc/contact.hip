@@ -507,7 +507,8 @@ __device__ inline void finish_granule(const DevParams &P, int64_t n, int64_t q, 
 // positions, so evaluating forces inside the candidate loop would run the
 // expensive branch for almost every candidate.  A granule with more
 // partners than the list holds walks its candidates in canonical order.
-template <typename T, int KIND, int NT>
+// U: candidates loaded together.
+template <typename T, int KIND, int NT, int U = kUnroll>
 __device__ inline void contact_global(const DevParams &P, int64_t n, const double *__restrict__ x,
                                       const double *__restrict__ v, const double *__restrict__ r,
                                       const int32_t *__restrict__ cb, const int32_t *__restrict__ ce, int64_t q,
@@ -539,10 +540,10 @@ __device__ inline void contact_global(const DevParams &P, int64_t n, const doubl
     };
     int32_t cnt = 0, nc = 0;
     for_each_run(P, n, lo, hi, cb, ce, [&](int32_t jb, int32_t je) {
-        for (int32_t j0 = jb; j0 < je; j0 += kUnroll) {
-            double cx[kUnroll], cy[kUnroll], cz[kUnroll], cr[kUnroll];
+        for (int32_t j0 = jb; j0 < je; j0 += U) {
+            double cx[U], cy[U], cz[U], cr[U];
 #pragma unroll
-            for (int u = 0; u < kUnroll; ++u) {
+            for (int u = 0; u < U; ++u) {
                 const int32_t j = j0 + u < je ? j0 + u : je - 1;  // in range; duplicates skipped below
                 cx[u] = x[j];
                 cy[u] = x[n + j];
@@ -550,7 +551,7 @@ __device__ inline void contact_global(const DevParams &P, int64_t n, const doubl
                 cr[u] = r[j];
             }
 #pragma unroll
-            for (int u = 0; u < kUnroll; ++u) {
+            for (int u = 0; u < U; ++u) {
                 const int32_t j = j0 + u;
                 if (j >= je || j == q) continue;
                 double d2;
@@ -568,6 +569,54 @@ __device__ inline void contact_global(const DevParams &P, int64_t n, const doubl
         for_each_canonical(P, n, q, lo, hi, cb, ce, [&](int32_t j) { nc += take(j); });
     }
     finish_granule<T, KIND>(P, n, q, xi, vi, ri, mi, gi, acc, nc, F, ncont, A, tot, FluidTile{});
+}
+
+// The workgroup's totals of the reverse step: sums of dL/dmu and dL/dC_d to part
+// `slot`, the largest |g_alpha_f| to gmax.
+template <int NT>
+__device__ inline void reverse_totals(double tot[3], const AdjArgs &A, int64_t slot)
+{
+    __shared__ double s_tot[3][NT / 64];
+    const int tid = threadIdx.x;
+    for (int off = 32; off > 0; off >>= 1) {
+        tot[0] += __shfl_xor(tot[0], off);
+        tot[1] += __shfl_xor(tot[1], off);
+        tot[2] = fmax(tot[2], __shfl_xor(tot[2], off));
+    }
+    if ((tid & 63) == 0)
+        for (int c = 0; c < 3; ++c) s_tot[c][tid >> 6] = tot[c];
+    __syncthreads();
+    if (tid == 0) {
+        double m = s_tot[0][0], d = s_tot[1][0], g = s_tot[2][0];
+        for (int w = 1; w < NT / 64; ++w) {
+            m += s_tot[0][w];
+            d += s_tot[1][w];
+            g = fmax(g, s_tot[2][w]);
+        }
+        A.psum[2 * slot] = m;
+        A.psum[2 * slot + 1] = d;
+        // the bits of non-negative doubles order as the doubles do
+        atomicMax(A.gmax, (unsigned long long)__double_as_longlong(g));
+    }
+}
+
+// The pullbacks with a thread per granule and no bricks: the same partners in the
+// same order, so the same bits (see pull_granules).  U: candidates loaded together,
+// one where a cell holds about one (300,000 granules, 9 a brick, 86 -> 83 us).
+template <int KIND, int U>
+__global__ void __launch_bounds__(256) k_pull_granules(DevParams P, int64_t n, const double *__restrict__ x,
+                                                       const double *__restrict__ v, const double *__restrict__ r,
+                                                       const int32_t *__restrict__ cb, const int32_t *__restrict__ ce,
+                                                       int64_t *err, AdjArgs A, const int32_t *__restrict__ bcnt)
+{
+    if (A.both && !pull_granules(n, *bcnt)) return;
+    __shared__ int32_t plist[kMaxPartners * 256];
+    double tot[3] = {0.0, 0.0, 0.0};
+    const int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (q < n)
+        contact_global<double, KIND, 256, U>(P, n, x, v, r, cb, ce, q, plist, threadIdx.x, nullptr, nullptr, nullptr, nullptr,
+                                             err, A, tot);
+    if constexpr (KIND == kReverse) reverse_totals<256>(tot, A, blockIdx.x);
 }
 
 // ---------------------------------------------------------------------------
@@ -741,6 +790,7 @@ k_contact_lds(DevParams P, int64_t n, const int32_t *__restrict__ bl,
     const int tid = threadIdx.x;
     if (hclr && blockIdx.x == 0 && tid == 0) *hclr = 0;  // the next recording call's record
     if (not_mine(only, kWaveFill, n, bcnt)) return;
+    if (KIND == kReverse && A.both && pull_granules(n, *bcnt)) return;
     constexpr int kBricks = GROUP ? kGroup * kGroup * kGroup : 1;
     __shared__ int32_t s_beg[kBricks], s_end[kBricks];  // granules of the bricks
     int64_t slot = 0, b;  // the brick's place in the list, and the (first) brick
@@ -770,29 +820,7 @@ k_contact_lds(DevParams P, int64_t n, const int32_t *__restrict__ bl,
     const int w0 = GROUP ? tid >> 6 : 0;
     double tot[3] = {0.0, 0.0, 0.0};  // kReverse: dL/dmu, dL/dC_d, largest |g_alpha_f| of the thread
     auto leave = [&]() {              // kReverse: those of the brick
-        if constexpr (KIND == kReverse) {
-            __shared__ double s_tot[3][NT / 64];
-            for (int off = 32; off > 0; off >>= 1) {
-                tot[0] += __shfl_xor(tot[0], off);
-                tot[1] += __shfl_xor(tot[1], off);
-                tot[2] = fmax(tot[2], __shfl_xor(tot[2], off));
-            }
-            if ((tid & 63) == 0)
-                for (int c = 0; c < 3; ++c) s_tot[c][tid >> 6] = tot[c];
-            __syncthreads();
-            if (tid == 0) {
-                double m = s_tot[0][0], d = s_tot[1][0], g = s_tot[2][0];
-                for (int w = 1; w < NT / 64; ++w) {
-                    m += s_tot[0][w];
-                    d += s_tot[1][w];
-                    g = fmax(g, s_tot[2][w]);
-                }
-                A.psum[2 * slot] = m;
-                A.psum[2 * slot + 1] = d;
-                // the bits of non-negative doubles order as the doubles do
-                atomicMax(A.gmax, (unsigned long long)__double_as_longlong(g));
-            }
-        }
+        if constexpr (KIND == kReverse) reverse_totals<NT>(tot, A, slot);
     };
     const int32_t bc[3] = {(int32_t)(b % P.nb[0]), (int32_t)((b / P.nb[0]) % P.nb[1]),
                            (int32_t)(b / ((int64_t)P.nb[0] * P.nb[1]))};
@@ -1570,20 +1598,49 @@ hipError_t launch_contact(const DevParams &P, int64_t n, const double *x, const 
     return contact_launch<T, kForce>(P, n, x, v, r, cb, ce, B, nullptr, nullptr, F, ncont, err, s, ss, AdjArgs{});
 }
 
+bool contact_vjp_bricks(const DevParams &P, int64_t n, const BrickList &B)
+{
+    return !pull_granules((double)n, brick_fill(P, n, B).bricks(n));
+}
+
 hipError_t launch_contact_vjp(const DevParams &P, int64_t n, const double *x, const double *v, const double *r,
                               const int32_t *cb, const int32_t *ce, const BrickList &B, const AdjArgs &A, int64_t *err,
-                              hipStream_t s, SizeRecord *ss)
+                              hipStream_t s, SizeRecord *ss, bool bricks)
 {
+    if (!bricks) {
+        if (brick_fill(P, n, B).avg < kBrickCells)
+            k_pull_granules<kPull, 1><<<grid_for(n, 256), 256, 0, s>>>(P, n, x, v, r, cb, ce, err, A, B.use_count);
+        else
+            k_pull_granules<kPull, kUnroll><<<grid_for(n, 256), 256, 0, s>>>(P, n, x, v, r, cb, ce, err, A, B.use_count);
+        return hipGetLastError();
+    }
     return contact_launch<double, kPull>(P, n, x, v, r, cb, ce, B, nullptr, nullptr, nullptr, nullptr, err, s, ss, A);
 }
 
 hipError_t launch_rollout_contact(const DevParams &P, int64_t n, const double *x, const double *v, const double *r,
                                   const int32_t *cb, const int32_t *ce, const BrickList &B, const AdjArgs &A,
-                                  bool reverse, int64_t *err, hipStream_t s, SizeRecord *ss)
+                                  bool reverse, int64_t *err, hipStream_t s, SizeRecord *ss, int *parts)
 {
-    if (reverse)
+    if (reverse) {
+        // before the bricks are counted both are launched and the device's count
+        // picks one, the one that later calls take: the parameter gradients are
+        // summed in its order
+        const BrickFill f = brick_fill(P, n, B);
+        const bool granules = f.known && pull_granules((double)n, f.bricks(n));
+        AdjArgs R = A;
+        R.both = f.known ? 0 : 1;
+        const int wgs = (int)grid_for(n, 256);
+        *parts = granules ? wgs : (f.known ? 0 : -wgs);
+        if (granules || !f.known) {
+            if (f.avg < kBrickCells)
+                k_pull_granules<kReverse, 1><<<wgs, 256, 0, s>>>(P, n, x, v, r, cb, ce, err, R, B.use_count);
+            else
+                k_pull_granules<kReverse, kUnroll><<<wgs, 256, 0, s>>>(P, n, x, v, r, cb, ce, err, R, B.use_count);
+        }
+        if (granules) return hipGetLastError();
         return contact_launch<double, kReverse>(P, n, x, v, r, cb, ce, B, nullptr, nullptr, nullptr, nullptr, err, s, ss,
-                                                A);
+                                                R);
+    }
     return contact_launch<double, kMove>(P, n, x, v, r, cb, ce, B, nullptr, nullptr, nullptr, nullptr, err, s, ss, A);
 }
 

@@ -472,8 +472,10 @@ gic_status gic_create(const gic_params *p, int64_t n_max, gic_ctx **out)
     ok &= hipMalloc(&c->fxs, sizeof(int64_t) * 4 * (size_t)(c->dp.G > 0 ? c->dp.G : 1)) == hipSuccess;
     ok &= hipMalloc(&c->fxp, sizeof(double) * (4 * 1024 + 8)) == hipSuccess;
     ok &= hipMalloc(&c->gmax, sizeof(unsigned long long)) == hipSuccess;
-    if (!fp32(c))
-        ok &= hipMalloc(&c->psum, sizeof(double) * 2 * (c->bricks.nbricks > 0 ? c->bricks.nbricks : 1)) == hipSuccess;
+    if (!fp32(c)) {
+        const int64_t groups = (nn + 255) / 256;
+        ok &= hipMalloc(&c->psum, sizeof(double) * 2 * (c->bricks.nbricks > groups ? c->bricks.nbricks : groups)) == hipSuccess;
+    }
     ok &= hipMalloc(&c->nl.nbr, sizeof(int32_t) * kNbrCap * nn) == hipSuccess;
     ok &= hipMalloc(&c->nl.cnt, sizeof(int32_t) * nn) == hipSuccess;
     ok &= hipMalloc(&c->nl.xref, sizeof(float) * 3 * nn) == hipSuccess;
@@ -1098,14 +1100,16 @@ gic_status gic_contact_forces_vjp(gic_ctx *c, int64_t n, const double *x, const 
     if (!n_ok(c, n) || fp32(c)) return GIC_E_ARG;
     if (n > 0 && (!x || !v || !r || !cell_begin || !cell_end || !g_f || !g_x || !g_v || !g_mu)) return GIC_E_ARG;
     if (n == 0) return GIC_OK;
-    if (brick_list(c, n, cell_begin, cell_end, (hipStream_t)stream, true) != hipSuccess) return GIC_E_HIP;
+    const bool bricks = contact_vjp_bricks(c->dp, n, c->bricks);
+    if (bricks && brick_list(c, n, cell_begin, cell_end, (hipStream_t)stream, true) != hipSuccess) return GIC_E_HIP;
     AdjArgs A = {};
     A.gF = g_f;
     A.gx = g_x;
     A.gv = g_v;
     A.gmu = g_mu;
     return hip_status(
-        launch_contact_vjp(c->dp, n, x, v, r, cell_begin, cell_end, c->bricks, A, c->err, (hipStream_t)stream, &c->shell));
+        launch_contact_vjp(c->dp, n, x, v, r, cell_begin, cell_end, c->bricks, A, c->err, (hipStream_t)stream, &c->shell,
+                           bricks));
 }
 
 static bool rollout_ok(const gic_ctx *c, int64_t n)
@@ -1173,15 +1177,16 @@ gic_status gic_rollout_step_vjp(gic_ctx *c, int64_t n, const double *xv, const d
     A.gaf = g_af;
     A.gmax = c->gmax;
     A.psum = c->psum;
+    int parts = 0;  // of the parameter gradients' sums, 0: one per occupied brick
     if (e == hipSuccess)
         e = launch_rollout_contact(c->dp, n, xv_sorted, xv_sorted + 3 * n, r_sorted, cell_begin, cell_end, c->bricks, A,
-                                   true, c->err, s, &c->shell);
+                                   true, c->err, s, &c->shell, &parts);
     if (e == hipSuccess)
         e = launch_rollout_galpha(c->dp, n, c->K, xv_sorted, g_af, cell_begin, cell_end, c->bricks, c->fxs, c->fxs + G,
                                   c->fxp, c->gmax, s);
     if (e == hipSuccess)
         e = launch_rollout_pull(c->dp, n, order, xv_sorted, r_sorted, c->fxs + G, c->gmax, g_sorted, g_xv, c->psum,
-                                c->bricks, g_mu, g_cdrag, s);
+                                c->bricks, parts, g_mu, g_cdrag, s);
     return hip_status(e);
 }
 

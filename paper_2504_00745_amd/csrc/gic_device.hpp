@@ -69,6 +69,15 @@ __device__ inline bool not_mine(int only, int64_t per, int64_t n, const int32_t 
     return only != 0 && (n <= per * (int64_t)*count) != (only == 1);
 }
 
+// Whether the pullbacks of the contact force run a thread per granule instead of a
+// workgroup per brick: with fewer than 24 granules in an occupied brick most of
+// its threads are idle, with more than 513 its shell is larger than the LDS array
+// and each brick's one workgroup searches global memory.  By brick and by granule,
+// us: 65,000 granules, 16 a brick 49 and 31, 130,000, 32 a brick 43 and 45;
+// 32,768, 512 a brick 44 and 45, 512,000, 512 a brick 104 and 228; 46,656, 729 a
+// brick 152 and 60, 262,144, 4,096 a brick 2,526 and 477.
+__host__ __device__ inline bool pull_granules(double n, double bricks) { return n < 24.0 * bricks || n > 513.0 * bricks; }
+
 // Brick kernels that loop: workgroup b takes the entries j = b / kXcds +
 // it * (gridDim.x / kXcds), it = 0, 1, ..., of its XCD's eighth of the list
 // (the same split as brick_of_block); -1 when it has no more.  The grid is

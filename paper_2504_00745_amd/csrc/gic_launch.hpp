@@ -177,7 +177,7 @@ hipError_t launch_rollout_galpha(const DevParams &P, int64_t n, int64_t K, const
                                  int64_t *fx2, double *part, const unsigned long long *gmax, hipStream_t s);
 hipError_t launch_rollout_pull(const DevParams &P, int64_t n, const int32_t *order, const double *x, const double *r,
                                const int64_t *fx2, const unsigned long long *gmax, const double *gs, double *gxv,
-                               const double *psum, const BrickList &B, double *gmu, double *gcd, hipStream_t s);
+                               const double *psum, const BrickList &B, int parts, double *gmu, double *gcd, hipStream_t s);
 hipError_t launch_reorder(int64_t n, const int32_t *order, const double *x, const double *v, const double *r,
                           const int32_t *id, double *xo, double *vo, double *ro, int32_t *ido, hipStream_t s);
 
@@ -210,6 +210,7 @@ struct BrickFill {
     double avg;
     bool known;
     double full;  // occupied bricks of a group that holds granules, 0 where not known
+    double bricks(int64_t n) const { return (double)n / avg; }
 };
 inline BrickFill brick_fill(const DevParams &P, int64_t n, const BrickList &B)
 {
@@ -388,15 +389,21 @@ struct AdjArgs {
     double *gs;                  // reverse step: adjoint of (x, v), sorted, in and out
     double *gaf;                 // reverse step: cotangent of the fluid fraction
     unsigned long long *gmax;    // reverse step: bits of the largest |gaf|
-    double *psum;                // reverse step: per brick, the sums of dL/dmu and dL/dC_d
+    double *psum;                // reverse step: per brick (or workgroup), the sums of dL/dmu and dL/dC_d
+    int both;                    // reverse step: both forms were launched, the count of bricks picks one
     int tile_at;                 // rollout: where the brick's node tile lies in LDS (bytes), 0 for none (set at the launch)
 };
+// Whether the contact pullback runs over the bricks (and reads their list).
+bool contact_vjp_bricks(const DevParams &P, int64_t n, const BrickList &B);
 hipError_t launch_contact_vjp(const DevParams &P, int64_t n, const double *x, const double *v, const double *r,
                               const int32_t *cb, const int32_t *ce, const BrickList &B, const AdjArgs &A, int64_t *err,
-                              hipStream_t s, SizeRecord *ss);
+                              hipStream_t s, SizeRecord *ss, bool bricks);
 hipError_t launch_rollout_contact(const DevParams &P, int64_t n, const double *x, const double *v, const double *r,
                                   const int32_t *cb, const int32_t *ce, const BrickList &B, const AdjArgs &A,
-                                  bool reverse, int64_t *err, hipStream_t s, SizeRecord *ss);
+                                  bool reverse, int64_t *err, hipStream_t s, SizeRecord *ss, int *parts = nullptr);
+// (*parts: how many sums of the parameter gradients a reverse step leaves in psum:
+// one per workgroup of 256 granules, that many; one per occupied brick, 0; the
+// number negated where the device picks, see pull_granules)
 hipError_t launch_drag_vjp(const DevParams &P, int64_t n, const double *r, const double *v, const double *uat,
                            const double *af, const double *gF, double *gv, double *guat, double *gaf, double *gcd,
                            hipStream_t s);
