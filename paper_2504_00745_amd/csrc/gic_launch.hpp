@@ -111,10 +111,13 @@ constexpr int64_t kSmallSort = (int64_t)1 << 18;
 //   4.2 million, sorted 64 354 and 353, 128 424 and 308; shuffled 1 580 and 477
 //   16.8 million, sorted 32 1,228 and 1,344, 64 1,384 and 1,346; shuffled 1 2,493 and 1,947
 // and 16 cells of 262,144 granules each, shuffled, 18,300 and 1,000.
-inline int64_t sort_limit(int64_t n, bool shuffled)
+// gathers: the counting sort's last pass gathers the state too (rollout; five
+// steps of 592,704 granules 1,567 and 1,653, of 1.0 million 2,564 and 2,577, of 2.1
+// million 5,715 and 5,632).
+inline int64_t sort_limit(int64_t n, bool shuffled, bool gathers = false)
 {
     if (n <= kSmallSort) return 160;
-    if (shuffled) return n <= 2 * kSmallSort ? 32 : 0;
+    if (shuffled) return n <= (gathers ? 4 : 2) * kSmallSort ? 32 : 0;
     return n <= 2 * kSmallSort ? 128 : (n <= 4 * kSmallSort ? 96 : 64);
 }
 // Whether a sort of n granules in K cells takes the digit passes, from the record

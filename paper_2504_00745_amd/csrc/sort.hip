@@ -1139,7 +1139,7 @@ hipError_t launch_rollout_sort(const DevParams &P, int64_t n, const double *xv, 
     B.use_count = B.count;
     uint32_t *begin = reinterpret_cast<uint32_t *>(cell_begin), *end = reinterpret_cast<uint32_t *>(cell_end);
     uint32_t *skeys = S.skeys[S.cur ^ 1];
-    const int64_t limit = sort_limit(n, true);  // input order
+    const int64_t limit = sort_limit(n, true, true);  // input order
     const bool digits = sort_by_digits(n, K, B, limit);
     const unsigned g = grid_for(n, 256), gl = g < kLoopGrid ? g : kLoopGrid, go = g < 1024u ? g : 1024u;
     k_cell_keys<<<g, 256, 0, s>>>(P, n, xv, key, err, nullptr, nullptr, S.ctl, nullptr, nullptr, order, skeys);

@@ -90,6 +90,9 @@ int main()
     printf("%d %d", form(200000, 64000, true), form(200001, 64000, true));
     seen.dense = 100001;
     printf(" %d %d\n", form(200000, 64000, true), form(200000, 64000, false));
+    // a rollout's
+    printf("%d %d\n", sort_by_digits(1048576, 1 << 20, B, sort_limit(1048576, true, true)) ? 1 : 0,
+           sort_by_digits(1048577, 1 << 20, B, sort_limit(1048577, true, true)) ? 1 : 0);
     // buffers: tiles and digits
     printf("%lld %lld %lld %d %d %d %d\n", (long long)sort_tiles_max(1), (long long)sort_tiles_max(262144),
            (long long)sort_tiles_max(16777216), sort_passes(64), sort_passes(257), sort_passes(65537), sort_passes(16777217));
@@ -98,4 +101,4 @@ int main()
 
 
 def test_sorts_by_digits_where_faster(tmp_path):
-    assert run(tmp_path, SORTS) == [[0, 1, 0, 1, 0], [0, 0, 1, 1], [1, 1024, 8192, 1, 2, 3, 4]]
+    assert run(tmp_path, SORTS) == [[0, 1, 0, 1, 0], [0, 0, 1, 1], [0, 1], [1, 1024, 8192, 1, 2, 3, 4]]

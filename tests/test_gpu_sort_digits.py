@@ -43,7 +43,7 @@ def test_digit_passes(G, orc, nc, n, box):  # noqa: F811
     check(G, gic, orc, cfg, ctx, y, buf)
 
 
-@pytest.mark.parametrize("n,dense", [(20000, True), (524291, False)])
+@pytest.mark.parametrize("n,dense", [(20000, True), (524291, False), (1048579, False)])
 def test_rollout_step(G, n, dense):  # noqa: F811
     import torch
     from paper_2504_00745_amd import gic
