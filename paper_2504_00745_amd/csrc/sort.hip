@@ -930,9 +930,11 @@ __global__ void __launch_bounds__(256) k_brick_scatter(int64_t nbricks, int64_t 
 // How full the groups are (groups; see fill_mode), from kGroupSample groups spread
 // over the box, each at a place of its own in its share so that no bed's period
 // falls in with theirs.  And how many of kDenseSample sorted granules lie in cells
-// of more than limit (skeys given; see sort_by_digits), as a share of n.
+// of more than limit (skeys given; see sort_by_digits), as a share of n: all, if one
+// lies in a cell of more than longest (so many that a sample meets it).
 __global__ void __launch_bounds__(1024) k_bed_sample(int32_t nbx, int32_t nby, int32_t nbz, int64_t n, int groups_too,
-                                                     uint32_t limit, const int32_t *__restrict__ slot_of,
+                                                     uint32_t limit, uint32_t longest,
+                                                     const int32_t *__restrict__ slot_of,
                                                      const uint32_t *__restrict__ skeys,
                                                      const uint32_t *__restrict__ begin, const uint32_t *__restrict__ end,
                                                      int32_t *__restrict__ count)
@@ -940,14 +942,18 @@ __global__ void __launch_bounds__(1024) k_bed_sample(int32_t nbx, int32_t nby, i
     __shared__ uint32_t lds[1024 / 64];
     if (skeys) {
         uint32_t dense = 0;
+        bool one = false;
 #pragma unroll
         for (int u = 0; u < kDenseSample / 1024; ++u) {
             const int64_t p = (threadIdx.x + u * 1024) * n / kDenseSample;
             const uint32_t k = skeys[p];
-            dense += end[k] - begin[k] > limit ? 1u : 0u;
+            const uint32_t len = end[k] - begin[k];
+            dense += len > limit ? 1u : 0u;
+            one |= len > longest;
         }
+        one = __syncthreads_or(one);
         dense = block_reduce_sum(dense, lds);
-        if (threadIdx.x == 0) count[5] = (int32_t)((int64_t)dense * n / kDenseSample);
+        if (threadIdx.x == 0) count[5] = one ? (int32_t)n : (int32_t)((int64_t)dense * n / kDenseSample);
     }
     if (!groups_too) return;
     const uint32_t ngx = (uint32_t)(nbx + kGroup - 1) / kGroup, ngy = (uint32_t)(nby + kGroup - 1) / kGroup;
@@ -1011,8 +1017,8 @@ hipError_t brick_count_copy(const DevParams &P, BrickList &B, int64_t n, hipStre
     const bool groups = n >= kWaveBricks * kBrickCells && B.nbricks >= kGroupBricks && brick_fill(P, n, B).avg <= kWaveFill;
     if ((fresh || (call & 63u) == 0u) && (groups || (S.skeys && n >= kDenseSorts))) {
         k_bed_sample<<<1, 1024, 0, s>>>(P.nb[0], P.nb[1], P.nb[2], n, groups ? 1 : 0,
-                                        (uint32_t)(S.limit ? S.limit : sort_limit(n, false)), B.slot_of, S.skeys, S.begin,
-                                        S.end, B.count);
+                                        (uint32_t)(S.limit ? S.limit : sort_limit(n, false)), (uint32_t)sort_long(n), B.slot_of,
+                                        S.skeys, S.begin, S.end, B.count);
         e = hipGetLastError();
     }
     if (e == hipSuccess) e = hipMemcpyAsync(B.seen, B.count, sizeof(BrickSeen), hipMemcpyDeviceToHost, s);

@@ -83,3 +83,35 @@ def test_rollout_step(G, n, dense):  # noqa: F811
             assert torch.equal(g, last), call
         last = g
     assert bool((Fc != 0).any()) and c.error()[0] == 0
+
+
+@pytest.mark.parametrize("n,m", [(262144, 65536), (100003, 30000)])
+def test_one_long_cell_among_short_ones(G, orc, n, m):  # noqa: F811
+    """A cell of m of the n granules, the rest some eight a cell: bit for bit, and,
+    once the record of the first sort has reached the host, not at the pace of the
+    one workgroup that puts a cell in order (18 us for every 1,024 granules; a sort of
+    as many granules spread evenly takes some 35 us, the digit passes some 65)."""
+    import torch
+    from paper_2504_00745_amd import gic
+    G.say(f"[sort digits] long cell {n} {m}")
+    rng = np.random.Generator(np.random.PCG64(n))
+    nc = (int(np.ceil((n / 8) ** (1 / 3))),) * 3
+    cfg = config(nc)
+    x = rng.random((3, n)) * np.array(nc, float)[:, None]
+    x[:, rng.choice(n, m, replace=False)] = rng.random((3, m)) * 0.9 + 0.05
+    ctx = gic.Context(cfg, n, "fp64", r_max=0.5)
+    buf = [torch.empty(k, dtype=torch.int32, device="cuda") for k in (n, n, ctx.K, ctx.K)]
+    for _ in range(2):
+        check(G, gic, orc, cfg, ctx, x, buf)
+    y = G.dev(x)
+    a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    times = []
+    for _ in range(5):
+        a.record()
+        for _ in range(4):
+            gic.gic_sort_cells(ctx, y, *buf)
+        b.record()
+        torch.cuda.synchronize()
+        times.append(a.elapsed_time(b) / 4 * 1e3)
+    G.say(f"[sort digits] us {min(times):.1f}")
+    assert min(times) < 18.0 * m / 1024 / 2  # half the time of the one workgroup
