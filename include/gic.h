@@ -197,7 +197,7 @@ gic_status gic_destroy(gic_ctx *ctx);
  * clear != 0 resets the latch. */
 gic_status gic_get_error(gic_ctx *ctx, void *stream, int32_t *code, int64_t *index, int32_t clear);
 
-/* ---- a1: binning and stable counting sort ---------------------------------
+/* ---- a1: binning and stable sort ------------------------------------------
  * Neighbour search support for the contact test of Sec. 3.1.
  *   x           3n positions (any order).
  *   key         out, n: cell key of granule i, cell coordinate per axis
@@ -564,7 +564,7 @@ gic_status gic_scale(gic_ctx *ctx, int64_t n, const double *a, const double *s, 
  * kernels' arithmetic as the stages
  *     gic_sort_cells -> gic_reorder -> gic_p2g_real -> gic_g2p -> gic_drag ->
  *     gic_contact_forces -> gic_integrate -> gic_permute
- * in eight launches, same bits.  Plain form (GIC_FP64) and linear drag only.
+ * in eight launches (more where its sort passes over digits), same bits.  Plain form (GIC_FP64) and linear drag only.
  * key, order (n int32), cell_begin, cell_end, xv_sorted (6n), r_sorted (n):
  * scratch; the sort's outputs and the sorted state are left in them. */
 gic_status gic_rollout_step(gic_ctx *ctx, int64_t n, const double *xv, const double *r, const double *u,

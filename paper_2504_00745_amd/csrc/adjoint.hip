@@ -13,7 +13,8 @@
 // every result is the same bits in every run.
 //
 // The rollout's step and its reverse (gic_rollout_step, gic_rollout_step_vjp)
-// run in eight and ten launches: on beds of 65,536 granules a launch costs 3
+// run in eight and ten launches (more where their sort passes over digits, or the
+// contact pulls run by granule): on beds of 65,536 granules a launch costs 3
 // to 5 us whatever it does, and the separate stages were 17 and 28 of them,
 // each reading the bed again.  Loss and gradients of 20 steps of that bed, as
 // a replayed graph: 10.07 -> 5.39 ms; of 6 steps of 4,096 granules launched

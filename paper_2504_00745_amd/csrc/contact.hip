@@ -1,18 +1,22 @@
 // a2 + a3: neighbour candidates and contact forces (Sec. 3.1, Eq. 1a-c) on
 // gfx950.
 //
-// The dry contact runs in two kernels: a neighbour-list build (k_nbr_build,
-// one workgroup per brick, candidates from an LDS copy of the brick's cell
-// shell) that lists every granule closer than r_i + r_j + skin, and the
-// contact forces from that list (k_contact_list, one thread per granule),
-// which runs the exact double test of Sec. 3.1 on every listed partner each
-// step.  The stepping path builds the list only when the sorted order
-// changed or a granule moved by skin / 2 since the last build; a granule's
-// force sum runs over its touching partners in one canonical order
-// (canon_before: by distance in sorted order) either way, so the forces do
-// not depend on when the list was built, nor on which kernel summed them.  The capillary
-// instantiation of k_contact_lds (candidates and forces in one brick kernel)
-// serves wet beds.
+// One kernel searches and sums, k_contact_lds: a workgroup per brick, or a
+// wave, or a workgroup per group of bricks (see fill_mode), candidates from an LDS copy
+// of the brick's or the group's cell shell, in five kinds: kForce (dry forces), kBridge (forces with liquid
+// bridges), kPull (their pullback), kMove (the rollout step's force, G2P, drag and move)
+// and kReverse (the pullbacks of that).  Beds of few or very many granules a brick
+// run the pulls by granule instead (k_pull_granules, see pull_granules).
+//
+// The stepping path keeps a neighbour list instead: k_nbr_build (one workgroup per
+// brick) lists every granule closer than r_i + r_j + skin, when the sorted order
+// changed or a granule moved by skin / 2 since the last build, and k_contact_list (one
+// thread per granule) runs the exact double test of Sec. 3.1 on every listed partner
+// each step.
+//
+// A granule's force sum runs over its touching partners in one canonical order
+// (canon_before: by distance in sorted order) in every form, so the forces do not
+// depend on when a list was built, nor on which kernel summed them.
 //
 // Each granule visits only the neighbour cells its search box
 // [x - (r_i + r_max), x + (r_i + r_max)] overlaps (at most 27, typically 8
@@ -1013,8 +1017,6 @@ k_contact_lds(DevParams P, int64_t n, const int32_t *__restrict__ bl,
     // ---- granules of the brick, one thread each: the listed partners are
     // evaluated in canonical order, the order of the dry contact's
     // neighbour list, so a bed without bridges gives the dry contact's bits
-    constexpr int L = 1;
-    constexpr int sub = 0;
     auto granules = [&](int64_t qb, int32_t ge) {  // called by whole waves
         const int64_t q = qb + tid % kStep;
         const bool live = q < ge;
@@ -1066,21 +1068,18 @@ k_contact_lds(DevParams P, int64_t n, const int32_t *__restrict__ bl,
                 const int own = (ca[2] * S + ca[1]) * S + ca[0];
                 const int32_t qoff = (int32_t)(q - cgb[own]);
                 const int32_t kself = qoff >= 0 && qoff < cnum[own] ? clo[own] + qoff : -1;
-                // this lane's rows (hz, hy) of the search box, f(first cell of the row)
-                auto for_rows = [&](auto &&f) {
-                    const int ny = hi[1] - lo[1] + 1, nz = hi[2] - lo[2] + 1;
-                    if (ny <= 0 || nz <= 0) return;  // empty box (a NaN or negative radius): no rows
-                    const int nrow = nz * ny;
-                    int hz = lo[2], hy = lo[1] + sub;
-                    while (hy > hi[1]) { hy -= ny; ++hz; }
-                    for (int row = sub; row < nrow; row += L) {
-                        f((hz * S + hy) * S);
-                        hy += L;
-                        while (hy > hi[1]) { hy -= ny; ++hz; }
-                    }
-                };
+                // the search box's rows (hz, hy) in one loop; none in an empty box (a NaN or
+                // negative radius)
+                const int ny = hi[1] - lo[1] + 1, nz = hi[2] - lo[2] + 1;
+                const int nrow = ny > 0 && nz > 0 ? nz * ny : 0;
+                int hz = lo[2], hy = lo[1];
                 int32_t cnt = 0;
-                for_rows([&](int c) {
+                for (int row = 0; row < nrow; ++row) {
+                    const int c = (hz * S + hy) * S;
+                    if (++hy > hi[1]) {
+                        hy = lo[1];
+                        ++hz;
+                    }
                     // cells lo..hi of this row: one contiguous run of slots
                     const int k0 = clo[c + lo[0]];
                     const int k1 = clo[c + hi[0]] + cnum[c + hi[0]];
@@ -1099,7 +1098,7 @@ k_contact_lds(DevParams P, int64_t n, const int32_t *__restrict__ bl,
                             ++cnt;
                         }
                     }
-                });
+                }
                 auto global_of = [&](int k) { const int c = scell[k]; return (int64_t)cgb[c] + (k - clo[c]); };
                 if (cnt <= kLdsPartners) lds_list_canonical<NT>(plist + tid, cnt, q, global_of);
                 vi[0] = v[q];

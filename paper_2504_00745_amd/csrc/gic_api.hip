@@ -138,26 +138,25 @@ bool params_valid(const gic_params *p)
     return true;
 }
 
-// Edge of the P2G LDS tile: the nodes touched by a brick's granules plus one
-// node of slack on each side.
-// Nodes per edge of a brick's node tile: the stencils of granules whose
-// cell lies in the brick span 4 cell / dx + 2 nodes when that is an integer
-// (the brick starts on a node boundary), one more otherwise.  Granules that
-// moved out of their cell since the sort reach outside the tile and take
-// the global path.
 // Whether a node lies in the tiles of at most two bricks per axis, which
 // k_p2g_assemble assumes: tile origins of bricks two apart differ by at
 // least the tile edge.  4 cell/dx an integer: cell/dx >= 1/2; otherwise
-// 4 cell/dx > 4.  (And at most 2,048 bricks along x.)
+// 4 cell/dx > 4.  And at most 512 bricks along x: it holds the slots of four
+// node rows' bricks in 32 KiB of LDS.
 bool tiles_assemble(const gic_params *p)
 {
-    if ((p->nc[0] + kBrick - 1) / kBrick > 512) return false;  // four rows' bricks in 32 KiB of LDS
+    if ((p->nc[0] + kBrick - 1) / kBrick > 512) return false;
     const double m4 = (double)kBrick * p->cell / p->dx;
     const double r = floor(m4 + 0.5);
     if (fabs(m4 - r) < 1e-9 * (r > 1.0 ? r : 1.0)) return r >= 2.0;
     return m4 > 4.0;
 }
 
+// Nodes per edge of the node tile of a brick (or of a cube of bricks): the
+// stencils of granules whose cell lies in it span 4 cell / dx + 2 nodes when
+// that is an integer (the brick starts on a node boundary), one more otherwise.
+// Granules that moved out of their cell since the sort reach outside the tile
+// and take the global path.
 int tile_edge(const gic_params *p, int bricks = 1)
 {
     const double m4 = (double)(kBrick * bricks) * p->cell / p->dx;

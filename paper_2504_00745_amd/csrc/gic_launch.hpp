@@ -96,7 +96,15 @@ struct NbrList {
 };
 
 // Up to this many keys a counting sort does not collect the changed ones:
-// counting everything again takes no longer than merging them in.
+// counting everything again is faster than merging them in.  Eight granules a
+// cell, sorted but for none, 512, 4,000 and 5 % of them, counting against merging, us:
+//   131,072: 19 to 25 in each case, and 22 to 29, 35, 84 and 27
+//   262,144: 20 to 25, and 22 to 30, 38, 93 and 35
+//   524,288: 27, and 24 to 32, 45, 111 and 53
+//   1.05 million: 39, 53, 75 and 92 to 94, and 28 to 33, 53, 132 and 84
+// Above it the changed keys are counted also where merging is no faster: their
+// number says whether the next input is shuffled, on which the choice between
+// counting and the digit passes depends there (see sort_limit).
 constexpr int64_t kSmallSort = (int64_t)1 << 18;
 
 // A sort counts, or passes over the keys' digits.  Counting places each granule
@@ -238,9 +246,10 @@ inline BrickFill brick_fill(const DevParams &P, int64_t n, const BrickList &B)
 // bricks: 16.8 million granules at 64 a brick take 0.88, 1.04 and 0.92 ms
 // instead of 1.25, 1.88 and 1.70 (gather, contact, P2G, FP32); at 205 a brick
 // the wave loops over its brick and takes 25 and 32 us instead of 19 and 26
-// (gather, P2G).  With fewer bricks than the chip holds of the larger workgroups
-// (1,024) more threads per brick are faster (216 bricks: 7.8 and 7.2 against
-// 6.4 and 6.5 us; 1,728 bricks: 11.0 and 12.8 against 11.9 and 15.4).
+// (gather, P2G).  Beds of fewer granules than fill a wave in each of the 1,024
+// larger workgroups that the chip holds (65,536) leave it room, and more threads
+// per brick are faster (216 bricks of 64: 7.8 and 7.2 against 6.4 and 6.5 us; 1,728:
+// 11.0 and 12.8 against 11.9 and 15.4).
 //
 // A workgroup of kGroupNT threads per group of 2x2x2 bricks, a wave per brick
 // and two bricks per wave, when there are many more bricks: eight tiles share

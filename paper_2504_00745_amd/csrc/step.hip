@@ -283,9 +283,10 @@ hipError_t launch_gather(const DevParams &P, int64_t n, int64_t K, const int32_t
     FillMode mode = fill_mode(P, n, B, sizeof(T) == 4 ? kGroupBricks : kGroupShells);
     // the FP64 fluid tile of a group leaves a CU two workgroups
     if (mode == kFillGroup && ((FLUID && sizeof(T) == 8) || glds > 65536)) mode = kFillWave;
-#define GIC_GATHER(NT, GROUP, ONLY)                                                                                  \
-    k_gather<T, FLUID, NT, GROUP><<<GROUP ? group_grid(P) : grid, NT, GROUP ? glds : lds, s>>>(P, n, B.use, B.use_count, order, x, v, r, id, xo, vo, ro, ido, u, afx, \
-                                                 gp, fa, cb, ce, Ff, uat, af, held, heldo, ONLY)
+#define GIC_GATHER(NT, GROUP, ONLY)                                                                           \
+    k_gather<T, FLUID, NT, GROUP><<<GROUP ? group_grid(P) : grid, NT, GROUP ? glds : lds, s>>>(               \
+        P, n, B.use, B.use_count, order, x, v, r, id, xo, vo, ro, ido, u, afx, gp, fa, cb, ce, Ff, uat, af,   \
+        held, heldo, ONLY)
     if (mode == kFillGroup) GIC_GATHER(kGatherNT, true, 0);
     if (mode == kFillWave || mode == kFillBoth) GIC_GATHER(64, false, mode == kFillBoth ? 1 : 0);
     if (mode == kFillBlock || mode == kFillBoth) GIC_GATHER(256, false, mode == kFillBoth ? 2 : 0);
