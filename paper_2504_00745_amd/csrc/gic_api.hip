@@ -396,23 +396,23 @@ gic_status gic_create(const gic_params *p, int64_t n_max, gic_ctx **out)
     ok &= hipMalloc(&c->sort.chg, sizeof(uint64_t) * kChgCap) == hipSuccess;
     ok &= hipMalloc(&c->sort.chg_s, sizeof(uint64_t) * kChgCap) == hipSuccess;
     ok &= hipMalloc(&c->sort.chg_p, sizeof(uint32_t) * kChgCap) == hipSuccess;
-    ok &= hipMalloc(&c->sort.ctl, sizeof(int32_t) * 4) == hipSuccess;
-    if (ok) ok = hipMemset(c->sort.ctl, 0, sizeof(int32_t) * 4) == hipSuccess;
+    ok &= hipMalloc(&c->sort.ctl, sizeof(int32_t) * 4 + sizeof(BrickSeen)) == hipSuccess;  // and the brick list's count
+    if (ok) ok = hipMemset(c->sort.ctl, 0, sizeof(int32_t) * 4 + sizeof(BrickSeen)) == hipSuccess;
+    if (ok) c->bricks.count = c->sort.ctl + 4;
     ok &= hipMalloc(&c->sort.tmp, sizeof(int32_t) * nn) == hipSuccess;
     ok &= hipMalloc(&c->sort.tmp2, sizeof(int32_t) * nn) == hipSuccess;
     c->sort.passes = sort_passes(c->K);
-    if (c->sort.passes > 2) ok &= hipMalloc(&c->sort.kB, sizeof(uint32_t) * nn) == hipSuccess;
-    ok &= hipMalloc(&c->sort.tcnt, sizeof(uint32_t) * 256 * sort_tiles_max(nn)) == hipSuccess;
-    ok &= hipMalloc(&c->sort.rowtot, sizeof(uint32_t) * 256) == hipSuccess;
-    ok &= hipMalloc(&c->sort.sums, sizeof(uint32_t) * 2048) == hipSuccess;
+    ok &= hipMalloc(&c->sort.sums, sizeof(uint32_t) * (2048 + 256 + 256 * sort_tiles_max(nn))) == hipSuccess;
+    if (ok) {
+        c->sort.rowtot = c->sort.sums + 2048;
+        c->sort.tcnt = c->sort.rowtot + 256;
+    }
     ok &= hipMalloc(&c->sort.cnt, sizeof(uint32_t) * (c->K > 0 ? c->K : 1)) == hipSuccess;
     if (ok) ok = hipMemset(c->sort.cnt, 0, sizeof(uint32_t) * (c->K > 0 ? c->K : 1)) == hipSuccess;
     ok &= hipMalloc(&c->err, sizeof(int64_t) * 2) == hipSuccess;
     ok &= hipMalloc(&c->part, sizeof(double) * kSumParts) == hipSuccess;
     c->bricks.nbricks = c->K / kBrickCells;
     ok &= hipMalloc(&c->bricks.list, sizeof(int32_t) * (c->bricks.nbricks > 0 ? c->bricks.nbricks : 1)) == hipSuccess;
-    ok &= hipMalloc(&c->bricks.count, sizeof(BrickSeen)) == hipSuccess;
-    if (ok) ok = hipMemset(c->bricks.count, 0, sizeof(BrickSeen)) == hipSuccess;
     if (ok && c->bricks.nbricks > 0 && c->bricks.nbricks <= kBoxBricks) {
         int32_t h[kBoxBricks + 1];
         const size_t bytes = sizeof(int32_t) * (size_t)(c->bricks.nbricks + 1);
@@ -428,10 +428,12 @@ gic_status gic_create(const gic_params *p, int64_t n_max, gic_ctx **out)
     if (ok) ok = hipMemset(c->esc_n2, 0, sizeof(uint32_t) * 2) == hipSuccess;
     ok &= hipMalloc(&c->shell.dev, sizeof(int32_t) * 2) == hipSuccess;
     if (ok) ok = hipMemset(c->shell.dev, 0, sizeof(int32_t) * 2) == hipSuccess;
-    ok &= hipHostMalloc(&c->shell.host, sizeof(int32_t) * 2, hipHostMallocDefault) == hipSuccess;
-    if (ok) c->shell.host[0] = 0;  // no record yet: the largest shell array
-    ok &= hipHostMalloc(&c->bricks.seen, sizeof(BrickSeen), hipHostMallocDefault) == hipSuccess;
-    if (ok) *c->bricks.seen = {};  // nor a count of occupied bricks
+    ok &= hipHostMalloc(&c->shell.host, sizeof(int32_t) * 2 + sizeof(BrickSeen), hipHostMallocDefault) == hipSuccess;
+    if (ok) {
+        c->shell.host[0] = 0;  // no record yet: the largest shell array
+        c->bricks.seen = reinterpret_cast<BrickSeen *>(c->shell.host + 2);
+        *c->bricks.seen = {};  // nor a count of occupied bricks
+    }
     if (ok && tiles_assemble(p)) {
         // one 4-channel node tile per occupied brick (at most min(bricks, n));
         // beyond 8 GiB the stepping path keeps the cleared grids and atomics
@@ -520,19 +522,14 @@ gic_status gic_destroy(gic_ctx *c)
     (void)hipFree(c->sort.ctl);
     (void)hipFree(c->sort.tmp);
     (void)hipFree(c->sort.tmp2);
-    (void)hipFree(c->sort.kB);
-    (void)hipFree(c->sort.tcnt);
-    (void)hipFree(c->sort.rowtot);
     (void)hipFree(c->sort.sums);
     (void)hipFree(c->sort.cnt);
     (void)hipFree(c->err);
     (void)hipFree(c->part);
     (void)hipFree(c->bricks.list);
-    (void)hipFree(c->bricks.count);
     (void)hipFree(c->bricks.box);
     (void)hipFree(c->bricks.sums);
     (void)hipFree(c->bricks.slot_of);
-    (void)hipHostFree(c->bricks.seen);
     (void)hipFree(c->p2gs.esc);
     (void)hipFree(c->p2gs.tiles);
     (void)hipFree(const_cast<int32_t *>(c->p2gs.cover));

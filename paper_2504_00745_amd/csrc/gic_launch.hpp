@@ -20,12 +20,12 @@ struct SortScratch {
     int64_t last_n;      // granules of the last sort, -1 before the first
     uint32_t *slot;      // [n] place of each granule in its cell, in order of arrival
     int32_t *tmp, *tmp2; // [n] granules by cell, in order of arrival; second array of long cells
-                         // (digit passes: the values' buffers, and slot the keys' first)
-    uint32_t *kB;        // [n] the keys' second buffer (keys of more than two digits), or NULL
-    uint32_t *tcnt;      // [256][sort_tiles_max] digit counts, then output offsets, of each tile in a digit pass
-    uint32_t *rowtot;    // [256] keys with each digit in a digit pass
+                         // (digit passes: the values' buffers; slot and the sorted keys are the keys')
     int passes;          // 8-bit digits of the keys
     uint32_t *sums;      // [2 x 1024] granules and occupied bricks of the scan's chunks
+    uint32_t *rowtot;    // [256] keys with each digit in a digit pass (after sums, in its allocation)
+    uint32_t *tcnt;      // [256][sort_tiles_max] digit counts, then output offsets, of each tile in a digit
+                         // pass (after rowtot)
     uint32_t *cnt;       // [K] granules per cell; zero between sorts
     uint64_t *chg;       // [kChgCap] changed granules as (key << 32 | position), in arrival order
     uint64_t *chg_s;     // [kChgCap] the same sorted

@@ -1045,7 +1045,7 @@ void digit_passes(int64_t n, const uint32_t *key, uint32_t *skeys, int32_t *orde
     const int32_t *vin = nullptr;
     for (int pass = 0; pass < S.passes; ++pass) {
         const bool last = pass == S.passes - 1;
-        uint32_t *kout = last ? skeys : ((pass & 1) ? S.kB : S.slot);
+        uint32_t *kout = ((S.passes - 1 - pass) & 1) ? S.slot : skeys;  // the last into skeys
         int32_t *vout = last ? order : ((pass & 1) ? S.tmp2 : S.tmp);
         if (sort_items(n) == 1)
             k_digit_count<1><<<tg, kSortThreads, 0, s>>>(kin, n, pass, tiles, S.tcnt, skip);
