@@ -40,7 +40,7 @@ struct SortScratch {
 // groups of a sample that hold granules and their occupied bricks (0: none taken).
 // Of the last sort: the granules whose key had changed since the one before (all,
 // where they were not compared); of the last sampled, those in cells larger than
-// its sort_limit (all, if one lies in a cell of more than sort_long).
+// its sort_limit (all, if one lies in a cell of more than sort_long; -1: none sampled).
 struct BrickSeen {
     int32_t count, n;
     int32_t groups, bricks;
@@ -63,8 +63,7 @@ struct BrickList {
     int64_t nbricks;
     BrickSeen *seen;   // pinned host: a copy of an earlier list's count (see brick_fill)
     int64_t seen_n;    // granules of the last list
-    unsigned calls;
-    bool again;        // the last list was the first of seen_n granules
+    unsigned calls, sorts;  // lists of seen_n granules in a row, and sorts among them
 };
 
 // Every brick of the box in the order of a brick list, runs of 16 neighbouring
@@ -134,7 +133,7 @@ inline bool sort_by_digits(int64_t n, int64_t K, const BrickList &B, int64_t lim
 {
     if (limit == 0) return true;
     const volatile BrickSeen *seen = B.seen;
-    if (n >= kDenseSorts && seen && seen->n == n && seen->count > 0) return 2 * (int64_t)seen->dense > n;
+    if (n >= kDenseSorts && seen && seen->n == n && seen->count > 0 && seen->dense >= 0) return 2 * (int64_t)seen->dense > n;
     return n > limit * K;
 }
 // Granules of a cell from which it alone calls for the digit passes: one workgroup

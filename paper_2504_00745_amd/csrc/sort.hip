@@ -286,10 +286,18 @@ __global__ void __launch_bounds__(256) k_cell_count(const uint32_t *__restrict__
 // counts are reset to zero for the next sort by k_cell_order).
 constexpr int64_t kDirectScan = 32768;
 
-// A list's count and the granules it is of (BrickSeen).
-__device__ inline void put_count(int32_t *count, int32_t nocc, int32_t n)
+// A list's count and the granules it is of (BrickSeen); of another number than the
+// list before, nothing else is known yet (a sort says itself how many keys changed).
+// n < 0: a list whose caller does not know, no record.
+__device__ inline void put_count(int32_t *count, int32_t nocc, int32_t n, bool sorted)
 {
     count[0] = nocc;
+    if (n < 0) return;
+    if (count[1] != n) {
+        count[2] = count[3] = 0;
+        if (!sorted) count[4] = n;
+        count[5] = -1;
+    }
     count[1] = n;
 }
 
@@ -386,7 +394,7 @@ __global__ void __launch_bounds__(kScanThreads) k_scan_down_ranges(uint32_t *__r
         carry += total;
         __syncthreads();  // s_occ is rewritten by the next round
     }
-    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) put_count(count, (int32_t)nocc, n);
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) put_count(count, (int32_t)nocc, n, true);
 }
 
 // Granule i to its place in its cell, in order of arrival; the key of the
@@ -893,7 +901,7 @@ __global__ void __launch_bounds__(kScanThreads) k_brick_list(int nbricks, const 
         slot_of[b0 + u] = occ ? (int32_t)at : -1;
         if (occ) list[at++] = b0 + u;
     }
-    if (threadIdx.x == 0) put_count(count, (int32_t)total, n);
+    if (threadIdx.x == 0) put_count(count, (int32_t)total, n, false);
 }
 
 // Each workgroup sums the counts before its own (at most kScanThreads words).
@@ -922,7 +930,7 @@ __global__ void __launch_bounds__(256) k_brick_scatter(int64_t nbricks, int64_t 
         if (b < hi) slot_of[b] = f ? (int32_t)(base + inc - 1) : -1;
         base += total;
     }
-    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) put_count(count, (int32_t)base, n);
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) put_count(count, (int32_t)base, n, false);
 }
 
 // Samples of a bed for its record, one workgroup.
@@ -1000,25 +1008,27 @@ struct Sorted {
 };
 
 // Every 16th list, and the first of another number of granules, leaves its record
-// in pinned host memory (see brick_fill); so does the second where a sort asks for
-// what changed (it is the first that can be compared).  Samples are taken of those
-// two and of every 64th list.
+// in pinned host memory (see brick_fill).  So do the first sort among them and,
+// where the next asks for what changed, the second (the first that can be compared).
+// Samples are taken of those, and of every 64th list (groups) and sort (cells).
 hipError_t brick_count_copy(const DevParams &P, BrickList &B, int64_t n, hipStream_t s, const Sorted &S = Sorted{})
 {
     hipError_t e = hipGetLastError();
     if (n <= 0 || !B.seen) return e;
-    const bool first = B.seen_n != n, fresh = first || (B.again && S.asks);
-    if (first) B.calls = 0;
-    const unsigned call = B.calls++;
-    B.again = first;
+    if (B.seen_n != n) B.calls = B.sorts = 0;
     B.seen_n = n;
-    if (!fresh && (call & 15u) != 0u) return e;
+    const bool sort = S.skeys != nullptr;
+    const unsigned call = B.calls++, nth = sort ? B.sorts++ : 0;
+    const bool fresh = call == 0 || (sort && (nth == 0 || (nth == 1 && S.asks)));
+    const bool cells = sort && n >= kDenseSorts && (fresh || (nth & 63u) == 0u);
+    if (!fresh && !cells && (call & 15u) != 0u) return e;
     // (groups: where the bed may be run by them, as far as is known)
     const bool groups = n >= kWaveBricks * kBrickCells && B.nbricks >= kGroupBricks && brick_fill(P, n, B).avg <= kWaveFill;
-    if ((fresh || (call & 63u) == 0u) && (groups || (S.skeys && n >= kDenseSorts))) {
-        k_bed_sample<<<1, 1024, 0, s>>>(P.nb[0], P.nb[1], P.nb[2], n, groups ? 1 : 0,
+    const bool sampled = groups && (fresh || (call & 63u) == 0u);
+    if (sampled || cells) {
+        k_bed_sample<<<1, 1024, 0, s>>>(P.nb[0], P.nb[1], P.nb[2], n, sampled ? 1 : 0,
                                         (uint32_t)(S.limit ? S.limit : sort_limit(n, false)), (uint32_t)sort_long(n), B.slot_of,
-                                        S.skeys, S.begin, S.end, B.count);
+                                        cells ? S.skeys : nullptr, S.begin, S.end, B.count);
         e = hipGetLastError();
     }
     if (e == hipSuccess) e = hipMemcpyAsync(B.seen, B.count, sizeof(BrickSeen), hipMemcpyDeviceToHost, s);

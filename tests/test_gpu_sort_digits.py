@@ -115,3 +115,38 @@ def test_one_long_cell_among_short_ones(G, orc, n, m):  # noqa: F811
         times.append(a.elapsed_time(b) / 4 * 1e3)
     G.say(f"[sort digits] us {min(times):.1f}")
     assert min(times) < 18.0 * m / 1024 / 2  # half the time of the one workgroup
+
+
+def test_sorts_among_brick_lists(G, orc):  # noqa: F811
+    """Stage calls whose brick lists come between the sorts: the sorts are sampled all
+    the same, so a long cell is known (see above), also where a list of the same number
+    of granules came first."""
+    import torch
+    from paper_2504_00745_amd import gic
+    n, m = 262144, 65536
+    G.say("[sort digits] lists between")
+    rng = np.random.Generator(np.random.PCG64(3))
+    cfg = dict(config((96,) * 3), kn=1.0)  # more bricks than a call takes without a list
+    x = rng.random((3, n)) * 96.0
+    x[:, rng.choice(n, m, replace=False)] = rng.random((3, m)) * 0.9 + 0.05
+    e = lambda k, t=torch.int32: torch.empty(k, dtype=t, device="cuda")  # noqa: E731
+    other = gic.Context(cfg, n, "fp64", r_max=0.5)
+    tab = [e(n), e(n), e(other.K), e(other.K)]
+    gic.gic_sort_cells(other, G.dev(x), *tab)
+    f64 = torch.float64
+    xs, r = G.dev(x)[:, tab[1].long()].contiguous(), torch.full((n,), 1e-3, dtype=f64, device="cuda")
+    ctx = gic.Context(cfg, n, "fp64", r_max=0.5)
+    buf = [e(n), e(n), e(ctx.K), e(ctx.K)]
+    y, A = G.dev(x), e(ctx.G, torch.int64)
+    a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    times = []
+    for k in range(6):
+        gic.gic_p2g(ctx, xs, None, r, tab[2], tab[3], A, None)  # builds a list
+        a.record()
+        gic.gic_sort_cells(ctx, y, *buf)
+        b.record()
+        torch.cuda.synchronize()
+        times.append(a.elapsed_time(b) * 1e3)
+    assert all(torch.equal(p, q) for p, q in zip(tab, buf))
+    G.say(f"[sort digits] us {times}")
+    assert min(times[2:]) < 18.0 * m / 1024 / 2
