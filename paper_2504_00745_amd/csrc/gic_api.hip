@@ -402,11 +402,8 @@ gic_status gic_create(const gic_params *p, int64_t n_max, gic_ctx **out)
     ok &= hipMalloc(&c->sort.tmp, sizeof(int32_t) * nn) == hipSuccess;
     ok &= hipMalloc(&c->sort.tmp2, sizeof(int32_t) * nn) == hipSuccess;
     c->sort.passes = sort_passes(c->K);
-    ok &= hipMalloc(&c->sort.sums, sizeof(uint32_t) * (2048 + 256 + 256 * sort_tiles_max(nn))) == hipSuccess;
-    if (ok) {
-        c->sort.rowtot = c->sort.sums + 2048;
-        c->sort.tcnt = c->sort.rowtot + 256;
-    }
+    ok &= hipMalloc(&c->sort.sums, sizeof(uint32_t) * (2048 + 256)) == hipSuccess;
+    if (ok) c->sort.rowtot = c->sort.sums + 2048;
     ok &= hipMalloc(&c->sort.cnt, sizeof(uint32_t) * (c->K > 0 ? c->K : 1)) == hipSuccess;
     if (ok) ok = hipMemset(c->sort.cnt, 0, sizeof(uint32_t) * (c->K > 0 ? c->K : 1)) == hipSuccess;
     ok &= hipMalloc(&c->err, sizeof(int64_t) * 2) == hipSuccess;
@@ -423,7 +420,9 @@ gic_status gic_create(const gic_params *p, int64_t n_max, gic_ctx **out)
     ok &= hipMalloc(&c->bricks.sums, sizeof(uint32_t) * 1024) == hipSuccess;
     ok &= hipMalloc(&c->bricks.slot_of, sizeof(int32_t) * (c->bricks.nbricks > 0 ? c->bricks.nbricks : 1)) ==
           hipSuccess;
-    ok &= hipMalloc(&c->p2gs.esc, sizeof(int32_t) * nn) == hipSuccess;
+    const int64_t nt = 256 * sort_tiles_max(nn);  // about n of small sorts, n / 8 of large ones
+    ok &= hipMalloc(&c->p2gs.esc, sizeof(int32_t) * (nn > nt ? nn : nt)) == hipSuccess;
+    c->sort.tcnt = reinterpret_cast<uint32_t *>(c->p2gs.esc);
     ok &= hipMalloc(&c->esc_n2, sizeof(uint32_t) * 2) == hipSuccess;
     if (ok) ok = hipMemset(c->esc_n2, 0, sizeof(uint32_t) * 2) == hipSuccess;
     ok &= hipMalloc(&c->shell.dev, sizeof(int32_t) * 2) == hipSuccess;

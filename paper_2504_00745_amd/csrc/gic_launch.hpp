@@ -25,7 +25,7 @@ struct SortScratch {
     uint32_t *sums;      // [2 x 1024] granules and occupied bricks of the scan's chunks
     uint32_t *rowtot;    // [256] keys with each digit in a digit pass (after sums, in its allocation)
     uint32_t *tcnt;      // [256][sort_tiles_max] digit counts, then output offsets, of each tile in a digit
-                         // pass (after rowtot)
+                         // pass (in the array of a deposit's escapes: no sort runs inside a deposit)
     uint32_t *cnt;       // [K] granules per cell; zero between sorts
     uint64_t *chg;       // [kChgCap] changed granules as (key << 32 | position), in arrival order
     uint64_t *chg_s;     // [kChgCap] the same sorted
